@@ -68,9 +68,14 @@ struct Core<float> {
     const f4a b = *reinterpret_cast<const f4a *>(rows + (lane & 31) * kRowPitch + 4 * (lane >> 5) + 8 * t);
     o.b[0] = b.x, o.b[1] = b.y, o.b[2] = b.z, o.b[3] = b.w;
   }
+  static constexpr int kChain = 4;  // matrix instructions of a group that add into one accumulator, one after the other
+  // link q of that chain: first operand from oa, second from ob
+  __device__ static void mma_link(const Ops &oa, const Ops &ob, int q, Acc &c) {
+    c.v = __builtin_amdgcn_mfma_f32_32x32x2f32(oa.a[q], ob.b[q], c.v, 0, 0, 0);
+  }
   __device__ static void mma(const Ops &o, Acc &c) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) c.v = __builtin_amdgcn_mfma_f32_32x32x2f32(o.a[q], o.b[q], c.v, 0, 0, 0);
+    for (int q = 0; q < kChain; ++q) mma_link(o, o, q, c);
   }
   // f(row, column, value) for every element of the wavefront's 32 x 32 sub-tile this lane holds:
   // register v of lane l is row 8*(v/4) + 4*(l/32) + v%4, column l%32
@@ -79,6 +84,23 @@ struct Core<float> {
 #pragma unroll
     for (int v = 0; v < 16; ++v) f(8 * (v / 4) + 4 * (lane >> 5) + (v % 4), lane & 31, c.v[v]);
   }
+  // the same, replacing every element by f's result
+  template <typename F>
+  __device__ static void update(Acc &c, int lane, F f) {
+#pragma unroll
+    for (int v = 0; v < 16; ++v) c.v[v] = f(8 * (v / 4) + 4 * (lane >> 5) + (v % 4), lane & 31, c.v[v]);
+  }
+  // whether any element of the sub-tile's first `cols` columns that this lane holds is Inf or NaN
+  __device__ static bool non_finite(const Acc &c, int lane, int64_t cols) {
+    float s = 0.0f;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) s = __builtin_fmaf(c.v[v], 0.0f, s);
+    return s != s && (lane & 31) < cols;
+  }
+  // operand q of a group of eight reduction indices: which index and which row (or column) this lane feeds
+  static constexpr int kGroup = 8, kOps = 4;
+  __device__ static int op_index(int lane, int q) { return 4 * (lane >> 5) + q; }
+  __device__ static int op_row(int lane, int) { return lane & 31; }
 };
 
 template <>
@@ -120,12 +142,14 @@ struct Core<double> {
     o.b[0] = p[0];
     o.b[1] = p[16 * kRowPitch];
   }
-  __device__ static void mma(const Ops &o, Acc &c) {
-    c.v[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(o.a[0], o.b[0], c.v[0], 0, 0, 0);
-    c.v[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(o.a[0], o.b[1], c.v[1], 0, 0, 0);
-    c.v[2] = __builtin_amdgcn_mfma_f64_16x16x4f64(o.a[1], o.b[0], c.v[2], 0, 0, 0);
-    c.v[3] = __builtin_amdgcn_mfma_f64_16x16x4f64(o.a[1], o.b[1], c.v[3], 0, 0, 0);
+  static constexpr int kChain = 1;
+  __device__ static void mma_link(const Ops &oa, const Ops &ob, int, Acc &c) {
+    c.v[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(oa.a[0], ob.b[0], c.v[0], 0, 0, 0);
+    c.v[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(oa.a[0], ob.b[1], c.v[1], 0, 0, 0);
+    c.v[2] = __builtin_amdgcn_mfma_f64_16x16x4f64(oa.a[1], ob.b[0], c.v[2], 0, 0, 0);
+    c.v[3] = __builtin_amdgcn_mfma_f64_16x16x4f64(oa.a[1], ob.b[1], c.v[3], 0, 0, 0);
   }
+  __device__ static void mma(const Ops &o, Acc &c) { mma_link(o, o, 0, c); }
   // element v of lane l of a 16 x 16 tile is row 4*v + l/16, column l%16
   template <typename F>
   __device__ static void for_each(const Acc &c, int lane, F f) {
@@ -136,6 +160,26 @@ struct Core<double> {
 #pragma unroll
         for (int v = 0; v < 4; ++v) f(16 * ra + 4 * v + (lane >> 4), 16 * ca + (lane & 15), c.v[2 * ra + ca][v]);
   }
+  template <typename F>
+  __device__ static void update(Acc &c, int lane, F f) {
+#pragma unroll
+    for (int ra = 0; ra < 2; ++ra)
+#pragma unroll
+      for (int ca = 0; ca < 2; ++ca)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) c.v[2 * ra + ca][v] = f(16 * ra + 4 * v + (lane >> 4), 16 * ca + (lane & 15), c.v[2 * ra + ca][v]);
+  }
+  __device__ static bool non_finite(const Acc &c, int lane, int64_t cols) {
+    double s[2] = {0.0, 0.0};
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) s[t & 1] = __builtin_fma(c.v[t][v], 0.0, s[t & 1]);
+    return (s[0] != s[0] && (lane & 15) < cols) || (s[1] != s[1] && 16 + (lane & 15) < cols);
+  }
+  static constexpr int kGroup = 4, kOps = 2;
+  __device__ static int op_index(int lane, int) { return lane >> 4; }
+  __device__ static int op_row(int lane, int q) { return 16 * q + (lane & 15); }
 };
 
 // The sweep over k-steps [lo, hi) of one workgroup tile, written once for every kernel and element type.
@@ -197,6 +241,52 @@ __device__ inline void sweep_groups(int lo, int hi, Load load, Store store, Read
     step(kt, 0);
     if (kt + 1 < hi) step(kt + 1, 1);
   }
+}
+
+// The same schedule with the global loads of TWO steps in flight and no test in a step: past the last step the loads
+// and stores repeat it (nobody reads what they bring).
+template <typename Ops, typename Stage, bool PIN = false, typename Load, typename Store, typename Read, typename Mma>
+__device__ inline void sweep_ahead(int lo, int hi, Load load, Store store, Read read, Mma mma) {
+  Stage s0, s1;
+  Ops oa, ob;
+  const int last = hi - 1;
+  auto upto = [&](int kt) { return kt < last ? kt : last; };
+  auto pin = [] {
+    if (PIN) __builtin_amdgcn_sched_barrier(0);
+  };
+  load(lo, s0);
+  load(upto(lo + 1), s1);
+  store(0, lo, s0);
+  __syncthreads();
+  read(0, lo, 0, oa);
+  auto step = [&](int kt, int buf, Stage &free, Stage &next) {
+    load(upto(kt + 2), free);
+    __builtin_amdgcn_sched_barrier(0);
+    read(buf, kt, 1, ob);
+    pin();
+    mma(oa);
+    pin();
+    read(buf, kt, 2, oa);
+    pin();
+    mma(ob);
+    pin();
+    read(buf, kt, 3, ob);
+    pin();
+    mma(oa);
+    pin();
+    store(buf ^ 1, upto(kt + 1), next);
+    __syncthreads();
+    read(buf ^ 1, kt + 1, 0, oa);
+    pin();
+    mma(ob);
+    pin();
+  };
+  int kt = lo;
+  for (; kt + 1 < hi; kt += 2) {
+    step(kt, 0, s0, s1);
+    step(kt + 1, 1, s1, s0);
+  }
+  if (kt < hi) step(kt, 0, s0, s1);
 }
 
 // The common case: one accumulator per wavefront, the operand groups and matrix instructions of Core<T>.

@@ -1,0 +1,72 @@
+// Single-precision contractions on the bf16 matrix cores, by an exact split of every operand in three.
+//
+// A float has 24 significand bits, a bfloat16 has 8 and the same exponent range, so x = h + m + l exactly with
+// h = bf16(x), m = bf16(x - h), l = x - h - m (rounded to nearest, each remainder is representable in the bits
+// that are left).  A product is then the sum of nine bf16 products, each exact in fp32; the three smallest (m*l, l*m,
+// l*l, together below 2^-26 of the product, a quarter of the rounding of one fp32 operation) are left out and the
+// six others are accumulated in fp32 by v_mfma_f32_32x32x16_bf16.  Six such instructions do 16 reduction indices in
+// 6 * 32 cycles where v_mfma_f32_32x32x2_f32 takes 8 * 64, and, unlike those, they run beside vector instructions of
+// the same SIMD (measured: six vector instructions behind every matrix instruction cost nothing, fp32 matrix
+// instructions and vector code simply add up).  Every element of the sum enters the fp32 accumulator with 15 others
+// in one rounding instead of one (or two) at a time, so the error of long sums falls: against a 64-bit evaluation the
+// 2-norm error of TRMM n=16384, m=256 is 1.0e-6 (fp32 instructions 1.9e-6 at the same partition 1.1e-6); with the five
+// small products in an accumulator of their own 3.6e-7.
+//
+// Range.  Operands are multiplied by 2^24 first (exact), so that the three parts of every normal float, down to the
+// smallest, are representable; results are multiplied by 2^-48.  What the split cannot hold -- an Inf or NaN
+// operand, |x| >= 2^103, partial sums beyond 2^80 -- leaves a non-finite accumulator: kernels test the accumulators
+// once at the end of a tile (Core<float>::non_finite) and evaluate that tile again with fp32 matrix instructions, so that such
+// inputs propagate as IEEE arithmetic has it.
+#pragma once
+#include "common.h"
+
+namespace dastac {
+
+typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
+typedef float f2v __attribute__((ext_vector_type(2)));
+typedef unsigned u2v __attribute__((ext_vector_type(2)));
+typedef unsigned u4v __attribute__((ext_vector_type(4)));
+
+constexpr float kSplitUp = 16777216.0f;               // 2^24
+constexpr float kSplitDown = 3.5527136788005009e-15f;  // 2^-48
+
+__device__ inline unsigned pack_bf16(float a, float b) {  // v_cvt_pk_bf16_f32: round to nearest even
+  const f2v v = {a, b};
+  return __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf2));
+}
+
+// The three parts of 2^24 a (low half of each word) and 2^24 b (high half): 6.5 vector instructions per element.
+__device__ inline void split3(float a, float b, unsigned &h, unsigned &m, unsigned &l) {
+  h = pack_bf16(a * kSplitUp, b * kSplitUp);
+  const float ra = __builtin_fmaf(a, kSplitUp, -__uint_as_float(h << 16));
+  const float rb = __builtin_fmaf(b, kSplitUp, -__uint_as_float(h & 0xffff0000u));
+  m = pack_bf16(ra, rb);
+  l = pack_bf16(ra - __uint_as_float(m << 16), rb - __uint_as_float(m & 0xffff0000u));
+}
+
+// Eight consecutive reduction indices of one row or column: the operand of one lane, part by part.
+struct Parts {
+  u4v v[3];
+};
+__device__ inline Parts split3x8(const float (&x)[8]) {
+  Parts p;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    unsigned h, m, l;
+    split3(x[2 * j], x[2 * j + 1], h, m, l);
+    p.v[0][j] = h, p.v[1][j] = m, p.v[2][j] = l;
+  }
+  return p;
+}
+
+// The six products, largest first: which part of the first and of the second operand.
+constexpr int kSplitProducts = 6;
+constexpr int kSplitA[kSplitProducts] = {0, 0, 1, 1, 0, 2};
+constexpr int kSplitB[kSplitProducts] = {0, 1, 0, 1, 2, 0};
+
+__device__ inline f16v mma_bf16(u4v a, u4v b, f16v c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8, a), __builtin_bit_cast(bf8, b), c, 0, 0, 0);
+}
+
+}  // namespace dastac

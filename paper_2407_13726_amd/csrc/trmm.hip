@@ -5,189 +5,556 @@
 // The rule is Table 1's SpMV_UT with a matrix right-hand side; U keeps the packed layout of
 // Section 4 (row i holds k=i..n-1 contiguously, starting at tri_row_start(n,i)).
 //
-// Tiling.  A workgroup (8 wavefronts) owns a 64-row x 128-column tile of C and sweeps k from the
-// diagonal of its row block to n in steps of 32 (fp32) or 16 (fp64: the paper's element type, Section
-// 6.1).  Per step the 64 x kKT tile of U (each packed row piece is 128 contiguous bytes, at its own
-// element-aligned offset) and the kKT x 128 tile of B are staged in LDS, double-buffered against the
-// global loads of the next step, and each wavefront multiplies its 32x32 sub-tile.  The sweep and the
-// per-type matrix-core pieces are those of mfma_tile.h (v_mfma_f32_32x32x2_f32, with the k values dealt
-// to the lane halves so that the U operand is one 16-byte LDS read; v_mfma_f64_16x16x4_f64 on 2x2 tiles
-// of 16x16); this file adds what is TRMM's own: the packed row bases, the masked diagonal steps, the
-// pairing of row blocks, the XCD numbering and the shares.
+// Work.  A workgroup owns a tile of C (Tile<..> below: its wavefronts, and how many 32x32 sub-tiles each of them holds)
+// and sweeps k from the diagonal of its row block to n in steps of 32 (fp32) or 16 (fp64: the paper's element type,
+// Section 6.1).  Row block b needs (n - kBM b)/step steps, so row blocks are taken in pairs of equal total
+// (b with nb-1-b; with an odd number of row blocks block 0 alone and b with nb-b), and the steps of a pair, the long
+// block's and then the short block's as one list, are cut into S equal shares, one workgroup each.  With S = 1
+// every element has one writer and plain stores; otherwise the pieces are added into a zeroed C with
+// floating-point atomics (two shares: an element gets at most two addends, whose order does not matter).  Shares are
+// numbered share-major and an XCD (ids equal mod 8) gets a run of consecutive numbers: its workgroups sweep the same
+// part of k of consecutive pairs, so that rows of B one of them reads are read again by its neighbours out of that
+// XCD's L2, and column blocks of one pair, which read the same packed rows, are neighbours too.
 //
-// Only the k-steps that touch the diagonal block (and the ragged last step / last row block) take
-// the masked loader, which writes zeros for k<i; every other tile is loaded without predicates, and those
-// steps run as a sweep of their own whose loop holds no test of the kind of step (benchmark shape: 585 -> 565 us).
+// Edges.  Every step but those of the last few rows is loaded with 16-byte loads and without tests: on the diagonal block
+// the elements left of the diagonal are read (they are the rows before, inside the buffer) and selected away when the
+// step is stored to LDS, and a ragged last step reads on into the next row and is selected away the same way.  The last
+// column block starts where it still is a whole one and leaves the columns it shares with its neighbour to that one;
+// with fewer columns than a tile has, a thread's piece is pulled back into the row (its columns then arrive twice, with
+// the same values), and columns past the last are garbage that is never stored.
 //
-// Load balance: row block b needs (n - 64 b)/32 k-steps, so a workgroup processes the pair
-// (b, nb-1-b), and every workgroup does the same amount of work.  Workgroups that share a
-// row-block pair (different column blocks) get ids that are equal modulo 8, i.e. land on the
-// same XCD, so the packed U rows they both read are fetched from HBM once and hit in that XCD's L2;
-// an XCD is given a run of consecutive pairs, which lets its L2 serve the re-reads of B as well.
-//
-// Few columns give few workgroups (m = 256: one per compute unit), and a compute unit whose only
-// workgroup waits at its barrier has nothing else to run.  Then the k-steps of a pair, taken as one
-// list (the long block's, then the short block's), are cut into S equal shares, one workgroup each;
-// a share covers pieces of at most two row blocks and adds each piece into a zeroed C with
-// floating-point atomics.  With S = 1 nothing changes: plain stores, no atomics, no fill.
+// Two kernels share this.  trmm_split_kernel (fp32, more than 32 columns) splits the operands in three bf16 parts when
+// they are staged and multiplies on the bf16 matrix cores (split3.h); trmm_native_kernel uses the instructions of the
+// element type (mfma_tile.h).
+#include "split3.h"
 #include "mfma_tile.h"
+
+#include <type_traits>
 
 using namespace dastac;
 
 namespace {
 
-template <typename T>
-struct Stage {
-  typename Core<T>::vec u;     // U: row ur of the tile, one 16-byte piece of k values
-  typename Core<T>::vec b[2];  // B: k rows bk and bk + kKT/2, one 16-byte piece of columns each
+// WR x WC wavefronts of WM x WN sub-tiles of 32 x 32 each
+template <int WR_, int WC_, int WM_, int WN_>
+struct Tile {
+  static constexpr int WR = WR_, WC = WC_, WM = WM_, WN = WN_;
+  static constexpr int kBM = 32 * WR * WM, kBN = 32 * WC * WN, kThreads = 64 * WR * WC;
 };
 
-// PIN: the sweep's instructions stay in the written order (mfma_tile.h); chosen where two workgroups share a CU.
-// The three sweeps of a whole tile (below) take the kernel past 128 registers.  Every launch but the one with a
-// single workgroup per CU (fp32, no shares, unpinned) wants two workgroups on a CU, so those instantiations are
-// held to the 128 registers of four wavefronts per SIMD; the few spilled values cost less than the second
-// workgroup brings (fp32 with shares, which had silently been running one workgroup per CU at 134 registers:
-// n=16384, m=384 0.92 -> 0.83 ms).
-template <typename T, bool SPLIT, bool PIN>
-__global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu((SPLIT || PIN || sizeof(T) == 8) ? 4 : 1)))
-void trmm_mfma_kernel(int64_t n, int64_t m, const T *__restrict__ U,
-                                                                 const T *__restrict__ B, int64_t ldb,
-                                                                 T *__restrict__ C, int64_t ldc, int nb, int npairs,
-                                                                 int ncb, int S) {
+// What a launch hands to its workgroups.
+template <typename T>
+struct Problem {
+  int64_t n, m;
+  const T *U, *B;
+  int64_t ldb;
+  T *C;
+  int64_t ldc;
+  int nb, npairs, ncb, S;  // row blocks, pairs of them, column blocks, shares per pair
+};
+
+DASTAC_HD int imin(int a, int b) { return a < b ? a : b; }
+DASTAC_HD int imax(int a, int b) { return a > b ? a : b; }
+
+// The one or two pieces of a workgroup: steps [lo, hi) of row block blk.
+struct Share {
+  int cb;                 // column block
+  int blk[2], lo[2], hi[2];
+};
+
+// (32-bit arithmetic, with sizes at most 2^24 and the number of workgroups below 2^31: a 64-bit division is some hundred
+// instructions, and this is all a short launch does before its first load)
+template <int BM, int STEP, typename T>
+__device__ inline bool my_share(const Problem<T> &p, Share &s) {
+  const unsigned total = (unsigned)p.npairs * (unsigned)p.ncb * (unsigned)p.S;
+  const unsigned xcd = blockIdx.x & 7u, part = total >> 3, rest = total & 7u;  // the first `rest` XCDs get one more
+  const unsigned slot = blockIdx.x >> 3;
+  if (slot >= part + (xcd < rest ? 1u : 0u)) return false;
+  const unsigned idx = part * xcd + (xcd < rest ? xcd : rest) + slot;
+  const unsigned ps = idx / (unsigned)p.ncb, share = ps / (unsigned)p.npairs;
+  s.cb = (int)(idx - ps * (unsigned)p.ncb);
+  const int pair = (int)(ps - share * (unsigned)p.npairs), n = (int)p.n;
+  s.blk[0] = pair;
+  s.blk[1] = (p.nb & 1) ? p.nb - pair : p.nb - 1 - pair;  // nb: there is none
+  const int steps_a = (n - pair * BM + STEP - 1) / STEP;
+  const int steps_b = s.blk[1] < p.nb ? (n - s.blk[1] * BM + STEP - 1) / STEP : 0;
+  const unsigned steps = (unsigned)(steps_a + steps_b);  // below 2^21, times at most 64 shares
+  const int t_lo = (int)(steps * share / (unsigned)p.S), t_hi = (int)(steps * (share + 1) / (unsigned)p.S);
+  s.lo[0] = t_lo, s.hi[0] = imin(t_hi, steps_a);
+  s.lo[1] = imax(t_lo - steps_a, 0), s.hi[1] = imin(t_hi - steps_a, steps_b);
+  return true;
+}
+
+// Steps [kt_lo, nk) of the tile at row i0 and columns [col0, col0+kBN) in the arithmetic of the element type, added up in
+// acc.  `shared` holds kNativeShared<T, G> elements; the caller has synchronised its use.
+template <typename T, typename G>
+constexpr int kNativeShared = 2 * (G::kBM * Core<T>::kRowPitch + Core<T>::kKT * G::kBN);
+
+// How B's rows are staged: in 16-byte pieces that all start on a 16-byte boundary of the LDS tile (m >= kBN or a multiple of
+// the piece), in pieces of which the last is pulled back to any element, or, with m below a piece, element by element.
+enum Columns { kAligned, kPulledBack, kFew };
+template <typename T, typename G, Columns COLS>
+__device__ __attribute__((always_inline)) inline void native_piece(const Problem<T> &pr, T *shared, int64_t i0, int64_t col0, int kt_lo,
+                                                                   int nk, typename Core<T>::Acc (&acc)[G::WM][G::WN]) {
   typedef Core<T> K;
   typedef typename K::vec vec;
   typedef typename K::uvec uvec;
-  constexpr int kBM = kTileM, kBN = kTileN, kKT = K::kKT, kV = K::kVec, kUP = K::kRowPitch;
-  constexpr int kDiagSteps = kBM / kKT;  // k-steps that overlap the diagonal block
-  __shared__ __attribute__((aligned(16))) T Us[2][kBM * kUP];
-  __shared__ __attribute__((aligned(16))) T Bs[2][kKT * kBN];
+  constexpr int kBM = G::kBM, kBN = G::kBN, kKT = K::kKT, kV = K::kVec, kUP = K::kRowPitch, kTh = G::kThreads;
+  constexpr int kDiagSteps = kBM / kKT;   // steps that overlap the diagonal block
+  constexpr int kURows = kTh / 8;         // rows of the U tile that one pass of the workgroup stages
+  constexpr int kPU = kBM / kURows;       // 16-byte pieces of U per thread
+  constexpr int kBPieces = kBN / kV;      // pieces per row of the B tile
+  constexpr int kBRows = kTh / kBPieces;  // rows of the B tile that one pass stages
+  constexpr int kPB = kKT / kBRows;       // pieces of B per thread
+  static_assert(kBM % kURows == 0 && kKT % kBRows == 0, "whole passes stage a step");
+  constexpr int kUBuf = kBM * kUP, kBBuf = kKT * kBN;
+  T *const Us = shared, *const Bs = shared + 2 * kUBuf;
+  const int64_t n = pr.n, m = pr.m, ldb = pr.ldb;
+  const T *B = pr.B;
 
-  // workgroup id -> (row-block pair, column block); ids equal mod 8 share an XCD.  An XCD gets a run of
-  // consecutive pairs: their sweeps over k start 64 rows apart and move at the same speed, so the rows
-  // of B one of them reads are read again by its neighbour a few k-steps later, out of that XCD's L2.
-  const int L = blockIdx.x;
-  const int xcd = L & 7, slot = L >> 3;
-  const int per_pair = SPLIT ? ncb * S : ncb;
-  const int pair_lo = (int)((int64_t)npairs * xcd / 8), pair_hi = (int)((int64_t)npairs * (xcd + 1) / 8);
-  const int pair = pair_lo + slot / per_pair;
-  const int cb = SPLIT ? (slot % per_pair) / S : slot % ncb;
-  const int share = SPLIT ? slot % S : 0;
-  if (pair >= pair_hi) return;
-  // this workgroup's share [t_lo, t_hi) of the pair's k-steps, numbered through both row blocks
-  const int steps_a = (int)ceil_div(n - (int64_t)pair * kBM, kKT);
-  const int steps_b = (nb - 1 - pair != pair) ? (int)ceil_div(n - (int64_t)(nb - 1 - pair) * kBM, kKT) : 0;
-  const int t_lo = SPLIT ? (int)((int64_t)(steps_a + steps_b) * share / S) : 0;
-  const int t_hi = SPLIT ? (int)((int64_t)(steps_a + steps_b) * (share + 1) / S) : steps_a + steps_b;
+  struct Stage {
+    vec u[kPU];
+    vec b[kPB];
+  };
+  struct Ops {
+    typename K::Ops a[G::WM], b[G::WN];
+  };
+  const int tid = threadIdx.x, lane = tid & 63, wave = uniform32(tid >> 6);
+  const int wr = wave / G::WC, wc = wave % G::WC;
+  const int ur = tid >> 3, uk = (tid & 7) * kV;
+  const int bk = tid / kBPieces, bc = (tid % kBPieces) * kV;
+  const bool b_live = bc < m;                                           // (bc is at most kBN: only a tile wider than C has dead threads)
+  const int bcl = (int)(COLS == kFew || col0 + bc + kV <= m ? bc : m - kV - col0);  // pulled back into the row
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wr = wave >> 2, wc = wave & 3;  // 2x4 wavefronts: 32 rows x 32 columns each
-
-  // staging roles: eight threads per row of the U tile, 128/kV per row of the B tile
-  const int ur = tid >> 3, uk = (tid & 7) * kV;                       // U: row ur, k offset uk
-  const int bk = tid / (kBN / kV), bc = (tid % (kBN / kV)) * kV;      // B: k row bk (and bk + kKT/2), column offset bc
-  const int64_t col0 = (int64_t)cb * kBN;
-  const bool cols_full = col0 + kBN <= m;
-
-  for (int which = 0; which < 2; ++which) {
-    const int blk = which == 0 ? pair : nb - 1 - pair;
-    if (which == 1 && blk == pair) break;  // odd number of row blocks: the middle one is alone
-    const int64_t i0 = (int64_t)blk * kBM;
-    const bool rows_full = i0 + kBM <= n;
-    // k-steps [kt_lo, nk) of this row block fall into the share
-    const int first = which == 0 ? 0 : steps_a;  // number of the block's step 0 in the pair's list
-    const int steps_blk = which == 0 ? steps_a : steps_b;
-    // (literal bounds without shares: the first sweep below then has a compile-time trip count)
-    const int kt_lo = SPLIT ? (t_lo > first ? t_lo - first : 0) : 0;
-    const int nk = SPLIT ? (t_hi - first < steps_blk ? t_hi - first : steps_blk) : (int)ceil_div(n - i0, kKT);
-    if (SPLIT && kt_lo >= nk) continue;
-
-    // per-thread packed row base: element (i,k) of U is at ub + k for this thread's row i
-    const int64_t iu = i0 + ur;
-    const bool urow_ok = iu < n;
-    const T *ub = U + (urow_ok ? tri_row_start(n, iu) - iu : 0);
-
-    auto load_stage = [&](int kt, Stage<T> &s) {
-      const int64_t k0 = i0 + (int64_t)kt * kKT;
-      const bool k_full = k0 + kKT <= n;
-      if (kt >= kDiagSteps && k_full && rows_full) {
-        s.u = *reinterpret_cast<const uvec *>(ub + k0 + uk);
-      } else {
+  const T *ub = pr.U + (tri_row_start(n, i0) - i0);  // element (i,k) of U is at ub + (offset of row i) + k
+  unsigned uoff[kPU];
+  int ir[kPU];  // row minus i0, clamped to the matrix
 #pragma unroll
-        for (int e = 0; e < kV; ++e) {
-          const int64_t k = k0 + uk + e;
-          s.u[e] = (urow_ok && k >= iu && k < n) ? ub[k] : T(0);
-        }
+  for (int p = 0; p < kPU; ++p) {
+    const int64_t i = i0 + ur + p * kURows < n ? i0 + ur + p * kURows : n - 1;
+    ir[p] = (int)(i - i0);
+    uoff[p] = (unsigned)sizeof(T) * (unsigned)((tri_row_start(n, i) - i) - (tri_row_start(n, i0) - i0) + uk);
+  }
+  const T *bp = B + (int64_t)bk * ldb + col0 + bcl;
+  const int nfull = (int)((n - i0) / kKT);  // steps that end inside the matrix
+  // a piece that starts inside a row may run kKT-1 elements past its end: inside the buffer if eight rows follow the block
+  const bool roomy = i0 + kBM + 8 <= n;
+  const int nvec = roomy ? nk : imin(nk, nfull);
+
+  auto load = [&](int kt, Stage &s) __attribute__((always_inline)) {
+    const int64_t k0 = i0 + (int64_t)kt * kKT;
+    const char *base = reinterpret_cast<const char *>(ub + k0);
+#pragma unroll
+    for (int p = 0; p < kPU; ++p) s.u[p] = *reinterpret_cast<const uvec *>(base + uoff[p]);
+    if (!b_live) return;
+    if (COLS == kFew) {
+#pragma unroll
+      for (int q = 0; q < kPB; ++q) {
+        const int64_t k = k0 + bk + q * kBRows;
+#pragma unroll
+        for (int e = 0; e < kV; ++e) s.b[q][e] = B[(k < n ? k : n - 1) * ldb + (e < m ? e : 0)];
       }
-      if (k_full && cols_full) {
+    } else if (kt < nfull) {  // (both ways issue the same number of loads: the compiler's counts of what is in flight stay exact)
 #pragma unroll
-        for (int q = 0; q < 2; ++q)
-          s.b[q] = *reinterpret_cast<const uvec *>(B + (k0 + bk + (kKT / 2) * q) * ldb + col0 + bc);
-      } else {
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-          const int64_t k = k0 + bk + (kKT / 2) * q;
-#pragma unroll
-          for (int e = 0; e < kV; ++e) s.b[q][e] = (k < n && col0 + bc + e < m) ? B[k * ldb + col0 + bc + e] : T(0);
-        }
-      }
-    };
-    auto store_stage = [&](int buf, int, const Stage<T> &s) {
-      *reinterpret_cast<vec *>(&Us[buf][ur * kUP + uk]) = s.u;
-#pragma unroll
-      for (int q = 0; q < 2; ++q) *reinterpret_cast<vec *>(&Bs[buf][(bk + (kKT / 2) * q) * kBN + bc]) = s.b[q];
-    };
-    auto read_ops = [&](int buf, int, int t, typename K::Ops &o) {
-      K::read_a(&Us[buf][wr * 32 * kUP], lane, t, o);
-      K::read_b(&Bs[buf][wc * 32], kBN, lane, t, o);
-    };
-
-    typename K::Acc acc;
-    K::clear(acc);
-    __syncthreads();  // the previous row block's last reads of buffer 0 are done
-    if (rows_full && cols_full) {
-      // A whole tile: the masked steps on the diagonal block, the whole steps behind it and a ragged last step are
-      // three sweeps, so that the long one carries no test of which kind of step it is on.
-      const int nfull = (int)((n - i0) / kKT);
-      const int a_hi = nk < kDiagSteps ? nk : kDiagSteps;
-      const int b_lo = kt_lo > kDiagSteps ? kt_lo : kDiagSteps, b_hi = nk < nfull ? nk : nfull;
-      const int c_lo = kt_lo > nfull ? kt_lo : nfull;
-      bool between = false;  // a sweep has run: barrier before the next one reuses the buffers
-      if (kt_lo < a_hi) {
-        sweep_steps<T, Stage<T>, PIN>(kt_lo, a_hi, acc, load_stage, store_stage, read_ops);
-        between = true;
-      }
-      if (b_lo < b_hi) {
-        if (between) __syncthreads();
-        sweep_steps<T, Stage<T>, PIN>(
-            b_lo, b_hi, acc,
-            [&](int kt, Stage<T> &s) {
-              const int64_t k0 = i0 + (int64_t)kt * kKT;
-              s.u = *reinterpret_cast<const uvec *>(ub + k0 + uk);
-#pragma unroll
-              for (int q = 0; q < 2; ++q)
-                s.b[q] = *reinterpret_cast<const uvec *>(B + (k0 + bk + (kKT / 2) * q) * ldb + col0 + bc);
-            },
-            store_stage, read_ops);
-        between = true;
-      }
-      if (c_lo < nk) {
-        if (between) __syncthreads();
-        sweep_steps<T, Stage<T>, PIN>(c_lo, nk, acc, load_stage, store_stage, read_ops);
-      }
+      for (int q = 0; q < kPB; ++q) s.b[q] = *reinterpret_cast<const uvec *>(bp + (k0 + q * kBRows) * ldb);
     } else {
-      sweep_steps<T, Stage<T>, PIN>(kt_lo, nk, acc, load_stage, store_stage, read_ops);
-    }
-    __syncthreads();  // all reads of this row block's buffers are done before the next block's stores
-
-    K::for_each(acc, lane, [&](int r, int c, T v) {
-      const int64_t i = i0 + wr * 32 + r, col = col0 + wc * 32 + c;
-      if (i < n && col < m) {
-        if (SPLIT)
-          unsafeAtomicAdd(&C[i * ldc + col], v);
-        else
-          C[i * ldc + col] = v;
+#pragma unroll
+      for (int q = 0; q < kPB; ++q) {
+        const int64_t k = k0 + bk + q * kBRows;
+        s.b[q] = *reinterpret_cast<const uvec *>(B + (k < n ? k : n - 1) * ldb + col0 + bcl);
       }
-    });
+    }
+  };
+  // the last steps of the last rows: element by element, addresses clamped into the row (a load behind a test would be
+  // waited for before the next one is issued), values selected when the step is stored
+  auto load_last = [&](int kt, Stage &s) __attribute__((always_inline)) {
+    const int64_t k0 = i0 + (int64_t)kt * kKT;
+#pragma unroll
+    for (int p = 0; p < kPU; ++p) {
+      const T *row = ub + (int64_t)(uoff[p] / (unsigned)sizeof(T)) - uk;
+      const int64_t i = i0 + ir[p];
+#pragma unroll
+      for (int e = 0; e < kV; ++e) {
+        const int64_t k = k0 + uk + e;
+        s.u[p][e] = row[k < i ? i : (k < n ? k : n - 1)];
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < kPB; ++q) {
+      const int64_t k = k0 + bk + q * kBRows;
+      const T *row = B + (k < n ? k : n - 1) * ldb + col0;
+#pragma unroll
+      for (int e = 0; e < kV; ++e) s.b[q][e] = row[col0 + bcl + e < m ? bcl + e : 0];
+    }
+  };
+  auto store = [&](int buf, int kt, Stage &s) __attribute__((always_inline)) {
+    if (kt < kDiagSteps || kt >= nfull) {
+      const int k0 = kt * kKT;  // relative to i0
+      const int64_t left = n - i0;
+#pragma unroll
+      for (int p = 0; p < kPU; ++p)
+#pragma unroll
+        for (int e = 0; e < kV; ++e) s.u[p][e] = (k0 + uk + e >= ir[p] && k0 + uk + e < left) ? s.u[p][e] : T(0);
+      if (kt >= nfull) {
+#pragma unroll
+        for (int q = 0; q < kPB; ++q)
+          if (k0 + bk + q * kBRows >= left) s.b[q] = vec(T(0));
+      }
+    }
+#pragma unroll
+    for (int p = 0; p < kPU; ++p) *reinterpret_cast<vec *>(&Us[buf * kUBuf + (ur + p * kURows) * kUP + uk]) = s.u[p];
+    if (b_live) {
+#pragma unroll
+      for (int q = 0; q < kPB; ++q) {
+        T *dst = &Bs[buf * kBBuf + (bk + q * kBRows) * kBN + bcl];
+        if (COLS != kPulledBack) {
+          *reinterpret_cast<vec *>(dst) = s.b[q];
+        } else {
+#pragma unroll
+          for (int e = 0; e < kV; ++e) dst[e] = s.b[q][e];
+        }
+      }
+    }
+  };
+  auto read = [&](int buf, int, int t, Ops &o) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < G::WM; ++i) K::read_a(&Us[buf * kUBuf + (wr * G::WM + i) * 32 * kUP], lane, t, o.a[i]);
+#pragma unroll
+    for (int j = 0; j < G::WN; ++j) K::read_b(&Bs[buf * kBBuf + (wc * G::WN + j) * 32], kBN, lane, t, o.b[j]);
+  };
+  auto mma = [&](const Ops &o) __attribute__((always_inline)) {
+#pragma unroll
+    for (int q = 0; q < K::kChain; ++q)
+#pragma unroll
+      for (int i = 0; i < G::WM; ++i)
+#pragma unroll
+        for (int j = 0; j < G::WN; ++j) K::mma_link(o.a[i], o.b[j], q, acc[i][j]);
+  };
+#pragma unroll
+  for (int i = 0; i < G::WM; ++i)
+#pragma unroll
+    for (int j = 0; j < G::WN; ++j) K::clear(acc[i][j]);
+  const int v_hi = imin(nk, nvec), l_lo = imax(kt_lo, nvec);
+  if (kt_lo < v_hi) {
+    sweep_ahead<Ops, Stage>(kt_lo, v_hi, load, store, read, mma);
+    if (l_lo < nk) __syncthreads();
+  }
+  if (l_lo < nk) sweep_groups<Ops, Stage>(l_lo, nk, load_last, store, read, mma);
+}
+
+// One 32 x 32 sub-tile of U(:, ka..kb-1) B(ka..kb-1, :) with operands straight from memory, small rather than fast: what a
+// sub-tile with a non-finite element is evaluated by again.  The tiles multiply the zeros left of the diagonal with
+// whatever B holds there, and the split turns an infinity into NaN; here the 32 x 32 square on the diagonal is evaluated
+// element by element and the rest, where no element is masked, with the matrix instructions of the element type,
+// so that Inf and NaN reach exactly the elements that IEEE arithmetic takes them to.
+// (A function of its own, called with scalars and returning in registers: inlined it costs the sweeps their registers.)
+template <typename T>
+__device__ __attribute__((noinline)) typename Core<T>::Acc plain_sub_tile(Problem<T> p, int64_t row0, int64_t col0, int64_t ka, int64_t kb, int lane) {
+  typedef Core<T> K;
+  typename K::Acc acc;
+  K::clear(acc);
+  const int64_t kd = row0 + 32 < kb ? row0 + 32 : kb, ks = kd > ka ? kd : ka;
+#pragma unroll 1
+  for (int64_t k0 = ks; k0 < kb; k0 += K::kGroup) {
+    typename K::Ops o;
+#pragma unroll
+    for (int q = 0; q < K::kOps; ++q) {
+      const int64_t k = k0 + K::op_index(lane, q), kc = k < kb ? k : kb - 1;
+      const int64_t i = row0 + K::op_row(lane, q) < p.n ? row0 + K::op_row(lane, q) : p.n - 1;
+      const int64_t c = col0 + K::op_row(lane, q) < p.m ? col0 + K::op_row(lane, q) : p.m - 1;
+      const T x = p.U[tri_row_start(p.n, i) - i + kc], y = p.B[kc * p.ldb + c];
+      o.a[q] = k < kb ? x : T(0);
+      o.b[q] = k < kb ? y : T(0);
+    }
+    K::mma(o, acc);
+  }
+  K::update(acc, lane, [&](int r, int c, T v) {
+    const int64_t i = row0 + r, col = col0 + c;
+    if (i < p.n && col < p.m) {
+      const T *u = p.U + (tri_row_start(p.n, i) - i);
+      for (int64_t k = i > ka ? i : ka; k < kd; ++k) v += u[k] * p.B[k * p.ldb + col];
+    }
+    return v;
+  });
+  return acc;
+}
+
+// Adds (or, with one share, stores) a 32 x 32 sub-tile; columns left of cmin are another block's.
+template <typename T>
+__device__ inline void put_tile(const Problem<T> &p, const typename Core<T>::Acc &acc, int64_t row0, int64_t col0, int64_t cmin, int lane) {
+  Core<T>::for_each(acc, lane, [&](int r, int c, T v) {
+    const int64_t row = row0 + r, col = col0 + c;
+    if (row < p.n && col < p.m && col >= cmin) {
+      if (p.S > 1)
+        unsafeAtomicAdd(&p.C[row * p.ldc + col], v);
+      else
+        p.C[row * p.ldc + col] = v;
+    }
+  });
+}
+
+// First column of column block cb: the last block of a C at least one tile wide is moved left until it is whole.
+template <typename G>
+__device__ inline int64_t first_column(int64_t m, int cb) {
+  const int64_t c = (int64_t)cb * G::kBN;
+  return c + G::kBN <= m ? c : (m > G::kBN ? m - G::kBN : 0);
+}
+
+template <typename T, typename G, int WAVES, Columns COLS>
+__global__ __launch_bounds__(G::kThreads) __attribute__((amdgpu_waves_per_eu(WAVES))) void trmm_native_kernel(Problem<T> p) {
+  __shared__ __attribute__((aligned(16))) T shared[kNativeShared<T, G>];
+  Share s;
+  if (!my_share<G::kBM, Core<T>::kKT>(p, s)) return;
+  const int lane = threadIdx.x & 63, wave = uniform32((int)threadIdx.x >> 6);
+  const int64_t col0 = first_column<G>(p.m, s.cb), cmin = (int64_t)s.cb * G::kBN;
+#pragma unroll 1
+  for (int which = 0; which < 2; ++which) {
+    if (s.blk[which] >= p.nb || s.lo[which] >= s.hi[which]) continue;
+    const int64_t i0 = (int64_t)s.blk[which] * G::kBM;
+    typename Core<T>::Acc acc[G::WM][G::WN];
+    __syncthreads();  // the previous piece's last reads of buffer 0 are done
+    native_piece<T, G, COLS>(p, shared, i0, col0, s.lo[which], s.hi[which], acc);
+#pragma unroll
+    for (int i = 0; i < G::WM; ++i)
+#pragma unroll
+      for (int j = 0; j < G::WN; ++j)
+      {
+        const int64_t row = i0 + ((wave / G::WC) * G::WM + i) * 32, col = col0 + ((wave % G::WC) * G::WN + j) * 32;
+        const int64_t ka = i0 + (int64_t)s.lo[which] * Core<T>::kKT, kb = i0 + (int64_t)s.hi[which] * Core<T>::kKT;
+        if (__any(Core<T>::non_finite(acc[i][j], lane, p.m - col))) acc[i][j] = plain_sub_tile<T>(p, row, col, ka, kb < p.n ? kb : p.n, lane);
+        put_tile<T>(p, acc[i][j], row, col, cmin, lane);
+      }
+  }
+}
+
+// The split product.  A step's 32 values of k are staged as bf16 parts, [part][row or column][32 k], 64 bytes a row with
+// its four 16-byte pieces permuted by the row number so that eight consecutive rows read from all banks.  U's pieces (four
+// k of a row per thread) and B's (eight k of a column per thread: a wavefront loads 256 contiguous bytes of each row of B
+// and the transposition costs nothing) are requested one step ahead of their conversion, which runs beside the matrix
+// instructions of the step before.  The operands of the first group's largest product are read before the last
+// twelve matrix instructions of the previous step, behind the barrier, so that the matrix cores have work while the
+// first reads of a step come back.
+// DUAL: the five smaller products have an accumulator of their own (where the registers allow it: 64 x 64 tiles).
+template <typename G, bool DUAL>
+__global__ __launch_bounds__(G::kThreads) __attribute__((amdgpu_waves_per_eu(2))) void trmm_split_kernel(Problem<float> pr) {
+  constexpr int kBM = G::kBM, kBN = G::kBN, kKT = 32, kTh = G::kThreads, WM = G::WM, WN = G::WN;
+  constexpr int kDiagSteps = kBM / kKT;
+  constexpr int kURows = kTh / 8, kPU = kBM / kURows;  // four k of a row per thread and pass
+  constexpr int kPB = kBN * 4 / kTh;                   // (column, eight k) pieces per thread
+  static_assert(kBM % kURows == 0 && kBN * 4 % kTh == 0 && kBN >= 64, "whole passes stage a step, a wavefront takes one group of k");
+  typedef unsigned short Parts16[3][(kBM + kBN) * kKT];  // part, then rows of U and columns of B
+  __shared__ __attribute__((aligned(16))) Parts16 parts[2];
+  auto place = [](int row, int piece) { return row * kKT + ((piece ^ ((row >> 1) & 3)) << 3); };
+
+  Share s;
+  if (!my_share<kBM, kKT>(pr, s)) return;
+  const int64_t n = pr.n, m = pr.m, ldb = pr.ldb;
+  const int tid = threadIdx.x, lane = tid & 63, wave = uniform32(tid >> 6);
+  const int wr = wave / G::WC, wc = wave % G::WC;
+  const int64_t col0 = first_column<G>(m, s.cb), cmin = (int64_t)s.cb * kBN;
+  const int ur = tid >> 3, uk = (tid & 7) * 4;
+  int bcol[kPB], bg[kPB];
+  unsigned boff[kPB];  // byte offset of the thread's column; columns past the last repeat it
+#pragma unroll
+  for (int q = 0; q < kPB; ++q) {
+    const int e = tid + q * kTh;
+    bcol[q] = e % kBN, bg[q] = uniform32((e / kBN) & 3);
+    boff[q] = 4u * (unsigned)(col0 + bcol[q] < m ? col0 + bcol[q] : m - 1);
+  }
+  struct Stage {
+    f4a u[kPU];
+    float b[kPB][8];
+  };
+  struct Plane {
+    u4v a[WM], b[WN];
+  };
+
+#pragma unroll 1
+  for (int which = 0; which < 2; ++which) {
+    if (s.blk[which] >= pr.nb || s.lo[which] >= s.hi[which]) continue;
+    const int64_t i0 = (int64_t)s.blk[which] * kBM;
+    const int kt_lo = s.lo[which], nk = s.hi[which];
+    const int nw = imin(nk, (int)((n - i0) / kKT));  // steps [kt_lo, nw) end inside the matrix; at most one more does not
+    const float *ub = pr.U + (tri_row_start(n, i0) - i0);
+    unsigned uoff[kPU];
+    int ir[kPU];
+#pragma unroll
+    for (int p = 0; p < kPU; ++p) {
+      const int64_t i = i0 + ur + p * kURows < n ? i0 + ur + p * kURows : n - 1;
+      ir[p] = (int)(i - i0);
+      uoff[p] = 4u * (unsigned)((tri_row_start(n, i) - i) - (tri_row_start(n, i0) - i0) + uk);
+    }
+    auto load_whole = [&](int kt, Stage &st) __attribute__((always_inline)) {
+      const int64_t k0 = i0 + (int64_t)kt * kKT;
+      const char *base = reinterpret_cast<const char *>(ub + k0);
+#pragma unroll
+      for (int p = 0; p < kPU; ++p) st.u[p] = *reinterpret_cast<const f4u *>(base + uoff[p]);
+#pragma unroll
+      for (int q = 0; q < kPB; ++q) {
+        const float *row = pr.B + (k0 + 8 * bg[q]) * ldb;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) st.b[q][j] = *reinterpret_cast<const float *>(reinterpret_cast<const char *>(row + j * ldb) + boff[q]);
+      }
+    };
+    // the ragged last step: addresses clamped into the row, values selected
+    auto load_ragged = [&](Stage &st) __attribute__((always_inline)) {
+      const int64_t k0 = i0 + (int64_t)(nk - 1) * kKT;
+      const int left = (int)(n - k0);
+#pragma unroll
+      for (int p = 0; p < kPU; ++p) {
+        const float *row = reinterpret_cast<const float *>(reinterpret_cast<const char *>(ub + k0) + uoff[p]) - uk;  // at k0
+        const int lo = ir[p] - (nk - 1) * kKT;  // the row's first k, relative to k0
+#pragma unroll
+        for (int e = 0; e < 4; ++e) st.u[p][e] = row[uk + e < lo ? lo : (uk + e < left ? uk + e : left - 1)];
+      }
+#pragma unroll
+      for (int q = 0; q < kPB; ++q)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const int k = 8 * bg[q] + j < left ? 8 * bg[q] + j : left - 1;
+          st.b[q][j] = *reinterpret_cast<const float *>(reinterpret_cast<const char *>(pr.B + (k0 + k) * ldb) + boff[q]);
+        }
+#pragma unroll
+      for (int p = 0; p < kPU; ++p)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) st.u[p][e] = (uk + e >= ir[p] - (nk - 1) * kKT && uk + e < left) ? st.u[p][e] : 0.0f;
+#pragma unroll
+      for (int q = 0; q < kPB; ++q)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) st.b[q][j] = 8 * bg[q] + j < left ? st.b[q][j] : 0.0f;
+    };
+    auto convert = [&](int buf, const Stage &st) __attribute__((always_inline)) {
+#pragma unroll
+      for (int p = 0; p < kPU; ++p) {
+        const int row = ur + p * kURows, at = place(row, uk >> 3) + (uk & 4);
+        u2v h, md, lw;
+        unsigned x, y, z;
+        split3(st.u[p][0], st.u[p][1], x, y, z);
+        h[0] = x, md[0] = y, lw[0] = z;
+        split3(st.u[p][2], st.u[p][3], x, y, z);
+        h[1] = x, md[1] = y, lw[1] = z;
+        *reinterpret_cast<u2v *>(&parts[buf][0][at]) = h;
+        *reinterpret_cast<u2v *>(&parts[buf][1][at]) = md;
+        *reinterpret_cast<u2v *>(&parts[buf][2][at]) = lw;
+      }
+#pragma unroll
+      for (int q = 0; q < kPB; ++q) {
+        const int at = kBM * kKT + place(bcol[q], bg[q]);
+        const Parts p = split3x8(st.b[q]);
+#pragma unroll
+        for (int x = 0; x < 3; ++x) *reinterpret_cast<u4v *>(&parts[buf][x][at]) = p.v[x];
+      }
+    };
+    auto mask = [&](int kt, Stage &st) __attribute__((always_inline)) {  // left of the diagonal
+      if (kt >= kDiagSteps) return;
+#pragma unroll
+      for (int p = 0; p < kPU; ++p)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) st.u[p][e] = kt * kKT + uk + e >= ir[p] ? st.u[p][e] : 0.0f;
+    };
+    typename Core<float>::Acc hi[WM][WN], lo[WM][WN];
+#pragma unroll
+    for (int i = 0; i < WM; ++i)
+#pragma unroll
+      for (int j = 0; j < WN; ++j) Core<float>::clear(hi[i][j]), Core<float>::clear(lo[i][j]);
+    auto read = [&](int buf, int t, int part, Plane &o) __attribute__((always_inline)) {
+#pragma unroll
+      for (int i = 0; i < WM; ++i)
+        o.a[i] = *reinterpret_cast<const u4v *>(&parts[buf][part][place((wr * WM + i) * 32 + (lane & 31), 2 * t + (lane >> 5))]);
+#pragma unroll
+      for (int j = 0; j < WN; ++j)
+        o.b[j] = *reinterpret_cast<const u4v *>(&parts[buf][part][kBM * kKT + place((wc * WN + j) * 32 + (lane & 31), 2 * t + (lane >> 5))]);
+    };
+    auto mma = [&](const Plane &a, const Plane &b, bool largest) __attribute__((always_inline)) {
+#pragma unroll
+      for (int i = 0; i < WM; ++i)
+#pragma unroll
+        for (int j = 0; j < WN; ++j) {
+          f16v &acc = (DUAL && !largest) ? lo[i][j].v : hi[i][j].v;
+          acc = mma_bf16(a.a[i], b.b[j], acc);
+        }
+    };
+    Stage s0, s1;
+    Plane h0, h1, md, lw;
+    // The next loads are requested first and converted a whole step later; past the last step they repeat it.
+    auto step = [&](int kt, int buf, Stage &freed, Stage &next, auto masked) __attribute__((always_inline)) {
+      load_whole(imin(kt + 2, nw - 1), freed);
+      read(buf, 0, 1, md);
+      read(buf, 0, 2, lw);
+      if (decltype(masked)::value) mask(kt + 1, next);
+      convert(buf ^ 1, next);
+      mma(h0, h0, true);
+      mma(h0, md, false);
+      mma(md, h0, false);
+      mma(md, md, false);
+      read(buf, 1, 0, h1);
+      mma(h0, lw, false);
+      mma(lw, h0, false);
+      read(buf, 1, 1, md);
+      read(buf, 1, 2, lw);
+      mma(h1, h1, true);
+      mma(h1, md, false);
+      mma(md, h1, false);
+      __syncthreads();
+      read(buf ^ 1, 0, 0, h0);
+      mma(md, md, false);
+      mma(h1, lw, false);
+      mma(lw, h1, false);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    __syncthreads();  // the previous piece is done with LDS
+    if (kt_lo < nw) {
+      load_whole(kt_lo, s0);
+      load_whole(imin(kt_lo + 1, nw - 1), s1);
+      mask(kt_lo, s0);
+      convert(0, s0);
+      __syncthreads();
+      read(0, 0, 0, h0);
+      int kt = kt_lo;
+      // small tiles run one loop with the mask's test in it: less code to fetch (a launch starts with cold instruction caches)
+      for (const int hi_masked = WM * WN == 1 ? nw : imin(nw, kDiagSteps); kt + 1 < nw && kt + 1 < hi_masked; kt += 2) {
+        step(kt, 0, s0, s1, std::true_type{});
+        step(kt + 1, 1, s1, s0, std::true_type{});
+      }
+      if (WM * WN > 1) {
+        for (; kt + 1 < nw; kt += 2) {
+          step(kt, 0, s0, s1, std::false_type{});
+          step(kt + 1, 1, s1, s0, std::false_type{});
+        }
+      }
+      if (kt < nw) step(kt, 0, s0, s1, std::true_type{});
+      if (nk > nw) __syncthreads();
+    }
+    if (nk > nw) {
+      load_ragged(s0);
+      convert(0, s0);
+      __syncthreads();
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        read(0, t, 0, h0);
+        read(0, t, 1, md);
+        read(0, t, 2, lw);
+        mma(h0, h0, true);
+        mma(h0, md, false);
+        mma(md, h0, false);
+        mma(md, md, false);
+        mma(h0, lw, false);
+        mma(lw, h0, false);
+      }
+    }
+
+    const int64_t ka = i0 + (int64_t)kt_lo * kKT, kb = i0 + (int64_t)nk * kKT < n ? i0 + (int64_t)nk * kKT : n;
+#pragma unroll
+    for (int i = 0; i < WM; ++i)
+#pragma unroll
+      for (int j = 0; j < WN; ++j) {
+        const int64_t row = i0 + (wr * WM + i) * 32, col = col0 + (wc * WN + j) * 32;
+        if (DUAL) hi[i][j].v += lo[i][j].v;
+        const bool bad = Core<float>::non_finite(hi[i][j], lane, m - col);
+        hi[i][j].v *= kSplitDown;
+        if (__any(bad)) hi[i][j] = plain_sub_tile<float>(pr, row, col, ka, kb, lane);
+        put_tile<float>(pr, hi[i][j], row, col, cmin, lane);
+      }
   }
 }
 
@@ -198,9 +565,75 @@ inline int trmv_contiguous(int64_t n, const double *Up, const double *x, double 
   return dastac_trmv_f64(n, Up, x, y, stream);
 }
 
+// Shares per pair: the S with the least estimated time, in microseconds.  c workgroups on a compute unit take max(c, alone)
+// times the steps of one (alone: what one workgroup by itself leaves of a compute unit's rate unused); every `slots` of
+// them pay 1.5 for first loads and last atomics; more than one share pays 4 for the launch that clears C and its atomics,
+// which land at 4.3e11 a second (fp64, n=1500, m=100: 17.9 us at S=12, 23.4 at 24, for 1.8e6 more of them).
+struct Pace {
+  double step, alone;  // microseconds per step of one workgroup, and see above
+  int64_t slots;       // workgroups a compute unit holds
+};
+int64_t choose_shares(int64_t base, int64_t steps, int64_t elements, int64_t cus, const Pace &pace) {
+  int64_t best = 1;
+  double least = 0.0;
+  for (int64_t S = 1; S <= 64 && 2 * S <= steps; ++S) {
+    const int64_t c = ceil_div(base * S, cus);
+    const double busy = (double)c > pace.alone ? (double)c : pace.alone;
+    double us = busy * (double)steps / (double)S * pace.step + 1.5 * (double)ceil_div(c, pace.slots);
+    if (S > 1) us += 4.0 + (double)S * (double)elements / 4.3e5;
+    if (S == 1 || us < 0.98 * least) best = S, least = us;
+  }
+  return best;
+}
+
+template <typename G, typename T, typename Kernel>
+int launch(Kernel kernel, Problem<T> p, int64_t step, int64_t cus, const Pace &pace, hipStream_t st) {
+  p.nb = (int)ceil_div(p.n, G::kBM);
+  p.npairs = (p.nb + 1) / 2;
+  const int64_t ncb = ceil_div(p.m, G::kBN), base = p.npairs * ncb;
+  if (base > 0x1000000) return DASTAC_EOVERFLOW;
+  p.ncb = (int)ncb;
+  p.S = (int)choose_shares(base, ceil_div(p.n, step) + G::kBM / step, p.n * p.m, cus, pace);
+  if (p.S > 1) {
+    const int64_t zb = ceil_div(p.n * ceil_div(p.m, 16 / (int64_t)sizeof(T)), 256);
+    zero_matrix_kernel<T><<<(unsigned)(zb < 4096 ? zb : 4096), 256, 0, st>>>(p.C, p.n, p.m, p.ldc);
+    if (hipGetLastError() != hipSuccess) return DASTAC_EHIP;
+  }
+  kernel<<<(unsigned)(8 * ceil_div(base * p.S, 8)), G::kThreads, 0, st>>>(p);
+  return launch_status();
+}
+
+typedef Tile<4, 1, 1, 1> Narrow;  // 128 x 32
+typedef Tile<2, 2, 1, 1> Small;   // 64 x 64
+typedef Tile<2, 2, 1, 2> Wide;    // 64 x 128
+typedef Tile<4, 2, 2, 2> Large;   // 256 x 128
+
+template <typename T, typename G, int WAVES>
+int launch_native(const Problem<T> &p, int64_t cus, const Pace &pace, hipStream_t st) {
+  constexpr int kV = Core<T>::kVec;
+  if (p.m >= G::kBN || p.m % kV == 0) return launch<G>(trmm_native_kernel<T, G, WAVES, kAligned>, p, Core<T>::kKT, cus, pace, st);
+  if (p.m >= kV) return launch<G>(trmm_native_kernel<T, G, WAVES, kPulledBack>, p, Core<T>::kKT, cus, pace, st);
+  return launch<G>(trmm_native_kernel<T, G, WAVES, kFew>, p, Core<T>::kKT, cus, pace, st);
+}
+
+// Tile by columns and work.  Up to 32 columns the pass over U is the work: 128 x 32, three workgroups per compute unit.  The
+// split product's 64 x 64 tiles and 256 x 128 tiles cross at n*n*m of about 1e10 (us: n=4096, m=300 53 and 63; n=8192, m=100 84 and
+// 85; n=8192, m=256 152 and 122; n=16384, m=256 388 with large tiles, 540 on the fp32 cores), the large ones only where C fills
+// more than half of their columns (n=16384, m=48: 167 and 228).
+int run_tiles(const Problem<float> &p, int64_t cus, hipStream_t st) {
+  if (p.m <= Narrow::kBN) return launch_native<float, Narrow, 3>(p, cus, {0.47, 1.6, 3}, st);
+  if (p.m > 64 && (double)p.n * (double)p.n * (double)p.m > 1e10) return launch<Large>(trmm_split_kernel<Large, false>, p, 32, cus, {2.9, 1.0, 1}, st);
+  return launch<Small>(trmm_split_kernel<Small, true>, p, 32, cus, {0.35, 1.3, 2}, st);
+}
+// fp64 (us, 64 x 64 and 64 x 128): n=4096, m=300 145 and 142; n=8192, m=100 157 and 170; n=16384, m=256 1097 and 1053.
+int run_tiles(const Problem<double> &p, int64_t cus, hipStream_t st) {
+  if (p.m <= Narrow::kBN) return launch_native<double, Narrow, 3>(p, cus, {0.47, 1.6, 3}, st);
+  if (p.m > 64 && (double)p.n * (double)p.n * (double)p.m > 2e10) return launch_native<double, Wide, 2>(p, cus, {1.0, 1.3, 2}, st);
+  return launch_native<double, Small, 3>(p, cus, {0.5, 1.2, 3}, st);
+}
+
 template <typename T>
 int run(int64_t n, int64_t m, const T *Up, const T *B, int64_t ldb, T *C, int64_t ldc, void *stream) {
-  constexpr int kBM = kTileM, kBN = kTileN, kKT = Core<T>::kKT, kBlock = kTileThreads;
   constexpr int64_t kB = (int64_t)sizeof(T);
   if (n < 0 || m < 1 || ldb < m || ldc < m) return DASTAC_EINVAL;
   if (n > (1 << 24) || m > (1 << 24) || ld_too_large(ldb, ldc)) return DASTAC_EOVERFLOW;
@@ -210,52 +643,12 @@ int run(int64_t n, int64_t m, const T *Up, const T *B, int64_t ldb, T *C, int64_
   if (overlaps(C, cb, Up, tri(n) * kB) || overlaps(C, cb, B, view_bytes(n, ldb, m, kB))) return DASTAC_EALIAS;
   // one contiguous right-hand side is the matrix-vector product
   if (m == 1 && ldb == 1 && ldc == 1) return trmv_contiguous(n, Up, B, C, stream);
-  // few right-hand sides on a tall triangle: the streaming kernel (one pass over U per 32 columns)
-  if (m <= 64 && n >= 1024) return trmm_few_columns(n, m, Up, B, ldb, C, ldc, stream);
-  const int nb = (int)ceil_div(n, kBM);
-  const int npairs = (nb + 1) / 2;
-  const int ncb = (int)ceil_div(m, kBN);
-  const int64_t base = (int64_t)8 * ceil_div(npairs, 8) * ncb;
-  if (base > 0x7fffffff) return DASTAC_EOVERFLOW;
-  hipStream_t st = (hipStream_t)stream;
-  // Shares of the k range per pair: the smallest S <= 16, with at least 32 k-steps per share, whose
-  // workgroups come in whole layers of two per compute unit (fp32, n = 16384: m = 128 58 -> 111 TFLOP/s, m = 384
-  // 93 -> 120; n = 8192, m = 256 114).  In fp32, where the column blocks alone give one full layer of one
-  // workgroup per compute unit (m = 256 at n = 16384), a second layer gains nothing (0.57 ms either way, the
-  // clearing of C included): no reason to give up plain stores and one writer per element, so S = 1 there.  In fp64 the
-  // second layer pays at every shape measured (n = 16384: m = 256 1.19 -> 1.12 ms, m = 128 0.63 -> 0.59;
-  // n = 8192, m = 256 0.32 -> 0.29), so there is no such exception; with two shares an element of C still gets
-  // at most two addends, whose sum does not depend on their order.
   int dev = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
     return DASTAC_EHIP;
-  const int64_t steps = ceil_div(n, kKT) + kBM / kKT;  // k-steps of a pair, about
-  const bool one_layer_is_enough = sizeof(T) == 4 && (double)base / (double)(ceil_div(base, cus) * cus) >= 0.95;
-  int64_t S = 1;
-  if (!one_layer_is_enough) {
-    const int64_t layer = 2 * (int64_t)cus;
-    double best = 0.0;
-    for (int64_t s = 1; s <= 16 && (s == 1 || steps / s >= 32); ++s) {
-      const int64_t wgs = base * s;
-      const double fill = (double)wgs / (double)(ceil_div(wgs, layer) * layer);
-      if (fill > best + 0.02) best = fill, S = s;
-      if (fill >= 0.95) break;
-    }
-  }
-  if (S <= 1) {
-    // workgroups that share a compute unit (n = 16384: m >= 512): the pinned schedule, 0.76 -> 0.82 of peak there
-    if (sizeof(T) == 4 && base > cus)
-      trmm_mfma_kernel<T, false, true><<<(unsigned)base, kBlock, 0, st>>>(n, m, Up, B, ldb, C, ldc, nb, npairs, ncb, 1);
-    else
-      trmm_mfma_kernel<T, false, false><<<(unsigned)base, kBlock, 0, st>>>(n, m, Up, B, ldb, C, ldc, nb, npairs, ncb, 1);
-    return launch_status();
-  }
-  const int64_t zb = ceil_div(n * ceil_div(m, 16 / kB), 256);
-  zero_matrix_kernel<T><<<(unsigned)(zb < 4096 ? zb : 4096), 256, 0, st>>>(C, n, m, ldc);
-  if (hipGetLastError() != hipSuccess) return DASTAC_EHIP;
-  trmm_mfma_kernel<T, true, false><<<(unsigned)(base * S), kBlock, 0, st>>>(n, m, Up, B, ldb, C, ldc, nb, npairs, ncb, (int)S);
-  return launch_status();
+  Problem<T> p{n, m, Up, B, ldb, C, ldc, 0, 0, 0, 1};
+  return run_tiles(p, cus, (hipStream_t)stream);
 }
 
 }  // namespace
@@ -265,7 +658,7 @@ extern "C" int dastac_trmm_f32(int64_t n, int64_t m, const float *Up, const floa
   return run<float>(n, m, Up, B, ldb, C, ldc, stream);
 }
 
-// Double precision (the paper's element type): the same kernel on the fp64 matrix cores.
+// Double precision (the paper's element type): the same tiles on the fp64 matrix cores.
 extern "C" int dastac_trmm_f64(int64_t n, int64_t m, const double *Up, const double *B, int64_t ldb, double *C,
                                int64_t ldc, void *stream) {
   return run<double>(n, m, Up, B, ldb, C, ldc, stream);

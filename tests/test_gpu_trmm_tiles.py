@@ -1,0 +1,81 @@
+"""TRMM at the edges of its tiles and of the three-part split that carries the single-precision product: remainders of every
+tile in rows, columns and steps, the large tiles, and operands that the split cannot hold."""
+import numpy as np
+import pytest
+
+from paper_2407_13726_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+def tri(n):
+    return n * (n + 1) // 2
+
+
+def run(gpu, dtype, n, m, Up, B, pad):
+    t = gpu.torch.float32 if dtype == "f32" else gpu.torch.float64
+    C = gpu.torch.full((n, m + pad), float("nan"), dtype=t, device=gpu.dev)
+    getattr(gpu.d, "trmm_" + dtype)(n, m, gpu.up(Up), gpu.up(B), m, C, m + pad)
+    out = gpu.down(C)
+    assert np.isnan(out[:, m:]).all(), "padding columns were written"
+    return out[:, :m]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("n,m,pad", [(1, 33, 0), (31, 1, 2), (63, 2, 0), (64, 64, 1), (65, 65, 0), (127, 3, 0), (128, 127, 3),
+                                     (129, 129, 0), (255, 31, 1), (256, 40, 0), (257, 63, 0), (417, 33, 5), (1025, 130, 0)])
+def test_tile_remainders(gpu, oracle, dtype, n, m, pad):
+    ref = oracle.trmm if dtype == "f32" else oracle.trmm_f64
+    draw = inputs.uniform if dtype == "f32" else inputs.uniform64
+    Up, B = draw(901, tri(n)), np.ascontiguousarray(draw(902, n * m).reshape(n, m))
+    want, scale = ref(n, m, Up, B)
+    got = run(gpu, dtype, n, m, Up, B, pad)
+    assert (np.abs(got - want) <= (1e-4 if dtype == "f32" else 1e-12) * scale).all()
+    # small integers: every product and partial sum is exact, also in the parts of the split
+    Ui, Bi = inputs.small_int(903, -8, 8, tri(n)).astype(Up.dtype), inputs.small_int(904, -8, 8, n * m).astype(Up.dtype).reshape(n, m)
+    want, _ = ref(n, m, Ui, Bi)
+    assert np.array_equal(run(gpu, dtype, n, m, Ui, Bi, pad), want)
+
+
+@pytest.mark.parametrize("n,m", [(9003, 129), (12300, 70)])
+def test_large_tiles_exact_on_integers(gpu, oracle, n, m):
+    Ui, Bi = inputs.small_int(905, -8, 8, tri(n)).astype(np.float32), inputs.small_int(906, -8, 8, n * m).astype(np.float32).reshape(n, m)
+    got = run(gpu, "f32", n, m, Ui, Bi, 1)
+    for lo, hi in ((0, 40), (n // 2 - 20, n // 2 + 20), (n - 300, n)):
+        want, _ = oracle.trmm(n, m, Ui, Bi, rows=(lo, hi))
+        assert np.array_equal(got[lo:hi], want[lo:hi] if len(want) == n else want)
+
+
+@pytest.mark.parametrize("scale_u,scale_b", [(1e-36, 1.0), (1e-30, 1e-6), (1e30, 1e-3), (3e37, 1e-20), (1e18, 1e18)])
+def test_split_holds_the_whole_range_of_a_float(gpu, oracle, scale_u, scale_b):
+    """The error stays the rounding of fp32 sums (a few times 2^-24 of the sum of magnitudes for sums of 300 terms; 1e-6
+    allows ten) at the ends of the exponent range, where the parts of an unscaled split would be lost."""
+    n, m = 300, 70
+    Up = (inputs.uniform(907, tri(n)) * np.float32(scale_u)).astype(np.float32)
+    B = (inputs.uniform(908, n * m).reshape(n, m) * np.float32(scale_b)).astype(np.float32)
+    want, scale = oracle.trmm(n, m, Up, B)
+    got = run(gpu, "f32", n, m, Up, B, 0)
+    assert np.isfinite(want).all()
+    assert (np.abs(got.astype(np.float64) - want) <= 1e-6 * scale + 1e-44).all()
+
+
+@pytest.mark.parametrize("dtype,m", [("f32", 24), ("f32", 90), ("f64", 24), ("f64", 90)])
+def test_non_finite_operands_propagate(gpu, oracle, dtype, m):
+    """Inf and NaN reach the elements whose sums hold them and no others: the rows below a non-finite row of B, whose tiles
+    multiply it with the zeros left of the diagonal, stay finite."""
+    n = 333
+    draw = inputs.uniform if dtype == "f32" else inputs.uniform64
+    Up, B = draw(909, tri(n)), draw(910, n * m).reshape(n, m).copy()
+    row = lambda i: i * n - i * (i - 1) // 2
+    Up[row(5) + 20] = np.inf
+    Up[row(100) + 7] = np.nan
+    Up[row(300)] = -np.inf
+    B[250, 3] = np.inf
+    B[17, m - 1] = np.nan
+    want, scale = (oracle.trmm if dtype == "f32" else oracle.trmm_f64)(n, m, Up, B)
+    got = run(gpu, dtype, n, m, Up, B, 0)
+    assert np.array_equal(np.isnan(got), np.isnan(want))
+    inf = np.isinf(want)
+    assert np.array_equal(got[inf], want[inf])
+    fine = np.isfinite(want)
+    assert (np.abs(got[fine] - want[fine]) <= (1e-4 if dtype == "f32" else 1e-12) * scale[fine]).all()
