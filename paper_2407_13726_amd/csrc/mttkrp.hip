@@ -252,10 +252,12 @@ __device__ inline void sweep(const Walk<T> &w, Acc<T> &acc) {
 // ratio*(a+1) block columns that reach the diagonal or lie right of it.
 __host__ __device__ inline int64_t blocks_of(int64_t P, int ratio) { return ratio * P * (P + 1) / 2; }
 
-template <typename T>
+// PARTS: a block's rows are dealt to that many wavefronts, each with a fold and an add into M of its own.
+// TILES: there is more than one column tile (kept apart: one tile pays nothing for it).
+template <typename T, int PARTS, bool TILES>
 __global__ __launch_bounds__(64 * Shape<T>::WPB) __attribute__((amdgpu_waves_per_eu(2, 2))) void mttkrp_block_kernel(
-    int64_t n, int R, const T *__restrict__ A, const T *__restrict__ Bm, int64_t ldb, const T *__restrict__ Cm,
-    int64_t ldc, T *__restrict__ M, int64_t ldm, int64_t total) {
+    int64_t n, int Rall, int ntiles, const T *__restrict__ A, const T *__restrict__ Ball, int64_t ldb, const T *__restrict__ Call,
+    int64_t ldc, T *__restrict__ Mall, int64_t ldm, int64_t total) {
   typedef Shape<T> S;
   constexpr int kC = kCols<T>, kRK = kRatio<T>, kSz = (int)sizeof(T);
   const int lane = threadIdx.x & 63, lr = lane % S::LPR, h = lane / S::LPR;
@@ -264,6 +266,18 @@ __global__ __launch_bounds__(64 * Shape<T>::WPB) __attribute__((amdgpu_waves_per
   // groups of eight consecutive orders dealt to the XCDs in alternating direction)
   const int x = (int)(blockIdx.x & 7u);
   unsigned seq = (blockIdx.x >> 3) * (unsigned)S::WPB + (unsigned)uniform32((int)(threadIdx.x >> 6));
+  // a block's column tiles (32 columns of the factor matrices each) and the parts of its rows are neighbours: what the
+  // first of them fetches of A the others find in the XCD's L2
+  int tile = 0;
+  if (TILES) {
+    tile = (int)(seq % (unsigned)ntiles);
+    seq /= (unsigned)ntiles;
+  }
+  const int sub = PARTS > 1 ? (int)(seq % PARTS) : 0;
+  seq /= (unsigned)PARTS;
+  const int R = Rall - 32 * tile < 32 ? Rall - 32 * tile : 32;
+  const T *Bm = Ball + 32 * tile, *Cm = Call + 32 * tile;
+  T *M = Mall + 32 * tile;
   const int gmax = (int)((n - 1) >> 3);  // group g holds the orders 8g+1 .. 8g+8, all ceil(m/128) = g/16+1 block rows high
   int P = gmax / 16 + 1;
   unsigned cnt = (unsigned)(gmax % 16 + 1);
@@ -287,9 +301,12 @@ __global__ __launch_bounds__(64 * Shape<T>::WPB) __attribute__((amdgpu_waves_per
 
   const int64_t i = n - m;
   const int64_t slice0 = tet_slice_start(n, i);
-  const int rhi = m - kRows * a, rlo = rhi > kRows ? rhi - kRows : 0;  // rows [rlo, rhi) of the slice triangle
+  // rows [rlo, rhi) of the slice triangle
+  const int rtop = m - kRows * (a + 1) + sub * (kRows / PARTS);
+  const int rhi = rtop + kRows / PARTS, rlo = rtop > 0 ? rtop : 0;
   const int khi = m - kC * p;                                         // k values [klo, khi)
   const int klo = khi > kC ? khi - kC : 0;  // (the leftmost block is shifted right to start at 0)
+  if (PARTS > 1 && (rhi <= 0 || rlo >= khi)) return;  // above the slice, or wholly left of the diagonal
   // rows [rlo, rfull) lie wholly above the diagonal and span the full width; rows from rdead on are all left of it
   const int rdead = rhi < khi ? rhi : khi;
   const int rfull = khi - klo == kC ? (klo < rdead ? (klo > rlo ? klo : rlo) : rdead) : rlo;
@@ -427,15 +444,23 @@ int run(int64_t n, int64_t R, const T *Ap, const T *B, int64_t ldb, const T *C, 
   const int64_t gmax = (n - 1) / 8, Ptop = gmax / 16 + 1;
   // sum of P(P+1)/2 over P = 1..Ptop-1 is Tet(Ptop-1)
   const int64_t per_xcd = (gmax % 16 + 1) * blocks_of(Ptop, kRatio<T>) + 16 * kRatio<T> * tet(Ptop - 1);
-  if (8 * per_xcd >= ((int64_t)1 << 31)) return DASTAC_EOVERFLOW;
-  // the kernel takes up to 32 columns of the factor matrices; wider ones go block by block (each
-  // block reads the packed tetrahedron once)
-  for (int64_t c0 = 0; c0 < R; c0 += 32) {
-    const int Rb = (int)(R - c0 < 32 ? R - c0 : 32);
-    mttkrp_block_kernel<T><<<(unsigned)(8 * ceil_div(per_xcd, Shape<T>::WPB)), 64 * Shape<T>::WPB, 0, st>>>(n, Rb, Ap, B + c0, ldb, C + c0, ldc, M + c0, ldm, tet(n));
-    if (hipGetLastError() != hipSuccess) return DASTAC_EHIP;
-  }
-  return DASTAC_OK;
+  if (8 * per_xcd >= ((int64_t)1 << 31) / 8) return DASTAC_EOVERFLOW;
+  // Column tiles share a launch (each launch of its own read the tetrahedron again: us, n=768, R=96 fp32 263 -> 214, fp64
+  // 407 -> 323; fp64 n=333, R=50 43.5 -> 40.6), and few blocks are cut into parts so that a wavefront's chain of
+  // steps gets short: a block of 128 rows is 25 us of latency in fp32, 13 in fp64.  us with 1, 2, 4, 8 parts, by blocks (times
+  // tiles): fp32 128 27.7 20.4 16.8 14.7; 344 26.5 18.6 16.2 14.8; 512 27.3 19.1 17.6 18.6; 1948 37.3 36.9 35.4 40.1; 2560 46.3 44.8
+  // 47.8 53.9; fp64 256 15.0 13.8 13.3 12.1; 768 16.9 16.7 14.3 14.9; 1024 19.6 17.9 21.4 21.2; 3896 40.6 49.4 47.0 61.6 (the adds of a
+  // slice's parts meet on one line of M).
+  const int64_t ntiles = ceil_div(R, 32), blocks = 8 * per_xcd * ntiles;
+  auto launch = [&](auto kernel, int64_t parts) {
+    const int64_t wgs = 8 * ceil_div(per_xcd * ntiles * parts, Shape<T>::WPB);
+    if (wgs >= ((int64_t)1 << 31)) return (int)DASTAC_EOVERFLOW;
+    kernel<<<(unsigned)wgs, 64 * Shape<T>::WPB, 0, st>>>(n, (int)R, (int)ntiles, Ap, B, ldb, C, ldc, M, ldm, tet(n));
+    return launch_status();
+  };
+  if (blocks < (sizeof(T) == 4 ? 400 : 800)) return launch(mttkrp_block_kernel<T, 8, true>, 8);
+  if (sizeof(T) == 4 && blocks < 2000) return launch(mttkrp_block_kernel<T, 4, true>, 4);
+  return ntiles == 1 ? launch(mttkrp_block_kernel<T, 1, false>, 1) : launch(mttkrp_block_kernel<T, 1, true>, 1);
 }
 
 }  // namespace
