@@ -13,6 +13,9 @@
 // with no structural zero left to skip and no index arithmetic beyond the row number: that is
 // the point of the layout.  It runs on the matrix cores, in single and in double precision.
 //
+// Single precision runs as a three-part split on the bf16 matrix cores (ttm_split_kernel below); this kernel serves double
+// precision, and single precision with Q < 4.
+//
 // Tiling.  A workgroup (8 wavefronts, 2 x 4) owns 64 packed rows x 128 values of k and sweeps l in
 // steps of kKT = 32 (fp32) or 16 (fp64); the 64 x kKT tile of Bp and the 128 x kKT tile of C are staged
 // in LDS, double-buffered against the global loads of the next step.  Both tiles keep l contiguous, so
@@ -23,6 +26,7 @@
 // XCD, so the rows of Bp they both read come from HBM once.  About two workgroups per compute unit
 // are launched; each walks a strided set of row blocks with one uninterrupted pipeline, so the
 // first loads of a row block are in flight while the previous block's last step is multiplied.
+#include "split3.h"
 #include "mfma_tile.h"
 
 using namespace dastac;
@@ -200,6 +204,219 @@ __global__ __launch_bounds__(kTileThreads) void ttm_mfma_kernel(int64_t rows, in
   }
 }
 
+// ---- single precision by the three-part split (split3.h) --------------------------------------------------------
+// The same product on the bf16 matrix cores: a workgroup of WR x WC wavefronts with WM x WN sub-tiles of 32 x 32 each walks
+// every (8*lanes)-th row block of its column block with one uninterrupted pipeline over (row block, step of 32 l).  Both
+// operands keep l contiguous: a thread stages pieces of four l of a row, split on the way into LDS, [part][row][32 l] with
+// the four 16-byte pieces of a row permuted by the row number, so that eight consecutive rows read from all banks.  The
+// requests run two steps ahead of their use and the conversion one; the last twelve matrix instructions of a step stand
+// behind the barrier, while the first operands of the next step come back.  A ragged last step reads its pieces pulled
+// back into the row and shifts them into place; rows past the last repeat it.
+template <int WR_, int WC_, int WM_, int WN_>
+struct Tile {
+  static constexpr int WR = WR_, WC = WC_, WM = WM_, WN = WN_;
+  static constexpr int kBM = 32 * WR * WM, kBN = 32 * WC * WN, kThreads = 64 * WR * WC;
+};
+
+// One 32 x 32 sub-tile in fp32, operands straight from memory: what a sub-tile with a non-finite element is evaluated by
+// again, so that Inf and NaN propagate as IEEE arithmetic has it.
+__device__ __attribute__((noinline)) Core<float>::Acc plain_sub_tile(int64_t rows, int Q, int K, const float *Bp, const float *C, int64_t ldc,
+                                                                     int64_t row0, int col0, int lane) {
+  typedef Core<float> Kc;
+  Kc::Acc acc;
+  Kc::clear(acc);
+  const float *a = Bp + (row0 + (lane & 31) < rows ? row0 + (lane & 31) : rows - 1) * Q;
+  const float *c = C + (int64_t)(col0 + (lane & 31) < K ? col0 + (lane & 31) : K - 1) * ldc;
+#pragma unroll 1
+  for (int l0 = 0; l0 < Q; l0 += Kc::kGroup) {
+    Kc::Ops o;
+#pragma unroll
+    for (int q = 0; q < Kc::kOps; ++q) {
+      const int l = l0 + Kc::op_index(lane, q), lc = l < Q ? l : Q - 1;
+      const float x = a[lc], y = c[lc];
+      o.a[q] = l < Q ? x : 0.0f;
+      o.b[q] = l < Q ? y : 0.0f;
+    }
+    Kc::mma(o, acc);
+  }
+  return acc;
+}
+
+template <typename G>
+__global__ __launch_bounds__(G::kThreads) __attribute__((amdgpu_waves_per_eu(2)))
+void ttm_split_kernel(int64_t rows, int Q, int K, const float *__restrict__ Bp, const float *__restrict__ C, int64_t ldc,
+                      float *__restrict__ Ap, int nrb, int lanes, int ncb) {
+  constexpr int kBM = G::kBM, kBN = G::kBN, kKT = 32, kTh = G::kThreads, WM = G::WM, WN = G::WN;
+  constexpr int kPass = kTh / 8, kPA = kBM / kPass, kPC = kBN / kPass;  // rows staged per pass; pieces per thread
+  static_assert(kBM % kPass == 0 && kBN % kPass == 0, "whole passes stage a step");
+  typedef unsigned short Parts16[3][(kBM + kBN) * kKT];
+  __shared__ __attribute__((aligned(16))) Parts16 parts[2];
+  auto place = [](int row, int piece) { return row * kKT + ((piece ^ ((row >> 1) & 3)) << 3); };
+
+  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+  const int cb = slot % ncb, stride = 8 * lanes;
+  const int tid = threadIdx.x, lane = tid & 63, wave = uniform32(tid >> 6);
+  const int wr = wave / G::WC, wc = wave % G::WC;
+  const int sr = tid >> 3, sl = (tid & 7) * 4;
+  const int c0 = cb * kBN, nk = (Q + kKT - 1) / kKT;
+
+  struct Cur {  // wave-uniform: row block and step
+    int rb, kt;
+  };
+  auto next = [&](Cur c) {  // past the last step: the last step again
+    Cur d{c.kt + 1 < nk ? c.rb : c.rb + stride, c.kt + 1 < nk ? c.kt + 1 : 0};
+    return d.rb < nrb ? d : c;
+  };
+  Cur cc{xcd + 8 * (slot / ncb), 0};  // the step being multiplied
+  if (cc.rb >= nrb) return;
+  int left = ((nrb - 1 - cc.rb) / stride + 1) * nk;  // steps of this workgroup
+
+  const float *cp[kPC];
+#pragma unroll
+  for (int q = 0; q < kPC; ++q) cp[q] = C + (int64_t)(c0 + sr + q * kPass < K ? c0 + sr + q * kPass : K - 1) * ldc;
+  unsigned aoff[kPA];  // the thread's rows within a row block, in elements
+#pragma unroll
+  for (int p = 0; p < kPA; ++p) aoff[p] = (unsigned)(sr + p * kPass) * (unsigned)Q;
+
+  struct Stage {
+    f4a a[kPA], c[kPC];
+  };
+  auto load = [&](const Cur &cu, Stage &s) __attribute__((always_inline)) {
+    const int64_t r0 = (int64_t)cu.rb * kBM;
+    const char *base = reinterpret_cast<const char *>(Bp + r0 * Q);
+    const unsigned lim = rows - r0 > kBM ? 0xffffffffu : (unsigned)(rows - 1 - r0) * (unsigned)Q;  // the last row's offset
+    const int l = cu.kt * kKT + sl < Q - 4 ? cu.kt * kKT + sl : Q - 4;
+#pragma unroll
+    for (int p = 0; p < kPA; ++p) s.a[p] = *reinterpret_cast<const f4u *>(base + 4u * ((aoff[p] < lim ? aoff[p] : lim) + (unsigned)l));
+#pragma unroll
+    for (int q = 0; q < kPC; ++q) s.c[q] = *reinterpret_cast<const f4u *>(cp[q] + l);
+  };
+  auto put = [&](int buf, int row, f4a v) __attribute__((always_inline)) {
+    u2v h, md, lw;
+    unsigned x, y, z;
+    split3(v[0], v[1], x, y, z);
+    h[0] = x, md[0] = y, lw[0] = z;
+    split3(v[2], v[3], x, y, z);
+    h[1] = x, md[1] = y, lw[1] = z;
+    const int at = place(row, sl >> 3) + (sl & 4);
+    *reinterpret_cast<u2v *>(&parts[buf][0][at]) = h;
+    *reinterpret_cast<u2v *>(&parts[buf][1][at]) = md;
+    *reinterpret_cast<u2v *>(&parts[buf][2][at]) = lw;
+  };
+  auto convert = [&](int buf, const Cur &cu, Stage &s) __attribute__((always_inline)) {
+    const int past = cu.kt * kKT + sl - (Q - 4);  // by how much the pieces were pulled back
+    if ((cu.kt + 1) * kKT > Q) {
+      auto shift = [&](f4a v) {
+        f4a w;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          w[e] = past <= 0 ? v[e] : 0.0f;
+#pragma unroll
+          for (int x = 1; e + x < 4; ++x) w[e] = past == x ? v[e + x] : w[e];
+        }
+        return w;
+      };
+#pragma unroll
+      for (int p = 0; p < kPA; ++p) s.a[p] = shift(s.a[p]);
+#pragma unroll
+      for (int q = 0; q < kPC; ++q) s.c[q] = shift(s.c[q]);
+    }
+#pragma unroll
+    for (int p = 0; p < kPA; ++p) put(buf, sr + p * kPass, s.a[p]);
+#pragma unroll
+    for (int q = 0; q < kPC; ++q) put(buf, kBM + sr + q * kPass, s.c[q]);
+  };
+  struct Plane {
+    u4v a[WM], b[WN];
+  };
+  auto read = [&](int buf, int t, int part, Plane &o) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < WM; ++i)
+      o.a[i] = *reinterpret_cast<const u4v *>(&parts[buf][part][place((wr * WM + i) * 32 + (lane & 31), 2 * t + (lane >> 5))]);
+#pragma unroll
+    for (int j = 0; j < WN; ++j)
+      o.b[j] = *reinterpret_cast<const u4v *>(&parts[buf][part][place(kBM + (wc * WN + j) * 32 + (lane & 31), 2 * t + (lane >> 5))]);
+  };
+  Core<float>::Acc hi[WM][WN], lo[WM][WN];  // the five smaller products have an accumulator of their own
+  auto clear = [&] {
+#pragma unroll
+    for (int i = 0; i < WM; ++i)
+#pragma unroll
+      for (int j = 0; j < WN; ++j) Core<float>::clear(hi[i][j]), Core<float>::clear(lo[i][j]);
+  };
+  auto mma = [&](const Plane &a, const Plane &b, bool largest) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < WM; ++i)
+#pragma unroll
+      for (int j = 0; j < WN; ++j) {
+        f16v &acc = largest ? hi[i][j].v : lo[i][j].v;
+        acc = mma_bf16(a.a[i], b.b[j], acc);
+      }
+  };
+  auto flush = [&](int rb) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < WM; ++i)
+#pragma unroll
+      for (int j = 0; j < WN; ++j) {
+        const int64_t row0 = (int64_t)rb * kBM + (wr * WM + i) * 32;
+        const int col0 = c0 + (wc * WN + j) * 32;
+        hi[i][j].v += lo[i][j].v;
+        const bool bad = Core<float>::non_finite(hi[i][j], lane, K - col0);
+        hi[i][j].v *= kSplitDown;
+        if (__any(bad)) hi[i][j] = plain_sub_tile(rows, Q, K, Bp, C, ldc, row0, col0, lane);
+        float *out = Ap + row0 * K + col0;
+        const int64_t rleft = rows - row0;
+        const int cleft = K - col0;
+        Core<float>::for_each(hi[i][j], lane, [&](int r, int c, float v) {
+          if (r < rleft && c < cleft) out[(int64_t)r * K + c] = v;
+        });
+      }
+    clear();
+  };
+  Stage s0, s1;
+  Plane h0, h1, md, lw;
+  clear();
+  Cur c1 = next(cc), c2 = next(c1);
+  load(cc, s0);
+  load(c1, s1);
+  convert(0, cc, s0);
+  __syncthreads();
+  read(0, 0, 0, h0);
+  auto step = [&](int buf, Stage &freed, Stage &coming) __attribute__((always_inline)) {
+    load(c2, freed);
+    read(buf, 0, 1, md);
+    read(buf, 0, 2, lw);
+    convert(buf ^ 1, c1, coming);
+    mma(h0, h0, true);
+    mma(h0, md, false);
+    mma(md, h0, false);
+    mma(md, md, false);
+    read(buf, 1, 0, h1);
+    mma(h0, lw, false);
+    mma(lw, h0, false);
+    read(buf, 1, 1, md);
+    read(buf, 1, 2, lw);
+    mma(h1, h1, true);
+    mma(h1, md, false);
+    mma(md, h1, false);
+    __syncthreads();
+    read(buf ^ 1, 0, 0, h0);
+    mma(md, md, false);
+    mma(h1, lw, false);
+    mma(lw, h1, false);
+    __builtin_amdgcn_sched_barrier(0);
+    if (cc.kt == nk - 1) flush(cc.rb);
+    cc = c1;
+    c1 = c2;
+    c2 = next(c2);
+  };
+  for (; left > 1; left -= 2) {
+    step(0, s0, s1);
+    step(1, s1, s0);
+  }
+  if (left > 0) step(0, s0, s1);
+}
+
 // ---- compression / decompression of the upper half cube ---------------------------------------
 // One workgroup per 256-element piece of one (i,j) row of the dense n x n x Q tensor.
 constexpr int kCopy = 256;
@@ -239,6 +456,32 @@ int uhc_copy(int64_t n, int64_t Q, const T *src, T *dst, void *stream) {
   return launch_status();
 }
 
+// The split's offsets within a row block are 32 bits and a piece needs four l; beyond that the fp32 matrix cores take over.
+inline bool split_serves(int64_t, int64_t Q, int64_t K, const float *) { return Q >= 4 && Q <= (1 << 20) && K <= (1 << 20); }
+inline bool split_serves(int64_t, int64_t, int64_t, const double *) { return false; }
+
+template <typename G>
+int launch_split(int64_t rows, int64_t Q, int64_t K, const float *Bp, const float *C, int64_t ldc, float *Ap, hipStream_t st) {
+  const int64_t nrb = ceil_div(rows, G::kBM), ncb = ceil_div(K, G::kBN);
+  if (nrb > 0x7fffffff || (nrb + 8) * ceil_div(Q, 32) > 0x7fffffff) return DASTAC_EOVERFLOW;
+  // at most what 256 compute units hold at once (one workgroup of eight wavefronts each, or two of four): a walker that has
+  // to wait for another to end doubles the time
+  int64_t lanes = (G::kThreads == 512 ? 256 : 512) / (8 * ncb);
+  if (lanes < 1) lanes = 1;
+  if (lanes > ceil_div(nrb, 8)) lanes = ceil_div(nrb, 8);
+  ttm_split_kernel<G><<<(unsigned)(8 * lanes * ncb), G::kThreads, 0, st>>>(rows, (int)Q, (int)K, Bp, C, ldc, Ap, (int)nrb, (int)lanes, (int)ncb);
+  return launch_status();
+}
+// Tiles by columns: 128 x 32 and 128 x 64 where C has no more (us, before: n=300, Q=512, K=16 25, 83; n=500, Q=K=64 17, 33; n=512,
+// Q=100, K=40 28, 58), else 128 x 128 with eight wavefronts (n=512, Q=K=256 130, 164 on the fp32 cores; 64 x 128 with two
+// workgroups per CU 144, 256 x 128 288: its registers spill).
+inline int ttm_split(int64_t rows, int64_t Q, int64_t K, const float *Bp, const float *C, int64_t ldc, float *Ap, hipStream_t st) {
+  if (K <= 32) return launch_split<Tile<4, 1, 1, 1>>(rows, Q, K, Bp, C, ldc, Ap, st);
+  if (K <= 64) return launch_split<Tile<4, 1, 1, 2>>(rows, Q, K, Bp, C, ldc, Ap, st);
+  return launch_split<Tile<4, 2, 1, 2>>(rows, Q, K, Bp, C, ldc, Ap, st);
+}
+inline int ttm_split(int64_t, int64_t, int64_t, const double *, const double *, int64_t, double *, hipStream_t) { return DASTAC_EINVAL; }
+
 template <typename T>
 int ttm_ut(int64_t n, int64_t Q, int64_t K, const T *Bp, const T *C, int64_t ldc, T *Ap, void *stream) {
   constexpr int64_t kB = (int64_t)sizeof(T);
@@ -249,6 +492,7 @@ int ttm_ut(int64_t n, int64_t Q, int64_t K, const T *Bp, const T *C, int64_t ldc
   const int64_t rows = tri(n);
   if (overlaps(Ap, rows * K * kB, Bp, rows * Q * kB) || overlaps(Ap, rows * K * kB, C, view_bytes(K, ldc, Q, kB)))
     return DASTAC_EALIAS;
+  if (split_serves(n, Q, K, Bp)) return ttm_split(rows, Q, K, Bp, C, ldc, Ap, (hipStream_t)stream);
   const int64_t nrb = ceil_div(rows, kTileM), ncb = ceil_div(K, kTileN);
   if (ncb > (1 << 20)) return DASTAC_EOVERFLOW;
   // about two workgroups per compute unit (256 of them), each walking a strided set of row blocks
