@@ -20,15 +20,16 @@
 // sub-tile lies below it skip their matrix instructions, and only j<=k is stored.
 //
 // For A3 the tiles are cut on a grid that is the same for every slice, and a workgroup takes its tile
-// for several consecutive slices i at once (two or four in fp32, two in fp64): the two staged tiles are shared
+// for two consecutive slices i at once: the two staged tiles are shared
 // by those slices, whose weights B(x,i) are staged beside them and multiplied onto the first operand in
-// registers, one accumulator per slice.  The global loads, LDS traffic and barriers of a step are thus
-// spent once per 64 (fp32) matrix instructions of a wavefront instead of once per 16.  A tile serves
+// registers, one accumulator per slice.  (In single precision A3 is a kernel of its own on the bf16 matrix cores,
+// pr3_split_kernel below.)  A tile serves
 // the slices i <= its last row; a wavefront whose rows all lie above the slices of the workgroup
 // (j < i) has nothing to compute.
 //
 // When the work items alone cannot fill the chip the sample range is split over several workgroups,
 // which then add into a pre-zeroed output with floating-point atomics.
+#include "split3.h"
 #include "mfma_tile.h"
 
 using namespace dastac;
@@ -42,27 +43,11 @@ constexpr int64_t kMaxD3 = 1 << 13;  // A3: the item count stays inside gridDim.
 constexpr int64_t kMaxN = (int64_t)1 << 31;
 // Up to these d the 64 x 64 tile is used: it wastes less on the diagonal and leaves more workgroups per CU,
 // which outweighs its lower operand reuse while diagonal tiles are a large share of all tiles.
-constexpr int64_t kNarrowMaxD2 = 768, kNarrowMaxD3 = 2048;
-constexpr int64_t kFewSlicesMaxD3 = 768;  // fp32 A3: two slices per workgroup up to here, four beyond
+constexpr int64_t kNarrowMaxD2 = 768, kNarrowMaxD3 = 2048;  // (D3: double precision; the split kernel has one tile)
 
 // Slices of A3 that share a workgroup's staged tiles, and how their weights reach the first operand.
 template <typename T>
 struct Slices;
-template <>
-struct Slices<float> {
-  // group t of a step: this lane's samples are 8t + 4*(lane/32) + q, q < 4; ws is [slice][sample]
-  template <int kNI, typename Ops3>
-  __device__ static void scale(const Core<float>::Ops &r, const float *ws, int lane, int t, Ops3 &o) {
-#pragma unroll
-    for (int ii = 0; ii < kNI; ++ii) {
-      const f4a w = *reinterpret_cast<const f4a *>(ws + ii * Core<float>::kKT + 8 * t + 4 * (lane >> 5));
-#pragma unroll
-      for (int q = 0; q < 4; ++q) o.a[ii][q] = r.a[q] * w[q];
-    }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) o.b[q] = r.b[q];
-  }
-};
 template <>
 struct Slices<double> {
   // group t of a step: this lane's sample is 4t + lane/16
@@ -294,12 +279,10 @@ struct Ops3 {
   T b[kNA];
 };
 
-// NI slices per workgroup: four in fp32 (two up to d = 768, where a third wavefront per SIMD is worth more than the
-// reuse: d=256 61 -> 63 TFLOP/s, d=512 82 -> 86, d=1024 104 -> 102), two in fp64.  Three wavefronts per SIMD with two
-// slices (in fp64 the register allocator reaches that with a few spilled dwords and the third wavefront gains 15 %);
-// the accumulators of four slices leave room for two.
+// NI slices per workgroup (double precision: two), three wavefronts per SIMD: the register allocator reaches that with a few
+// spilled dwords and the third wavefront gains 15 %.
 template <typename T, bool ATOMIC, int BK, int NI>
-__global__ __launch_bounds__(4 * BK) __attribute__((amdgpu_waves_per_eu(NI == 2 ? 3 : 2, NI == 2 ? 3 : 2)))
+__global__ __launch_bounds__(4 * BK) __attribute__((amdgpu_waves_per_eu(3, 3)))
 void pr3_mfma_kernel(int64_t N, int64_t d, const T *__restrict__ B, int64_t ldb, T *__restrict__ out, int64_t chunk,
                      int64_t units, int64_t split) {
   typedef Core<T> K;
@@ -397,6 +380,193 @@ void pr3_mfma_kernel(int64_t N, int64_t d, const T *__restrict__ B, int64_t ldb,
   }
 }
 
+// ---- A3 in single precision, by the three-part split (split3.h) --------------------------------------------------
+// The same units with 64 x 64 tiles and four wavefronts, on the bf16 matrix cores.  A thread stages eight samples of one
+// column of each tile (a wavefront reads 256 contiguous bytes of each sample and shares the eight samples, so the slices'
+// weights are one load, a lane each, and reach the others through scalar registers; as scalar loads they would make every
+// wait for LDS a wait for memory), multiplies the j column with each slice's weights in fp32, as the rule has it, and splits the
+// products and the k column in three: [part][column][32 samples], the four 16-byte pieces of a column permuted by its
+// number.  Requests run two steps ahead of their use, the split one, beside the matrix instructions; the last six of
+// every slice stand behind the barrier.  N=10000, d=256: 696 us (848 on the fp32 cores); of the 1970 cycles of a workgroup's step
+// the vector instructions take 1000 (the split and the products, a quarter of them for sub-tiles that are dead), LDS
+// 1050 and the matrix instructions 576.
+__device__ __attribute__((noinline)) Core<float>::Acc plain_sub_tile(const float *B, int64_t ldb, int64_t d, int64_t i, int64_t j0, int64_t k0,
+                                                                     int64_t xbeg, int64_t xend, int lane) {
+  typedef Core<float> K;
+  K::Acc acc;
+  K::clear(acc);
+  const int64_t j = j0 + (lane & 31) < d ? j0 + (lane & 31) : d - 1, k = k0 + (lane & 31) < d ? k0 + (lane & 31) : d - 1;
+#pragma unroll 1
+  for (int64_t x0 = xbeg; x0 < xend; x0 += K::kGroup) {
+    K::Ops o;
+#pragma unroll
+    for (int q = 0; q < K::kOps; ++q) {
+      const int64_t x = x0 + K::op_index(lane, q);
+      const float *row = B + (x < xend ? x : xend - 1) * ldb;
+      const float a = row[j] * row[i], b = row[k];
+      o.a[q] = x < xend ? a : 0.0f;
+      o.b[q] = x < xend ? b : 0.0f;
+    }
+    K::mma(o, acc);
+  }
+  return acc;
+}
+
+template <bool ATOMIC, int NI>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
+void pr3_split_kernel(int64_t N, int64_t d, const float *__restrict__ B, int64_t ldb, float *__restrict__ out, int64_t chunk,
+                      int64_t units, int64_t split) {
+  constexpr int kXT = 32, BK = 64, kT = 64 * kXT;  // elements of one staged tile
+  typedef unsigned short Parts16[3][(NI + 1) * kT];  // part; the slices' products, then the k columns
+  __shared__ __attribute__((aligned(16))) Parts16 parts[2];
+  auto place = [](int col, int piece) { return col * kXT + ((piece ^ ((col >> 1) & 3)) << 3); };
+
+  int64_t share, unit;
+  if (!my_item(units, split, share, unit)) return;
+  int64_t J = 0;
+  while (unit >= units_of_row_block(d, BK, NI, J)) unit -= units_of_row_block(d, BK, NI, J), ++J;
+  const int64_t nK = ceil_div(d, kBJ), firstK = J;
+  const int64_t i0 = NI * (unit / (nK - firstK));  // first slice of the group
+  const int64_t Kb = firstK + unit % (nK - firstK);
+  const int64_t xbeg = share * chunk;
+  const int64_t xend = xbeg + chunk < N ? xbeg + chunk : N;
+  if (xbeg >= xend) return;
+  const int nk = (int)ceil_div(xend - xbeg, kXT);
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = uniform32(tid >> 6);
+  const int wr = wave >> 1, wc = wave & 1;
+  const int64_t jw = J * kBJ + wr * 32, kw = Kb * BK + wc * 32;  // first row and column of this wavefront's sub-tile
+  const bool live = uniform32((kw + 31 >= jw && jw + 31 >= i0) ? 1 : 0) != 0;  // see pr3_mfma_kernel
+  const unsigned jcol = 4u * (unsigned)(J * kBJ + lane < d ? J * kBJ + lane : d - 1);
+  const unsigned kcol = 4u * (unsigned)(Kb * BK + lane < d ? Kb * BK + lane : d - 1);
+  static_assert(NI <= 8, "one lane holds one weight");
+  const int we = lane & 7, wi = lane >> 3;  // lane 8 ii + e holds the weight of slice i0 + ii for sample e
+  const int64_t icol = wi < NI && i0 + wi < d ? i0 + wi : d - 1;
+
+  struct Stage {
+    float j[8], k[8], w;
+  };
+  auto load = [&](int kt, Stage &s) __attribute__((always_inline)) {
+    const int64_t x0 = xbeg + (int64_t)kt * kXT + 8 * wave;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int64_t x = x0 + e < xend ? x0 + e : xend - 1;
+      const float *row = B + x * ldb;
+      s.j[e] = *reinterpret_cast<const float *>(reinterpret_cast<const char *>(row) + jcol);
+      s.k[e] = *reinterpret_cast<const float *>(reinterpret_cast<const char *>(row) + kcol);
+    }
+    s.w = B[(x0 + we < xend ? x0 + we : xend - 1) * ldb + icol];
+  };
+  auto put = [&](int buf, int tile, const float (&x)[8]) __attribute__((always_inline)) {
+    const Parts p = split3x8(x);
+    const int at = tile * kT + place(lane, wave);
+#pragma unroll
+    for (int y = 0; y < 3; ++y) *reinterpret_cast<u4v *>(&parts[buf][y][at]) = p.v[y];
+  };
+  auto convert = [&](int buf, int kt, Stage &s) __attribute__((always_inline)) {
+    const int left = (int)(xend - xbeg) - kt * kXT - 8 * wave;  // samples of this wavefront's eight that exist
+    if (left < 8) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        s.k[e] = e < left ? s.k[e] : 0.0f;
+        s.j[e] = e < left ? s.j[e] : 0.0f;
+      }
+      s.w = we < left ? s.w : 0.0f;
+    }
+#pragma unroll
+    for (int ii = 0; ii < NI; ++ii) {
+      float p[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) p[e] = s.j[e] * __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(s.w), 8 * ii + e));
+      put(buf, ii, p);
+    }
+    put(buf, NI, s.k);
+  };
+  struct Plane {
+    u4v a[NI], b;
+  };
+  auto read = [&](int buf, int t, int part, Plane &o) __attribute__((always_inline)) {
+#pragma unroll
+    for (int ii = 0; ii < NI; ++ii)
+      o.a[ii] = *reinterpret_cast<const u4v *>(&parts[buf][part][ii * kT + place(wr * 32 + (lane & 31), 2 * t + (lane >> 5))]);
+    o.b = *reinterpret_cast<const u4v *>(&parts[buf][part][NI * kT + place(wc * 32 + (lane & 31), 2 * t + (lane >> 5))]);
+  };
+  Core<float>::Acc hi[NI], lo[NI];  // the five smaller products have an accumulator of their own
+#pragma unroll
+  for (int ii = 0; ii < NI; ++ii) Core<float>::clear(hi[ii]), Core<float>::clear(lo[ii]);
+  auto mma = [&](const Plane &a, const Plane &b, bool largest) __attribute__((always_inline)) {
+#pragma unroll
+    for (int ii = 0; ii < NI; ++ii) {
+      f16v &acc = largest ? hi[ii].v : lo[ii].v;
+      acc = mma_bf16(a.a[ii], b.b, acc);
+    }
+  };
+  Stage s0, s1;
+  Plane h0, h1, md, lw;
+  auto upto = [&](int kt) { return kt < nk ? kt : nk - 1; };  // past the last step: that step again
+  load(0, s0);
+  load(upto(1), s1);
+  convert(0, 0, s0);
+  __syncthreads();
+  read(0, 0, 0, h0);
+  auto step = [&](int kt, int buf, Stage &freed, Stage &coming) __attribute__((always_inline)) {
+    load(upto(kt + 2), freed);
+    read(buf, 0, 1, md);
+    read(buf, 0, 2, lw);
+    convert(buf ^ 1, upto(kt + 1), coming);
+    if (live) {
+      mma(h0, h0, true);
+      mma(h0, md, false);
+      mma(md, h0, false);
+      mma(md, md, false);
+      read(buf, 1, 0, h1);
+      mma(h0, lw, false);
+      mma(lw, h0, false);
+      read(buf, 1, 1, md);
+      read(buf, 1, 2, lw);
+      mma(h1, h1, true);
+      mma(h1, md, false);
+      mma(md, h1, false);
+    }
+    __syncthreads();
+    read(buf ^ 1, 0, 0, h0);
+    if (live) {
+      mma(md, md, false);
+      mma(h1, lw, false);
+      mma(lw, h1, false);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  int kt = 0;
+  for (; kt + 1 < nk; kt += 2) {
+    step(kt, 0, s0, s1);
+    step(kt + 1, 1, s1, s0);
+  }
+  if (kt < nk) step(kt, 0, s0, s1);
+  if (!live) return;
+
+#pragma unroll
+  for (int ii = 0; ii < NI; ++ii) {
+    const int64_t i = i0 + ii, q = d - i;  // slice and the order of its triangle
+    if (i >= d) break;
+    hi[ii].v += lo[ii].v;
+    const bool bad = Core<float>::non_finite(hi[ii], lane, d - kw);
+    hi[ii].v *= kSplitDown;
+    if (__any(bad)) hi[ii] = plain_sub_tile(B, ldb, d, i, jw, kw, xbeg, xend, lane);
+    float *slice = out + tet_slice_start(d, i);
+    Core<float>::for_each(hi[ii], lane, [&](int r, int c, float v) {
+      const int64_t j = jw + r, k = kw + c;
+      if (i <= j && j <= k && k < d) {
+        float *p = slice + tri_offset(q, j - i, k - i);
+        if (ATOMIC)
+          unsafeAtomicAdd(p, v);
+        else
+          *p = v;
+      }
+    });
+  }
+}
+
 template <typename T>
 __global__ void fill_zero_kernel(T *__restrict__ y, int64_t count) {
   for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < count; t += (int64_t)gridDim.x * blockDim.x)
@@ -406,7 +576,9 @@ __global__ void fill_zero_kernel(T *__restrict__ y, int64_t count) {
 template <typename T, bool CUBE, bool ATOMIC, int BK, int NI>
 void launch(unsigned grid, hipStream_t st, int64_t N, int64_t d, const T *B, int64_t ldb, T *out, int64_t chunk,
             int64_t units, int64_t split) {
-  if (CUBE)
+  if constexpr (CUBE && sizeof(T) == 4)
+    pr3_split_kernel<ATOMIC, NI><<<grid, 4 * BK, 0, st>>>(N, d, B, ldb, out, chunk, units, split);
+  else if constexpr (CUBE)
     pr3_mfma_kernel<T, ATOMIC, BK, NI><<<grid, 4 * BK, 0, st>>>(N, d, B, ldb, out, chunk, units, split);
   else
     pr2_mfma_kernel<T, ATOMIC, BK><<<grid, 4 * BK, 0, st>>>(N, d, B, ldb, out, chunk, units, split);
@@ -432,8 +604,13 @@ int run(int64_t N, int64_t d, const T *B, int64_t ldb, T *out, void *stream) {
   // round to 90 %, or else the best one found; every share is a multiple of a step and at least 8 steps.
   int64_t split = 1, chunk = kXT;
   if (N > 0) {
-    const int64_t slots = CUBE ? resident_blocks(pr3_mfma_kernel<T, true, BK, NI>, kBlock)
-                               : resident_blocks(pr2_mfma_kernel<T, true, BK>, kBlock);
+    int64_t slots;
+    if constexpr (CUBE && sizeof(T) == 4)
+      slots = resident_blocks(pr3_split_kernel<true, NI>, kBlock);
+    else if constexpr (CUBE)
+      slots = resident_blocks(pr3_mfma_kernel<T, true, BK, NI>, kBlock);
+    else
+      slots = resident_blocks(pr2_mfma_kernel<T, true, BK>, kBlock);
     if (slots <= 0) return DASTAC_EHIP;
     const int64_t max_split = N / (8 * kXT) > 1 ? N / (8 * kXT) : 1;
     double best = -1.0;
@@ -478,9 +655,7 @@ int dastac_pr_a2_f32(int64_t N, int64_t d, const float *B, int64_t ldb, float *A
 }
 
 int dastac_pr_a3_f32(int64_t N, int64_t d, const float *B, int64_t ldb, float *A3p, void *stream) {
-  return d <= kFewSlicesMaxD3 ? run<float, true, 64, 2>(N, d, B, ldb, A3p, stream)
-         : d <= kNarrowMaxD3  ? run<float, true, 64, 4>(N, d, B, ldb, A3p, stream)
-                              : run<float, true, 128, 4>(N, d, B, ldb, A3p, stream);
+  return run<float, true, 64, 2>(N, d, B, ldb, A3p, stream);
 }
 
 // Double precision (the paper's element type): the same kernel on the fp64 matrix cores.

@@ -1,0 +1,86 @@
+"""TTM_UT and the third-order polynomial-regression tensor in single precision, which run as a three-part split on the bf16
+matrix cores: edges of their tiles and steps, the ends of the exponent range, and operands that the split cannot hold."""
+import numpy as np
+import pytest
+
+from paper_2407_13726_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+def tri(n):
+    return n * (n + 1) // 2
+
+
+def ttm(gpu, n, Q, K, Bp, C):
+    out = gpu.empty(tri(n) * K)
+    gpu.d.ttm_ut_f32(n, Q, K, gpu.up(Bp), gpu.up(C), Q, out)
+    return gpu.down(out)
+
+
+def a3(gpu, N, d, B):
+    out = gpu.empty(d * (d + 1) * (d + 2) // 6)
+    gpu.d.pr_a3_f32(N, d, gpu.up(B), d, out)
+    return gpu.down(out)
+
+
+# one row block and several, a single step and several with every kind of remainder, each tile width and its edges
+@pytest.mark.parametrize("n,Q,K", [(1, 4, 1), (3, 5, 32), (15, 31, 33), (16, 32, 64), (23, 33, 65), (40, 3, 7), (40, 66, 128), (47, 130, 129),
+                                   (61, 64, 300)])
+def test_ttm_tile_remainders(gpu, oracle, n, Q, K):
+    Bi, Ci = inputs.small_int(921, -8, 8, tri(n) * Q), inputs.small_int(922, -8, 8, K, Q)
+    assert np.array_equal(ttm(gpu, n, Q, K, Bi, Ci), oracle.ttm_ut(n, Q, K, Bi, Ci)[0].ravel())
+    B, C = inputs.uniform(923, tri(n) * Q), inputs.normal(924, K, Q)
+    want, scale = oracle.ttm_ut(n, Q, K, B, C)
+    # fp32 sums of at most 130 terms: well inside ten roundings of the sum of magnitudes
+    assert (np.abs(ttm(gpu, n, Q, K, B, C).astype(np.float64) - want.ravel()) <= 1e-6 * scale.ravel()).all()
+
+
+@pytest.mark.parametrize("su,sc", [(1e-36, 1.0), (3e37, 1e-20), (1e18, 1e18)])
+def test_ttm_holds_the_whole_range_of_a_float(gpu, oracle, su, sc):
+    n, Q, K = 20, 50, 70
+    B = (inputs.uniform(925, tri(n) * Q) * np.float32(su)).astype(np.float32)
+    C = (inputs.uniform(926, K, Q) * np.float32(sc)).astype(np.float32)
+    want, scale = oracle.ttm_ut(n, Q, K, B, C)
+    assert (np.abs(ttm(gpu, n, Q, K, B, C).astype(np.float64) - want.ravel()) <= 1e-6 * scale.ravel() + 1e-44).all()
+
+
+def same_non_finite(got, want):
+    assert np.array_equal(np.isnan(got), np.isnan(want))
+    inf = np.isinf(want)
+    assert np.array_equal(got[inf], want[inf])
+    return np.isfinite(want)
+
+
+def test_ttm_non_finite_operands_propagate(gpu, oracle):
+    n, Q, K = 30, 45, 100
+    B, C = inputs.uniform(927, tri(n) * Q).copy(), inputs.normal(928, K, Q).copy()
+    B[7 * Q + 3], B[200 * Q + 44], C[50, 9], C[99, 0] = np.inf, np.nan, -np.inf, np.nan
+    want, scale = oracle.ttm_ut(n, Q, K, B, C)
+    got = ttm(gpu, n, Q, K, B, C)
+    fine = same_non_finite(got, want.ravel())
+    assert (np.abs(got[fine] - want.ravel()[fine]) <= 1e-4 * scale.ravel()[fine]).all()
+
+
+@pytest.mark.parametrize("N,d", [(1, 1), (7, 2), (31, 63), (33, 64), (64, 65), (257, 66), (300, 129)])
+def test_a3_tile_remainders(gpu, oracle, N, d):
+    Bi = inputs.small_int(931, -4, 4, N, d)
+    assert np.array_equal(a3(gpu, N, d, Bi), oracle.pr_a3(Bi)[0].ravel())
+    B = inputs.normal(932, N, d)
+    want, scale = oracle.pr_a3(B)
+    # the product of two samples is rounded once (6e-8), then fp32 sums of at most 300 terms
+    assert (np.abs(a3(gpu, N, d, B).astype(np.float64) - want.ravel()) <= 2e-6 * scale.ravel()).all()
+
+
+def test_a3_non_finite_and_large_samples(gpu, oracle):
+    N, d = 90, 70
+    B = inputs.normal(933, N, d).copy()
+    B[40, 66], B[17, 3], B[80, 30] = np.inf, np.nan, 3e25
+    want, scale = oracle.pr_a3(B)
+    got = a3(gpu, N, d, B)
+    with np.errstate(invalid="ignore"):
+        # fp32 products overflow where the oracle's double sums do not: compare where the magnitudes fit
+        fits = np.isfinite(want.ravel()) & (scale.ravel() < 1e38)
+        assert (np.abs(got[fits] - want.ravel()[fits]) <= 1e-4 * scale.ravel()[fits]).all()
+        bad = np.isnan(want.ravel())
+        assert np.isnan(got[bad]).all()
