@@ -141,14 +141,14 @@ def _check(status: int, where: str) -> None:
 
 
 def _ptr(t):
-    """Device address of a tensor (None -> NULL)."""
+    """Device address of a float32 tensor (None -> NULL)."""
     if t is None:
         return None
     if not t.is_cuda:
         raise ValueError("device tensor expected")
-    if t.dtype.__str__() != "torch.float32":
+    if t.dtype is not _dtypes()[0]:
         raise ValueError("float32 tensor expected")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _ptr64(t):
@@ -157,17 +157,36 @@ def _ptr64(t):
         return None
     if not t.is_cuda:
         raise ValueError("device tensor expected")
-    if t.dtype.__str__() != "torch.float64":
+    if t.dtype is not _dtypes()[1]:
         raise ValueError("float64 tensor expected")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
+
+
+# torch is imported at the first call that needs it (the index polynomials do not) and looked up once: its dtypes, and
+# the raw handle of a device's current stream, which costs a call a tenth of what building a Stream object does (a
+# small product is called in 4 us; through the object it was 7).
+_torch_parts = None
+
+
+def _dtypes():
+    global _torch_parts
+    if _torch_parts is None:
+        import torch
+
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        device = getattr(torch._C, "_cuda_getDevice", None)
+        _torch_parts = (torch.float32, torch.float64, torch.cuda, raw if device is not None else None, device)
+    return _torch_parts
 
 
 def _stream(stream=None):
-    import torch
-
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    """Handle of `stream`, or of the current device's current stream, asked anew at every call."""
+    if stream is not None:
+        return stream.cuda_stream
+    _, _, cuda, raw, device = _dtypes()
+    if raw is not None and cuda.is_initialized():
+        return raw(device())
+    return cuda.current_stream().cuda_stream
 
 
 # ---- index polynomials (host) -------------------------------------------------
