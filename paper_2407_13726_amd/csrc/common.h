@@ -75,6 +75,11 @@ int trmv_then_zeros(int64_t n, const double *Up, const double *x, double *y, int
 // defined in trimv.hip
 int trmv_upper_by_panels(int64_t n, const float *Up, const float *x, float *y, void *stream);
 int trmv_upper_by_panels(int64_t n, const double *Up, const double *x, double *y, void *stream);
+// defined in trmm_skinny.hip: C := U B for at most 32 columns by panels of k (arguments already validated)
+int trmm_by_panels(int64_t n, int64_t m, const float *Up, const float *B, int64_t ldb, float *C, int64_t ldc, void *stream);
+int trmm_by_panels(int64_t n, int64_t m, const double *Up, const double *B, int64_t ldb, double *C, int64_t ldc, void *stream);
+// defined in trmm_columns.hip: C := U B with m a multiple of 128 (arguments already validated)
+int trmm_by_columns(int64_t n, int64_t m, const double *Up, const double *B, int64_t ldb, double *C, int64_t ldc, int64_t cus, void *stream);
 #if defined(__HIPCC__)
 // 16-byte vector of floats that only promises 4-byte alignment: packed rows start at arbitrary
 // element offsets, and gfx950 global loads of four dwords need dword alignment only.

@@ -568,10 +568,13 @@ inline int trmv_contiguous(int64_t n, const double *Up, const double *x, double 
 // Shares per pair: the S with the least estimated time, in microseconds.  c workgroups on a compute unit take max(c, alone)
 // times the steps of one (alone: what one workgroup by itself leaves of a compute unit's rate unused); every `slots` of
 // them pay 1.5 for first loads and last atomics; more than one share pays 4 for the launch that clears C and its atomics,
-// which land at 4.3e11 a second (fp64, n=1500, m=100: 17.9 us at S=12, 23.4 at 24, for 1.8e6 more of them).
+// which land at 4.3e11 a second (fp64, n=1500, m=100: 17.9 us at S=12, 23.4 at 24, for 1.8e6 more of them); with `hidden`
+// those of every layer of workgroups but the last run beside the next layer's products (fp64 64 x 64 tiles, n=3300,
+// m=512: 137 us at S=4, 117 at 6; n=10000, m=100: 271 and 241 at 8; n=4100, m=512: 192 and 176 at 8).
 struct Pace {
   double step, alone;  // microseconds per step of one workgroup, and see above
   int64_t slots;       // workgroups a compute unit holds
+  bool hidden;         // see below
 };
 int64_t choose_shares(int64_t base, int64_t steps, int64_t elements, int64_t cus, const Pace &pace) {
   int64_t best = 1;
@@ -580,7 +583,8 @@ int64_t choose_shares(int64_t base, int64_t steps, int64_t elements, int64_t cus
     const int64_t c = ceil_div(base * S, cus);
     const double busy = (double)c > pace.alone ? (double)c : pace.alone;
     double us = busy * (double)steps / (double)S * pace.step + 1.5 * (double)ceil_div(c, pace.slots);
-    if (S > 1) us += 4.0 + (double)S * (double)elements / 4.3e5;
+    const double seen = pace.hidden && c > pace.slots ? (double)pace.slots / (double)c : 1.0;
+    if (S > 1) us += 4.0 + (double)S * (double)elements / 4.3e5 * seen;
     if (S == 1 || us < 0.98 * least) best = S, least = us;
   }
   return best;
@@ -616,20 +620,44 @@ int launch_native(const Problem<T> &p, int64_t cus, const Pace &pace, hipStream_
   return launch<G>(trmm_native_kernel<T, G, WAVES, kFew>, p, Core<T>::kKT, cus, pace, st);
 }
 
-// Tile by columns and work.  Up to 32 columns the pass over U is the work: 128 x 32, three workgroups per compute unit.  The
+// Up to 32 columns the pass over U is the work.  The panels (trmm_skinny.hip) run in layers of one workgroup per compute unit, each
+// of the same time however full it is, the Narrow tiles at the rate of their steps; x counts a panel's workgroups, those
+// cut by the diagonal as half.  Panels where x fills more than 0.15 of one layer, three quarters of two or 0.93 of three
+// (us, tiles and panels, m=2, x in layers: fp32 n=2700 0.14: 24.8, 26.6; 4800 0.39: 31.7, 27.7; 7500 0.88: 43.9, 30.0; 9000 1.27: 55.6, 57.2; 10000
+// 1.56: 65.2, 60.7; 12500 2.44: 85.2, 91.1; 13500 2.85: 102.7, 95.2; 16384: 124, 146; fp64 n=1900 0.13: 24.4, 25.4; 2300, m=17 0.16: 29.5, 25.4; 4800 0.70: 38.9, 27.5; 7500 1.76:
+// 64.4, 61.4; 8500 2.26: 76.3, 86.5).
+template <typename T>
+bool panels_serve(int64_t n, int64_t cus) {
+  constexpr int64_t kPanel = 2048 / (int64_t)sizeof(T), kG = kPanel / 256;
+  const int64_t np = ceil_div(n, kPanel);
+  if (np > 64) return false;
+  const double x = (double)(kG * np * np) / 2.0 / (double)cus;  // kG np(np-1)/2 whole ones and kG np cut ones
+  return (x > 0.15 && x <= 1.0) || (x >= 1.5 && x <= 2.0) || (x >= 2.8 && x <= 3.0);
+}
+
+// Tile by columns and work.  Up to 32 columns: 128 x 32, three workgroups per compute unit, or panels.  The
 // split product's 64 x 64 tiles and 256 x 128 tiles cross at n*n*m of about 1e10 (us: n=4096, m=300 53 and 63; n=8192, m=100 84 and
-// 85; n=8192, m=256 152 and 122; n=16384, m=256 388 with large tiles, 540 on the fp32 cores), the large ones only where C fills
+// 85; n=8192, m=256 152 and 122; n=16384, m=256 396 with large tiles, 540 on the fp32 cores), the large ones only where C fills
 // more than half of their columns (n=16384, m=48: 167 and 228).
 int run_tiles(const Problem<float> &p, int64_t cus, hipStream_t st) {
-  if (p.m <= Narrow::kBN) return launch_native<float, Narrow, 3>(p, cus, {0.47, 1.6, 3}, st);
-  if (p.m > 64 && (double)p.n * (double)p.n * (double)p.m > 1e10) return launch<Large>(trmm_split_kernel<Large, false>, p, 32, cus, {2.9, 1.0, 1}, st);
-  return launch<Small>(trmm_split_kernel<Small, true>, p, 32, cus, {0.35, 1.3, 2}, st);
+  if (p.m <= Narrow::kBN) {
+    if (panels_serve<float>(p.n, cus)) return trmm_by_panels(p.n, p.m, p.U, p.B, p.ldb, p.C, p.ldc, st);
+    return launch_native<float, Narrow, 3>(p, cus, {0.47, 1.6, 3, false}, st);
+  }
+  if (p.m > 64 && (double)p.n * (double)p.n * (double)p.m > 1e10)
+    return launch<Large>(trmm_split_kernel<Large, false>, p, 32, cus, {2.9, 1.0, 1, false}, st);
+  return launch<Small>(trmm_split_kernel<Small, true>, p, 32, cus, {0.35, 1.3, 2, false}, st);
 }
-// fp64 (us, 64 x 64 and 64 x 128): n=4096, m=300 145 and 142; n=8192, m=100 157 and 170; n=16384, m=256 1097 and 1053.
+// fp64: whole tiles of 128 columns from n = 4600 on have a kernel of their own (trmm_columns.hip, with both sides measured); else 64 x 64
+// and 64 x 128 cross at n*n*m of about 1e10 (us: n=4096, m=300 145 and 142; n=7500, m=100 149 and 146; n=13000, m=100 400 and 374; n=16384, m=70 603 and 573).
 int run_tiles(const Problem<double> &p, int64_t cus, hipStream_t st) {
-  if (p.m <= Narrow::kBN) return launch_native<double, Narrow, 3>(p, cus, {0.47, 1.6, 3}, st);
-  if (p.m > 64 && (double)p.n * (double)p.n * (double)p.m > 2e10) return launch_native<double, Wide, 2>(p, cus, {1.0, 1.3, 2}, st);
-  return launch_native<double, Small, 3>(p, cus, {0.5, 1.2, 3}, st);
+  if (p.m <= Narrow::kBN) {
+    if (panels_serve<double>(p.n, cus)) return trmm_by_panels(p.n, p.m, p.U, p.B, p.ldb, p.C, p.ldc, st);
+    return launch_native<double, Narrow, 3>(p, cus, {0.47, 1.6, 3, false}, st);
+  }
+  if (p.n >= 4600 && p.m % 128 == 0) return trmm_by_columns(p.n, p.m, p.U, p.B, p.ldb, p.C, p.ldc, cus, st);
+  if (p.m > 64 && (double)p.n * (double)p.n * (double)p.m > 1e10) return launch_native<double, Wide, 2>(p, cus, {1.05, 1.2, 2, true}, st);
+  return launch_native<double, Small, 3>(p, cus, {0.57, 1.4, 3, true}, st);
 }
 
 template <typename T>

@@ -1,0 +1,196 @@
+// TRMM over a packed upper triangle, double precision, where the columns of C fill whole tiles of 128 and the triangle is tall:
+//
+//   C(i,c) := U(i,k) * B(k,c),  i<=k        U packed row-major, B and C dense row-major
+//
+// A workgroup (8 wavefronts) owns a 64-row x 128-column tile of C and sweeps k from the diagonal of its row block to n in
+// steps of 16, double-buffered in LDS against the global loads of the next step; sweep and matrix-core pieces are those of
+// mfma_tile.h.  The bound is the fp64 matrix cores: 55-66 TFLOP/s here, 71.8 in a large library product.  The tiles of the general
+// kernel run the same products 2-6 % slower at these shapes (us, this kernel and the general one with its best tile and
+// shares: n=4800, m=384 169 and 174; n=7500, m=512 488 and 502; n=16384, m=128 570 and 592; n=16384, m=256 1066 and 1118): their sweeps
+// keep two steps in flight and test the columns, which pays where a tile is partly empty (n=13000, m=100: 479 and 374) and below a
+// few thousand rows (n=3300, m=128: 51 and 44; n=4100, m=384: 144 and 134).
+//
+// Only the k-steps that touch the diagonal block, and the ragged last step and row block, take the masked loader; the others
+// run as a sweep of their own whose loop holds no test of the kind of step.
+//
+// Row block b needs (n - 64 b)/16 steps, so a workgroup takes the pair (b, nb-1-b).  The steps of a pair, as one list, are cut into
+// S equal shares, one workgroup each; a share covers pieces of at most two row blocks and adds each into a zeroed C with
+// atomics.  With S = 1: plain stores, no fill.
+#include "mfma_tile.h"
+
+using namespace dastac;
+
+namespace {
+
+struct Stage {
+  Core<double>::vec u;     // U: row ur of the tile, one 16-byte piece of k values
+  Core<double>::vec b[2];  // B: k rows bk and bk + kKT/2, one 16-byte piece of columns each
+};
+
+// Held to the 128 registers of four wavefronts per SIMD, so that two workgroups share a CU.
+template <bool SPLIT>
+__global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(4))) void trmm_columns_kernel(
+    int64_t n, const double *__restrict__ U, const double *__restrict__ B, int64_t ldb, double *__restrict__ C, int64_t ldc, int nb,
+    int npairs, int ncb, int S) {
+  typedef double T;
+  typedef Core<T> K;
+  typedef K::vec vec;
+  typedef K::uvec uvec;
+  constexpr int kBM = kTileM, kBN = kTileN, kKT = K::kKT, kV = K::kVec, kUP = K::kRowPitch;
+  constexpr int kDiagSteps = kBM / kKT;  // k-steps that overlap the diagonal block
+  __shared__ __attribute__((aligned(16))) T Us[2][kBM * kUP];
+  __shared__ __attribute__((aligned(16))) T Bs[2][kKT * kBN];
+
+  // workgroup id -> (row-block pair, column block); ids equal mod 8 share an XCD.  An XCD gets a run of
+  // consecutive pairs: their sweeps over k start 64 rows apart and move at the same speed, so the rows
+  // of B one of them reads are read again by its neighbour a few k-steps later, out of that XCD's L2.
+  const int L = blockIdx.x;
+  const int xcd = L & 7, slot = L >> 3;
+  const int per_pair = SPLIT ? ncb * S : ncb;
+  const int pair_lo = (int)((int64_t)npairs * xcd / 8), pair_hi = (int)((int64_t)npairs * (xcd + 1) / 8);
+  const int pair = pair_lo + slot / per_pair;
+  const int cb = SPLIT ? (slot % per_pair) / S : slot % ncb;
+  const int share = SPLIT ? slot % S : 0;
+  if (pair >= pair_hi) return;
+  // this workgroup's share [t_lo, t_hi) of the pair's k-steps, numbered through both row blocks
+  const int steps_a = (int)ceil_div(n - (int64_t)pair * kBM, kKT);
+  const int steps_b = (nb - 1 - pair != pair) ? (int)ceil_div(n - (int64_t)(nb - 1 - pair) * kBM, kKT) : 0;
+  const int t_lo = SPLIT ? (int)((int64_t)(steps_a + steps_b) * share / S) : 0;
+  const int t_hi = SPLIT ? (int)((int64_t)(steps_a + steps_b) * (share + 1) / S) : steps_a + steps_b;
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wr = wave >> 2, wc = wave & 3;  // 2x4 wavefronts: 32 rows x 32 columns each
+
+  // staging roles: eight threads per row of the U tile, 128/kV per row of the B tile
+  const int ur = tid >> 3, uk = (tid & 7) * kV;                       // U: row ur, k offset uk
+  const int bk = tid / (kBN / kV), bc = (tid % (kBN / kV)) * kV;      // B: k row bk (and bk + kKT/2), column offset bc
+  const int64_t col0 = (int64_t)cb * kBN;
+
+  for (int which = 0; which < 2; ++which) {
+    const int blk = which == 0 ? pair : nb - 1 - pair;
+    if (which == 1 && blk == pair) break;  // odd number of row blocks: the middle one is alone
+    const int64_t i0 = (int64_t)blk * kBM;
+    const bool rows_full = i0 + kBM <= n;
+    // k-steps [kt_lo, nk) of this row block fall into the share
+    const int first = which == 0 ? 0 : steps_a;  // number of the block's step 0 in the pair's list
+    const int steps_blk = which == 0 ? steps_a : steps_b;
+    // (literal bounds without shares: the first sweep below then has a compile-time trip count)
+    const int kt_lo = SPLIT ? (t_lo > first ? t_lo - first : 0) : 0;
+    const int nk = SPLIT ? (t_hi - first < steps_blk ? t_hi - first : steps_blk) : (int)ceil_div(n - i0, kKT);
+    if (SPLIT && kt_lo >= nk) continue;
+
+    // per-thread packed row base: element (i,k) of U is at ub + k for this thread's row i
+    const int64_t iu = i0 + ur;
+    const bool urow_ok = iu < n;
+    const T *ub = U + (urow_ok ? tri_row_start(n, iu) - iu : 0);
+
+    auto load_stage = [&](int kt, Stage &s) {
+      const int64_t k0 = i0 + (int64_t)kt * kKT;
+      const bool k_full = k0 + kKT <= n;
+      if (kt >= kDiagSteps && k_full && rows_full) {
+        s.u = *reinterpret_cast<const uvec *>(ub + k0 + uk);
+      } else {
+#pragma unroll
+        for (int e = 0; e < kV; ++e) {
+          const int64_t k = k0 + uk + e;
+          s.u[e] = (urow_ok && k >= iu && k < n) ? ub[k] : T(0);
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const int64_t k = k0 + bk + (kKT / 2) * q;
+        s.b[q] = vec{0.0, 0.0};
+        if (k < n) s.b[q] = *reinterpret_cast<const uvec *>(B + k * ldb + col0 + bc);
+      }
+    };
+    auto store_stage = [&](int buf, int, const Stage &s) {
+      *reinterpret_cast<vec *>(&Us[buf][ur * kUP + uk]) = s.u;
+#pragma unroll
+      for (int q = 0; q < 2; ++q) *reinterpret_cast<vec *>(&Bs[buf][(bk + (kKT / 2) * q) * kBN + bc]) = s.b[q];
+    };
+    auto read_ops = [&](int buf, int, int t, K::Ops &o) {
+      K::read_a(&Us[buf][wr * 32 * kUP], lane, t, o);
+      K::read_b(&Bs[buf][wc * 32], kBN, lane, t, o);
+    };
+
+    K::Acc acc;
+    K::clear(acc);
+    __syncthreads();  // the previous row block's last reads of buffer 0 are done
+    if (rows_full) {
+      // A whole tile: the masked steps on the diagonal block, the whole steps behind it and a ragged last step are
+      // three sweeps, so that the long one carries no test of which kind of step it is on.
+      const int nfull = (int)((n - i0) / kKT);
+      const int a_hi = nk < kDiagSteps ? nk : kDiagSteps;
+      const int b_lo = kt_lo > kDiagSteps ? kt_lo : kDiagSteps, b_hi = nk < nfull ? nk : nfull;
+      const int c_lo = kt_lo > nfull ? kt_lo : nfull;
+      bool between = false;  // a sweep has run: barrier before the next one reuses the buffers
+      if (kt_lo < a_hi) {
+        sweep_steps<T, Stage>(kt_lo, a_hi, acc, load_stage, store_stage, read_ops);
+        between = true;
+      }
+      if (b_lo < b_hi) {
+        if (between) __syncthreads();
+        sweep_steps<T, Stage>(
+            b_lo, b_hi, acc,
+            [&](int kt, Stage &s) {
+              const int64_t k0 = i0 + (int64_t)kt * kKT;
+              s.u = *reinterpret_cast<const uvec *>(ub + k0 + uk);
+#pragma unroll
+              for (int q = 0; q < 2; ++q)
+                s.b[q] = *reinterpret_cast<const uvec *>(B + (k0 + bk + (kKT / 2) * q) * ldb + col0 + bc);
+            },
+            store_stage, read_ops);
+        between = true;
+      }
+      if (c_lo < nk) {
+        if (between) __syncthreads();
+        sweep_steps<T, Stage>(c_lo, nk, acc, load_stage, store_stage, read_ops);
+      }
+    } else {
+      sweep_steps<T, Stage>(kt_lo, nk, acc, load_stage, store_stage, read_ops);
+    }
+    __syncthreads();  // all reads of this row block's buffers are done before the next block's stores
+
+    K::for_each(acc, lane, [&](int r, int c, T v) {
+      const int64_t i = i0 + wr * 32 + r, col = col0 + wc * 32 + c;
+      if (i < n) {
+        if (SPLIT)
+          unsafeAtomicAdd(&C[i * ldc + col], v);
+        else
+          C[i * ldc + col] = v;
+      }
+    });
+  }
+}
+
+}  // namespace
+
+// The smallest S <= 16, with at least 32 steps per share, whose workgroups come in whole layers of two per compute unit
+// (n = 16384: m = 256 1.19 -> 1.12 ms, m = 128 0.63 -> 0.59; n = 8192, m = 256 0.32 -> 0.29).
+int dastac::trmm_by_columns(int64_t n, int64_t m, const double *Up, const double *B, int64_t ldb, double *C, int64_t ldc, int64_t cus,
+                            void *stream) {
+  constexpr int kBM = kTileM, kBN = kTileN, kKT = Core<double>::kKT;
+  if (m % kBN) return DASTAC_EINVAL;
+  const int nb = (int)ceil_div(n, kBM), npairs = (nb + 1) / 2, ncb = (int)(m / kBN);
+  const int64_t base = (int64_t)8 * ceil_div(npairs, 8) * ncb;
+  if (base > 0x7ffffff) return DASTAC_EOVERFLOW;
+  hipStream_t st = (hipStream_t)stream;
+  const int64_t steps = ceil_div(n, kKT) + kBM / kKT, layer = 2 * cus;
+  int64_t S = 1;
+  double best = 0.0;
+  for (int64_t s = 1; s <= 16 && (s == 1 || steps / s >= 32); ++s) {
+    const int64_t wgs = base * s;
+    const double fill = (double)wgs / (double)(ceil_div(wgs, layer) * layer);
+    if (fill > best + 0.02) best = fill, S = s;
+    if (fill >= 0.95) break;
+  }
+  if (S == 1) {
+    trmm_columns_kernel<false><<<(unsigned)base, kTileThreads, 0, st>>>(n, Up, B, ldb, C, ldc, nb, npairs, ncb, 1);
+    return launch_status();
+  }
+  const int64_t zb = ceil_div(n * (m / 2), 256);
+  zero_matrix_kernel<double><<<(unsigned)(zb < 4096 ? zb : 4096), 256, 0, st>>>(C, n, m, ldc);
+  if (hipGetLastError() != hipSuccess) return DASTAC_EHIP;
+  trmm_columns_kernel<true><<<(unsigned)(base * S), kTileThreads, 0, st>>>(n, Up, B, ldb, C, ldc, nb, npairs, ncb, (int)S);
+  return launch_status();
+}

@@ -456,8 +456,13 @@ int uhc_copy(int64_t n, int64_t Q, const T *src, T *dst, void *stream) {
   return launch_status();
 }
 
-// The split's offsets within a row block are 32 bits and a piece needs four l; beyond that the fp32 matrix cores take over.
-inline bool split_serves(int64_t, int64_t Q, int64_t K, const float *) { return Q >= 4 && Q <= (1 << 20) && K <= (1 << 20); }
+// The split's offsets within a row block are 32 bits and a piece needs four l; beyond that the fp32 matrix cores take over, and
+// where one step is all there is and the tiles do not fill the chip: the split's conversion then only adds to the latency
+// (us, split and fp32 cores: n=60, Q=20, K=512 6.0, 5.1; n=150, Q=20, K=100 6.1, 5.1; past one layer, n=150, Q=20, K=300, 9.7, 10.7).
+inline bool split_serves(int64_t rows, int64_t Q, int64_t K, const float *) {
+  if (Q <= 32 && ceil_div(rows, kTileM) * ceil_div(K, kTileN) <= 256) return false;
+  return Q >= 4 && Q <= (1 << 20) && K <= (1 << 20);
+}
 inline bool split_serves(int64_t, int64_t, int64_t, const double *) { return false; }
 
 template <typename G>
@@ -492,7 +497,7 @@ int ttm_ut(int64_t n, int64_t Q, int64_t K, const T *Bp, const T *C, int64_t ldc
   const int64_t rows = tri(n);
   if (overlaps(Ap, rows * K * kB, Bp, rows * Q * kB) || overlaps(Ap, rows * K * kB, C, view_bytes(K, ldc, Q, kB)))
     return DASTAC_EALIAS;
-  if (split_serves(n, Q, K, Bp)) return ttm_split(rows, Q, K, Bp, C, ldc, Ap, (hipStream_t)stream);
+  if (split_serves(rows, Q, K, Bp)) return ttm_split(rows, Q, K, Bp, C, ldc, Ap, (hipStream_t)stream);
   const int64_t nrb = ceil_div(rows, kTileM), ncb = ceil_div(K, kTileN);
   if (ncb > (1 << 20)) return DASTAC_EOVERFLOW;
   // about two workgroups per compute unit (256 of them), each walking a strided set of row blocks

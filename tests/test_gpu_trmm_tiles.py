@@ -46,6 +46,19 @@ def test_large_tiles_exact_on_integers(gpu, oracle, n, m):
         assert np.array_equal(got[lo:hi], want[lo:hi] if len(want) == n else want)
 
 
+@pytest.mark.parametrize("dtype,n,m", [("f32", 3073, 17), ("f32", 5000, 32), ("f32", 10001, 3), ("f64", 2305, 31), ("f64", 7501, 2),
+                                       ("f64", 4600, 128), ("f64", 4737, 256)])
+def test_panels_and_whole_columns_exact_on_integers(gpu, oracle, dtype, n, m):
+    """The kernels that take over between the tiles' ranges: nearly whole layers of panels of k (at most 32 columns), and
+    whole tiles of 128 columns in double precision."""
+    t, ref = (np.float32, oracle.trmm) if dtype == "f32" else (np.float64, oracle.trmm_f64)
+    Ui, Bi = inputs.small_int(911, -8, 8, tri(n)).astype(t), inputs.small_int(912, -8, 8, n * m).astype(t).reshape(n, m)
+    got = run(gpu, dtype, n, m, Ui, Bi, 3)
+    for lo, hi in ((0, 70), (n // 2 - 40, n // 2 + 40), (n - 300, n)):
+        want, _ = ref(n, m, Ui, Bi, rows=(lo, hi))
+        assert np.array_equal(got[lo:hi], want[lo:hi] if len(want) == n else want)
+
+
 @pytest.mark.parametrize("scale_u,scale_b", [(1e-36, 1.0), (1e-30, 1e-6), (1e30, 1e-3), (3e37, 1e-20), (1e18, 1e18)])
 def test_split_holds_the_whole_range_of_a_float(gpu, oracle, scale_u, scale_b):
     """The error stays the rounding of fp32 sums (a few times 2^-24 of the sum of magnitudes for sums of 300 terms; 1e-6
