@@ -141,7 +141,8 @@ int dastac_unpack_subtri_f32(int64_t N, int64_t k, const float *packed, float *d
 int dastac_pack_leslie_f32(int64_t n, const float *dense, int64_t ld, float *R, float *S, void *stream);
 int dastac_unpack_leslie_f32(int64_t n, const float *R, const float *S, float *dense, int64_t ld, void *stream);
 
-/* ---- contractions: DEVICE, fp32 storage and arithmetic ---------------------------
+/* ---- contractions: DEVICE, fp32 storage and precision (TRMM, TTM_UT and A3 by
+ * exact bf16 parts with fp32 accumulation, with smaller errors than fp32 products) ----
  * Summation order is unspecified (the paper compiles with fast-math, Section 6.1);
  * each output element is within 1e-4 * sum|products| of the exactly rounded result.
  *
@@ -218,8 +219,8 @@ int dastac_tet_ttv_f32(int64_t n, const float *Ap, const float *v, float *Mp, vo
 
 /* M(i,r) := A(i,j,k) * B(j,r) * C(k,r), i<=j<=k, 0<=r<R  (Table 1 MTTKRP rule on the upper tetrahedron).
  * B, C are n x R row-major with row strides ldb, ldc >= R; M is n x R with row stride ldm >= R.
- * 1 <= R <= 2^20.  The kernel takes 32 columns of the factor
- * matrices at a time: R > 32 runs block by block, each block reading the packed tetrahedron once.  M is
+ * 1 <= R <= 2^20.  One launch covers all tiles of 32
+ * columns of the factor matrices; each tile reads the packed tetrahedron once.  M is
  * cleared first and the blocks of a slice add their parts with floating-point atomics, so the last bits
  * may differ between calls (integer-valued inputs whose partial sums are exact give identical results).
  * The sum is evaluated factored (A with B first, then with C) on blocks padded with zeros, so a non-finite

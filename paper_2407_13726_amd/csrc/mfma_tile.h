@@ -1,7 +1,7 @@
-// What the matrix-core kernels with a 64 x 128 workgroup tile share, per element type.
+// What the kernels on the fp32 and fp64 matrix instructions share, per element type.
 //
-// TRMM, SYMM, TTM_UT and the polynomial-regression tensors all let a workgroup of eight wavefronts own a
-// 64 x 128 tile of the result and sweep the reduction index in steps: per step a 64 x kKT tile of the
+// SYMM, A2, TTM_UT (double precision), A3 (double precision) and TRMM on whole columns let a workgroup of eight wavefronts own a
+// 64 x 128 or 64 x 64 tile of the result (TRMM's other tiles: trmm.hip, with sweep_ahead) and sweep the reduction index in steps: per step a 64 x kKT tile of the
 // first operand and a kKT x 128 tile of the second are staged in LDS (double-buffered against the global
 // loads of the next step) and each wavefront multiplies its 32 x 32 sub-tile.  The schedule of such a
 // sweep is written once (sweep_steps below); what depends on the element type -- the step length, the

@@ -1,6 +1,6 @@
 // MTTKRP over a packed upper tetrahedron on the matrix cores, single and double precision:
 //
-//   M(i,r) := A(i,j,k) * B(j,r) * C(k,r),   i<=j<=k, 0<=r<R (32 columns r per launch)     (Table 1, MTTKRP rule)
+//   M(i,r) := A(i,j,k) * B(j,r) * C(k,r),   i<=j<=k, 0<=r<R (tiles of 32 columns r in one launch)     (Table 1, MTTKRP rule)
 //
 // Factored evaluation, contracting over the ROW index first.  Slice i of the packed tetrahedron is a
 // packed upper triangle U_i of order m = n-i, so

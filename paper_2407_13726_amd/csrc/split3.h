@@ -15,7 +15,7 @@
 // Range.  Operands are multiplied by 2^24 first (exact), so that the three parts of every normal float, down to the
 // smallest, are representable; results are multiplied by 2^-48.  What the split cannot hold -- an Inf or NaN
 // operand, |x| >= 2^103, partial sums beyond 2^80 -- leaves a non-finite accumulator: kernels test the accumulators
-// once at the end of a tile (Core<float>::non_finite) and evaluate that tile again with fp32 matrix instructions, so that such
+// once at the end of a tile (Core<float>::non_finite) and evaluate that tile again in plain fp32, so that such
 // inputs propagate as IEEE arithmetic has it.
 #pragma once
 #include "common.h"
@@ -59,11 +59,6 @@ __device__ inline Parts split3x8(const float (&x)[8]) {
   }
   return p;
 }
-
-// The six products, largest first: which part of the first and of the second operand.
-constexpr int kSplitProducts = 6;
-constexpr int kSplitA[kSplitProducts] = {0, 0, 1, 1, 0, 2};
-constexpr int kSplitB[kSplitProducts] = {0, 1, 0, 1, 2, 0};
 
 __device__ inline f16v mma_bf16(u4v a, u4v b, f16v c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8, a), __builtin_bit_cast(bf8, b), c, 0, 0, 0);
