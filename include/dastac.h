@@ -181,7 +181,8 @@ int dastac_symv_lower_f32(int64_t n, const float *Lp, const float *x, float *y, 
  * Only columns 0..m-1 of every row of C are written.  Where the tiles of C do not fill the device the reduction range
  * is shared out over several workgroups, which add into a cleared C with floating-point atomics; from three shares on the last
  * bits may differ between calls, with one share (enough columns) every element of C has one writer, with two the order of
- * its two addends does not matter. */
+ * its two addends does not matter.  An Inf or NaN in row k of B may also make NaN of rows k+1 .. k+63 of its column: with at
+ * most 32 columns, and in fp64 on whole blocks of 128, some sizes multiply it by the zeros that stand left of the diagonal. */
 int dastac_trmm_f32(int64_t n, int64_t m, const float *Up, const float *B, int64_t ldb, float *C, int64_t ldc,
                     void *stream);
 
