@@ -102,6 +102,14 @@ __device__ inline int64_t uniform64(int64_t v) {
 }
 __device__ inline int uniform32(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
+// Pins a wave-uniform address to a scalar register pair and hides how it was computed, so that "this address
+// plus a 32-bit offset per lane" stays one load with a scalar base instead of 64-bit vector arithmetic per load.
+typedef const char __attribute__((address_space(1))) *global_bytes;  // a device-memory address, known as such
+__device__ inline global_bytes in_scalar_registers(global_bytes p) {
+  asm volatile("" : "+s"(p));
+  return p;
+}
+
 // Barrier for what the workgroup exchanges through LDS: unlike __syncthreads it does not wait for stores to memory that are on
 // their way, a microsecond at the end of a kernel.
 __device__ inline void lds_barrier() {

@@ -90,14 +90,6 @@ constexpr int kCols = Shape<T>::LPR * Shape<T>::V * Shape<T>::NP;
 template <typename T>
 constexpr int kRatio = kRows / kCols<T>;
 
-// Pins a wave-uniform address to a scalar register pair and hides how it was computed, so that "this address
-// plus a 32-bit offset per lane" stays one load with a scalar base instead of 64-bit vector arithmetic per load.
-typedef const char __attribute__((address_space(1))) *global_bytes;  // a device-memory address, known as such
-__device__ inline global_bytes in_scalar_registers(global_bytes p) {
-  asm volatile("" : "+s"(p));
-  return p;
-}
-
 // A wavefront's walk over the steps of its block.  Step t covers the rows row0 + RS*t of the lane
 // groups (lane group h = lane / LPR takes row rlo + RS*t + h); the byte offset of a lane's piece grows
 // from step to step by a difference that itself shrinks by RS*RS elements (a packed row is one element

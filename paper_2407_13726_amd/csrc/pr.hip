@@ -1,14 +1,10 @@
-// Polynomial-regression tensors (Table 1, "Polynomial Regression Degree-D") written straight
-// into packed hyper-triangles on the matrix cores, single and double precision:
+// The second-order polynomial-regression tensor (Table 1, "Polynomial Regression Degree-D") written straight into a packed
+// triangle on the matrix cores, single and double precision (the third-order one: pr3.hip):
 //
 //   A2(i,j)   := B(x,i) * B(x,j)            i<=j        packed upper triangle,   tri(d,i,j)
-//   A3(i,j,k) := B(x,i) * B(x,j) * B(x,k)   i<=j<=k     packed upper tetrahedron, tet(d,i,j,k)
 //
-// B is the dense N x d sample matrix; both outputs are symmetric under any permutation of their
-// indices and only the unique elements are computed and stored (the output inherits the structure,
-// Section 3).  A2 is the upper triangle of the Gram matrix; slice i of A3 is a weighted Gram matrix,
-// sum_x w(x) B(x,j) B(x,k) with w = B(.,i), restricted to i <= j <= k, stored contiguously at
-// tet_slice_start(d,i).
+// B is the dense N x d sample matrix; the output is symmetric and only the unique elements are computed and stored (the output
+// inherits the structure, Section 3): the upper triangle of the Gram matrix.  Rows and columns of the output are called j and k below.
 //
 // A workgroup owns a 64 (j) x 128 (k) tile of the (j,k) plane (eight wavefronts; for small d a 64 x 64
 // tile and four wavefronts) and a range of samples x, which is the reduction index: per step of kXT
@@ -19,17 +15,8 @@
 // diagonal are never launched; tiles on the diagonal stage their full rectangle, wavefronts whose
 // sub-tile lies below it skip their matrix instructions, and only j<=k is stored.
 //
-// For A3 the tiles are cut on a grid that is the same for every slice, and a workgroup takes its tile
-// for two consecutive slices i at once: the two staged tiles are shared
-// by those slices, whose weights B(x,i) are staged beside them and multiplied onto the first operand in
-// registers, one accumulator per slice.  (In single precision all but a few samples run as a kernel of its own on the bf16 matrix
-// cores, pr3_split_kernel below.)  A tile serves
-// the slices i <= its last row; a wavefront whose rows all lie above the slices of the workgroup
-// (j < i) has nothing to compute.
-//
 // When the work items alone cannot fill the chip the sample range is split over several workgroups,
 // which then add into a pre-zeroed output with floating-point atomics.
-#include "split3.h"
 #include "mfma_tile.h"
 
 using namespace dastac;
@@ -39,54 +26,18 @@ namespace {
 constexpr int kBJ = kTileM;  // j extent of a workgroup tile
 // k extent of a workgroup tile: BK = 128 (eight wavefronts) or BK = 64 (four), a template parameter
 constexpr int64_t kMaxD2 = 1 << 16;  // A2: tile grid and tri(d) stay small
-constexpr int64_t kMaxD3 = 1 << 13;  // A3: the item count stays inside gridDim.x
 constexpr int64_t kMaxN = (int64_t)1 << 31;
 // Up to these d the 64 x 64 tile is used: it wastes less on the diagonal and leaves more workgroups per CU,
 // which outweighs its lower operand reuse while diagonal tiles are a large share of all tiles.
-constexpr int64_t kNarrowMaxD2 = 768, kNarrowMaxD3 = 2048;  // (D3: double precision; in single precision A3 has one tile)
-
-// Slices of A3 that share a workgroup's staged tiles, and how their weights reach the first operand.
-template <typename T>
-struct Slices;
-template <>
-struct Slices<float> {
-  // group t of a step: this lane's samples are 8t + 4*(lane/32) + q, q < 4; ws is [slice][sample]
-  template <int kNI, typename Ops3>
-  __device__ static void scale(const Core<float>::Ops &r, const float *ws, int lane, int t, Ops3 &o) {
-#pragma unroll
-    for (int ii = 0; ii < kNI; ++ii) {
-      const f4a w = *reinterpret_cast<const f4a *>(ws + ii * Core<float>::kKT + 8 * t + 4 * (lane >> 5));
-#pragma unroll
-      for (int q = 0; q < 4; ++q) o.a[ii][q] = r.a[q] * w[q];
-    }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) o.b[q] = r.b[q];
-  }
-};
-template <>
-struct Slices<double> {
-  // group t of a step: this lane's sample is 4t + lane/16
-  template <int kNI, typename Ops3>
-  __device__ static void scale(const Core<double>::Ops &r, const double *ws, int lane, int t, Ops3 &o) {
-#pragma unroll
-    for (int ii = 0; ii < kNI; ++ii) {
-      const double w = ws[ii * Core<double>::kKT + 4 * t + (lane >> 4)];
-      o.a[ii][0] = r.a[0] * w;
-      o.a[ii][1] = r.a[1] * w;
-    }
-    o.b[0] = r.b[0];
-    o.b[1] = r.b[1];
-  }
-};
+constexpr int64_t kNarrowMaxD2 = 768;
 
 template <typename T>
 struct Stage {
   typename Core<T>::vec a[2];  // j tile: one or two sample rows, one 16-byte piece of columns each
   typename Core<T>::vec b[2];  // k tile: sample rows bk and bk + kXT/2, one 16-byte piece of columns each
-  T w;                         // A3: one weight (first threads only)
 };
 
-// Staging of the two column tiles of B, the same for both kernels: columns j0.. (64 of them) and k0.. (BK),
+// Staging of the two column tiles of B: columns j0.. (64 of them) and k0.. (BK),
 // sample rows x0 .. x0+kXT-1, zeros from column d and from sample xend on.
 template <typename T, int BK>
 struct Tiles {
@@ -268,384 +219,32 @@ __global__ __launch_bounds__(4 * BK) void pr2_mfma_kernel(int64_t N, int64_t d, 
   });
 }
 
-// ---- A3 ----------------------------------------------------------------------------------------------
-
-// Units of A3: tile (J,K) of the (j,k) plane -- the same grid for every slice -- times a group of NI
-// consecutive slices.  Row block J serves the slices 0 .. min(64(J+1), d)-1 (a slice needs i <= j), in
-// ceil(that / NI) groups, and has as many tiles as in A2; units are numbered densely: row block after row
-// block, slice group after slice group, column block after column block.
-DASTAC_HD int64_t units_of_row_block(int64_t d, int BK, int NI, int64_t J) {
-  const int64_t m = ceil_div(d, kBJ), nK = BK == 64 ? m : (m + 1) / 2;
-  const int64_t slices = kBJ * (J + 1) < d ? kBJ * (J + 1) : d;
-  return (nK - J * kBJ / BK) * ceil_div(slices, NI);
-}
-
-DASTAC_HD int64_t total_units(int64_t d, int BK, int NI) {
-  int64_t total = 0;
-  for (int64_t J = 0; J < ceil_div(d, kBJ); ++J) total += units_of_row_block(d, BK, NI, J);
-  return total;
-}
-
-// One operand group of a step for NI slices: the first operand scaled by each slice's weights, the second shared.
-template <typename T, int NI>
-struct Ops3 {
-  static constexpr int kNA = (int)(sizeof(typename Core<T>::Ops) / sizeof(T)) / 2;
-  T a[NI][kNA];
-  T b[kNA];
-};
-
-// One unit of A3 and its share [xbeg, xend) of the samples.
-struct Unit3 {
-  int64_t J, Kb, i0;  // row block, column block, first slice of the group
-  int64_t xbeg, xend;
-};
-
-// What a unit keeps in LDS, double-buffered: the two tiles and the weights [slice][sample].
-template <typename T, int BK, int NI>
-struct Shared3 {
-  __attribute__((aligned(16))) T As[2][Core<T>::kKT * Core<T>::kColPitch];
-  __attribute__((aligned(16))) T Bs[2][Core<T>::kKT * BK];
-  __attribute__((aligned(16))) T Ws[2][NI * Core<T>::kKT];
-};
-
-// NI slices per workgroup.
-template <typename T, bool ATOMIC, int BK, int NI>
-__device__ __attribute__((always_inline)) inline void pr3_unit(int64_t d, const T *B, int64_t ldb, T *out, const Unit3 &u, Shared3<T, BK, NI> &sh) {
-  typedef Core<T> K;
-  constexpr int kXT = K::kKT, kJP = K::kColPitch, kWC = BK / 32, kNI = NI;
-  constexpr int kWThreads = kXT * kNI;  // threads that stage one weight each
-  static_assert(32 % kNI == 0 && kWThreads <= 4 * BK, "slice groups never straddle a sub-tile's first row");
-  const int64_t J = u.J, Kb = u.Kb, i0 = u.i0, xbeg = u.xbeg, xend = u.xend;
-  const int nk = (int)ceil_div(xend - xbeg, kXT);
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wr = wave / kWC, wc = wave % kWC;  // 2 x kWC wavefronts: 32 (j) x 32 (k) each
-  const int64_t jw = J * kBJ + wr * 32, kw = Kb * BK + wc * 32;  // first row and column of this wavefront's sub-tile
-  // Nothing to compute where the sub-tile lies wholly below the diagonal (largest k < smallest j) or wholly
-  // above the group's slices (largest j < i0; i0 and the sub-tile's first row are both multiples of kNI, so
-  // the group's slices are then all above it or all not).
-  const bool live = uniform32((kw + 31 >= jw && jw + 31 >= i0) ? 1 : 0) != 0;
-  const Tiles<T, BK> tiles_io(B, ldb, d, J * kBJ, Kb * BK, tid);
-  const int wx = tid % kXT, wi = tid / kXT;  // weights: sample wx of slice i0 + wi (threads below kWThreads)
-
-  auto load_stage = [&](int kt, Stage<T> &s) {
-    const int64_t x0 = xbeg + (int64_t)kt * kXT;
-    tiles_io.load(x0, xend, s);
-    if (tid < kWThreads) {
-      const int64_t xw = x0 + wx, iw = i0 + wi;
-      s.w = (xw < xend && iw < d) ? B[xw * ldb + iw] : T(0);
-    }
-  };
-  auto store_stage = [&](int buf, int, const Stage<T> &s) {
-    tiles_io.store(sh.As[buf], sh.Bs[buf], s);
-    if (tid < kWThreads) sh.Ws[buf][wi * kXT + wx] = s.w;
-  };
-  auto read_ops = [&](int buf, int, int t, Ops3<T, NI> &o) {
-    typename K::Ops r;
-    K::read_a_t(&sh.As[buf][wr * 32], kJP, lane, t, r);
-    K::read_b(&sh.Bs[buf][wc * 32], BK, lane, t, r);
-    Slices<T>::template scale<NI>(r, sh.Ws[buf], lane, t, o);
-  };
-  typename K::Acc acc[kNI];
-#pragma unroll
-  for (int ii = 0; ii < kNI; ++ii) K::clear(acc[ii]);
-  auto mma = [&](const Ops3<T, NI> &o) {
-#pragma unroll
-    for (int ii = 0; ii < kNI; ++ii) {
-      typename K::Ops r;
-#pragma unroll
-      for (int q = 0; q < Ops3<T, NI>::kNA; ++q) r.a[q] = o.a[ii][q], r.b[q] = o.b[q];
-      K::mma(r, acc[ii]);
-    }
-  };
-  // whole steps of a whole tile first, in a sweep without edge tests, then the ragged last step
-  const int nwhole = (tiles_io.j_full && tiles_io.k_full) ? (int)((xend - xbeg) / kXT) : 0;
-  if (nwhole > 0) {
-    const bool w_mine = tid < kWThreads && i0 + wi < d;
-    sweep_groups<Ops3<T, NI>, Stage<T>>(
-        0, nwhole,
-        [&](int kt, Stage<T> &s) {
-          const int64_t x0 = xbeg + (int64_t)kt * kXT;
-          tiles_io.load_whole(x0, s);
-          if (tid < kWThreads) s.w = w_mine ? B[(x0 + wx) * ldb + i0 + wi] : T(0);
-        },
-        store_stage, read_ops, mma, live);
-    if (nk > nwhole) __syncthreads();
-  }
-  if (nk > nwhole) sweep_groups<Ops3<T, NI>, Stage<T>>(nwhole, nk, load_stage, store_stage, read_ops, mma, live);
-  if (!live) return;
-
-#pragma unroll
-  for (int ii = 0; ii < kNI; ++ii) {
-    const int64_t i = i0 + ii, q = d - i;  // slice and the order of its triangle
-    if (i >= d) break;
-    T *slice = out + tet_slice_start(d, i);
-    K::for_each(acc[ii], lane, [&](int r, int c, T v) {
-      const int64_t j = jw + r, k = kw + c;
-      if (i <= j && j <= k && k < d) {
-        T *p = slice + tri_offset(q, j - i, k - i);
-        if (ATOMIC)
-          unsafeAtomicAdd(p, v);
-        else
-          *p = v;
-      }
-    });
-  }
-}
-
-// Three wavefronts per SIMD: in fp64 the register allocator reaches that with a few spilled dwords and the third wavefront
-// gains 15 %.
-template <typename T, bool ATOMIC, int BK, int NI>
-__global__ __launch_bounds__(4 * BK) __attribute__((amdgpu_waves_per_eu(3, 3)))
-void pr3_mfma_kernel(int64_t N, int64_t d, const T *__restrict__ B, int64_t ldb, T *__restrict__ out, int64_t chunk,
-                     int64_t units, int64_t split) {
-  __shared__ Shared3<T, BK, NI> sh;
-  int64_t share, unit;
-  if (!my_item(units, split, share, unit)) return;
-  int64_t J = 0;
-  while (unit >= units_of_row_block(d, BK, NI, J)) unit -= units_of_row_block(d, BK, NI, J), ++J;
-  const int64_t m = ceil_div(d, kBJ), nK = BK == 64 ? m : (m + 1) / 2, firstK = J * kBJ / BK;
-  const int64_t xbeg = share * chunk, xend = xbeg + chunk < N ? xbeg + chunk : N;
-  if (xbeg >= xend) return;
-  const Unit3 u = {J, firstK + unit % (nK - firstK), NI * (unit / (nK - firstK)), xbeg, xend};
-  pr3_unit<T, ATOMIC, BK, NI>(d, B, ldb, out, u, sh);
-}
-
-// ---- A3 in single precision, by the three-part split (split3.h) --------------------------------------------------
-// The same units with 64 x 64 tiles and four wavefronts, on the bf16 matrix cores.  A thread stages eight samples of one
-// column of each tile (a wavefront reads 256 contiguous bytes of each sample and shares the eight samples, so the slices'
-// weights are one load, a lane each, and reach the others through scalar registers; as scalar loads they would make every
-// wait for LDS a wait for memory), multiplies the j column with each slice's weights in fp32, as the rule has it, and splits the
-// products and the k column in three (split3.h).  Requests run two steps ahead of their use, the split one, beside the matrix instructions; the last six of
-// every slice stand behind the barrier.  N=10000, d=256: 696 us (848 on the fp32 cores); of the 1970 cycles of a workgroup's step
-// the vector instructions take 1000 (the split and the products, a quarter of them for sub-tiles that are dead), LDS
-// 1050 and the matrix instructions 576.  Other sizes, us here and on the fp32 instructions: N=1000, d=320 187, 182; N=2000, d=512 865,
-// 1015; N=1000, d=1024 3050, 3590; N=1000, d=2048 23800, 26400; where a few hundred samples leave a last round nearly empty the split is up to
-// 7 % slower (N=600, d=256 77, 72).
-//
-// A unit whose sums are not finite -- operands that the split cannot hold, or results that are not finite -- is evaluated again on
-// the fp32 instructions, in the same LDS (us, N=10000, d=256: 693, with one NaN among the samples 908, with nothing else 1612; the fp32
-// instructions alone 843.  Asking after the first steps already spares such units the split, 970, but costs every other call 2 %).
-template <bool ATOMIC, int NI>
-__device__ __attribute__((noinline)) void pr3_again(int64_t d, const float *B, int64_t ldb, float *out, Unit3 u,
-                                                    __attribute__((address_space(3))) Shared3<float, 64, NI> *sh) {
-  pr3_unit<float, ATOMIC, 64, NI>(d, B, ldb, out, u, *(Shared3<float, 64, NI> *)sh);
-}
-
-template <bool ATOMIC, int NI>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
-void pr3_split_kernel(int64_t N, int64_t d, const float *__restrict__ B, int64_t ldb, float *__restrict__ out, int64_t chunk,
-                      int64_t units, int64_t split) {
-  constexpr int kXT = 32, BK = 64, kT = 64 * kXT;  // elements of one staged tile
-  typedef unsigned short Parts16[3][(NI + 1) * kT];  // part; the slices' products, then the k columns
-  __shared__ __attribute__((aligned(16))) Parts16 parts[2];
-  static_assert(sizeof(Shared3<float, BK, NI>) <= sizeof parts, "the second evaluation uses the same memory");
-  __shared__ int again;  // some wavefront's sums are not finite
-
-  int64_t share, unit;
-  if (!my_item(units, split, share, unit)) return;
-  int64_t J = 0;
-  while (unit >= units_of_row_block(d, BK, NI, J)) unit -= units_of_row_block(d, BK, NI, J), ++J;
-  const int64_t nK = ceil_div(d, kBJ), firstK = J;
-  const int64_t i0 = NI * (unit / (nK - firstK));  // first slice of the group
-  const int64_t Kb = firstK + unit % (nK - firstK);
-  const int64_t xbeg = share * chunk;
-  const int64_t xend = xbeg + chunk < N ? xbeg + chunk : N;
-  if (xbeg >= xend) return;
-  const int nk = (int)ceil_div(xend - xbeg, kXT);
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = uniform32(tid >> 6);
-  const int wr = wave >> 1, wc = wave & 1;
-  const int64_t jw = J * kBJ + wr * 32, kw = Kb * BK + wc * 32;  // first row and column of this wavefront's sub-tile
-  const bool live = uniform32((kw + 31 >= jw && jw + 31 >= i0) ? 1 : 0) != 0;  // see pr3_mfma_kernel
-  const unsigned jcol = 4u * (unsigned)(J * kBJ + lane < d ? J * kBJ + lane : d - 1);
-  const unsigned kcol = 4u * (unsigned)(Kb * BK + lane < d ? Kb * BK + lane : d - 1);
-  static_assert(NI <= 8, "one lane holds one weight");
-  const int we = lane & 7, wi = lane >> 3;  // lane 8 ii + e holds the weight of slice i0 + ii for sample e
-  const int64_t icol = wi < NI && i0 + wi < d ? i0 + wi : d - 1;
-
-  struct Stage {
-    float j[8], k[8], w;
-  };
-  auto load = [&](int kt, Stage &s) __attribute__((always_inline)) {
-    const int64_t x0 = xbeg + (int64_t)kt * kXT + 8 * wave;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int64_t x = x0 + e < xend ? x0 + e : xend - 1;
-      const float *row = B + x * ldb;
-      s.j[e] = *reinterpret_cast<const float *>(reinterpret_cast<const char *>(row) + jcol);
-      s.k[e] = *reinterpret_cast<const float *>(reinterpret_cast<const char *>(row) + kcol);
-    }
-    s.w = B[(x0 + we < xend ? x0 + we : xend - 1) * ldb + icol];
-  };
-  auto put = [&](int buf, int tile, const float (&x)[8]) __attribute__((always_inline)) {
-    const Parts p = split3x8(x);
-    const int at = tile * kT + part_place(lane, wave);
-#pragma unroll
-    for (int y = 0; y < 3; ++y) *reinterpret_cast<u4v *>(&parts[buf][y][at]) = p.v[y];
-  };
-  auto convert = [&](int buf, int kt, Stage &s) __attribute__((always_inline)) {
-    const int left = (int)(xend - xbeg) - kt * kXT - 8 * wave;  // samples of this wavefront's eight that exist
-    if (left < 8) {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        s.k[e] = e < left ? s.k[e] : 0.0f;
-        s.j[e] = e < left ? s.j[e] : 0.0f;
-      }
-      s.w = we < left ? s.w : 0.0f;
-    }
-#pragma unroll
-    for (int ii = 0; ii < NI; ++ii) {
-      float p[8];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) p[e] = s.j[e] * __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(s.w), 8 * ii + e));
-      put(buf, ii, p);
-    }
-    put(buf, NI, s.k);
-  };
-  struct Plane {
-    u4v a[NI], b;
-  };
-  auto read = [&](int buf, int t, int part, Plane &o) __attribute__((always_inline)) {
-#pragma unroll
-    for (int ii = 0; ii < NI; ++ii)
-      o.a[ii] = *reinterpret_cast<const u4v *>(&parts[buf][part][ii * kT + part_place(wr * 32 + (lane & 31), 2 * t + (lane >> 5))]);
-    o.b = *reinterpret_cast<const u4v *>(&parts[buf][part][NI * kT + part_place(wc * 32 + (lane & 31), 2 * t + (lane >> 5))]);
-  };
-  Core<float>::Acc hi[NI], lo[NI];  // the five smaller products have an accumulator of their own
-#pragma unroll
-  for (int ii = 0; ii < NI; ++ii) Core<float>::clear(hi[ii]), Core<float>::clear(lo[ii]);
-  auto mma = [&](const Plane &a, const Plane &b, bool largest) __attribute__((always_inline)) {
-#pragma unroll
-    for (int ii = 0; ii < NI; ++ii) {
-      f16v &acc = largest ? hi[ii].v : lo[ii].v;
-      acc = mma_bf16(a.a[ii], b.b, acc);
-    }
-  };
-  Stage s0, s1;
-  Plane h0, h1, md, lw;
-  auto upto = [&](int kt) { return kt < nk ? kt : nk - 1; };  // past the last step: that step again
-  if (tid == 0) again = 0;
-  load(0, s0);
-  load(upto(1), s1);
-  convert(0, 0, s0);
-  __syncthreads();
-  read(0, 0, 0, h0);
-  auto step = [&](int kt, int buf, Stage &freed, Stage &coming) __attribute__((always_inline)) {
-    load(upto(kt + 2), freed);
-    read(buf, 0, 1, md);
-    read(buf, 0, 2, lw);
-    convert(buf ^ 1, upto(kt + 1), coming);
-    if (live) {
-      mma(h0, h0, true);
-      mma(h0, md, false);
-      mma(md, h0, false);
-      mma(md, md, false);
-      read(buf, 1, 0, h1);
-      mma(h0, lw, false);
-      mma(lw, h0, false);
-      read(buf, 1, 1, md);
-      read(buf, 1, 2, lw);
-      mma(h1, h1, true);
-      mma(h1, md, false);
-      mma(md, h1, false);
-    }
-    __syncthreads();
-    read(buf ^ 1, 0, 0, h0);
-    if (live) {
-      mma(md, md, false);
-      mma(h1, lw, false);
-      mma(lw, h1, false);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-  };
-  int kt = 0;
-  for (; kt + 1 < nk; kt += 2) {
-    step(kt, 0, s0, s1);
-    step(kt + 1, 1, s1, s0);
-  }
-  if (kt + 1 == nk) step(kt, 0, s0, s1);
-
-  bool bad = false;
-#pragma unroll
-  for (int ii = 0; ii < NI; ++ii) {
-    hi[ii].v += lo[ii].v;
-    if (i0 + ii < d) bad |= Core<float>::non_finite(hi[ii], lane, d - kw);
-  }
-  if (live && __any(bad) && lane == 0) again = 1;
-  __syncthreads();
-  if (uniform32(again)) {
-    pr3_again<ATOMIC, NI>(d, B, ldb, out, Unit3{J, Kb, i0, xbeg, xend}, (__attribute__((address_space(3))) Shared3<float, BK, NI> *)&parts);
-    return;
-  }
-  if (!live) return;
-
-#pragma unroll
-  for (int ii = 0; ii < NI; ++ii) {
-    const int64_t i = i0 + ii, q = d - i;  // slice and the order of its triangle
-    if (i >= d) break;
-    hi[ii].v *= kSplitDown;
-    float *slice = out + tet_slice_start(d, i);
-    Core<float>::for_each(hi[ii], lane, [&](int r, int c, float v) {
-      const int64_t j = jw + r, k = kw + c;
-      if (i <= j && j <= k && k < d) {
-        float *p = slice + tri_offset(q, j - i, k - i);
-        if (ATOMIC)
-          unsafeAtomicAdd(p, v);
-        else
-          *p = v;
-      }
-    });
-  }
-}
-
 template <typename T>
 __global__ void fill_zero_kernel(T *__restrict__ y, int64_t count) {
   for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < count; t += (int64_t)gridDim.x * blockDim.x)
     y[t] = T(0);
 }
 
-// Which kernel: A2, A3 on the instructions of the type, A3 by the split.
-enum Kind { kSquare, kCube, kCubeSplit };
-template <typename T, Kind KIND, bool ATOMIC, int BK, int NI>
-void launch(unsigned grid, hipStream_t st, int64_t N, int64_t d, const T *B, int64_t ldb, T *out, int64_t chunk,
-            int64_t units, int64_t split) {
-  if constexpr (KIND == kCubeSplit)
-    pr3_split_kernel<ATOMIC, NI><<<grid, 4 * BK, 0, st>>>(N, d, B, ldb, out, chunk, units, split);
-  else if constexpr (KIND == kCube)
-    pr3_mfma_kernel<T, ATOMIC, BK, NI><<<grid, 4 * BK, 0, st>>>(N, d, B, ldb, out, chunk, units, split);
-  else
-    pr2_mfma_kernel<T, ATOMIC, BK><<<grid, 4 * BK, 0, st>>>(N, d, B, ldb, out, chunk, units, split);
-}
-
-// NI: slices per workgroup of the A3 kernel (not used for A2)
-template <typename T, Kind KIND, int BK, int NI = 2>
+template <typename T, int BK>
 int run(int64_t N, int64_t d, const T *B, int64_t ldb, T *out, void *stream) {
   constexpr int kBlock = 4 * BK, kXT = Core<T>::kKT;
-  constexpr bool CUBE = KIND != kSquare;
   constexpr int64_t kB = (int64_t)sizeof(T);
   if (N < 0 || d < 0 || ldb < d) return DASTAC_EINVAL;
-  if (d > (CUBE ? kMaxD3 : kMaxD2) || N > kMaxN || ld_too_large(ldb)) return DASTAC_EOVERFLOW;
+  if (d > kMaxD2 || N > kMaxN || ld_too_large(ldb)) return DASTAC_EOVERFLOW;
   if (d == 0) return DASTAC_OK;
   if (!out || (N > 0 && !B)) return DASTAC_ENULL;
-  const int64_t count = CUBE ? tet(d) : tri(d);
+  const int64_t count = tri(d);
   if (overlaps(out, count * kB, B, view_bytes(N, ldb, d, kB))) return DASTAC_EALIAS;
   hipStream_t st = (hipStream_t)stream;
 
-  const int64_t units = CUBE ? total_units(d, BK, NI) : tiles_of(ceil_div(d, kBJ), BK);
+  const int64_t units = tiles_of(ceil_div(d, kBJ), BK);
   if (units > 0x7fffffff) return DASTAC_EOVERFLOW;
   // Split the samples when the units alone cannot fill the chip.  All workgroups cost the same, so the
   // launch runs in rounds of `slots` resident workgroups: take the smallest split that fills its last
   // round to 90 %, or else the best one found; every share is a multiple of a step and at least 8 steps.
   int64_t split = 1, chunk = kXT;
   if (N > 0) {
-    int64_t slots;
-    if constexpr (KIND == kCubeSplit)
-      slots = resident_blocks(pr3_split_kernel<true, NI>, kBlock);
-    else if constexpr (KIND == kCube)
-      slots = resident_blocks(pr3_mfma_kernel<T, true, BK, NI>, kBlock);
-    else
-      slots = resident_blocks(pr2_mfma_kernel<T, true, BK>, kBlock);
+    const int64_t slots = resident_blocks(pr2_mfma_kernel<T, true, BK>, kBlock);
     if (slots <= 0) return DASTAC_EHIP;
     const int64_t max_split = N / (8 * kXT) > 1 ? N / (8 * kXT) : 1;
     double best = -1.0;
@@ -674,9 +273,9 @@ int run(int64_t N, int64_t d, const T *B, int64_t ldb, T *out, void *stream) {
   }
   const unsigned grid = (unsigned)(8 * per_xcd);
   if (atomic)
-    launch<T, KIND, true, BK, NI>(grid, st, N, d, B, ldb, out, chunk, units, split);
+    pr2_mfma_kernel<T, true, BK><<<grid, kBlock, 0, st>>>(N, d, B, ldb, out, chunk, units, split);
   else
-    launch<T, KIND, false, BK, NI>(grid, st, N, d, B, ldb, out, chunk, units, split);
+    pr2_mfma_kernel<T, false, BK><<<grid, kBlock, 0, st>>>(N, d, B, ldb, out, chunk, units, split);
   return launch_status();
 }
 
@@ -685,28 +284,14 @@ int run(int64_t N, int64_t d, const T *B, int64_t ldb, T *out, void *stream) {
 extern "C" {
 
 int dastac_pr_a2_f32(int64_t N, int64_t d, const float *B, int64_t ldb, float *A2p, void *stream) {
-  return d <= kNarrowMaxD2 ? run<float, kSquare, 64>(N, d, B, ldb, A2p, stream)
-                           : run<float, kSquare, 128>(N, d, B, ldb, A2p, stream);
-}
-
-// A few samples run on the fp32 instructions: with two steps, or four where the units come in several rounds, the split's
-// two workgroups per compute unit against three and its longer start cost more than its rate brings (us, fp32 instructions and
-// split: N=32, d=64 6.7, 7.8; d=256 12.4, 16.7; d=1024 324, 431; N=100, d=100 13.3, 12.6; d=256 23.5, 26.3; d=1024 669, 705; N=150, d=256 27.4,
-// 28.3; d=1024 780, 750).
-int dastac_pr_a3_f32(int64_t N, int64_t d, const float *B, int64_t ldb, float *A3p, void *stream) {
-  return N <= 64 || (N <= 128 && d >= 256) ? run<float, kCube, 64>(N, d, B, ldb, A3p, stream)
-                                           : run<float, kCubeSplit, 64>(N, d, B, ldb, A3p, stream);
+  return d <= kNarrowMaxD2 ? run<float, 64>(N, d, B, ldb, A2p, stream)
+                           : run<float, 128>(N, d, B, ldb, A2p, stream);
 }
 
 // Double precision (the paper's element type): the same kernel on the fp64 matrix cores.
 int dastac_pr_a2_f64(int64_t N, int64_t d, const double *B, int64_t ldb, double *A2p, void *stream) {
-  return d <= kNarrowMaxD2 ? run<double, kSquare, 64>(N, d, B, ldb, A2p, stream)
-                           : run<double, kSquare, 128>(N, d, B, ldb, A2p, stream);
-}
-
-int dastac_pr_a3_f64(int64_t N, int64_t d, const double *B, int64_t ldb, double *A3p, void *stream) {
-  return d <= kNarrowMaxD3 ? run<double, kCube, 64, 2>(N, d, B, ldb, A3p, stream)
-                           : run<double, kCube, 128, 2>(N, d, B, ldb, A3p, stream);
+  return d <= kNarrowMaxD2 ? run<double, 64>(N, d, B, ldb, A2p, stream)
+                           : run<double, 128>(N, d, B, ldb, A2p, stream);
 }
 
 }  // extern "C"

@@ -1,0 +1,754 @@
+// The third-order polynomial-regression tensor (Table 1, "Polynomial Regression Degree-D") written straight into a packed
+// hyper-tetrahedron on the matrix cores, single and double precision:
+//
+//   A3(i,j,k) := B(x,i) * B(x,j) * B(x,k)   i<=j<=k     packed upper tetrahedron, tet(d,i,j,k)
+//
+// B is the dense N x d sample matrix.  As a matrix product: rows are pairs (i,j), columns are k, and the first operand is the product
+// B(x,i) B(x,j), formed (and, in single precision, split in three bf16 parts, split3.h) on the way to the matrix instruction.  A tile of 32 rows
+// is 4 i times 8 j or 2 i times 16 j and its columns start at its first j, so that little of it lies outside i<=j<=k: at d=256 the tiles
+// hold 1.2 to 1.3 times the elements that are wanted (tiles of 64 j by 64 k for one slice i each, of which a workgroup's wavefronts
+// wait for each other: 1.85).
+//
+// Three kernels, chosen in run() by the sizes:
+//   few      fewer than 16 samples: vector instructions, a column a lane;
+//   direct   a wavefront owns a tile and every WX-th step of 16 samples; operands come straight from memory, nothing is staged and nobody
+//            waits for anybody until the workgroup's WX wavefronts add their sums through LDS.  All of double precision, small
+//            products in single;
+//   staged   single precision, where operands are read and split often enough to share: eight wavefronts of 32 x (32..128) elements
+//            on one set of k columns, split once into LDS.
+// Where workgroups share a tile's samples they add into an output cleared by a fill kernel, with floating-point atomics.
+#include "cube_units.h"
+#include "launch_limits.h"
+#include "split3.h"
+
+using namespace dastac;
+
+namespace {
+
+constexpr int64_t kMaxD3 = 1 << 13;  // unit counts stay inside 32 bits
+constexpr int64_t kMaxN = (int64_t)1 << 31;
+constexpr int kStep = 16;  // samples per step of a wavefront of the direct kernel
+constexpr int kSub = kCubeSub;
+
+// ---- fewer than 16 samples ---------------------------------------------------------------------------------------
+// Bound by the writes and by the latency of N reads: a workgroup takes slice i and sixteen rows j, its wavefronts 64 columns k each, a column a
+// lane with sixteen sums; the sixteen factors of a sample are scalars (N=3, d=1024 216 us, tiles on the matrix instructions 350; N=10, d=256 18 and 13;
+// with 64 samples the scalar reads take longer than those tiles, 1000 and 419).
+template <typename T>
+__global__ __launch_bounds__(256) void pr3_few_kernel(int N, int d, const T *__restrict__ B, int64_t ldb, T *__restrict__ out) {
+  constexpr int kJ = 16;
+  const int i = blockIdx.y, j0 = i + kJ * (int)blockIdx.x;
+  if (j0 >= d) return;
+  const bool whole = j0 + kJ <= d;
+  for (int k0 = j0 + 64 * uniform32(threadIdx.x >> 6); k0 < d; k0 += 256) {
+    const int k = k0 + (int)(threadIdx.x & 63), kc = k < d ? k : d - 1;
+    T s[kJ];
+#pragma unroll
+    for (int q = 0; q < kJ; ++q) s[q] = T(0);
+    if (whole) {
+#pragma unroll 4
+      for (int x = 0; x < N; ++x) {
+        const T *sample = B + x * ldb;
+        const T c = sample[i] * sample[kc];
+#pragma unroll
+        for (int q = 0; q < kJ; ++q) s[q] += c * sample[j0 + q];
+      }
+    } else {
+      for (int x = 0; x < N; ++x) {
+        const T *sample = B + x * ldb;
+        const T c = sample[i] * sample[kc];
+#pragma unroll
+        for (int q = 0; q < kJ; ++q) s[q] += c * sample[j0 + q < d ? j0 + q : d - 1];
+      }
+    }
+    T *const slice = out + tet_slice_start(d, i) + tri(d - i);
+#pragma unroll
+    for (int q = 0; q < kJ; ++q) {
+      const int j = j0 + q;
+      if (j <= k && k < d) slice[k - j - tri(d - j)] = s[q];
+    }
+  }
+}
+
+// The output's row (i,j), less the 32-bit element number that row_offset() gives it: wave-uniform, so that the 64-bit polynomial is scalar work.
+template <typename T>
+__device__ inline T *slice_base(T *out, int d, int i, int j0) {
+  return out + (tet_slice_start(d, i) + tri(d - i) - tri(d - j0));
+}
+// Element (i,j,k) from there, j >= j0 (rows of slice i are tri(d-i) - tri(d-j) into it, d <= 8192).
+__device__ inline unsigned row_offset(int d, int j0, int j, int k) {
+  const unsigned a = (unsigned)(d - j0), b = (unsigned)(d - j);
+  return (a * (a + 1) - b * (b + 1)) / 2 + (unsigned)(k - j);
+}
+
+// ---- direct ------------------------------------------------------------------------------------------------------
+// A tile of 32 rows holds four slices i and eight j: row r is slice r / 8 and j = r % 8 (cube_units.h).
+
+// A wavefront's operands and sums: NT tiles of 32 rows by 32 columns.
+template <typename T, int NT>
+struct Cube;
+
+// Lane l takes row (column) l % 32 and, of a step's samples, those with number 2 e + l / 32.
+template <int NT>
+struct Cube<float, NT> {
+  static constexpr int kRegs = 16;
+  struct Raw {
+    float j[8], k[8], i[8][NT];
+  };
+  struct Sums {
+    f16v hi[NT], lo[NT];  // the largest of the six partial products, and the five smaller ones
+  };
+  global_bytes base;
+  int64_t pitch;  // bytes per sample
+  unsigned oj, ok, oi[NT];
+  int h;
+  template <typename F>
+  __device__ Cube(const float *B, int64_t ldb, int64_t i0, int64_t j0, int64_t k0, int lane, F column) {
+    base = (global_bytes) reinterpret_cast<const char *>(B), pitch = 4 * ldb, h = lane >> 5;
+    const unsigned row = (unsigned)h * (unsigned)pitch;
+    const int r = lane & 31;
+    oj = row + 4u * (unsigned)column(j0 + (r & 7)), ok = row + 4u * (unsigned)column(k0 + r);
+#pragma unroll
+    for (int q = 0; q < NT; ++q) oi[q] = row + 4u * (unsigned)column(i0 + 4 * q + (r >> 3));
+  }
+  __device__ void load(int64_t x0, Raw &s) const {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const global_bytes row = in_scalar_registers(base + (x0 + 2 * e) * pitch);
+      s.j[e] = *(const float __attribute__((address_space(1))) *)(row + oj);
+      s.k[e] = *(const float __attribute__((address_space(1))) *)(row + ok);
+#pragma unroll
+      for (int q = 0; q < NT; ++q) s.i[e][q] = *(const float __attribute__((address_space(1))) *)(row + oi[q]);
+    }
+  }
+  __device__ void skip(int n, Raw &s) const {  // the step's first n samples count nothing
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const bool out = 2 * e + h < n;
+      s.j[e] = out ? 0.0f : s.j[e];
+      s.k[e] = out ? 0.0f : s.k[e];
+#pragma unroll
+      for (int q = 0; q < NT; ++q) s.i[e][q] = out ? 0.0f : s.i[e][q];
+    }
+  }
+  __device__ static void clear(Sums &c) {
+#pragma unroll
+    for (int q = 0; q < NT; ++q)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) c.hi[q][v] = 0.0f, c.lo[q][v] = 0.0f;
+  }
+  // between() runs when the raw values are used up, in front of the matrix instructions: it requests the next step
+  template <typename F>
+  __device__ static void multiply(const Raw &s, Sums &c, F between) {
+    const Parts k = split3x8(s.k);
+    Parts a[NT];
+#pragma unroll
+    for (int q = 0; q < NT; ++q) {
+      float p[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) p[e] = s.j[e] * s.i[e][q];
+      a[q] = split3x8(p);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    between();
+    constexpr int PA[6] = {0, 2, 0, 1, 0, 1}, PK[6] = {0, 0, 2, 1, 1, 0};
+#pragma unroll
+    for (int g = 0; g < 6; ++g)
+#pragma unroll
+      for (int q = 0; q < NT; ++q) {
+        f16v &acc = g == 0 ? c.hi[q] : c.lo[q];
+        acc = mma_bf16(a[q].v[PA[g]], k.v[PK[g]], acc);
+      }
+  }
+  // false: not all of this lane's sums are finite
+  __device__ static bool finish(Sums &c) {
+    float z = 0.0f;
+#pragma unroll
+    for (int q = 0; q < NT; ++q) {
+      c.hi[q] += c.lo[q];
+#pragma unroll
+      for (int v = 0; v < 16; ++v) z = __builtin_fmaf(c.hi[q][v], 0.0f, z);
+      c.hi[q] *= kSplitDown;
+    }
+    return z == z;
+  }
+  __device__ static void plain(const Raw &s, Sums &c) {  // the same step on the fp32 instructions
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+#pragma unroll
+      for (int q = 0; q < NT; ++q) c.hi[q] = __builtin_amdgcn_mfma_f32_32x32x2f32(s.j[e] * s.i[e][q], s.k[e], c.hi[q], 0, 0, 0);
+  }
+  __device__ static float at(const Sums &c, int q, int v) { return c.hi[q][v]; }
+  // register v is row 8 (v / 4) + 4 (lane / 32) + v % 4, column lane % 32
+  __device__ static int slice_of(int v) { return v / 4; }
+  __device__ static int j_of(int v, int lane) { return 4 * (lane >> 5) + v % 4; }
+  __device__ static int col_of(int, int lane) { return lane & 31; }
+};
+
+// v_mfma_f64_16x16x4_f64: lane l takes row (column) l % 16 and the samples with number 4 e + l / 16; a tile is 2 x 2 of its results.
+template <int NT>
+struct Cube<double, NT> {
+  static constexpr int kRegs = 16;
+  struct Raw {
+    double j[4], k[4][2], i[4][2 * NT];
+  };
+  struct Sums {
+    d4v v[NT][4];
+  };
+  const char *pj, *pk, *pi[2 * NT];
+  int64_t pitch, knext;
+  int h;
+  template <typename F>
+  __device__ Cube(const double *B, int64_t ldb, int64_t i0, int64_t j0, int64_t k0, int lane, F column) {
+    pitch = 8 * ldb, h = lane >> 4;
+    const char *row = reinterpret_cast<const char *>(B) + h * pitch;
+    const int r = lane & 15;
+    pj = row + 8 * column(j0 + (r & 7)), pk = row + 8 * column(k0 + r);
+    knext = 8 * (column(k0 + 16 + r) - column(k0 + r));
+#pragma unroll
+    for (int q = 0; q < 2 * NT; ++q) pi[q] = row + 8 * column(i0 + 2 * q + (r >> 3));
+  }
+  __device__ void load(int64_t x0, Raw &s) const {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int64_t row = (x0 + 4 * e) * pitch;
+      s.j[e] = *reinterpret_cast<const double *>(pj + row);
+      s.k[e][0] = *reinterpret_cast<const double *>(pk + row);
+      s.k[e][1] = *reinterpret_cast<const double *>(pk + row + knext);
+#pragma unroll
+      for (int q = 0; q < 2 * NT; ++q) s.i[e][q] = *reinterpret_cast<const double *>(pi[q] + row);
+    }
+  }
+  __device__ void skip(int n, Raw &s) const {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const bool out = 4 * e + h < n;
+      s.j[e] = out ? 0.0 : s.j[e];
+#pragma unroll
+      for (int q = 0; q < 2; ++q) s.k[e][q] = out ? 0.0 : s.k[e][q];
+#pragma unroll
+      for (int q = 0; q < 2 * NT; ++q) s.i[e][q] = out ? 0.0 : s.i[e][q];
+    }
+  }
+  __device__ static void clear(Sums &c) {
+#pragma unroll
+    for (int q = 0; q < NT; ++q)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) c.v[q][t] = d4v{0.0, 0.0, 0.0, 0.0};
+  }
+  template <typename F>
+  __device__ static void multiply(const Raw &s, Sums &c, F between) {
+    const Raw o = s;
+    between();
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int q = 0; q < NT; ++q) {
+        const double a0 = o.j[e] * o.i[e][2 * q], a1 = o.j[e] * o.i[e][2 * q + 1];
+        c.v[q][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, o.k[e][0], c.v[q][0], 0, 0, 0);
+        c.v[q][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, o.k[e][1], c.v[q][1], 0, 0, 0);
+        c.v[q][2] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, o.k[e][0], c.v[q][2], 0, 0, 0);
+        c.v[q][3] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, o.k[e][1], c.v[q][3], 0, 0, 0);
+      }
+  }
+  __device__ static bool finish(Sums &) { return true; }
+  __device__ static void plain(const Raw &, Sums &) {}
+  __device__ static double at(const Sums &c, int q, int v) { return c.v[q][v / 4][v % 4]; }
+  // register v is row 16 (v / 8) + 4 (v % 4) + lane / 16, column 16 (v / 4 % 2) + lane % 16
+  __device__ static int slice_of(int v) { return 2 * (v / 8) + v % 4 / 2; }
+  __device__ static int j_of(int v, int lane) { return 4 * (v % 2) + (lane >> 4); }
+  __device__ static int col_of(int v, int lane) { return 16 * ((v / 4) & 1) + (lane & 15); }
+};
+
+// Wavefronts per SIMD: what the registers hold (92 with one tile, 136 with two in single precision; the accumulators are half of them).
+// Work items are (sample share, unit) pairs, share-major; id%8 is the XCD, id/8 the position in that XCD's run of consecutive items, so
+// that the units of a share read the same rows of B out of one L2.  `base`: the first unit of this launch (more than one launch only where
+// the units' work-items pass 32 bits, with one share).
+// Bound by the vector instructions of the split in single precision (170 beside 6 matrix instructions a step of one tile, 230 beside 12 of two),
+// by the matrix instructions in double (N=10000, d=200: 676 us, of which 0.77 at their peak; per-slice tiles of 64 x 64 through LDS took 1700).  us
+// in single precision here and in the tiles of 64 x 64: N=620, d=36 7.3, 22; N=381, d=104 9.9, 23; N=9504, d=24 10.2, 23.7; N=1018, d=114 15.4, 27.9;
+// N=3000, d=100 28, 53; in double N=1322, d=18 6.8, 23; N=3993, d=31 11, 34; N=604, d=314 175, 238; N=20000, d=40 33, 137.
+template <int WX>
+constexpr int kUnitsPerGroup = WX == 1 ? 4 : 1;  // single wavefronts go four to a workgroup: fewer to dispatch
+template <typename T, int NT, int WX, bool ATOMIC>
+__global__ __launch_bounds__(64 * WX * kUnitsPerGroup<WX>) __attribute__((amdgpu_waves_per_eu(NT == 1 ? 4 : 3, NT == 1 ? 4 : 3)))
+void pr3_direct_kernel(int64_t N, int d, const T *__restrict__ B, int64_t ldb, T *__restrict__ out, int64_t chunk, unsigned base,
+                       unsigned units, unsigned split) {
+  typedef Cube<T, NT> C;
+  constexpr int kSlots = WX > 1 ? WX / 2 : 1;
+  __shared__ T slots[kSlots][NT * C::kRegs * 64];
+  constexpr unsigned kOwn = kUnitsPerGroup<WX>;
+  const int lane = threadIdx.x & 63, wave = kOwn > 1 ? 0 : uniform32(threadIdx.x >> 6);
+  const unsigned items = units * split, xcd = blockIdx.x & 7;
+  const unsigned item = (unsigned)((uint64_t)items * xcd / 8) + (blockIdx.x >> 3) * kOwn + (kOwn > 1 ? (unsigned)uniform32(threadIdx.x >> 6) : 0u);
+  if (item >= (unsigned)((uint64_t)items * (xcd + 1) / 8)) return;
+  const unsigned share = split == 1 ? 0 : item / units;
+  const CubeTile u = direct_tile(d, NT, (int)(base + item - share * units));
+  const int i0 = uniform32(u.i0), j0 = uniform32(u.j0), k0 = uniform32(u.k0);
+  const int64_t xbeg = uniform64(share * chunk), xend = xbeg + chunk < N ? xbeg + chunk : N;
+  if (xbeg >= xend) return;
+  // columns past the last are read as the last; nothing of them is kept
+  const C cube(B, ldb, i0, j0, k0, lane, [&](int c) { return c < d ? c : d - 1; });
+  const int steps = (int)((xend - xbeg + kStep - 1) / kStep);
+  // Step s begins at sample xbeg + 16 s; one that would pass xend is moved back to end there (N >= 16), and what it repeats is made zero.
+  const int64_t last = xend - kStep;
+  auto first = [&](int s) { return xbeg + (int64_t)kStep * s < last ? xbeg + (int64_t)kStep * s : last; };
+  auto repeats = [&](int s) { return (int)(xbeg + (int64_t)kStep * s - first(s)); };
+  typename C::Sums acc;
+  C::clear(acc);
+  typename C::Raw raw;
+  if (wave < steps) cube.load(first(wave), raw);
+  for (int s = wave; s < steps; s += WX) {
+    if (repeats(s) > 0) cube.skip(repeats(s), raw);
+    const int next = s + WX < steps ? s + WX : s;
+    C::multiply(raw, acc, [&] { cube.load(first(next), raw); });
+  }
+  // Operands that the split cannot hold, or results that are not finite: this wavefront's steps again on the fp32 instructions.
+  if (!__all(C::finish(acc))) {
+    C::clear(acc);
+    for (int s = wave; s < steps; s += WX) {
+      cube.load(first(s), raw);
+      if (repeats(s) > 0) cube.skip(repeats(s), raw);
+      C::plain(raw, acc);
+    }
+  }
+  if constexpr (WX > 1) {
+    // the upper half of the wavefronts leave their sums, the lower half add their own, then all add up the slots and write
+    T *mine = slots[wave % kSlots];
+    if (wave >= kSlots) {
+#pragma unroll
+      for (int q = 0; q < NT; ++q)
+#pragma unroll
+        for (int v = 0; v < C::kRegs; ++v) mine[(q * C::kRegs + v) * 64 + lane] = C::at(acc, q, v);
+    }
+    __syncthreads();
+    if (wave < kSlots) {
+#pragma unroll
+      for (int q = 0; q < NT; ++q)
+#pragma unroll
+        for (int v = 0; v < C::kRegs; ++v) mine[(q * C::kRegs + v) * 64 + lane] += C::at(acc, q, v);
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int t = 0; t < NT * C::kRegs / WX; ++t) {
+    const int g = (WX > 1 ? wave : 0) + WX * t, q = g / C::kRegs, v = g % C::kRegs;
+    T sum;
+    if constexpr (WX == 1) {
+      sum = C::at(acc, q, v);
+    } else {
+      sum = slots[0][g * 64 + lane];
+#pragma unroll
+      for (int s = 1; s < kSlots; ++s) sum += slots[s][g * 64 + lane];
+    }
+    const int i = i0 + 4 * q + C::slice_of(v), j = j0 + C::j_of(v, lane), k = k0 + C::col_of(v, lane);
+    if (i >= d) continue;
+    T *const base = slice_base(out, d, i, j0);
+    if (i <= j && j <= k && k < d) {
+      T *p = base + row_offset(d, j0, j, k);
+      if (ATOMIC)
+        unsafeAtomicAdd(p, sum);
+      else
+        *p = sum;
+    }
+  }
+}
+
+// ---- staged (single precision) -----------------------------------------------------------------------------------
+// A workgroup of eight wavefronts takes 16 j, 16 slices i (two a wavefront: row r of its tile is slice r / 16 and j = r % 16) and
+// 32 WN columns k, WN <= 4.  Per step of 32 samples the k columns are split into LDS once for all wavefronts, the columns j and i stay
+// floats there ([column][sample], the i times 2^24 as the split wants it) and every wavefront multiplies and splits its own rows beside its
+// matrix instructions; each row's parts meet WN column blocks.  Reads of a step run two steps ahead of their use (buffer instructions: the
+// row is a scalar offset, so ldb <= 2^24).  The order of the steps is written down with scheduling fences: left alone, the compiler splits
+// a tile's rows in one run with the matrix cores idle.
+//
+// The work of all units (row block, columns, slices, samples) is one line in units of cube_weight(WN) per step, cut into equal parts, one
+// workgroup per compute unit; a part may begin and end inside a unit, all parts add into a cleared output.  The weights are fitted: a step
+// of one column block costs more than half of one of four (N=10000, d=256 with weights 16:19:24:29 411-415 us, 13:14:23:33 475, 20:22:25:28 441; WN at most
+// 3, 2: 462, 491).  Bound by the matrix cores at the clock that their power leaves (half of the 1.86 GHz cycles, 0.98 PFLOP/s of bf16; a library product
+// 1.35) -- neither bank conflicts, nor reads from another XCD's L2, nor the split's instruction count show in the time any more.
+// us here and in the tiles of 64 x 64: N=10000, d=256 411, 687; N=2000, d=256 105, 170; N=20000, d=160 266, 611.
+// Measured and not kept: v_dot2_f32_bf16 for the remainders of the split (a third fewer instructions, the same time; in the other kernels it
+// takes the matrix cores' time); two and four row tiles a wavefront where there are few columns (414 against 411, and 138 against 105 at N=2000); one
+// range of samples per XCD (no difference); two to five times as many parts (up to 479).
+constexpr int kXT = 32;
+constexpr int kPitch = kXT + 4;  // of the staged columns j and i: 16 columns fall on distinct banks
+constexpr int64_t kMaxStagedLd = 1 << 24;
+
+struct Staged {
+  __attribute__((aligned(16))) unsigned short parts[2][3][4 * kSub * kXT];
+  __attribute__((aligned(16))) float ji[2][32 * kPitch];  // columns j (16), columns i (16); [column][sample]
+};
+
+// A wavefront's tiles of a piece once more, on the fp32 instructions with operands straight from memory, two column blocks at a time and the
+// next sixteen samples on their way: where operands or results are beyond what the split can hold.  A function of its own: in the middle of the kernel it cost the
+// main loop its registers (N=10000, d=512 2.7 -> 3.1 ms).
+__device__ __attribute__((noinline)) void again(int64_t N, int d, const float *B, int64_t ldb, float *out, CubeTile u, int wn, int s0, int s1) {
+  const int lane = threadIdx.x & 63, wave = uniform32(threadIdx.x >> 6), r = lane & 31, h = lane >> 5;
+  auto column = [&](int c) { return c < d ? c : d - 1; };
+  const int cj = column(u.j0 + (r & 15)), ci = column(u.i0 + 2 * wave + (r >> 4));
+  const int64_t end = (int64_t)s1 * kXT < N ? (int64_t)s1 * kXT : N;
+  for (int n = 0; n < wn; n += 2) {
+    const int k = u.k0 + 32 * n + r, ck0 = column(k), ck1 = column(k + 32);
+    struct Raw {
+      float a[8], b0[8], b1[8];
+    };
+    auto load = [&](int64_t x0, Raw &o) __attribute__((always_inline)) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int64_t x = x0 + 2 * e + h;
+        const float *row = B + (x < end ? x : end - 1) * ldb;
+        o.a[e] = x < end ? row[cj] * row[ci] : 0.0f;
+        o.b0[e] = x < end ? row[ck0] : 0.0f;
+        o.b1[e] = x < end ? row[ck1] : 0.0f;
+      }
+    };
+    f16v sum[2];
+#pragma unroll
+    for (int v = 0; v < 16; ++v) sum[0][v] = 0.0f, sum[1][v] = 0.0f;
+    Raw next;
+    load((int64_t)s0 * kXT, next);
+    for (int64_t x0 = (int64_t)s0 * kXT; x0 < end; x0 += 16) {
+      const Raw o = next;
+      load(x0 + 16 < end ? x0 + 16 : x0, next);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        sum[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(o.a[e], o.b0[e], sum[0], 0, 0, 0);
+        sum[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(o.a[e], o.b1[e], sum[1], 0, 0, 0);
+      }
+    }
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {  // slice v / 8 of the wavefront's two, j = 8 (v / 4 % 2) + 4 h + v % 4
+      const int i = u.i0 + 2 * wave + v / 8, j = u.j0 + 8 * (v / 4 % 2) + 4 * h + v % 4;
+      if (i <= j && j < d) {
+        float *p = out + tet_row_start(d, i, j) - j;
+        if (j <= k && k < d) unsafeAtomicAdd(p + k, sum[0][v]);
+        if (n + 1 < wn && j <= k + 32 && k + 32 < d) unsafeAtomicAdd(p + k + 32, sum[1][v]);
+      }
+    }
+  }
+}
+
+// Steps [s0, s1) of one unit.  False: the wavefront's sums are not all finite, and nothing was added.
+template <int WN>
+__device__ __attribute__((always_inline)) inline bool piece(int64_t N, int d, const float *__restrict__ B, int64_t ldb, float *__restrict__ out,
+                                                            const CubeTile &u, int s0, int s1, Staged &sh) {
+  const int i0 = u.i0, j0 = u.j0, k0 = u.k0;
+  const int tid = threadIdx.x, lane = tid & 63, wave = uniform32(tid >> 6);
+  const int r = lane & 31, h = lane >> 5;
+  auto column = [&](int c) { return c < d ? c : d - 1; };
+  // staging: wavefront w brings samples 8 (w / 2) .. + 7 of k columns 64 (w % 2) + lane, and of samples 4 w .. 4 w + 3 the columns j (lanes
+  // l % 32 < 16) and i
+  const int kc = tid & 127, oct = wave >> 1;
+  const unsigned pitch = 4u * (unsigned)ldb;  // bytes of a sample, ldb <= 2^24
+  const unsigned kcol = 4u * (unsigned)column(k0 + kc);
+  const unsigned wcol = 4u * (unsigned)column(r < 16 ? j0 + r : i0 + r - 16) + (unsigned)h * pitch;
+  const float wscale = r < 16 ? 1.0f : kSplitUp;
+  struct Stage {
+    float k[8], w[2];
+  };
+  auto first = [&](int s) { return s * kXT < (int)(N - kXT) ? s * kXT : (int)(N - kXT); };
+  auto load = [&](int s, Stage &st) __attribute__((always_inline)) {
+    const auto rows = __builtin_amdgcn_make_buffer_rsrc((void *)(B + (int64_t)first(s) * ldb), 0, -1, 0x00020000);
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      st.k[e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rows, kcol, (unsigned)(8 * oct + e) * pitch, 0));
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+      st.w[e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rows, wcol, (unsigned)(4 * wave + 2 * e) * pitch, 0));
+  };
+  // the last step is moved back to end with the samples: what it repeats is zero in the products
+  auto mask = [&](int s, Stage &st) __attribute__((always_inline)) {
+    const int skip = s * kXT - first(s);
+#pragma unroll
+    for (int e = 0; e < 2; ++e) st.w[e] = 4 * wave + 2 * e + h < skip ? 0.0f : st.w[e] * wscale;
+  };
+  auto put_w = [&](int buf, const Stage &st) __attribute__((always_inline)) {
+#pragma unroll
+    for (int e = 0; e < 2; ++e) sh.ji[buf][r * kPitch + 4 * wave + 2 * e + h] = st.w[e];
+  };
+  auto put_k = [&](int buf, const Parts &p) __attribute__((always_inline)) {
+#pragma unroll
+    for (int y = 0; y < 3; ++y) *reinterpret_cast<u4v *>(&sh.parts[buf][y][part_place(kc, oct)]) = p.v[y];
+  };
+  f16v hi[WN], lo[WN];
+#pragma unroll
+  for (int n = 0; n < WN; ++n)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) hi[n][v] = 0.0f, lo[n][v] = 0.0f;
+
+  struct Factors {
+    f4a j[2], i[2];
+  };
+  auto factors = [&](int buf, int t) __attribute__((always_inline)) {
+    Factors f;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      f.j[q] = *reinterpret_cast<const f4a *>(&sh.ji[buf][(r & 15) * kPitch + 16 * t + 8 * h + 4 * q]);
+      f.i[q] = *reinterpret_cast<const f4a *>(&sh.ji[buf][(16 + 2 * wave + (r >> 4)) * kPitch + 16 * t + 8 * h + 4 * q]);
+    }
+    return f;
+  };
+  auto split_pair = [&](Parts &p, int j, float a, float b) __attribute__((always_inline)) {
+    unsigned x, y, z;
+    split3_scaled(a, b, x, y, z);
+    p.v[0][j] = x, p.v[1][j] = y, p.v[2][j] = z;
+  };
+  auto product_pair = [&](Parts &p, const Factors &f, int j) __attribute__((always_inline)) {
+    split_pair(p, j, f.j[j / 2][2 * j % 4] * f.i[j / 2][2 * j % 4], f.j[j / 2][2 * j % 4 + 1] * f.i[j / 2][2 * j % 4 + 1]);
+  };
+  auto columns = [&](int buf, int t, int n) __attribute__((always_inline)) {
+    Parts b;
+#pragma unroll
+    for (int y = 0; y < 3; ++y) b.v[y] = *reinterpret_cast<const u4v *>(&sh.parts[buf][y][part_place(32 * n + r, 2 * t + h)]);
+    return b;
+  };
+  auto mma = [&](const Parts &a, const Parts &b, int n) __attribute__((always_inline)) {
+    lo[n] = mma_bf16(a.v[2], b.v[0], lo[n]);
+    hi[n] = mma_bf16(a.v[0], b.v[0], hi[n]);
+    lo[n] = mma_bf16(a.v[0], b.v[2], lo[n]);
+    lo[n] = mma_bf16(a.v[1], b.v[1], lo[n]);
+    lo[n] = mma_bf16(a.v[1], b.v[0], lo[n]);
+    lo[n] = mma_bf16(a.v[0], b.v[1], lo[n]);
+  };
+  auto fence = [] { __builtin_amdgcn_sched_barrier(0); };
+  Stage st;
+  Parts kp;
+  __syncthreads();  // the buffers of the piece before
+  load(s0, st);
+  mask(s0, st);
+#pragma unroll
+  for (int j = 0; j < 4; ++j) split_pair(kp, j, st.k[2 * j] * kSplitUp, st.k[2 * j + 1] * kSplitUp);
+  put_k(0, kp);
+  put_w(0, st);
+  auto upto = [&](int s) { return s < s1 ? s : s1 - 1; };
+  load(upto(s0 + 1), st);
+  lds_barrier();
+  Parts a0, a1, b0;
+  Factors f = factors(0, 0);
+#pragma unroll
+  for (int j = 0; j < 4; ++j) product_pair(a0, f, j);
+  b0 = columns(0, 0, 0);
+  constexpr int kBefore = WN / 2;
+  // entry: a0 and b0 hold the step's first products and columns, st the next step
+  auto step = [&](int s, int buf) __attribute__((always_inline)) {
+    Parts b[WN + 1];
+    b[0] = b0;
+    f = factors(buf, 1);
+#pragma unroll
+    for (int n = 0; n < WN; ++n) {
+      b[n + 1] = n + 1 < WN ? columns(buf, 0, n + 1) : columns(buf, 1, 0);
+      mma(a0, b[n], n);
+      if (n == (WN > 1 ? 1 : 0)) product_pair(a1, f, 0), product_pair(a1, f, 1);
+      if (n == (WN > 2 ? 2 : WN - 1)) product_pair(a1, f, 2), product_pair(a1, f, 3);
+      fence();
+    }
+    b[0] = b[WN];
+    mask(upto(s + 1), st);
+#pragma unroll
+    for (int n = 0; n < kBefore; ++n) {
+      if (n + 1 < WN) b[n + 1] = columns(buf, 1, n + 1);
+      if (n == kBefore - 1) {
+#pragma unroll
+        for (int m = n + 2; m < WN; ++m) b[m] = columns(buf, 1, m);
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (j * kBefore / 4 == n) split_pair(kp, j, st.k[2 * j] * kSplitUp, st.k[2 * j + 1] * kSplitUp);
+      if (n == kBefore - 1) put_k(buf ^ 1, kp), put_w(buf ^ 1, st);
+      mma(a1, b[n], n);
+      if (n == kBefore - 1) load(upto(s + 2), st);
+      fence();
+    }
+    if (kBefore == 0) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) split_pair(kp, j, st.k[2 * j] * kSplitUp, st.k[2 * j + 1] * kSplitUp);
+      put_k(buf ^ 1, kp), put_w(buf ^ 1, st);
+      load(upto(s + 2), st);
+    }
+    lds_barrier();
+    f = factors(buf ^ 1, 0);
+    b0 = columns(buf ^ 1, 0, 0);
+#pragma unroll
+    for (int n = kBefore; n < WN; ++n) {
+      mma(a1, b[n], n);
+      if (n == WN - 1) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) product_pair(a0, f, j);
+      }
+      fence();
+    }
+  };
+  for (int s = s0; s < s1; s += 2) {
+    step(s, 0);
+    if (s + 1 < s1) step(s + 1, 1);
+  }
+  float z = 0.0f;
+#pragma unroll
+  for (int n = 0; n < WN; ++n) {
+    hi[n] += lo[n];
+#pragma unroll
+    for (int v = 0; v < 16; ++v) z = __builtin_fmaf(hi[n][v], 0.0f, z);
+    hi[n] *= kSplitDown;
+  }
+  if (__any(z != z)) return false;
+  // register v of a lane is slice v / 8 of the wavefront's two, j = 8 (v / 4 % 2) + 4 h + v % 4, column r.  (The lane number is hidden from
+  // the compiler here: it would compute the rows' places before the steps and keep them in memory meanwhile.)
+  int l = lane;
+  asm volatile("" : "+v"(l));
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    const int i = i0 + 2 * wave + v / 8, j = j0 + 8 * (v / 4 % 2) + 4 * (l >> 5) + v % 4;
+    if (i >= d) continue;
+    float *const base = slice_base(out, d, i, j0);
+    if (i <= j && j < d) {
+      float *p = base + row_offset(d, j0, j, j);
+#pragma unroll
+      for (int n = 0; n < WN; ++n) {
+        const int k = k0 + 32 * n + (l & 31);
+        if (j <= k && k < d) unsafeAtomicAdd(p + (k - j), hi[n][v]);
+      }
+    }
+  }
+  return true;
+}
+
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void pr3_staged_kernel(int64_t N, int d, const float *__restrict__ B, int64_t ldb, float *__restrict__ out, int64_t total, int steps, int most) {
+  __shared__ Staged sh;
+  staged_part(d, steps, total, blockIdx.x, gridDim.x, [&](const CubeTile &t, int wn, int s0, int s1) __attribute__((always_inline)) {
+    const CubeTile u = {uniform32(t.i0), uniform32(t.j0), uniform32(t.k0)};
+    for (; s0 < s1; s0 += most) {
+      const int a = uniform32(s0), b = uniform32(s1 - s0 < most ? s1 : s0 + most);
+      bool done;
+      switch (uniform32(wn)) {
+        case 1: done = piece<1>(N, d, B, ldb, out, u, a, b, sh); break;
+        case 2: done = piece<2>(N, d, B, ldb, out, u, a, b, sh); break;
+        case 3: done = piece<3>(N, d, B, ldb, out, u, a, b, sh); break;
+        default: done = piece<4>(N, d, B, ldb, out, u, a, b, sh); break;
+      }
+      if (uniform32(done ? 0 : 1)) again(N, d, B, ldb, out, u, uniform32(wn), a, b);
+    }
+  });
+}
+
+template <typename T>
+__global__ void fill_zero_kernel(T *__restrict__ y, int64_t count) {
+  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < count; t += (int64_t)gridDim.x * blockDim.x)
+    y[t] = T(0);
+}
+template <typename T>
+int clear(int64_t d, T *out, hipStream_t st) {
+  const int64_t zb = ceil_div(tet(d), 256);
+  fill_zero_kernel<T><<<(unsigned)(zb < 8192 ? zb : 8192), 256, 0, st>>>(out, tet(d));
+  return launch_status();
+}
+
+// Compute units of the current device, asked of the runtime on every call.
+int64_t compute_units() {
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+  return cus;
+}
+
+template <typename T, int NT, int WX>
+int launch_direct(int64_t N, int64_t d, const T *B, int64_t ldb, T *out, int64_t units, int64_t split, hipStream_t st) {
+  constexpr int kOwn = kUnitsPerGroup<WX>;
+  const int64_t chunk = ceil_div(ceil_div(N, split), kStep) * kStep;
+  split = ceil_div(N, chunk);
+  if (split > 1) {
+    if (const int rc = clear(d, out, st)) return rc;
+    pr3_direct_kernel<T, NT, WX, true><<<(unsigned)(8 * ceil_div(ceil_div(units * split, 8), kOwn)), 64 * WX * kOwn, 0, st>>>(
+        N, (int)d, B, ldb, out, chunk, 0, (unsigned)units, (unsigned)split);
+    return launch_status();
+  }
+  constexpr int64_t kMost = kMaxWorkItems / (64 * WX * kOwn) / 8 * 8;  // units that one launch surely can count
+  for (int64_t base = 0; base < units; base += kMost) {
+    const int64_t n = units - base < kMost ? units - base : kMost;
+    pr3_direct_kernel<T, NT, WX, false><<<(unsigned)(8 * ceil_div(ceil_div(n, 8), kOwn)), 64 * WX * kOwn, 0, st>>>(N, (int)d, B, ldb, out, chunk, (unsigned)base, (unsigned)n, 1);
+    if (launch_status() != DASTAC_OK) return DASTAC_EHIP;
+  }
+  return DASTAC_OK;
+}
+
+// Time in us of the direct kernel, by its parts: a launch; the output (4 MB a us); with several shares, clearing it and the atomics (1.5 MB a us); the
+// steps of a wavefront times what a step costs (us per step of a SIMD: one tile 0.37 in single, 0.62 in double precision, two tiles 0.57), times
+// the wavefronts that a SIMD runs one after the other or side by side.  Within a fifth of 40 measured sizes.
+inline double direct_time(int64_t N, int64_t d, int elem, int NT, int WX, int64_t units, int64_t split, int64_t cus) {
+  const double step = elem == 8 ? 0.62 : NT == 1 ? 0.37 : 0.57;
+  const int64_t own = ceil_div(ceil_div(N, kStep), split * WX);
+  const double rounds = (double)(units * split) / (double)cus, mb = 1e-6 * (double)(tet(d) * elem);
+  const double side = rounds <= 1.0 ? 1.0 : rounds < 4.0 ? (double)ceil_div(units * split, cus) : rounds;
+  return 4.0 + mb / 4.0 + (split > 1 ? 2.5 + (double)split * mb / 1.5 : 0.0) + (double)own * step * side * (WX / 4.0);
+}
+
+template <typename T>
+int run(int64_t N, int64_t d, const T *B, int64_t ldb, T *out, void *stream) {
+  constexpr int64_t kB = (int64_t)sizeof(T);
+  if (N < 0 || d < 0 || ldb < d) return DASTAC_EINVAL;
+  if (d > kMaxD3 || N > kMaxN || ld_too_large(ldb)) return DASTAC_EOVERFLOW;
+  if (d == 0) return DASTAC_OK;
+  if (!out || (N > 0 && !B)) return DASTAC_ENULL;
+  if (overlaps(out, tet(d) * kB, B, view_bytes(N, ldb, d, kB))) return DASTAC_EALIAS;
+  hipStream_t st = (hipStream_t)stream;
+  if (N == 0) return clear(d, out, st);
+  if (N < kStep) {
+    pr3_few_kernel<T><<<dim3((unsigned)ceil_div(d, 16), (unsigned)d), 256, 0, st>>>((int)N, (int)d, B, ldb, out);
+    return launch_status();
+  }
+  const int64_t cus = compute_units();
+  if (cus <= 0) return DASTAC_EHIP;
+  // One tile a wavefront and eight wavefronts where that leaves two workgroups or fewer for a compute unit; in single precision two tiles
+  // beyond (N=976, d=152 24.9 us, 28.7 with one; N=381, d=104 10.4, 10.0), in double never (N=10000, d=200 676, 671; N=604, d=314 187, 195).  Four wavefronts,
+  // or two where few steps would leave them with little but the sum through LDS (N=200, d=320 49 us, with four 59; double, N=604, d=314
+  // 175, 187; N=976, d=152 35.7, 24.9).
+  const int64_t one = direct_units((int)d, 1);
+  const bool small = one <= 2 * cus;
+  const int NT = small || kB == 8 ? 1 : 2, WX = small ? 8 : N >= 48 * kStep ? 4 : N > 8 * kStep ? 2 : 1;
+  const int64_t units = NT == 1 ? one : direct_units((int)d, NT);
+  int64_t split = 1;
+  double best = direct_time(N, d, (int)kB, NT, WX, units, 1, cus);
+  for (int64_t s = 2; s <= 64 && s * WX * kStep <= N && units * s < (1 << 20); ++s) {
+    const double t = direct_time(N, d, (int)kB, NT, WX, units, s, cus);
+    if (t < 0.97 * best) best = t, split = s;
+  }
+  if constexpr (kB == 4) {
+    // The staged kernel: 22 us of launches and prologues, the output cleared and one and a half times added to, and 0.083 us per unit of
+    // weight and compute unit (N=1018, d=114 30.5 us, direct 15.4; N=976, d=152 38.7, 24.9; N=8598, d=111 67, 65; N=2000, d=256 105, 130;
+    // N=20000, d=160 266, 331).
+    const int64_t steps = ceil_div(N, kXT), total = staged_weight((int)d) * steps;
+    const double staged = 22.0 + 1.25e-6 * (double)(tet(d) * kB) + 0.083 * (double)total / (double)cus;
+    if (ldb <= kMaxStagedLd && N >= kXT && staged < best) {
+      if (const int rc = clear(d, out, st)) return rc;
+      // A sum runs in one accumulator for a quarter of the samples, between 512 and 2048: its truncation error grows with the length
+      // (N=2000, d=256 2.0e-7 in pieces of 2000, 1.4e-7 in pieces of 512; N=10000 2.8e-7 in pieces of 2048, 2.2e-7 of 1250 and 3 % slower).
+      const int64_t quarter = ceil_div(steps, 4);
+      const int most = (int)(quarter < 16 ? 16 : quarter > 64 ? 64 : quarter);
+      pr3_staged_kernel<<<(unsigned)cus, 512, 0, st>>>(N, (int)d, B, ldb, out, total, (int)steps, most);
+      return launch_status();
+    }
+    if (NT == 2 && WX == 4) return launch_direct<T, 2, 4>(N, d, B, ldb, out, units, split, st);
+    if (NT == 2 && WX == 2) return launch_direct<T, 2, 2>(N, d, B, ldb, out, units, split, st);
+    if (NT == 2) return launch_direct<T, 2, 1>(N, d, B, ldb, out, units, split, st);
+  } else {
+    if (WX == 4) return launch_direct<T, 1, 4>(N, d, B, ldb, out, units, split, st);
+    if (WX == 2) return launch_direct<T, 1, 2>(N, d, B, ldb, out, units, split, st);
+    if (WX == 1) return launch_direct<T, 1, 1>(N, d, B, ldb, out, units, split, st);
+  }
+  return launch_direct<T, 1, 8>(N, d, B, ldb, out, units, split, st);
+}
+
+}  // namespace
+
+extern "C" {
+
+int dastac_pr_a3_f32(int64_t N, int64_t d, const float *B, int64_t ldb, float *A3p, void *stream) {
+  return run<float>(N, d, B, ldb, A3p, stream);
+}
+
+// Double precision (the paper's element type)
+int dastac_pr_a3_f64(int64_t N, int64_t d, const double *B, int64_t ldb, double *A3p, void *stream) {
+  return run<double>(N, d, B, ldb, A3p, stream);
+}
+
+}  // extern "C"

@@ -42,6 +42,13 @@ __device__ inline unsigned pack_bf16(float a, float b) {  // v_cvt_pk_bf16_f32: 
   return __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf2));
 }
 
+// The three parts of a (low half of each word) and b (high half), which are already multiplied by 2^24.
+__device__ inline void split3_scaled(float a, float b, unsigned &h, unsigned &m, unsigned &l) {
+  h = pack_bf16(a, b);
+  const float ra = a - __uint_as_float(h << 16), rb = b - __uint_as_float(h & 0xffff0000u);
+  m = pack_bf16(ra, rb);
+  l = pack_bf16(ra - __uint_as_float(m << 16), rb - __uint_as_float(m & 0xffff0000u));
+}
 // The three parts of 2^24 a (low half of each word) and 2^24 b (high half): 6.5 vector instructions per element.
 __device__ inline void split3(float a, float b, unsigned &h, unsigned &m, unsigned &l) {
   h = pack_bf16(a * kSplitUp, b * kSplitUp);

@@ -1,0 +1,67 @@
+"""How the third-order polynomial-regression tensor is cut into tiles: every element i<=j<=k in exactly one tile of the direct kernel and,
+for every step of samples, in exactly one part of the staged one; closed forms of the counts against the sums."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+PROGRAM = r"""
+#include <stdio.h>
+#include <stdlib.h>
+#include <vector>
+#include "cube_units.h"
+using namespace dastac;
+// adds `by` to every element of the tile that belongs to the tensor
+static void cover(std::vector<int> &seen, int d, CubeTile t, int ni, int nj, int nk, int by) {
+  for (int i = t.i0; i < t.i0 + ni; ++i)
+    for (int j = t.j0; j < t.j0 + nj; ++j)
+      for (int k = t.k0; k < t.k0 + nk; ++k)
+        if (i <= j && j <= k && k < d) seen[tet_offset(d, i, j, k)] += by;
+}
+static bool all(const std::vector<int> &seen, int value) {
+  for (int v : seen) if (v != value) return false;
+  return true;
+}
+int main(int, char **argv) {
+  const int d = atoi(argv[1]), steps = atoi(argv[2]);
+  for (int NT = 1; NT <= 2; ++NT) {
+    std::vector<int> seen(tet(d), 0);
+    const int64_t units = direct_units(d, NT);
+    for (int64_t u = 0; u < units; ++u) {
+      const CubeTile t = direct_tile(d, NT, (int)u);
+      if (t.i0 >= d || t.j0 >= d || t.k0 >= d) return printf("direct: empty tile\n"), 1;
+      cover(seen, d, t, 4 * NT, 8, 32, 1);
+    }
+    if (!all(seen, 1)) return printf("direct, NT=%d: not a partition\n", NT), 1;
+  }
+  for (int parts : {1, 7, 256}) {
+    std::vector<int> seen(tet(d), 0);
+    const int64_t total = staged_weight(d) * steps;
+    bool inside = true;
+    for (int p = 0; p < parts; ++p)
+      staged_part(d, steps, total, p, parts, [&](const CubeTile &t, int wn, int s0, int s1) {
+        inside = inside && 0 <= s0 && s0 < s1 && s1 <= steps && 1 <= wn && wn <= 4;
+        cover(seen, d, t, 16, 16, 32 * wn, s1 - s0);
+      });
+    if (!inside || !all(seen, steps)) return printf("staged, %d parts: not a partition\n", parts), 1;
+  }
+  return 0;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def program(tmp_path_factory):
+    d = tmp_path_factory.mktemp("cube")
+    src, exe = d / "cube.cpp", d / "cube"
+    src.write_text(PROGRAM)
+    subprocess.check_call(["g++", "-O1", "-std=c++17", "-Wall", "-Werror", "-I", os.path.join(ROOT, "paper_2407_13726_amd", "csrc"), str(src), "-o", str(exe)])
+    return str(exe)
+
+
+@pytest.mark.parametrize("d,steps", [(1, 1), (3, 2), (7, 5), (8, 1), (9, 3), (15, 2), (16, 7), (17, 1), (25, 4), (31, 3), (32, 5), (33, 1), (40, 9), (63, 2), (64, 1),
+                                     (65, 3), (95, 1), (104, 4), (127, 1), (128, 3), (129, 2), (160, 1), (209, 5)])
+def test_tiles_partition_the_tensor(program, d, steps):
+    subprocess.check_output([program, str(d), str(steps)])
