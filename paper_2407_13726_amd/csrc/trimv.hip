@@ -245,6 +245,104 @@ __global__ __launch_bounds__(kBlock) void trimv_kernel(int n, const E *__restric
   }
 }
 
+// ---- small triangles: one launch, every output written once ------------------------------------------------------
+// A workgroup owns kOwned outputs c: its wavefronts take a row each for the row sums, and all rows together, 16 bytes a lane of the kOwned
+// columns, for the column sums, which meet in LDS.  The symmetric product reads the triangle twice, but nothing is cleared first (a launch of 4 to 5 us
+// in front of a kernel) and nothing added with atomics, so that equal calls give equal bits.  Bound by the latency of a few rounds of eight
+// reads a lane: symv fp32 n=300 8.5 -> 4.7 us a call, n=1500 8.4 -> 5.7, n=3000 12.9 -> 10.2; fp64 n=1500 8.9 -> 6.8; trmv_lower fp32 n=4000 12.1 -> 8.5.
+constexpr int kAhead = 8;
+
+template <typename E, int kOwned, bool LOWER, int MODE>
+__global__ __launch_bounds__(64 * kOwned) void trimv_small_kernel(int n, const E *__restrict__ T, const E *__restrict__ x, E *__restrict__ y) {
+  constexpr int P = Piece<E>::kPer, kLanes = kOwned / P, kRows = 64 * kOwned / kLanes;  // lanes a row, rows a round
+  typedef typename Piece<E>::vec vec;
+  typedef typename Piece<E>::uvec uvec;
+  constexpr bool ROWS = MODE != MODE_COLS, COLS = MODE != MODE_ROWS;
+  __shared__ E rows[kOwned], cols[kOwned][kOwned];
+  const int tid = threadIdx.x, lane = tid & 63, wave = uniform32(tid >> 6);
+  // consecutive blocks of columns on one XCD: they share the lines of the rows above them
+  const int blocks = (n + kOwned - 1) / kOwned, xcd = blockIdx.x & 7;
+  const int block = blocks * xcd / 8 + (int)(blockIdx.x >> 3);
+  if (block >= blocks * (xcd + 1) / 8) return;
+  // the last block is moved back to end with the matrix and writes what is its own (n >= 8)
+  const int c0 = kOwned * block + kOwned <= n ? kOwned * block : n - kOwned;
+  // element (i,c) of the triangle is at T[row_base(i) + c] (n <= 4096: 32 bits hold it)
+  auto row_base = [&](int i) -> unsigned {
+    return LOWER ? (unsigned)i * (unsigned)(i + 1) / 2 : (unsigned)i * (unsigned)(2 * n - i + 1) / 2 - (unsigned)i;
+  };
+  if (COLS) {
+    const int cc = c0 + P * (tid % kLanes);  // this lane's columns cc .. cc + P - 1
+    vec acc;
+#pragma unroll
+    for (int t = 0; t < P; ++t) acc[t] = E(0);
+    // rows that reach all eight columns, off the diagonal, kAhead reads at a time (past the last row: that row again, not added)
+    const int lo = LOWER ? c0 + kOwned : 0, hi = LOWER ? n : c0;
+    for (int i0 = lo + tid / kLanes; i0 < hi; i0 += kAhead * kRows) {
+      vec a[kAhead];
+      E xi[kAhead];
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) {
+        const int i = i0 + u * kRows < hi ? i0 + u * kRows : i0;
+        a[u] = *reinterpret_cast<const uvec *>(T + (row_base(i) + (unsigned)cc));
+        xi[u] = x[i];
+      }
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) {
+        const vec sum = acc + a[u] * xi[u];
+        if (i0 + u * kRows < hi) acc = sum;
+      }
+    }
+    // the eight rows on the diagonal: those that reach column c, the diagonal itself only where no row sums count it
+    const int i = c0 + tid / kLanes;
+    if (tid / kLanes < kOwned) {
+#pragma unroll
+      for (int t = 0; t < P; ++t) {
+        const int c = cc + t;
+        if (i == c ? MODE == MODE_COLS : LOWER ? i > c : i < c) acc[t] += T[row_base(i) + (unsigned)c] * x[i];
+      }
+    }
+#pragma unroll
+    for (int t = 0; t < P; ++t) {
+#pragma unroll
+      for (int m = kLanes; m < 64; m *= 2) acc[t] += __shfl_xor(acc[t], m, 64);
+      if (lane < kLanes) cols[wave][P * lane + t] = acc[t];
+    }
+  }
+  if (ROWS) {
+    const int i = c0 + wave, first = LOWER ? 0 : i, len = LOWER ? i + 1 : n - i, whole = len / P * P;
+    const E *row = T + (row_base(i) + (unsigned)first), *xs = x + first;
+    E sum = E(0);
+    for (int e0 = P * lane; e0 < whole; e0 += kAhead * 64 * P) {
+      vec a[kAhead], b[kAhead];
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) {
+        const int e = e0 + u * 64 * P < whole ? e0 + u * 64 * P : e0;
+        a[u] = *reinterpret_cast<const uvec *>(row + e), b[u] = *reinterpret_cast<const uvec *>(xs + e);
+      }
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) {
+        E part = E(0);
+#pragma unroll
+        for (int t = 0; t < P; ++t) part += a[u][t] * b[u][t];
+        if (e0 + u * 64 * P < whole) sum += part;
+      }
+    }
+    if (lane < len - whole) sum += row[whole + lane] * xs[whole + lane];
+    sum = wave_sum(sum);
+    if (lane == 0) rows[wave] = sum;
+  }
+  __syncthreads();
+  if (tid < kOwned && c0 + tid >= kOwned * block) {
+    E s = E(0);
+    if (COLS) {
+#pragma unroll
+      for (int w = 0; w < kOwned; ++w) s += cols[w][tid];
+    }
+    if (ROWS) s += rows[tid];
+    y[c0 + tid] = s;
+  }
+}
+
 template <typename E>
 __global__ void zero_kernel(E *__restrict__ y, int64_t n) {
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -296,7 +394,17 @@ int run(int64_t n, const E *Tp, const E *x, E *y, void *stream) {
   if (n == 0) return DASTAC_OK;
   if (!Tp || !x || !y) return DASTAC_ENULL;
   if (overlaps(y, n * kB, Tp, tri(n) * kB) || overlaps(y, n * kB, x, n * kB)) return DASTAC_EALIAS;
-  if (n <= 2048) return launch<E, 1, LOWER, MODE>(n, Tp, x, y, (hipStream_t)stream);
+  auto small = [&](auto kernel, int owned) {
+    kernel<<<(unsigned)(8 * ceil_div(ceil_div(n, owned), 8)), 64 * owned, 0, (hipStream_t)stream>>>((int)n, Tp, x, y);
+    return launch_status();
+  };
+  // Eight outputs a workgroup fill one layer of workgroups up to n=2048, sixteen up to 4096 (us, eight and sixteen: n=2300 10.8, 8.4; n=3000
+  // 13.7, 10.2).  The panels take over where a second read of the triangle costs more than the launch that clears (us, panels and one launch: fp32
+  // n=2048 9.0, 6.9; n=4000 15.7, 12.8; fp64 symv n=2048 10.4, 8.1; n=2300 11.0, 11.7; trmv_t n=3000 12.4, 11.5; n=3500 14.3, 14.5; trmv_lower
+  // n=3000 10.4, 9.9; n=3500 12.7, 13.1).
+  constexpr int64_t kMostSmall = sizeof(E) == 4 ? 4096 : MODE == MODE_SYM ? 2048 : 3072;
+  if (n >= 8 && n <= 2048) return small(trimv_small_kernel<E, 8, LOWER, MODE>, 8);
+  if (kMostSmall > 2048 && n > 2048 && n <= kMostSmall) return small(trimv_small_kernel<E, 16, LOWER, MODE>, 16);
   return launch<E, 4, LOWER, MODE>(n, Tp, x, y, (hipStream_t)stream);
 }
 
