@@ -78,6 +78,9 @@ int trmv_upper_by_panels(int64_t n, const double *Up, const double *x, double *y
 // defined in trmm_skinny.hip: C := U B for at most 32 columns by panels of k (arguments already validated)
 int trmm_by_panels(int64_t n, int64_t m, const float *Up, const float *B, int64_t ldb, float *C, int64_t ldc, void *stream);
 int trmm_by_panels(int64_t n, int64_t m, const double *Up, const double *B, int64_t ldb, double *C, int64_t ldc, void *stream);
+// defined in trmm_direct.hip: C := U B, 64 <= n < 2^15, in one launch (arguments already validated)
+int trmm_direct(int64_t n, int64_t m, const float *Up, const float *B, int64_t ldb, float *C, int64_t ldc, void *stream);
+int trmm_direct(int64_t n, int64_t m, const double *Up, const double *B, int64_t ldb, double *C, int64_t ldc, void *stream);
 // defined in trmm_columns.hip: C := U B with m a multiple of 128 (arguments already validated)
 // (and the part of its last layer of workgroups that has work)
 double trmm_columns_fill(int64_t n, int64_t m, int64_t cus);
