@@ -397,6 +397,73 @@ __global__ __launch_bounds__(64 * Shape<T>::WPB) __attribute__((amdgpu_waves_per
   }
 }
 
+// ---- small tensors: one launch, every output written once ---------------------------------------------------------
+// A workgroup owns slice i and 64 columns r, a column a lane; wavefront w owns eight values of k (counted from the last), whose rows of C stay in
+// registers, and walks the rows j <= its last k: eight elements of A, the same for all lanes and so read as scalars, times its C, times B(j,r).  The
+// wavefronts' sums meet in LDS.  Bound by the latency of the scalar reads, 64 of them at a time, along a chain of n rows (one row's at a time: n=90 12.0 us);
+// nothing is cleared first and nothing added with atomics, so equal calls give equal bits.
+constexpr int kMostSmall = 110;  // values of n
+template <typename T>
+__global__ __launch_bounds__(64 * ((kMostSmall + 7) / 8)) void mttkrp_small_kernel(int n, int R, const T *__restrict__ A, const T *__restrict__ Bm, int64_t ldb,
+                                                            const T *__restrict__ Cm, int64_t ldc, T *__restrict__ M, int64_t ldm) {
+  constexpr int KW = 8;
+  __shared__ T sums[(kMostSmall + KW - 1) / KW][64];
+  const int i = blockIdx.x, lane = threadIdx.x & 63, wave = uniform32(threadIdx.x >> 6), waves = (int)(blockDim.x >> 6);
+  const int r = 64 * (int)blockIdx.y + lane, rc = r < R ? r : R - 1;  // lanes past the last column repeat it and write nothing
+  const int k0 = n - KW * (wave + 1);
+  T acc = T(0);
+  if (k0 + KW > i) {
+    T c[KW];
+#pragma unroll
+    for (int e = 0; e < KW; ++e) c[e] = Cm[(int64_t)(k0 + e > 0 ? k0 + e : 0) * ldc + rc];
+    // element (i,j,k) is at slice - tri(n-j) + (k - j)
+    const int slice = (int)(tet_slice_start(n, i) + tri(n - i));
+    int j = i;
+    constexpr int kAhead = 64 / (KW * (int)sizeof(T) / 4);  // rows whose elements fill the scalar registers
+    for (; j + kAhead <= k0 + 1; j += kAhead) {
+      T a[kAhead][KW], b[kAhead];
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) {
+        const T *row = A + (slice - (n - j - u) * (n - j - u + 1) / 2 + (k0 - j - u));
+#pragma unroll
+        for (int e = 0; e < KW; ++e) a[u][e] = row[e];
+        b[u] = Bm[(int64_t)(j + u) * ldb + rc];
+      }
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) {
+        T t = a[u][0] * c[0];
+#pragma unroll
+        for (int e = 1; e < KW; ++e) t += a[u][e] * c[e];
+        acc += t * b[u];
+      }
+    }
+    for (; j <= k0; ++j) {
+      const T *a = A + (slice - (n - j) * (n - j + 1) / 2 + (k0 - j));
+      T t = T(0);
+#pragma unroll
+      for (int e = 0; e < KW; ++e) t += a[e] * c[e];
+      acc += t * Bm[(int64_t)j * ldb + rc];
+    }
+    // the rows that begin inside the wavefront's values of k:
+#pragma unroll
+    for (int u = 1; u < KW; ++u) {
+      const int jj = k0 + u;
+      if (jj < i) continue;
+      const T *a = A + (slice - (n - jj) * (n - jj + 1) / 2);
+      T t = T(0);
+#pragma unroll
+      for (int e = u; e < KW; ++e) t += a[e - u] * c[e];
+      acc += t * Bm[(int64_t)jj * ldb + rc];
+    }
+  }
+  sums[wave][lane] = acc;
+  __syncthreads();
+  if (wave == 0) {
+    for (int w = 1; w < waves; ++w) acc += sums[w][lane];
+    if (r < R) M[(int64_t)i * ldm + r] = acc;
+  }
+}
+
 // Clears M (the block kernel adds into it) and computes the slices of order 1 and 2 -- the last four
 // elements of the packed buffer, where a 16-byte load has no room -- directly from the rule.
 template <typename T>
@@ -431,6 +498,12 @@ int run(int64_t n, int64_t R, const T *Ap, const T *B, int64_t ldb, const T *C, 
       overlaps(M, mb, C, view_bytes(n, ldc, R, kSz)))
     return DASTAC_EALIAS;
   hipStream_t st = (hipStream_t)stream;
+  // (us, two launches and one: fp32 R=8, n=48 10.1, 6.4; n=64 10.2, 8.2; n=90 11.5, 10.5; n=110 12.4, 12.6; R=50, n=90 13.0, 10.8; n=110 14.2, 12.8; n=128
+  // 14.8, 15.4; fp64 R=8, n=64 10.2, 8.7; n=90 10.8, 11.4; R=50, n=90 11.3, 11.5)
+  if (n <= (sizeof(T) == 8 ? 80 : R > 32 ? kMostSmall : 88)) {
+    mttkrp_small_kernel<T><<<dim3((unsigned)n, (unsigned)ceil_div(R, 64)), 64 * (unsigned)ceil_div(n, 8), 0, st>>>((int)n, (int)R, Ap, B, ldb, C, ldc, M, ldm);
+    return launch_status();
+  }
   // the XCD lists: group g (orders 8g+1..8g+8) gives one slice to each XCD; 16 groups share a height P
   const int64_t gmax = (n - 1) / 8, Ptop = gmax / 16 + 1;
   // sum of P(P+1)/2 over P = 1..Ptop-1 is Tet(Ptop-1)
@@ -439,7 +512,6 @@ int run(int64_t n, int64_t R, const T *Ap, const T *B, int64_t ldb, const T *C, 
   const int64_t cb = ceil_div(n * R, 256);
   mttkrp_clear_kernel<T><<<(unsigned)(cb < (1 << 23) ? cb : 1 << 23), 256, 0, st>>>(n, R, Ap, B, ldb, C, ldc, M, ldm);
   if (hipGetLastError() != hipSuccess) return DASTAC_EHIP;
-  if (n < kMinOrder) return DASTAC_OK;
   // Column tiles share a launch (each launch of its own read the tetrahedron again: us, n=768, R=96 fp32 263 -> 214, fp64
   // 407 -> 323; fp64 n=333, R=50 43.5 -> 40.6), and few blocks are cut into parts so that a wavefront's chain of
   // steps gets short: a block of 128 rows is 25 us of latency in fp32, 13 in fp64.  us with 1, 2, 4, 8 parts, by blocks (times
