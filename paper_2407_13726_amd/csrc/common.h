@@ -81,6 +81,9 @@ int trmm_by_panels(int64_t n, int64_t m, const double *Up, const double *B, int6
 // defined in trmm_direct.hip: C := U B, 64 <= n < 2^15, in one launch (arguments already validated)
 int trmm_direct(int64_t n, int64_t m, const float *Up, const float *B, int64_t ldb, float *C, int64_t ldc, void *stream);
 int trmm_direct(int64_t n, int64_t m, const double *Up, const double *B, int64_t ldb, double *C, int64_t ldc, void *stream);
+// defined in ttm_direct.hip: Ap[p, k] = sum over l of Bp[p, l] C[k, l], 16 <= Q, rows, Q and K < 2^24 (arguments already validated)
+int ttm_direct(int64_t rows, int64_t Q, int64_t K, const float *Bp, const float *C, int64_t ldc, float *Ap, void *stream);
+int ttm_direct(int64_t rows, int64_t Q, int64_t K, const double *Bp, const double *C, int64_t ldc, double *Ap, void *stream);
 // defined in trmm_columns.hip: C := U B with m a multiple of 128 (arguments already validated)
 // (and the part of its last layer of workgroups that has work)
 double trmm_columns_fill(int64_t n, int64_t m, int64_t cus);

@@ -468,6 +468,17 @@ int uhc_copy(int64_t n, int64_t Q, const T *src, T *dst, void *stream) {
   return launch_status();
 }
 
+// Few rows run straight from memory with l cut among wavefronts (ttm_direct.hip).  A workgroup of the kernels here takes a time that grows with Q, the
+// direct tiles together one that grows with their number times Q, so the line is a number of direct tiles (us, here and there, fp32: 1068 tiles
+// n=130, Q=250, K=100 14.4, 12.5; 1280 n=90, Q=400, K=300 20.4, 17.0; 2122 n=260, Q=K=60 9.5, 9.0; 2550 n=180, Q=200, K=150 15.8, 20.6; fp64: 2038 n=180, Q=500,
+// K=50 58.9, 42.2; 2132 n=130, Q=250, K=100 31.2, 24.5; 2560 n=90, Q=400, K=300 45.9, 50.5; 5095 n=180, Q=200, K=150 36.7, 43.0).  Q and K above 2^20
+// stay here.
+template <typename T>
+bool direct_serves(int64_t rows, int64_t Q, int64_t K) {
+  const int64_t tiles = ceil_div(rows, sizeof(T) == 4 ? 32 : 16) * ceil_div(K, 32);
+  return Q >= 16 && Q <= (1 << 20) && K <= (1 << 20) && tiles <= (sizeof(T) == 4 ? 1280 : 2048);
+}
+
 // The split's offsets within a row block are 32 bits and a piece needs four l; beyond that the fp32 matrix cores take over, and
 // where one step is all there is and the tiles do not fill the chip: the split's conversion then only adds to the latency
 // (us, split and fp32 cores: n=60, Q=20, K=512 6.0, 5.1; n=150, Q=20, K=100 6.1, 5.1; past one layer, n=150, Q=20, K=300, 9.7, 10.7).
@@ -511,6 +522,7 @@ int ttm_ut(int64_t n, int64_t Q, int64_t K, const T *Bp, const T *C, int64_t ldc
   const int64_t rows = tri(n);
   if (overlaps(Ap, rows * K * kB, Bp, rows * Q * kB) || overlaps(Ap, rows * K * kB, C, view_bytes(K, ldc, Q, kB)))
     return DASTAC_EALIAS;
+  if (direct_serves<T>(rows, Q, K)) return ttm_direct(rows, Q, K, Bp, C, ldc, Ap, stream);
   if (split_serves(rows, Q, K, Bp)) return ttm_split(rows, Q, K, Bp, C, ldc, Ap, (hipStream_t)stream);
   const int64_t nrb = ceil_div(rows, kTileM), ncb = ceil_div(K, kTileN);
   if (ncb > (1 << 20)) return DASTAC_EOVERFLOW;
