@@ -471,12 +471,14 @@ int uhc_copy(int64_t n, int64_t Q, const T *src, T *dst, void *stream) {
 // Few rows run straight from memory with l cut among wavefronts (ttm_direct.hip).  A workgroup of the kernels here takes a time that grows with Q, the
 // direct tiles together one that grows with their number times Q, so the line is a number of direct tiles (us, here and there, fp32: 1068 tiles
 // n=130, Q=250, K=100 14.4, 12.5; 1280 n=90, Q=400, K=300 20.4, 17.0; 2122 n=260, Q=K=60 9.5, 9.0; 2550 n=180, Q=200, K=150 15.8, 20.6; fp64: 2038 n=180, Q=500,
-// K=50 58.9, 42.2; 2132 n=130, Q=250, K=100 31.2, 24.5; 2560 n=90, Q=400, K=300 45.9, 50.5; 5095 n=180, Q=200, K=150 36.7, 43.0).  Q and K above 2^20
-// stay here.
+// K=50 58.9, 42.2; 2132 n=130, Q=250, K=100 31.2, 24.5; 2560 n=90, Q=400, K=300 45.9, 50.5; 5095 n=180, Q=200, K=150 36.7, 43.0).  In double precision
+// the tiles here are 128 columns wide, so a few columns go there with any number of rows (n=500, Q=434, K=16 310, 149; K=48 317, 294; K=64 322, 358; n=200, K=64,
+// 2514 tiles 79, 52; n=350, Q=250, K=64, 7680 tiles 96.6, 99.6).  Q and K above 2^20 stay here.
 template <typename T>
 bool direct_serves(int64_t rows, int64_t Q, int64_t K) {
   const int64_t tiles = ceil_div(rows, sizeof(T) == 4 ? 32 : 16) * ceil_div(K, 32);
-  return Q >= 16 && Q <= (1 << 20) && K <= (1 << 20) && tiles <= (sizeof(T) == 4 ? 1280 : 2048);
+  if (Q < 16 || Q > (1 << 20) || K > (1 << 20) || rows > (1 << 24)) return false;
+  return sizeof(T) == 4 ? tiles <= 1280 : K <= 48 || tiles <= (K <= 64 ? 4096 : 2048);
 }
 
 // The split's offsets within a row block are 32 bits and a piece needs four l; beyond that the fp32 matrix cores take over, and

@@ -22,7 +22,8 @@ def ttm(gpu, n, Q, K, ldc, B, C):
 @pytest.mark.parametrize("f64", [False, True])
 @pytest.mark.parametrize("n,Q,K,ldc", [(1, 16, 1, 16), (1, 15, 1, 15), (2, 17, 3, 20), (5, 31, 33, 31), (7, 32, 32, 32), (8, 48, 31, 48), (8, 49, 65, 49), (24, 500, 100, 501),
                                        (30, 47, 64, 47), (33, 261, 112, 261), (63, 100, 20, 100), (100, 33, 40, 33), (130, 65, 100, 65), (150, 40, 120, 40),
-                                       (202, 20, 64, 20), (203, 20, 64, 20), (180, 50, 62, 50), (256, 16, 30, 16)])
+                                       (202, 20, 64, 20), (203, 20, 64, 20), (180, 50, 62, 50), (256, 16, 30, 16), (260, 35, 48, 35),
+                                       (260, 18, 49, 18)])
 def test_exact_on_integers(gpu, oracle, n, Q, K, ldc, f64):
     B, C = operands(n, Q, K, ldc, f64)
     want, _ = (oracle.ttm_ut_f64 if f64 else oracle.ttm_ut)(n, Q, K, B, np.ascontiguousarray(C[:, :Q]))
