@@ -22,6 +22,21 @@ using namespace dastac;
 namespace {
 
 constexpr int kBlock = 256;
+// Diagonals read at a time where their number is not known at compile time, and by the first and last rows of any: one at a time, the chain of 2w+1
+// latencies was the time of small calls and the tail of large ones (us, before and now: fp32 w=3, n=4194304 37.8, 24.7; w=11, n=500000 21, 9.1; w=23, n=20000
+// 23.6, 6.6; w=32, n=4194304 307, 179; w=16, whose interior rows are unrolled, n=4194304 94.5, 89; fp64 w=5, n=4194304 79, 72; w=20, n=20000 24.6, 7.1).
+constexpr int kAhead = 8;
+
+// acc + the products of N diagonals' slots (n apart) with consecutive elements of x, all reads requested first
+template <int N, typename T>
+__device__ inline T add_diagonals(T acc, const T *d, int64_t n, const T *x) {
+  T a[N], b[N];
+#pragma unroll
+  for (int u = 0; u < N; ++u) a[u] = __builtin_nontemporal_load(d + (int64_t)u * n), b[u] = x[u];
+#pragma unroll
+  for (int u = 0; u < N; ++u) acc += a[u] * b[u];
+  return acc;
+}
 
 // W >= 0: half-width known at compile time (fully unrolled); W < 0: run-time half-width `w`.
 // With 33 streams per lane, four wavefronts per SIMD keep as much in flight as the memory system takes; the
@@ -43,12 +58,32 @@ void band_kernel(int64_t n, int w, const T *__restrict__ D,
       for (int dd = 0; dd <= 2 * (W >= 0 ? W : 0); ++dd)
         acc += __builtin_nontemporal_load(d + (int64_t)dd * n) * xw[dd];
     } else {
-      for (int dd = 0; dd <= 2 * hw; ++dd) acc += __builtin_nontemporal_load(d + (int64_t)dd * n) * xw[dd];
+      // eight diagonals' reads at a time (one by one, each would be waited for), then at once the one to seven that are left
+      const int count = 2 * hw + 1;
+      int dd = 0;
+      for (; dd + kAhead <= count; dd += kAhead) acc = add_diagonals<kAhead>(acc, d + (int64_t)dd * n, n, xw + dd);
+      d += (int64_t)dd * n, xw += dd;
+      switch (count - dd) {
+        case 1: acc = add_diagonals<1>(acc, d, n, xw); break;
+        case 2: acc = add_diagonals<2>(acc, d, n, xw); break;
+        case 3: acc = add_diagonals<3>(acc, d, n, xw); break;
+        case 4: acc = add_diagonals<4>(acc, d, n, xw); break;
+        case 5: acc = add_diagonals<5>(acc, d, n, xw); break;
+        case 6: acc = add_diagonals<6>(acc, d, n, xw); break;
+        case 7: acc = add_diagonals<7>(acc, d, n, xw); break;
+      }
     }
   } else {  // one of the first or last w rows: skip the padding slots
-    for (int dd = 0; dd <= 2 * hw; ++dd) {
-      const int64_t c = i + dd - hw;
-      if (c >= 0 && c < n) acc += d[(int64_t)dd * n] * x[c];
+    const int lo = i < hw ? (int)(hw - i) : 0, hi = n - 1 - i < hw ? hw + (int)(n - 1 - i) : 2 * hw;  // diagonals whose column exists
+    for (int dd = lo; dd <= hi; dd += kAhead) {
+      T a[kAhead], b[kAhead];
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) {
+        const int at = dd + u <= hi ? dd + u : hi;
+        a[u] = d[(int64_t)at * n], b[u] = x[i + at - hw];
+      }
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) acc = dd + u <= hi ? acc + a[u] * b[u] : acc;
     }
   }
   __builtin_nontemporal_store(acc, y + i);
