@@ -142,8 +142,8 @@ int dastac_pack_leslie_f32(int64_t n, const float *dense, int64_t ld, float *R, 
 int dastac_unpack_leslie_f32(int64_t n, const float *R, const float *S, float *dense, int64_t ld, void *stream);
 
 /* ---- contractions: DEVICE, fp32 storage and precision ----------------------------
- * TRMM with more than 32 columns, TTM_UT and A3 split their operands exactly into bf16 parts, at all but
- * small sizes, and accumulate in fp32.  Sums of more than a few terms are then closer to the exact result than
+ * TRMM (with at most 32 columns up to n = 1536, 2048), TTM_UT and A3 split their operands exactly into bf16 parts, at all but
+ * the smallest sizes, and accumulate in fp32.  Sums of more than a few terms are then closer to the exact result than
  * with fp32 products; a single product is within 2^-22.4 of its value (2^-23 outside the largest TRMM calls)
  * against 2^-24.  Operands that the split cannot hold -- Inf, NaN, sums beyond 2^80 -- are evaluated again with
  * fp32 products; such a call takes up to three times as long as with these alone.
@@ -165,10 +165,11 @@ int dastac_trmv_f32(int64_t n, const float *Up, const float *x, float *y, void *
 /* y(i) := S(i,j) * x(j), S symmetric with its unique elements S(i,j), i<=j, packed as an upper triangle
  * (Section 3, "Redundancy map": the other half is reached by swapping the two indices).  Every packed
  * element is read once and used twice.  Up[tri_count(n)], x[n], y[n]; n <= 524288 (beyond: DASTAC_EOVERFLOW).
- * The output is accumulated with floating-point atomics, so its last bits may differ between calls. */
+ * Up to n = 4096 (fp64: 2048) every output has one writer and equal calls give equal bits; above, the output is accumulated with
+ * floating-point atomics, so its last bits may differ between calls. */
 int dastac_symv_f32(int64_t n, const float *Up, const float *x, float *y, void *stream);
 
-/* The other products one packed triangle admits, same limits and same atomic accumulation as symv:
+/* The other products one packed triangle admits, same limits and same accumulation as symv (fp64: one writer up to n = 3072):
  *   trmv_t        y(j) := U(i,j) * x(i), i<=j     the transposed product of the packed upper triangle
  *   trmv_lower    y(i) := L(i,j) * x(j), j<=i     L packed as a LOWER triangle: row i holds columns 0..i, at
  *                                                 tril(n,i,j) = i(i+1)/2 + j (Section 4, worked example, Eq. 2)
@@ -182,7 +183,8 @@ int dastac_symv_lower_f32(int64_t n, const float *Lp, const float *x, float *y, 
 
 /* C(i,c) := U(i,k) * B(k,c), i<=k, 0<=c<m  (the SpMV_UT rule with a matrix right-hand side).
  * B is n x m row-major with row stride ldb >= m, C is n x m with row stride ldc >= m; m >= 1.
- * Only columns 0..m-1 of every row of C are written.  Where the tiles of C do not fill the
+ * Only columns 0..m-1 of every row of C are written.  Small products (about n*n*m <= 2e9, fp64 8.5e8) give every element of C one writer.
+ * Beyond, where the tiles of C do not fill the
  * device the reduction range is shared out over several workgroups, which add into a cleared C with
  * floating-point atomics.  From three shares on the last bits may differ between calls (fp32 n=16384, m=256 has
  * four); with two the order of the two addends does not matter, with one (enough columns: n=16384, m=1024) every
@@ -201,7 +203,7 @@ int dastac_symm_f32(int64_t n, int64_t m, const float *Up, const float *B, int64
 /* y(i) := sum_{d=-w..w, 0<=i+d<n} D(d,i) * x(i+d)   (Section 6.4 strided-band rule, unit stride,
  * 2w+1 summands; w=0 is Table 2's SpMV_D).  D[(2w+1)*n] diagonal-major as described above; padding
  * slots are never used for their value.  0 <= w <= 2^20 (beyond: DASTAC_EOVERFLOW); the half-widths
- * 0, 1, 2, 4, 8 and 16 have unrolled kernels. */
+ * 0, 1, 2, 4, 8 and 16 have unrolled kernels, the others read eight diagonals at a time. */
 int dastac_band_spmv_f32(int64_t n, int64_t w, const float *D, const float *x, float *y, void *stream);
 
 /* y(i) := sum_{d=-w..w, 0<=i+d*s<n} D(d,i) * x(i+d*s)   (Section 6.4, strided band; the paper's experiment
@@ -226,11 +228,11 @@ int dastac_tet_ttv_f32(int64_t n, const float *Ap, const float *v, float *Mp, vo
 
 /* M(i,r) := A(i,j,k) * B(j,r) * C(k,r), i<=j<=k, 0<=r<R  (Table 1 MTTKRP rule on the upper tetrahedron).
  * B, C are n x R row-major with row strides ldb, ldc >= R; M is n x R with row stride ldm >= R.
- * 1 <= R <= 2^20.  Tiles of 32 columns of the factor
+ * 1 <= R <= 2^20.  Up to n = 88 (110 with R > 32; fp64 80) every output has one writer.  Above, tiles of 32 columns of the factor
  * matrices share a launch, in groups where their work-items pass 2^32; each tile reads the packed tetrahedron once.  M is
  * cleared first and the blocks of a slice add their parts with floating-point atomics, so the last bits
  * may differ between calls (integer-valued inputs whose partial sums are exact give identical results).
- * The sum is evaluated factored (A with B first, then with C) on blocks padded with zeros, so a non-finite
+ * The sum is evaluated factored (A with one factor first, then with the other), above these sizes on blocks padded with zeros, so a non-finite
  * element of B(j,:) or C(k,:), j,k >= i, makes M(i,r) non-finite as the plain rule does, but possibly NaN
  * where the plain rule gives an infinity. */
 int dastac_tet_mttkrp_f32(int64_t n, int64_t R, const float *Ap, const float *B, int64_t ldb, const float *C,
@@ -248,8 +250,8 @@ int dastac_ttm_ut_f32(int64_t n, int64_t Q, int64_t K, const float *Bp, const fl
  *   pr_a2   A2(i,j)   := B(x,i) * B(x,j),          i<=j      A2p[tri_count(d)] at tri(d,i,j)
  *   pr_a3   A3(i,j,k) := B(x,i) * B(x,j) * B(x,k), i<=j<=k   A3p[tet_count(d)] at tet(d,i,j,k)
  * B is N x d row-major with row stride ldb >= d.  d == 0 is a no-op; N == 0 writes zeros.  d <= 65536 (a2),
- * d <= 8192 (a3), N <= 2^31.  When the output has few tiles the sample range is split over workgroups that
- * add into the zeroed output with floating-point atomics (last bits may then differ between calls). */
+ * d <= 8192 (a3), N <= 2^31.  When the output has few tiles, and in large fp32 a3 calls, the sample range is split over workgroups
+ * that add into the zeroed output with floating-point atomics (last bits may then differ between calls). */
 int dastac_pr_a2_f32(int64_t N, int64_t d, const float *B, int64_t ldb, float *A2p, void *stream);
 int dastac_pr_a3_f32(int64_t N, int64_t d, const float *B, int64_t ldb, float *A3p, void *stream);
 

@@ -1,6 +1,6 @@
 // What the kernels on the fp32 and fp64 matrix instructions share, per element type.
 //
-// SYMM, A2, TTM_UT and A3 (in single precision a few sizes only) and TRMM on whole columns let a workgroup of eight wavefronts own
+// SYMM, A2, TTM_UT (in single precision a few sizes only) and TRMM on whole columns let a workgroup of eight wavefronts own
 // a 64 x 128 or 64 x 64 tile of the result (TRMM's other tiles: trmm.hip, with sweep_ahead) and sweep the reduction index in steps:
 // per step a 64 x kKT tile of the first operand and a kKT x 128 tile of the second are staged in LDS (double-buffered against the global
 // loads of the next step) and each wavefront multiplies its 32 x 32 sub-tile.  The schedule of such a

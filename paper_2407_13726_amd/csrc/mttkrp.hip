@@ -19,6 +19,8 @@
 // l%32; double: row l/16, columns 2*(l%16) and 2*(l%16)+1 -- the second operands) and the matrix
 // instructions.  Shape<T> below holds what differs between the two.
 //
+// Small tensors run in one launch that writes every output once (mttkrp_small_kernel below).  The rest:
+//
 // Work items.  The slice triangle is cut into blocks of 128 rows x 512 bytes of k (128 values in
 // single, 64 in double precision), aligned to its lower right corner (so that only the blocks at its
 // top and left edges are ragged).  A block is one wavefront's job (workgroups are single wavefronts,

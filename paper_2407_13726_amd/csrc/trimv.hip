@@ -12,6 +12,8 @@
 // i/2 + i^2/2 + j is the row base used here).  The packed buffer is read once; an element U(i,j)
 // gives U x(j) to the row sum of i and U x(i) to the column sum of j from the same registers.
 //
+// Small triangles run in one launch that writes every output once (trimv_small_kernel below).  The rest:
+//
 // Work split.  A lane's load is one 16-byte piece: P = 4 single-precision or 2 double-precision
 // elements.  The triangle is cut into column panels of kW = 64*P*NQ columns, and the rows that
 // reach a panel into chunks of R consecutive rows; a wavefront owns one (panel, chunk) pair, and the

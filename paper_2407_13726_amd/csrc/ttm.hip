@@ -14,7 +14,7 @@
 // the point of the layout.  It runs on the matrix cores, in single and in double precision.
 //
 // Single precision runs as a three-part split on the bf16 matrix cores (ttm_split_kernel below).  This kernel serves double
-// precision, and single precision with Q < 4, with Q <= 32 where its tiles are at most 256, and with Q or K above 2^20 (split_serves).
+// precision, and single precision where split_serves() declines; few rows, and in double precision few columns, go to ttm_direct.hip first (direct_serves).
 //
 // Tiling.  A workgroup (8 wavefronts, 2 x 4) owns 64 packed rows x 128 values of k and sweeps l in
 // steps of kKT = 32 (fp32) or 16 (fp64); the 64 x kKT tile of Bp and the 128 x kKT tile of C are staged
