@@ -49,16 +49,16 @@ __global__ __launch_bounds__(256) void pr3_few_kernel(int N, int d, const T *__r
 #pragma unroll 4
       for (int x = 0; x < N; ++x) {
         const T *sample = B + x * ldb;
-        const T c = sample[i] * sample[kc];
+        const T a = sample[i], c = sample[kc];
 #pragma unroll
-        for (int q = 0; q < kJ; ++q) s[q] += c * sample[j0 + q];
+        for (int q = 0; q < kJ; ++q) s[q] += a * sample[j0 + q] * c;
       }
     } else {
       for (int x = 0; x < N; ++x) {
         const T *sample = B + x * ldb;
-        const T c = sample[i] * sample[kc];
+        const T a = sample[i], c = sample[kc];
 #pragma unroll
-        for (int q = 0; q < kJ; ++q) s[q] += c * sample[j0 + q < d ? j0 + q : d - 1];
+        for (int q = 0; q < kJ; ++q) s[q] += a * sample[j0 + q < d ? j0 + q : d - 1] * c;
       }
     }
     T *const slice = out + tet_slice_start(d, i) + tri(d - i);

@@ -65,3 +65,33 @@ def test_one_sample_that_is_not_finite(gpu, oracle, N, d, value):
     else:  # value, 2 value and 4 value: the last two are beyond the range
         ok = np.isfinite(want[meets].astype(np.float32))
         assert np.allclose(got[meets][ok], want[meets][ok], rtol=1e-6)
+
+
+ORDER = [(1, 5, 5), (3, 20, 20), (15, 33, 40), (16, 33, 33), (40, 70, 71), (300, 97, 97), (4500, 105, 107)]
+
+
+@pytest.mark.parametrize("f64", [False, True])
+@pytest.mark.parametrize("N,d,ld", ORDER)
+def test_products_are_formed_in_the_order_of_the_rule(gpu, N, d, ld, f64):
+    """(B(x,i) B(x,j)) B(x,k): a pair that cancels in magnitude comes first where i and j have it, so that the third factor neither overflows nor
+    vanishes; pairs that overflow by themselves give infinity.  (Pairs below the normal range may come out closer than the type has them.)"""
+    t, big, small, nothing = (np.float64, 515, -510, -540) if f64 else (np.float32, 66, -62, -76)
+    at = [d // 4, d // 2, d - 1]
+    for values in ((big, small, big), (nothing, big, nothing)):
+        B = np.zeros((N, ld), dtype=t)
+        B[N // 2, :d] = 1.5
+        B[N // 2, at] = np.ldexp(1.0, values)
+        b = B[N // 2, :d]
+        with np.errstate(all="ignore"):
+            pair = (b[:, None] * b[None, :])[:, :, None]
+            cube = pair * b
+        k = np.arange(d)
+        wanted = (k[:, None] <= k[None, :])[:, :, None] & (k[None, :, None] <= k[None, None, :])
+        want, pair = cube[wanted], np.broadcast_to(pair, cube.shape)[wanted]
+        out = gpu.up(np.full(tet(d), np.nan, dtype=t))
+        (gpu.d.pr_a3_f64 if f64 else gpu.d.pr_a3_f32)(N, d, gpu.up(B), ld, out)
+        got, tiny = gpu.down(out), np.finfo(t).tiny
+        assert np.array_equal(np.isposinf(got), np.isposinf(want)) and not np.isnan(got).any()
+        normal = np.isfinite(want) & (pair >= tiny)
+        # one term of two rounded products (the split leaves out up to 2^-22 of it); below the normal range products lose bits or vanish
+        assert np.allclose(got[normal], want[normal], rtol=2.0 ** -20, atol=tiny)
