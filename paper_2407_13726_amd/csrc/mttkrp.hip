@@ -400,9 +400,9 @@ __global__ __launch_bounds__(64 * Shape<T>::WPB) __attribute__((amdgpu_waves_per
 }
 
 // ---- small tensors: one launch, every output written once ---------------------------------------------------------
-// A workgroup owns slice i and 64 columns r, a column a lane; wavefront w owns eight values of k (counted from the last), whose rows of C stay in
-// registers, and walks the rows j <= its last k: eight elements of A, the same for all lanes and so read as scalars, times its C, times B(j,r).  The
-// wavefronts' sums meet in LDS.  Bound by the latency of the scalar reads, 64 of them at a time, along a chain of n rows (one row's at a time: n=90 12.0 us);
+// A workgroup owns slice i and 64 columns r, a column a lane; wavefront w owns eight values of k (counted from the last), for which it keeps
+// S_i(k,r), and walks the rows j <= its last k: eight elements of A, the same for all lanes and so read as scalars, times B(j,r).  The sums over
+// j are then multiplied with C (in this order, as in the blocks: A times B first), and the wavefronts' sums meet in LDS.  Bound by the latency of the scalar reads, 64 of them at a time, along a chain of n rows (one row's at a time: n=90 12.0 us);
 // nothing is cleared first and nothing added with atomics, so equal calls give equal bits.
 constexpr int kMostSmall = 110;  // values of n
 template <typename T>
@@ -415,9 +415,9 @@ __global__ __launch_bounds__(64 * ((kMostSmall + 7) / 8)) void mttkrp_small_kern
   const int k0 = n - KW * (wave + 1);
   T acc = T(0);
   if (k0 + KW > i) {
-    T c[KW];
+    T c[KW], t[KW];
 #pragma unroll
-    for (int e = 0; e < KW; ++e) c[e] = Cm[(int64_t)(k0 + e > 0 ? k0 + e : 0) * ldc + rc];
+    for (int e = 0; e < KW; ++e) c[e] = Cm[(int64_t)(k0 + e > 0 ? k0 + e : 0) * ldc + rc], t[e] = T(0);
     // element (i,j,k) is at slice - tri(n-j) + (k - j)
     const int slice = (int)(tet_slice_start(n, i) + tri(n - i));
     int j = i;
@@ -431,20 +431,17 @@ __global__ __launch_bounds__(64 * ((kMostSmall + 7) / 8)) void mttkrp_small_kern
         for (int e = 0; e < KW; ++e) a[u][e] = row[e];
         b[u] = Bm[(int64_t)(j + u) * ldb + rc];
       }
+      __builtin_amdgcn_sched_barrier(0);  // all reads are requested first: left alone, the compiler waits for one row's after the other
 #pragma unroll
-      for (int u = 0; u < kAhead; ++u) {
-        T t = a[u][0] * c[0];
+      for (int u = 0; u < kAhead; ++u)
 #pragma unroll
-        for (int e = 1; e < KW; ++e) t += a[u][e] * c[e];
-        acc += t * b[u];
-      }
+        for (int e = 0; e < KW; ++e) t[e] += a[u][e] * b[u];
     }
     for (; j <= k0; ++j) {
       const T *a = A + (slice - (n - j) * (n - j + 1) / 2 + (k0 - j));
-      T t = T(0);
+      const T b = Bm[(int64_t)j * ldb + rc];
 #pragma unroll
-      for (int e = 0; e < KW; ++e) t += a[e] * c[e];
-      acc += t * Bm[(int64_t)j * ldb + rc];
+      for (int e = 0; e < KW; ++e) t[e] += a[e] * b;
     }
     // the rows that begin inside the wavefront's values of k:
 #pragma unroll
@@ -452,11 +449,13 @@ __global__ __launch_bounds__(64 * ((kMostSmall + 7) / 8)) void mttkrp_small_kern
       const int jj = k0 + u;
       if (jj < i) continue;
       const T *a = A + (slice - (n - jj) * (n - jj + 1) / 2);
-      T t = T(0);
+      const T b = Bm[(int64_t)jj * ldb + rc];
 #pragma unroll
-      for (int e = u; e < KW; ++e) t += a[e - u] * c[e];
-      acc += t * Bm[(int64_t)jj * ldb + rc];
+      for (int e = u; e < KW; ++e) t[e] += a[e - u] * b;
     }
+#pragma unroll
+    for (int e = 0; e < KW; ++e)
+      if (k0 + e >= i) acc += t[e] * c[e];  // rows of C above the slice count nothing, whatever they hold
   }
   sums[wave][lane] = acc;
   __syncthreads();

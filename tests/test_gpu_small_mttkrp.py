@@ -47,3 +47,16 @@ def test_factor_rows_of_smaller_index_do_not_reach_a_slice(gpu, n):
             spoilt[at] = np.nan
             got = mttkrp(gpu, n, 5, 5, A, spoilt, other) if bad is B else mttkrp(gpu, n, 5, 5, A, other, spoilt)
             assert np.array_equal(got[at + 1:], whole[at + 1:]) and np.isnan(got[:at + 1]).all()
+
+
+@pytest.mark.parametrize("f64", [False, True])
+@pytest.mark.parametrize("n,R", [(2, 3), (9, 5), (40, 33), (88, 20), (130, 20)])
+def test_a_meets_b_before_c(gpu, n, R, f64):
+    """(A(i,j,k) B(j,r)) C(k,r), as the rule has it: what cancels in magnitude between A and B neither overflows nor vanishes, on both sides of
+    the line between the kernels."""
+    t, e = (np.float64, 160) if f64 else (np.float32, 20)
+    for a, b, c in ((10.0 ** e, 10.0 ** -e, 10.0 ** e), (10.0 ** -e, 10.0 ** e, 10.0 ** -e)):
+        A, B, C = np.full(tet(n), a, dtype=t), np.full((n, R), b, dtype=t), np.full((n, R), c, dtype=t)
+        got = mttkrp(gpu, n, R, R, A, B, C)
+        terms = np.array([(n - i) * (n - i + 1) // 2 for i in range(n)], dtype=np.float64)
+        assert np.allclose(got, (terms * c)[:, None], rtol=tet(n) * np.finfo(t).eps, atol=0)
