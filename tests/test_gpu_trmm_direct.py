@@ -73,3 +73,17 @@ def test_values_beyond_the_split(gpu, oracle, scale):
     assert np.array_equal(np.isinf(got), np.isinf(want))
     ok = np.isfinite(want)
     assert np.allclose(got[ok], want[ok], rtol=1e-6, atol=0)
+
+
+@pytest.mark.parametrize("n,m", [(64, 2), (65, 32), (130, 17), (1000, 8), (1536, 32), (2048, 9), (3000, 5)])
+def test_few_columns_have_the_products_of_the_type(gpu, n, m):
+    """A row of C that meets one row of B is one rounded product in single precision, with every bit."""
+    U, B = inputs.uniform(6300 + n, n * (n + 1) // 2), np.zeros((n, m), dtype=np.float32)
+    k = n - 1 - np.arange(m) % 3 * (n // 3)  # the one row that column c meets
+    B[k, np.arange(m)] = inputs.uniform(6400 + n, m)
+    got = product(gpu, n, m, m, U, B)
+    i = np.arange(n)
+    for c in range(m):
+        rows = i[i <= k[c]]
+        assert np.array_equal(got[rows, c], U[rows * n - rows * (rows - 1) // 2 + k[c] - rows] * B[k[c], c])
+        assert not got[k[c] + 1:, c].any()
