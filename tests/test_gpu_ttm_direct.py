@@ -50,4 +50,16 @@ def test_values_that_are_not_finite_stay_where_they_belong(gpu, Q, f64, value):
         bad[35, l] = value
         got = ttm(gpu, n, Q, K, Q, B, bad).reshape(-1, K)
         assert np.array_equal(np.delete(got, 35, 1), np.delete(whole, 35, 1))
-        assert not np.isfinite(got[:, 35]).all() or np.allclose(got[:, 35], value, rtol=3)
+        with np.errstate(all="ignore"):
+            want = (B.reshape(-1, Q).astype(np.float64) @ bad[35].astype(np.float64)).astype(B.dtype)
+        assert np.array_equal(np.isnan(got[:, 35]), np.isnan(want)) and np.allclose(got[:, 35], want, rtol=1e-6, equal_nan=True)
+
+
+@pytest.mark.parametrize("n,Q,K", [(10, 16, 5), (30, 20, 40), (60, 25, 100), (60, 32, 500), (80, 31, 256)])
+def test_few_terms_have_the_products_of_the_type(gpu, n, Q, K):
+    """Where a row of C has one element, a result is one rounded product in single precision, with every bit."""
+    B, C = inputs.uniform(8200 + n, n * (n + 1) // 2 * Q), np.zeros((K, Q), dtype=np.float32)
+    l = np.arange(K) % Q
+    C[np.arange(K), l] = inputs.uniform(8300 + n, K)
+    got = ttm(gpu, n, Q, K, Q, B, C).reshape(-1, K)
+    assert np.array_equal(got, B.reshape(-1, Q)[:, l] * C[np.arange(K), l])
