@@ -18,8 +18,8 @@
 //            on one set of k columns, split once into LDS.
 // Where workgroups share a tile's samples they add into an output cleared by a fill kernel, with floating-point atomics.
 #include "cube_units.h"
+#include "direct_tile.h"
 #include "launch_limits.h"
-#include "split3.h"
 
 using namespace dastac;
 
@@ -275,8 +275,6 @@ __global__ __launch_bounds__(64 * WX * kUnitsPerGroup<WX>) __attribute__((amdgpu
 void pr3_direct_kernel(int64_t N, int d, const T *__restrict__ B, int64_t ldb, T *__restrict__ out, int64_t chunk, unsigned base,
                        unsigned units, unsigned split) {
   typedef Cube<T, NT> C;
-  constexpr int kSlots = WX > 1 ? WX / 2 : 1;
-  __shared__ T slots[kSlots][NT * C::kRegs * 64];
   constexpr unsigned kOwn = kUnitsPerGroup<WX>;
   const int lane = threadIdx.x & 63, wave = kOwn > 1 ? 0 : uniform32(threadIdx.x >> 6);
   const unsigned items = units * split, xcd = blockIdx.x & 7;
@@ -312,37 +310,11 @@ void pr3_direct_kernel(int64_t N, int d, const T *__restrict__ B, int64_t ldb, T
       C::plain(raw, acc);
     }
   }
-  if constexpr (WX > 1) {
-    // the upper half of the wavefronts leave their sums, the lower half add their own, then all add up the slots and write
-    T *mine = slots[wave % kSlots];
-    if (wave >= kSlots) {
-#pragma unroll
-      for (int q = 0; q < NT; ++q)
-#pragma unroll
-        for (int v = 0; v < C::kRegs; ++v) mine[(q * C::kRegs + v) * 64 + lane] = C::at(acc, q, v);
-    }
-    __syncthreads();
-    if (wave < kSlots) {
-#pragma unroll
-      for (int q = 0; q < NT; ++q)
-#pragma unroll
-        for (int v = 0; v < C::kRegs; ++v) mine[(q * C::kRegs + v) * 64 + lane] += C::at(acc, q, v);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int t = 0; t < NT * C::kRegs / WX; ++t) {
-    const int g = (WX > 1 ? wave : 0) + WX * t, q = g / C::kRegs, v = g % C::kRegs;
-    T sum;
-    if constexpr (WX == 1) {
-      sum = C::at(acc, q, v);
-    } else {
-      sum = slots[0][g * 64 + lane];
-#pragma unroll
-      for (int s = 1; s < kSlots; ++s) sum += slots[s][g * 64 + lane];
-    }
+  auto at = [&](int g) { return C::at(acc, g / C::kRegs, g % C::kRegs); };
+  auto put = [&](int g, T sum) {
+    const int q = g / C::kRegs, v = g % C::kRegs;
     const int i = i0 + 4 * q + C::slice_of(v), j = j0 + C::j_of(v, lane), k = k0 + C::col_of(v, lane);
-    if (i >= d) continue;
+    if (i >= d) return;
     T *const base = slice_base(out, d, i, j0);
     if (i <= j && j <= k && k < d) {
       T *p = base + row_offset(d, j0, j, k);
@@ -351,7 +323,8 @@ void pr3_direct_kernel(int64_t N, int d, const T *__restrict__ B, int64_t ldb, T
       else
         *p = sum;
     }
-  }
+  };
+  add_up<WX, NT * C::kRegs, T>(wave, lane, at, put);
 }
 
 // ---- staged (single precision) -----------------------------------------------------------------------------------
