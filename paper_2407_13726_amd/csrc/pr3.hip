@@ -81,6 +81,12 @@ __device__ inline unsigned row_offset(int d, int j0, int j, int k) {
   return (a * (a + 1) - b * (b + 1)) / 2 + (unsigned)(k - j);
 }
 
+// Element (i0+t,j,k) from the start of slice i0, t <= 8: t slices of orders d-i0, d-i0-1, ..., rows i0+t..j-1 of the next, k-j.  32 bits hold it.
+__device__ inline unsigned near_slice(int d, int i0, int t, int j, int k) {
+  const unsigned q = (unsigned)(d - i0), u = (unsigned)t, a = q - u, b = (unsigned)(d - j);
+  return u * (q * (q + 1) / 2) - q * (u * (u - 1) / 2) + u * (u - 1) * (u - 2) / 6 + (a * (a + 1) - b * (b + 1)) / 2 + (unsigned)(k - j);
+}
+
 // ---- direct ------------------------------------------------------------------------------------------------------
 // A tile of 32 rows holds four slices i and eight j: row r is slice r / 8 and j = r % 8 (cube_units.h).
 
@@ -311,13 +317,11 @@ void pr3_direct_kernel(int64_t N, int d, const T *__restrict__ B, int64_t ldb, T
     }
   }
   auto at = [&](int g) { return C::at(acc, g / C::kRegs, g % C::kRegs); };
+  T *const slice = out + tet_slice_start(d, i0);
   auto put = [&](int g, T sum) {
-    const int q = g / C::kRegs, v = g % C::kRegs;
-    const int i = i0 + 4 * q + C::slice_of(v), j = j0 + C::j_of(v, lane), k = k0 + C::col_of(v, lane);
-    if (i >= d) return;
-    T *const base = slice_base(out, d, i, j0);
-    if (i <= j && j <= k && k < d) {
-      T *p = base + row_offset(d, j0, j, k);
+    const int t = 4 * (g / C::kRegs) + C::slice_of(g % C::kRegs), j = j0 + C::j_of(g % C::kRegs, lane), k = k0 + C::col_of(g % C::kRegs, lane);
+    if (i0 + t <= j && j <= k && k < d) {
+      T *const p = slice + near_slice(d, i0, t, j, k);
       if (ATOMIC)
         unsafeAtomicAdd(p, sum);
       else
