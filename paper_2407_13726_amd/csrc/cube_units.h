@@ -6,6 +6,19 @@ namespace dastac {
 
 constexpr int kCubeSub = 32;  // columns k of a tile
 
+// ---- rows kernel: strips of NS slices i and sixteen rows j, from the group's first slice on -------------------------
+// Groups of slices from the two ends share a line of workgroups: together they have as many row blocks as the first alone, or one more.
+DASTAC_HD int strip_columns(int d) { return (d + 15) / 16 + 1; }
+DASTAC_HD int strip_lines(int d, int NS) { return ((d + NS - 1) / NS + 1) / 2; }
+// Group and row block of workgroup (x, y); false: none.
+DASTAC_HD bool strip_of(int d, int NS, int x, int y, int &group, int &block) {
+  const int mine = (d - NS * y + 15) / 16;
+  group = x < mine ? y : (d + NS - 1) / NS - 1 - y;
+  block = x < mine ? x : x - mine;
+  if (x >= mine && group == y) return false;  // the group in the middle has no other
+  return NS * group + 16 * block < d;
+}
+
 // ---- direct kernel: tiles of NT * 4 slices i, 8 rows j and 32 columns k --------------------------------------------
 // Units: row block J (eight j), a group of 4 NT slices, 32 columns k from 8 J on (NT is 1 or 2).
 constexpr int kCubeRowsD = 8;

@@ -10,7 +10,7 @@
 // wait for each other: 1.85).
 //
 // Three kernels, chosen in run() by the sizes:
-//   few      fewer than 16 samples: vector instructions, a column a lane;
+//   rows     fewer than 16 samples: a wavefront writes whole runs of sixteen rows j, on the instructions of the type;
 //   direct   a wavefront owns a tile and every WX-th step of 16 samples; operands come straight from memory, nothing is staged and nobody
 //            waits for anybody until the workgroup's WX wavefronts add their sums through LDS.  All of double precision, small
 //            products in single;
@@ -21,6 +21,8 @@
 #include "direct_tile.h"
 #include "launch_limits.h"
 
+#include <type_traits>
+
 using namespace dastac;
 
 namespace {
@@ -29,46 +31,6 @@ constexpr int64_t kMaxD3 = 1 << 13;  // unit counts stay inside 32 bits
 constexpr int64_t kMaxN = (int64_t)1 << 31;
 constexpr int kStep = 16;  // samples per step of a wavefront of the direct kernel
 constexpr int kSub = kCubeSub;
-
-// ---- fewer than 16 samples ---------------------------------------------------------------------------------------
-// Bound by the writes and by the latency of N reads: a workgroup takes slice i and sixteen rows j, its wavefronts 64 columns k each, a column a
-// lane with sixteen sums; the sixteen factors of a sample are scalars (N=3, d=1024 216 us, tiles on the matrix instructions 350; N=10, d=256 18 and 13;
-// with 64 samples the scalar reads take longer than those tiles, 1000 and 419).
-template <typename T>
-__global__ __launch_bounds__(256) void pr3_few_kernel(int N, int d, const T *__restrict__ B, int64_t ldb, T *__restrict__ out) {
-  constexpr int kJ = 16;
-  const int i = blockIdx.y, j0 = i + kJ * (int)blockIdx.x;
-  if (j0 >= d) return;
-  const bool whole = j0 + kJ <= d;
-  for (int k0 = j0 + 64 * uniform32(threadIdx.x >> 6); k0 < d; k0 += 256) {
-    const int k = k0 + (int)(threadIdx.x & 63), kc = k < d ? k : d - 1;
-    T s[kJ];
-#pragma unroll
-    for (int q = 0; q < kJ; ++q) s[q] = T(0);
-    if (whole) {
-#pragma unroll 4
-      for (int x = 0; x < N; ++x) {
-        const T *sample = B + x * ldb;
-        const T a = sample[i], c = sample[kc];
-#pragma unroll
-        for (int q = 0; q < kJ; ++q) s[q] += a * sample[j0 + q] * c;
-      }
-    } else {
-      for (int x = 0; x < N; ++x) {
-        const T *sample = B + x * ldb;
-        const T a = sample[i], c = sample[kc];
-#pragma unroll
-        for (int q = 0; q < kJ; ++q) s[q] += a * sample[j0 + q < d ? j0 + q : d - 1] * c;
-      }
-    }
-    T *const slice = out + tet_slice_start(d, i) + tri(d - i);
-#pragma unroll
-    for (int q = 0; q < kJ; ++q) {
-      const int j = j0 + q;
-      if (j <= k && k < d) slice[k - j - tri(d - j)] = s[q];
-    }
-  }
-}
 
 // The output's row (i,j), less the 32-bit element number that row_offset() gives it: wave-uniform, so that the 64-bit polynomial is scalar work.
 template <typename T>
@@ -85,6 +47,124 @@ __device__ inline unsigned row_offset(int d, int j0, int j, int k) {
 __device__ inline unsigned near_slice(int d, int i0, int t, int j, int k) {
   const unsigned q = (unsigned)(d - i0), u = (unsigned)t, a = q - u, b = (unsigned)(d - j);
   return u * (q * (q + 1) / 2) - q * (u * (u - 1) / 2) + u * (u - 1) * (u - 2) / 6 + (a * (a + 1) - b * (b + 1)) / 2 + (unsigned)(k - j);
+}
+
+// ---- rows --------------------------------------------------------------------------------------------------------
+// A wavefront owns two slices i, sixteen rows j and 64 columns k, a workgroup those rows: two contiguous runs of the output.  Rows of the matrix instruction are
+// columns k, its columns the rows j with their products B(x,i) B(x,j), so that a lane ends up with four consecutive elements and writes them at once.
+// Four samples an instruction, all requested at once; nothing is staged, split or shared.  Bound by the writes (N=1, d=1024 fp32 186-220 us for 718 MB, fp64 368 for
+// 1436) and, below d=300, by the latency of one load and a launch.  us, columns a lane on vector instructions and here: fp32 N=8, d=64 5.2, 3.5; d=256 18,
+// 7.8; N=15, d=512 104, 24; fp64 N=8, d=64 5.8, 2.9; N=15, d=256 33, 10; d=512 168, 43; d=1024 757, 371.  In double precision two slices of 32 columns, with runs
+// half as long: d=1024 458.  Stores past the caches (nontemporal): 600 and 1260.
+template <typename T>
+struct Strip;
+template <>
+struct Strip<float> {
+  typedef f4a acc;
+  typedef f4u run;  // what a lane writes at once
+  static constexpr int kRun = 4, kSlices = 2, kBlocks = 4;
+  __device__ static acc mma(float k, float p, acc c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(k, p, c, 0, 0, 0); }
+  // Which of sixteen columns operand row r holds, and where a lane's run of results from register v on begins: register v is operand row 4 (lane / 16) + v.
+  __device__ static int column(int r) { return r; }
+  __device__ static int begins(int, int h) { return 4 * h; }
+};
+template <>
+struct Strip<double> {
+  typedef d4v acc;
+  typedef d2u run;
+  static constexpr int kRun = 2, kSlices = 1, kBlocks = 4;
+  __device__ static acc mma(double k, double p, acc c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(k, p, c, 0, 0, 0); }
+  // register v is operand row 4 v + lane / 16; the four lanes of a row write 64 contiguous bytes
+  __device__ static int column(int r) { return 8 * (r / 8) + 2 * (r % 4) + r / 4 % 2; }
+  __device__ static int begins(int v, int h) { return 4 * v + 2 * h; }
+};
+
+template <typename T, int NS, int NB>
+__device__ __attribute__((always_inline)) inline void pr3_strip(int N, int d, const T *__restrict__ B, int64_t ldb, T *__restrict__ slice, int i0, int j0, int k0,
+                                                                int lane) {
+  typedef Strip<T> S;
+  const int h = lane >> 4, r = lane & 15, j = j0 + r;
+  auto column = [&](int c) { return c < d ? c : d - 1; };  // columns past the last are read as the last and not kept
+  const T *const sample = B + h * ldb, *const pj = sample + column(j);
+  const T *pi[NS], *pk[NB];
+#pragma unroll
+  for (int s = 0; s < NS; ++s) pi[s] = sample + column(i0 + s);
+#pragma unroll
+  for (int b = 0; b < NB; ++b) pk[b] = sample + column(k0 + 16 * b + S::column(r));
+  typename S::acc acc[NS][NB];
+#pragma unroll
+  for (int s = 0; s < NS; ++s)
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) acc[s][b][v] = T(0);
+  auto steps = [&](auto count) __attribute__((always_inline)) {
+    constexpr int STEPS = decltype(count)::value;  // 4 STEPS >= N
+    T p[STEPS][NS], q[STEPS], k[STEPS][NB];
+#pragma unroll
+    for (int e = 0; e < STEPS; ++e) {
+      // samples past the last are read as the last and made zero
+      const int64_t at = (4 * e + h < N ? 4 * e : N - 1 - h) * ldb;
+      q[e] = pj[at];
+#pragma unroll
+      for (int s = 0; s < NS; ++s) p[e][s] = pi[s][at];
+#pragma unroll
+      for (int b = 0; b < NB; ++b) k[e][b] = pk[b][at];
+    }
+#pragma unroll
+    for (int e = 0; e < STEPS; ++e) {
+      const bool out = 4 * e + h >= N;
+#pragma unroll
+      for (int s = 0; s < NS; ++s) p[e][s] = out ? T(0) : p[e][s] * q[e];
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+        k[e][b] = out ? T(0) : k[e][b];
+#pragma unroll
+        for (int s = 0; s < NS; ++s) acc[s][b] = S::mma(k[e][b], p[e][s], acc[s][b]);
+      }
+    }
+  };
+  if (N > 8)
+    steps(std::integral_constant<int, 4>());
+  else if (N > 4)
+    steps(std::integral_constant<int, 2>());
+  else
+    steps(std::integral_constant<int, 1>());
+#pragma unroll
+  for (int s = 0; s < NS; ++s)
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      if (i0 + s > j || j >= d) continue;
+#pragma unroll
+      for (int v = 0; v < 4; v += S::kRun) {
+        const int k = k0 + 16 * b + S::begins(v, h);
+        T *const p = slice + near_slice(d, i0, s, j, k);  // (a run that begins left of the diagonal begins within the slices' earlier rows)
+        if (j <= k && k + S::kRun <= d) {
+          typename S::run x;
+#pragma unroll
+          for (int e = 0; e < S::kRun; ++e) x[e] = acc[s][b][v + e];
+          *reinterpret_cast<typename S::run *>(p) = x;
+        } else {
+#pragma unroll
+          for (int e = 0; e < S::kRun; ++e)
+            if (j <= k + e && k + e < d) p[e] = acc[s][b][v + e];
+        }
+      }
+    }
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
+void pr3_rows_kernel(int N, int d, const T *__restrict__ B, int64_t ldb, T *__restrict__ out) {
+  constexpr int NS = Strip<T>::kSlices;
+  int group, block;
+  if (!strip_of(d, NS, blockIdx.x, blockIdx.y, group, block)) return;
+  const int i0 = NS * group, j0 = i0 + 16 * block, lane = threadIdx.x & 63;
+  T *const slice = out + tet_slice_start(d, i0);
+  constexpr int kBlocks = Strip<T>::kBlocks;
+  int k0 = j0 + 16 * kBlocks * uniform32(threadIdx.x >> 6);
+  for (; k0 + 8 * kBlocks < d; k0 += 64 * kBlocks) pr3_strip<T, NS, kBlocks>(N, d, B, ldb, slice, i0, j0, k0, lane);
+  if (k0 < d) pr3_strip<T, NS, kBlocks / 2>(N, d, B, ldb, slice, i0, j0, k0, lane);
 }
 
 // ---- direct ------------------------------------------------------------------------------------------------------
@@ -670,7 +750,8 @@ int run(int64_t N, int64_t d, const T *B, int64_t ldb, T *out, void *stream) {
   hipStream_t st = (hipStream_t)stream;
   if (N == 0) return clear(d, out, st);
   if (N < kStep) {
-    pr3_few_kernel<T><<<dim3((unsigned)ceil_div(d, 16), (unsigned)d), 256, 0, st>>>((int)N, (int)d, B, ldb, out);
+    constexpr int NS = Strip<T>::kSlices;
+    pr3_rows_kernel<T><<<dim3((unsigned)strip_columns((int)d), (unsigned)strip_lines((int)d, NS)), 256, 0, st>>>((int)N, (int)d, B, ldb, out);
     return launch_status();
   }
   const int64_t cus = compute_units();

@@ -1,5 +1,5 @@
-"""How the third-order polynomial-regression tensor is cut into tiles: every element i<=j<=k in exactly one tile of the direct kernel and,
-for every step of samples, in exactly one part of the staged one; closed forms of the counts against the sums."""
+"""How the third-order polynomial-regression tensor is cut into tiles: every element i<=j<=k in exactly one strip of the rows kernel, one
+tile of the direct kernel and, for every step of samples, in exactly one part of the staged one; closed forms of the counts against the sums."""
 import os
 import subprocess
 
@@ -35,6 +35,16 @@ int main(int, char **argv) {
       cover(seen, d, t, 4 * NT, 8, 32, 1);
     }
     if (!all(seen, 1)) return printf("direct, NT=%d: not a partition\n", NT), 1;
+  }
+  for (int NS = 1; NS <= 2; ++NS) {
+    std::vector<int> seen(tet(d), 0);
+    for (int y = 0; y < strip_lines(d, NS); ++y)
+      for (int x = 0; x < strip_columns(d); ++x) {
+        int group, block;
+        if (!strip_of(d, NS, x, y, group, block)) continue;
+        cover(seen, d, CubeTile{NS * group, NS * group + 16 * block, NS * group + 16 * block}, NS, 16, d, 1);
+      }
+    if (!all(seen, 1)) return printf("rows, NS=%d: not a partition\n", NS), 1;
   }
   for (int parts : {1, 7, 256}) {
     std::vector<int> seen(tet(d), 0);

@@ -95,3 +95,15 @@ def test_products_are_formed_in_the_order_of_the_rule(gpu, N, d, ld, f64):
         normal = np.isfinite(want) & (pair >= tiny)
         # one term of two rounded products (the split leaves out up to 2^-22 of it); below the normal range products lose bits or vanish
         assert np.allclose(got[normal], want[normal], rtol=2.0 ** -20, atol=tiny)
+
+
+@pytest.mark.parametrize("f64", [False, True])
+@pytest.mark.parametrize("N", [1, 4, 5, 8, 9, 15])
+def test_strips_of_few_samples(gpu, oracle, N, f64):
+    """Whole and cut blocks of sixteen rows and columns, one slice and two, runs that begin left of the diagonal or end with the matrix."""
+    for d in (1, 2, 3, 15, 16, 17, 31, 34, 63, 64, 67, 129, 260):
+        B = inputs.small_int(2900 + N + d, -2, 2, N, d + d % 3).astype(np.float64 if f64 else np.float32)
+        want, _ = (oracle.pr_a3_f64 if f64 else oracle.pr_a3)(np.ascontiguousarray(B[:, :d]))
+        out = gpu.up(np.full(tet(d), np.nan, dtype=B.dtype))
+        (gpu.d.pr_a3_f64 if f64 else gpu.d.pr_a3_f32)(N, d, gpu.up(B), B.shape[1], out)
+        assert gpu.down(out).tobytes() == want.astype(B.dtype).tobytes(), d
