@@ -12,7 +12,7 @@
 // Three kernels, chosen in run() by the sizes:
 //   rows     fewer than 16 samples: a wavefront writes whole runs of sixteen rows j, on the instructions of the type;
 //   direct   a wavefront owns a tile and every WX-th step of 16 samples; operands come straight from memory, nothing is staged and nobody
-//            waits for anybody until the workgroup's WX wavefronts add their sums through LDS.  All of double precision, small
+//            waits for anybody until the workgroup's WX wavefronts add their sums through LDS.  All of double precision, few samples and small
 //            products in single;
 //   staged   single precision, where operands are read and split often enough to share: eight wavefronts of 32 x (32..128) elements
 //            on one set of k columns, split once into LDS.
@@ -171,18 +171,19 @@ void pr3_rows_kernel(int N, int d, const T *__restrict__ B, int64_t ldb, T *__re
 // A tile of 32 rows holds four slices i and eight j: row r is slice r / 8 and j = r % 8 (cube_units.h).
 
 // A wavefront's operands and sums: NT tiles of 32 rows by 32 columns.
-template <typename T, int NT>
+// PARTIAL: how many of the nine products of two split operands are formed (0: operands are not split).
+template <typename T, int NT, int PARTIAL>
 struct Cube;
 
 // Lane l takes row (column) l % 32 and, of a step's samples, those with number 2 e + l / 32.
-template <int NT>
-struct Cube<float, NT> {
+template <int NT, int PARTIAL>
+struct Cube<float, NT, PARTIAL> {
   static constexpr int kRegs = 16;
   struct Raw {
     float j[8], k[8], i[8][NT];
   };
   struct Sums {
-    f16v hi[NT], lo[NT];  // the largest of the six partial products, and the five smaller ones
+    f16v hi[NT], lo[NT];  // the largest of the partial products, and the smaller ones
   };
   global_bytes base;
   int64_t pitch;  // bytes per sample
@@ -237,9 +238,9 @@ struct Cube<float, NT> {
     }
     __builtin_amdgcn_sched_barrier(0);
     between();
-    constexpr int PA[6] = {0, 2, 0, 1, 0, 1}, PK[6] = {0, 0, 2, 1, 1, 0};
+    constexpr int PA[9] = {0, 2, 0, 1, 0, 1, 2, 1, 2}, PK[9] = {0, 0, 2, 1, 1, 0, 1, 2, 2};
 #pragma unroll
-    for (int g = 0; g < 6; ++g)
+    for (int g = 0; g < PARTIAL; ++g)
 #pragma unroll
       for (int q = 0; q < NT; ++q) {
         f16v &acc = g == 0 ? c.hi[q] : c.lo[q];
@@ -273,7 +274,7 @@ struct Cube<float, NT> {
 
 // v_mfma_f64_16x16x4_f64: lane l takes row (column) l % 16 and the samples with number 4 e + l / 16; a tile is 2 x 2 of its results.
 template <int NT>
-struct Cube<double, NT> {
+struct Cube<double, NT, 0> {
   static constexpr int kRegs = 16;
   struct Raw {
     double j[4], k[4][2], i[4][2 * NT];
@@ -337,8 +338,6 @@ struct Cube<double, NT> {
         c.v[q][3] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, o.k[e][1], c.v[q][3], 0, 0, 0);
       }
   }
-  __device__ static bool finish(Sums &) { return true; }
-  __device__ static void plain(const Raw &, Sums &) {}
   __device__ static double at(const Sums &c, int q, int v) { return c.v[q][v / 4][v % 4]; }
   // register v is row 16 (v / 8) + 4 (v % 4) + lane / 16, column 16 (v / 4 % 2) + lane % 16
   __device__ static int slice_of(int v) { return 2 * (v / 8) + v % 4 / 2; }
@@ -353,14 +352,14 @@ struct Cube<double, NT> {
 // Bound by the vector instructions of the split in single precision (170 beside 6 matrix instructions a step of one tile, 230 beside 12 of two),
 // by the matrix instructions in double (N=10000, d=200: 676 us, of which 0.77 at their peak; per-slice tiles of 64 x 64 through LDS took 1700).  us
 // in single precision here and in the tiles of 64 x 64: N=620, d=36 7.3, 22; N=381, d=104 9.9, 23; N=9504, d=24 10.2, 23.7; N=1018, d=114 15.4, 27.9;
-// N=3000, d=100 28, 53; in double N=1322, d=18 6.8, 23; N=3993, d=31 11, 34; N=604, d=314 175, 238; N=20000, d=40 33, 137.
+// N=3000, d=100 28, 53; few samples N=32, d=1024 275, 335; N=64, d=512 52, 65; in double N=1322, d=18 6.8, 23; N=3993, d=31 11, 34; N=604, d=314 175, 238; N=20000, d=40 33, 137.
 template <int WX>
 constexpr int kUnitsPerGroup = WX == 1 ? 4 : 1;  // single wavefronts go four to a workgroup: fewer to dispatch
-template <typename T, int NT, int WX, bool ATOMIC>
+template <typename T, int NT, int WX, int PARTIAL, bool ATOMIC>
 __global__ __launch_bounds__(64 * WX * kUnitsPerGroup<WX>) __attribute__((amdgpu_waves_per_eu(NT == 1 ? 4 : 3, NT == 1 ? 4 : 3)))
 void pr3_direct_kernel(int64_t N, int d, const T *__restrict__ B, int64_t ldb, T *__restrict__ out, int64_t chunk, unsigned base,
                        unsigned units, unsigned split) {
-  typedef Cube<T, NT> C;
+  typedef Cube<T, NT, PARTIAL> C;
   constexpr unsigned kOwn = kUnitsPerGroup<WX>;
   const int lane = threadIdx.x & 63, wave = kOwn > 1 ? 0 : uniform32(threadIdx.x >> 6);
   const unsigned items = units * split, xcd = blockIdx.x & 7;
@@ -388,12 +387,14 @@ void pr3_direct_kernel(int64_t N, int d, const T *__restrict__ B, int64_t ldb, T
     C::multiply(raw, acc, [&] { cube.load(first(next), raw); });
   }
   // Operands that the split cannot hold, or results that are not finite: this wavefront's steps again on the fp32 instructions.
-  if (!__all(C::finish(acc))) {
-    C::clear(acc);
-    for (int s = wave; s < steps; s += WX) {
-      cube.load(first(s), raw);
-      if (repeats(s) > 0) cube.skip(repeats(s), raw);
-      C::plain(raw, acc);
+  if constexpr (PARTIAL > 0) {
+    if (!__all(C::finish(acc))) {
+      C::clear(acc);
+      for (int s = wave; s < steps; s += WX) {
+        cube.load(first(s), raw);
+        if (repeats(s) > 0) cube.skip(repeats(s), raw);
+        C::plain(raw, acc);
+      }
     }
   }
   auto at = [&](int g) { return C::at(acc, g / C::kRegs, g % C::kRegs); };
@@ -708,21 +709,21 @@ int64_t compute_units() {
   return cus;
 }
 
-template <typename T, int NT, int WX>
+template <typename T, int NT, int WX, int PARTIAL = sizeof(T) == 4 ? 6 : 0>
 int launch_direct(int64_t N, int64_t d, const T *B, int64_t ldb, T *out, int64_t units, int64_t split, hipStream_t st) {
   constexpr int kOwn = kUnitsPerGroup<WX>;
   const int64_t chunk = ceil_div(ceil_div(N, split), kStep) * kStep;
   split = ceil_div(N, chunk);
   if (split > 1) {
     if (const int rc = clear(d, out, st)) return rc;
-    pr3_direct_kernel<T, NT, WX, true><<<(unsigned)(8 * ceil_div(ceil_div(units * split, 8), kOwn)), 64 * WX * kOwn, 0, st>>>(
+    pr3_direct_kernel<T, NT, WX, PARTIAL, true><<<(unsigned)(8 * ceil_div(ceil_div(units * split, 8), kOwn)), 64 * WX * kOwn, 0, st>>>(
         N, (int)d, B, ldb, out, chunk, 0, (unsigned)units, (unsigned)split);
     return launch_status();
   }
   constexpr int64_t kMost = kMaxWorkItems / (64 * WX * kOwn) / 8 * 8;  // units that one launch surely can count
   for (int64_t base = 0; base < units; base += kMost) {
     const int64_t n = units - base < kMost ? units - base : kMost;
-    pr3_direct_kernel<T, NT, WX, false><<<(unsigned)(8 * ceil_div(ceil_div(n, 8), kOwn)), 64 * WX * kOwn, 0, st>>>(N, (int)d, B, ldb, out, chunk, (unsigned)base, (unsigned)n, 1);
+    pr3_direct_kernel<T, NT, WX, PARTIAL, false><<<(unsigned)(8 * ceil_div(ceil_div(n, 8), kOwn)), 64 * WX * kOwn, 0, st>>>(N, (int)d, B, ldb, out, chunk, (unsigned)base, (unsigned)n, 1);
     if (launch_status() != DASTAC_OK) return DASTAC_EHIP;
   }
   return DASTAC_OK;
@@ -771,17 +772,21 @@ int run(int64_t N, int64_t d, const T *B, int64_t ldb, T *out, void *stream) {
     if (t < 0.97 * best) best = t, split = s;
   }
   if constexpr (kB == 4) {
+    // All nine products of the parts for few samples: a term is its rounded value then, to 2^-24, where the six leave out up to 2^-23 of it (us, N=64, d=512 52,
+    // with six 47; N=128, d=1024 621, 536; on the fp32 instructions 53 and 657, with 2.4 times the error).
+    if (N <= 4 * kStep || (N <= 8 * kStep && d >= 256))
+      return NT == 1 ? launch_direct<T, 1, 8, 9>(N, d, B, ldb, out, units, split, st) : launch_direct<T, 2, 1, 9>(N, d, B, ldb, out, units, split, st);
     // The staged kernel: 22 us of launches and prologues, the output cleared and one and a half times added to, and 0.083 us per unit of
     // weight and compute unit (N=1018, d=114 30.5 us, direct 15.4; N=976, d=152 38.7, 24.9; N=8598, d=111 67, 65; N=2000, d=256 105, 130;
     // N=20000, d=160 266, 331).
     const int64_t steps = ceil_div(N, kXT), total = staged_weight((int)d) * steps;
     const double staged = 22.0 + 1.25e-6 * (double)(tet(d) * kB) + 0.083 * (double)total / (double)cus;
     if (ldb <= kMaxStagedLd && N >= kXT && staged < best) {
-      if (const int rc = clear(d, out, st)) return rc;
       // A sum runs in one accumulator for a quarter of the samples, between 512 and 2048: its truncation error grows with the length
       // (N=2000, d=256 2.0e-7 in pieces of 2000, 1.4e-7 in pieces of 512; N=10000 2.8e-7 in pieces of 2048, 2.2e-7 of 1250 and 3 % slower).
       const int64_t quarter = ceil_div(steps, 4);
       const int most = (int)(quarter < 16 ? 16 : quarter > 64 ? 64 : quarter);
+      if (const int rc = clear(d, out, st)) return rc;
       pr3_staged_kernel<<<(unsigned)cus, 512, 0, st>>>(N, (int)d, B, ldb, out, total, (int)steps, most);
       return launch_status();
     }

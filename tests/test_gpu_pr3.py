@@ -97,6 +97,13 @@ def test_products_are_formed_in_the_order_of_the_rule(gpu, N, d, ld, f64):
         assert np.allclose(got[normal], want[normal], rtol=2.0 ** -20, atol=tiny)
 
 
+def expected(b):
+    """(b_i b_j) b_k of one row of samples, packed: the pair rounded to its type, the product with b_k in double precision; and where they stand."""
+    k = np.arange(len(b))
+    wanted = (k[:, None] <= k[None, :])[:, :, None] & (k[None, :, None] <= k[None, None, :])
+    return ((b[:, None] * b[None, :]).astype(np.float64)[:, :, None] * b.astype(np.float64))[wanted]
+
+
 @pytest.mark.parametrize("f64", [False, True])
 @pytest.mark.parametrize("N", [1, 4, 5, 8, 9, 15])
 def test_strips_of_few_samples(gpu, oracle, N, f64):
@@ -107,3 +114,15 @@ def test_strips_of_few_samples(gpu, oracle, N, f64):
         out = gpu.up(np.full(tet(d), np.nan, dtype=B.dtype))
         (gpu.d.pr_a3_f64 if f64 else gpu.d.pr_a3_f32)(N, d, gpu.up(B), B.shape[1], out)
         assert gpu.down(out).tobytes() == want.astype(B.dtype).tobytes(), d
+
+
+@pytest.mark.parametrize("N,d", [(1, 40), (15, 97), (16, 97), (40, 33), (64, 150), (64, 260), (100, 256), (128, 257)])
+def test_terms_of_few_samples_are_rounded_products(gpu, N, d):
+    """One sample that is not zero: the pair rounded, times the third factor within one rounding to nearest (where operands are split, all nine products
+    of their parts are added, the smaller eight among themselves: 2^-24 for the last addition, 2^-8 of that for theirs)."""
+    B = np.zeros((N, d), dtype=np.float32)
+    B[N // 2] = inputs.uniform(3000 + N + d, d)
+    out = gpu.empty(tet(d))
+    gpu.d.pr_a3_f32(N, d, gpu.up(B), d, out)
+    want = expected(B[N // 2])
+    assert (np.abs(gpu.down(out).astype(np.float64) - want) <= 2.0 ** -24 * (1 + 2.0 ** -7) * np.abs(want)).all()
