@@ -438,50 +438,72 @@ struct Staged {
   __attribute__((aligned(16))) float ji[2][32 * kPitch];  // columns j (16), columns i (16); [column][sample]
 };
 
-// A wavefront's tiles of a piece once more, on the fp32 instructions with operands straight from memory, two column blocks at a time and the
+// A wavefront's tiles of a piece once more, on the fp32 instructions with operands straight from memory, NB column blocks at a time and the
 // next sixteen samples on their way: where operands or results are beyond what the split can hold.  A function of its own: in the middle of the kernel it cost the
 // main loop its registers (N=10000, d=512 2.7 -> 3.1 ms).
+template <int NB>
 __device__ __attribute__((noinline)) void again(int64_t N, int d, const float *B, int64_t ldb, float *out, CubeTile u, int wn, int s0, int s1) {
   const int lane = threadIdx.x & 63, wave = uniform32(threadIdx.x >> 6), r = lane & 31, h = lane >> 5;
-  auto column = [&](int c) { return c < d ? c : d - 1; };
-  const int cj = column(u.j0 + (r & 15)), ci = column(u.i0 + 2 * wave + (r >> 4));
-  const int64_t end = (int64_t)s1 * kXT < N ? (int64_t)s1 * kXT : N;
-  for (int n = 0; n < wn; n += 2) {
-    const int k = u.k0 + 32 * n + r, ck0 = column(k), ck1 = column(k + 32);
-    struct Raw {
-      float a[8], b0[8], b1[8];
+  // (arguments of a function come in vector registers)
+  N = uniform64(N), ldb = uniform64(ldb), d = uniform32(d), wn = uniform32(wn), s0 = uniform32(s0), s1 = uniform32(s1);
+  B = reinterpret_cast<const float *>(uniform64(reinterpret_cast<int64_t>(B))), out = reinterpret_cast<float *>(uniform64(reinterpret_cast<int64_t>(out)));
+  u = CubeTile{uniform32(u.i0), uniform32(u.j0), uniform32(u.k0)};
+  const unsigned pitch = 4u * (unsigned)ldb;
+  auto place = [&](int c) { return 4u * (unsigned)(c < d ? c : d - 1) + (unsigned)h * pitch; };
+  const unsigned cj = place(u.j0 + (r & 15)), ci = place(u.i0 + 2 * wave + (r >> 4));
+  unsigned ck[NB];
+#pragma unroll
+  for (int n = 0; n < NB; ++n) ck[n] = place(u.k0 + 32 * n + r);
+  struct Raw {
+    float j[8], i[8], k[NB][8];
+  };
+  const int64_t begin = uniform64((int64_t)s0 * kXT), end = uniform64((int64_t)s1 * kXT < N ? (int64_t)s1 * kXT : N);
+  auto first = [&](int64_t x) { return x + 16 < end ? x : end - 16; };  // the last sixteen end with the samples (N >= 32)
+  auto load = [&](int64_t x, Raw &o) __attribute__((always_inline)) {
+    const auto rows = __builtin_amdgcn_make_buffer_rsrc((void *)(B + first(x) * ldb), 0, -1, 0x00020000);
+    auto at = [&](unsigned c, int e) __attribute__((always_inline)) {
+      return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rows, c, (unsigned)(2 * e) * pitch, 0));
     };
-    auto load = [&](int64_t x0, Raw &o) __attribute__((always_inline)) {
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const int64_t x = x0 + 2 * e + h;
-        const float *row = B + (x < end ? x : end - 1) * ldb;
-        o.a[e] = x < end ? row[cj] * row[ci] : 0.0f;
-        o.b0[e] = x < end ? row[ck0] : 0.0f;
-        o.b1[e] = x < end ? row[ck1] : 0.0f;
-      }
-    };
-    f16v sum[2];
+    for (int e = 0; e < 8; ++e) {
+      o.j[e] = at(cj, e), o.i[e] = at(ci, e);
 #pragma unroll
-    for (int v = 0; v < 16; ++v) sum[0][v] = 0.0f, sum[1][v] = 0.0f;
-    Raw next;
-    load((int64_t)s0 * kXT, next);
-    for (int64_t x0 = (int64_t)s0 * kXT; x0 < end; x0 += 16) {
-      const Raw o = next;
-      load(x0 + 16 < end ? x0 + 16 : x0, next);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        sum[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(o.a[e], o.b0[e], sum[0], 0, 0, 0);
-        sum[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(o.a[e], o.b1[e], sum[1], 0, 0, 0);
-      }
+      for (int n = 0; n < NB; ++n) o.k[n][e] = at(ck[n], e);
     }
+  };
+  f16v sum[NB];
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {  // slice v / 8 of the wavefront's two, j = 8 (v / 4 % 2) + 4 h + v % 4
-      const int i = u.i0 + 2 * wave + v / 8, j = u.j0 + 8 * (v / 4 % 2) + 4 * h + v % 4;
-      if (i <= j && j < d) {
-        float *p = out + tet_row_start(d, i, j) - j;
-        if (j <= k && k < d) unsafeAtomicAdd(p + k, sum[0][v]);
-        if (n + 1 < wn && j <= k + 32 && k + 32 < d) unsafeAtomicAdd(p + k + 32, sum[1][v]);
+  for (int n = 0; n < NB; ++n)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) sum[n][v] = 0.0f;
+  Raw next;
+  load(begin, next);
+  for (int64_t x = begin; x < end; x += 16) {
+    Raw o = next;
+    load(x + 16 < end ? x + 16 : x, next);
+    const int repeats = (int)(x - first(x));
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      o.j[e] *= o.i[e];
+      if (repeats > 0) {
+        const bool out = 2 * e + h < repeats;
+        o.j[e] = out ? 0.0f : o.j[e];
+#pragma unroll
+        for (int n = 0; n < NB; ++n) o.k[n][e] = out ? 0.0f : o.k[n][e];
+      }
+#pragma unroll
+      for (int n = 0; n < NB; ++n) sum[n] = __builtin_amdgcn_mfma_f32_32x32x2f32(o.j[e], o.k[n][e], sum[n], 0, 0, 0);
+    }
+  }
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {  // slice v / 8 of the wavefront's two, j = 8 (v / 4 % 2) + 4 h + v % 4
+    const int i = u.i0 + 2 * wave + v / 8, j = u.j0 + 8 * (v / 4 % 2) + 4 * h + v % 4;
+    if (i <= j && j < d) {
+      float *p = out + tet_row_start(d, i, j) - j;
+#pragma unroll
+      for (int n = 0; n < NB; ++n) {
+        const int k = u.k0 + 32 * n + r;
+        if (n < wn && j <= k && k < d) unsafeAtomicAdd(p + k, sum[n][v]);
       }
     }
   }
@@ -685,7 +707,12 @@ void pr3_staged_kernel(int64_t N, int d, const float *__restrict__ B, int64_t ld
         case 3: done = piece<3>(N, d, B, ldb, out, u, a, b, sh); break;
         default: done = piece<4>(N, d, B, ldb, out, u, a, b, sh); break;
       }
-      if (uniform32(done ? 0 : 1)) again(N, d, B, ldb, out, u, uniform32(wn), a, b);
+      if (uniform32(done ? 0 : 1)) {
+        if (wn <= 2)
+          again<2>(N, d, B, ldb, out, u, wn, a, b);
+        else
+          again<4>(N, d, B, ldb, out, u, wn, a, b);
+      }
     }
   });
 }
