@@ -62,6 +62,35 @@ DASTAC_HD int64_t staged_weight(int d) {  // of one step of all units
   for (int J = 0; kCubeRowsS * J < d; ++J) t += (int64_t)groups_of(d, J) * weight_of_chunks(subs_of(d, J), chunks_of(subs_of(d, J)));
   return t;
 }
+// Row blocks with one number of chunks follow each other, eight at a time (the first of them fewer).  f(number of chunks, first row block, end) for each run,
+// until f returns true.
+template <typename F>
+DASTAC_HD void chunk_runs(int d, F f) {
+  const int blocks = (d + kCubeRowsS - 1) / kCubeRowsS;
+  int nch = (d + 4 * kCubeSub - 1) / (4 * kCubeSub), J = 0;
+  while (J < blocks) {
+    const int end = (d - 4 * kCubeSub * (nch - 1) + kCubeRowsS - 1) / kCubeRowsS;
+    if (f(nch, J, end)) return;
+    J = end, --nch;
+  }
+}
+// Units in all, and f(tile, wn) for unit number `unit`: row block after row block (widest chunks first, so that a launch ends with small units), group, chunk.
+DASTAC_HD int64_t staged_units(int d) {
+  int64_t t = 0;
+  chunk_runs(d, [&](int nch, int J, int end) { return t += (int64_t)nch * (end * (end + 1) / 2 - J * (J + 1) / 2), false; });
+  return t;
+}
+template <typename F>
+DASTAC_HD void staged_unit(int d, int unit, F f) {
+  chunk_runs(d, [&](int nch, int J, int end) {
+    const int all = nch * (end * (end + 1) / 2 - J * (J + 1) / 2);  // row block J has J + 1 groups
+    if (unit >= all) return unit -= all, false;
+    while (unit >= nch * (J + 1)) unit -= nch * (J + 1), ++J;
+    const int nsub = subs_of(d, J), c = unit % nch, more = c < nsub % nch ? 1 : 0;
+    f(CubeTile{kCubeSlices * (unit / nch), kCubeRowsS * J, kCubeRowsS * J + kCubeSub * (c * (nsub / nch) + (more ? c : nsub % nch))}, nsub / nch + more);
+    return true;
+  });
+}
 // The steps of all units (row block, group, chunk, `steps` each) stand on one line, cube_weight(wn) apart; total = staged_weight * steps is cut
 // into `parts` equal parts.  f(tile, wn, s0, s1) for every unit that has steps beginning in part `part`.
 template <typename F>

@@ -16,7 +16,7 @@
 //            products in single;
 //   staged   single precision, where operands are read and split often enough to share: eight wavefronts of 32 x (32..128) elements
 //            on one set of k columns, split once into LDS.
-// Where workgroups share a tile's samples they add into an output cleared by a fill kernel, with floating-point atomics.
+// Where workgroups share a tile's samples they add into an output cleared by a fill kernel, with floating-point atomics; from d = 449 on none do.
 #include "cube_units.h"
 #include "direct_tile.h"
 #include "launch_limits.h"
@@ -31,6 +31,10 @@ constexpr int64_t kMaxD3 = 1 << 13;  // unit counts stay inside 32 bits
 constexpr int64_t kMaxN = (int64_t)1 << 31;
 constexpr int kStep = 16;  // samples per step of a wavefront of the direct kernel
 constexpr int kSub = kCubeSub;
+// From this d on every element has one writer: the direct kernel does not share samples, the staged one takes a workgroup a unit.  (There are then 700 units and
+// more, so that the last ones leave little idle, and the output is neither cleared nor added to: us, shared and owned: N=1000, d=512 342, 328; N=3000 875,
+// 917; N=10000 2640, 2730; N=10000, d=449 2045, 2220; N=1000, d=1024 2415, 2318; d=2000 18000, 16460.)
+constexpr int64_t kOwnedFrom = 449;
 
 // The output's row (i,j), less the 32-bit element number that row_offset() gives it: wave-uniform, so that the 64-bit polynomial is scalar work.
 template <typename T>
@@ -438,11 +442,19 @@ struct Staged {
   __attribute__((aligned(16))) float ji[2][32 * kPitch];  // columns j (16), columns i (16); [column][sample]
 };
 
+// A sum goes to its element: the first of a unit's pieces writes where the unit has one owner, all others add.
+__device__ inline void settle(float *p, float sum, bool add) {
+  if (add)
+    unsafeAtomicAdd(p, sum);
+  else
+    *p = sum;
+}
+
 // A wavefront's tiles of a piece once more, on the fp32 instructions with operands straight from memory, NB column blocks at a time and the
 // next sixteen samples on their way: where operands or results are beyond what the split can hold.  A function of its own: in the middle of the kernel it cost the
 // main loop its registers (N=10000, d=512 2.7 -> 3.1 ms).
 template <int NB>
-__device__ __attribute__((noinline)) void again(int64_t N, int d, const float *B, int64_t ldb, float *out, CubeTile u, int wn, int s0, int s1) {
+__device__ __attribute__((noinline)) void again(int64_t N, int d, const float *B, int64_t ldb, float *out, CubeTile u, int wn, int s0, int s1, bool add) {
   const int lane = threadIdx.x & 63, wave = uniform32(threadIdx.x >> 6), r = lane & 31, h = lane >> 5;
   // (arguments of a function come in vector registers)
   N = uniform64(N), ldb = uniform64(ldb), d = uniform32(d), wn = uniform32(wn), s0 = uniform32(s0), s1 = uniform32(s1);
@@ -503,7 +515,7 @@ __device__ __attribute__((noinline)) void again(int64_t N, int d, const float *B
 #pragma unroll
       for (int n = 0; n < NB; ++n) {
         const int k = u.k0 + 32 * n + r;
-        if (n < wn && j <= k && k < d) unsafeAtomicAdd(p + k, sum[n][v]);
+        if (n < wn && j <= k && k < d) settle(p + k, sum[n][v], add);
       }
     }
   }
@@ -512,7 +524,7 @@ __device__ __attribute__((noinline)) void again(int64_t N, int d, const float *B
 // Steps [s0, s1) of one unit.  False: the wavefront's sums are not all finite, and nothing was added.
 template <int WN>
 __device__ __attribute__((always_inline)) inline bool piece(int64_t N, int d, const float *__restrict__ B, int64_t ldb, float *__restrict__ out,
-                                                            const CubeTile &u, int s0, int s1, Staged &sh) {
+                                                            const CubeTile &u, int s0, int s1, bool add, Staged &sh) {
   const int i0 = u.i0, j0 = u.j0, k0 = u.k0;
   const int tid = threadIdx.x, lane = tid & 63, wave = uniform32(tid >> 6);
   const int r = lane & 31, h = lane >> 5;
@@ -686,35 +698,41 @@ __device__ __attribute__((always_inline)) inline bool piece(int64_t N, int d, co
 #pragma unroll
       for (int n = 0; n < WN; ++n) {
         const int k = k0 + 32 * n + (l & 31);
-        if (j <= k && k < d) unsafeAtomicAdd(p + (k - j), hi[n][v]);
+        if (j <= k && k < d) settle(p + (k - j), hi[n][v], add);
       }
     }
   }
   return true;
 }
 
+// OWNED: a workgroup a unit, all of whose steps are its own.
+template <bool OWNED>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void pr3_staged_kernel(int64_t N, int d, const float *__restrict__ B, int64_t ldb, float *__restrict__ out, int64_t total, int steps, int most) {
   __shared__ Staged sh;
-  staged_part(d, steps, total, blockIdx.x, gridDim.x, [&](const CubeTile &t, int wn, int s0, int s1) __attribute__((always_inline)) {
+  auto work = [&](const CubeTile &t, int wn, int s0, int s1) __attribute__((always_inline)) {
     const CubeTile u = {uniform32(t.i0), uniform32(t.j0), uniform32(t.k0)};
-    for (; s0 < s1; s0 += most) {
+    for (bool add = !OWNED; s0 < s1; s0 += most, add = true) {
       const int a = uniform32(s0), b = uniform32(s1 - s0 < most ? s1 : s0 + most);
       bool done;
       switch (uniform32(wn)) {
-        case 1: done = piece<1>(N, d, B, ldb, out, u, a, b, sh); break;
-        case 2: done = piece<2>(N, d, B, ldb, out, u, a, b, sh); break;
-        case 3: done = piece<3>(N, d, B, ldb, out, u, a, b, sh); break;
-        default: done = piece<4>(N, d, B, ldb, out, u, a, b, sh); break;
+        case 1: done = piece<1>(N, d, B, ldb, out, u, a, b, add, sh); break;
+        case 2: done = piece<2>(N, d, B, ldb, out, u, a, b, add, sh); break;
+        case 3: done = piece<3>(N, d, B, ldb, out, u, a, b, add, sh); break;
+        default: done = piece<4>(N, d, B, ldb, out, u, a, b, add, sh); break;
       }
       if (uniform32(done ? 0 : 1)) {
         if (wn <= 2)
-          again<2>(N, d, B, ldb, out, u, wn, a, b);
+          again<2>(N, d, B, ldb, out, u, wn, a, b, add);
         else
-          again<4>(N, d, B, ldb, out, u, wn, a, b);
+          again<4>(N, d, B, ldb, out, u, wn, a, b, add);
       }
     }
-  });
+  };
+  if constexpr (OWNED)
+    staged_unit(d, blockIdx.x, [&](const CubeTile &t, int wn) __attribute__((always_inline)) { work(t, wn, 0, steps); });
+  else
+    staged_part(d, steps, total, blockIdx.x, gridDim.x, work);
 }
 
 template <typename T>
@@ -794,7 +812,7 @@ int run(int64_t N, int64_t d, const T *B, int64_t ldb, T *out, void *stream) {
   const int64_t units = NT == 1 ? one : direct_units((int)d, NT);
   int64_t split = 1;
   double best = direct_time(N, d, (int)kB, NT, WX, units, 1, cus);
-  for (int64_t s = 2; s <= 64 && s * WX * kStep <= N && units * s < (1 << 20); ++s) {
+  for (int64_t s = 2; d < kOwnedFrom && s <= 64 && s * WX * kStep <= N && units * s < (1 << 20); ++s) {
     const double t = direct_time(N, d, (int)kB, NT, WX, units, s, cus);
     if (t < 0.97 * best) best = t, split = s;
   }
@@ -813,8 +831,12 @@ int run(int64_t N, int64_t d, const T *B, int64_t ldb, T *out, void *stream) {
       // (N=2000, d=256 2.0e-7 in pieces of 2000, 1.4e-7 in pieces of 512; N=10000 2.8e-7 in pieces of 2048, 2.2e-7 of 1250 and 3 % slower).
       const int64_t quarter = ceil_div(steps, 4);
       const int most = (int)(quarter < 16 ? 16 : quarter > 64 ? 64 : quarter);
+      if (d >= kOwnedFrom) {
+        pr3_staged_kernel<true><<<(unsigned)staged_units((int)d), 512, 0, st>>>(N, (int)d, B, ldb, out, 0, (int)steps, most);
+        return launch_status();
+      }
       if (const int rc = clear(d, out, st)) return rc;
-      pr3_staged_kernel<<<(unsigned)cus, 512, 0, st>>>(N, (int)d, B, ldb, out, total, (int)steps, most);
+      pr3_staged_kernel<false><<<(unsigned)cus, 512, 0, st>>>(N, (int)d, B, ldb, out, total, (int)steps, most);
       return launch_status();
     }
     if (NT == 2 && WX == 4) return launch_direct<T, 2, 4>(N, d, B, ldb, out, units, split, st);

@@ -1,5 +1,5 @@
 """How the third-order polynomial-regression tensor is cut into tiles: every element i<=j<=k in exactly one strip of the rows kernel, one
-tile of the direct kernel and, for every step of samples, in exactly one part of the staged one; closed forms of the counts against the sums."""
+tile of the direct kernel, one unit of the staged one and, for every step of samples, in exactly one of its parts; closed forms of the counts against the sums."""
 import os
 import subprocess
 
@@ -46,6 +46,18 @@ int main(int, char **argv) {
       }
     if (!all(seen, 1)) return printf("rows, NS=%d: not a partition\n", NS), 1;
   }
+  {
+    std::vector<int> seen(tet(d), 0);
+    const int64_t units = staged_units(d);
+    bool inside = true;
+    int calls = 0;
+    for (int64_t u = 0; u < units; ++u)
+      staged_unit(d, (int)u, [&](const CubeTile &t, int wn) {
+        inside = inside && t.i0 < d && t.j0 < d && t.k0 < d && 1 <= wn && wn <= 4;
+        cover(seen, d, t, 16, 16, 32 * wn, 1), ++calls;
+      });
+    if (!inside || calls != units || !all(seen, 1)) return printf("staged, units: not a partition\n"), 1;
+  }
   for (int parts : {1, 7, 256}) {
     std::vector<int> seen(tet(d), 0);
     const int64_t total = staged_weight(d) * steps;
@@ -72,6 +84,6 @@ def program(tmp_path_factory):
 
 
 @pytest.mark.parametrize("d,steps", [(1, 1), (3, 2), (7, 5), (8, 1), (9, 3), (15, 2), (16, 7), (17, 1), (25, 4), (31, 3), (32, 5), (33, 1), (40, 9), (63, 2), (64, 1),
-                                     (65, 3), (95, 1), (104, 4), (127, 1), (128, 3), (129, 2), (160, 1), (209, 5)])
+                                     (65, 3), (95, 1), (104, 4), (127, 1), (128, 3), (129, 2), (160, 1), (209, 5), (257, 1)])
 def test_tiles_partition_the_tensor(program, d, steps):
     subprocess.check_output([program, str(d), str(steps)])

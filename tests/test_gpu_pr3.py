@@ -126,3 +126,81 @@ def test_terms_of_few_samples_are_rounded_products(gpu, N, d):
     gpu.d.pr_a3_f32(N, d, gpu.up(B), d, out)
     want = expected(B[N // 2])
     assert (np.abs(gpu.down(out).astype(np.float64) - want) <= 2.0 ** -24 * (1 + 2.0 ** -7) * np.abs(want)).all()
+
+
+WIDE = [(4500, 200, 203), (3001, 257, 257), (1030, 460, 461)]  # staged by more than 15 % of the time that the choice goes by; the last with a workgroup a unit
+
+
+@pytest.mark.parametrize("N,d,ld", WIDE)
+def test_every_part_of_the_split_counts(gpu, N, d, ld):
+    """Operands of one bit and of 24, in one sample: a result with one wide operand is exact, whichever of the three it is; with more, the pair is rounded and
+    the split leaves out up to 2^-22.4 of a product.  Dropping a third part, or the middle parts' product, would cost 2^-17 of it."""
+    b = np.ldexp(1.0, inputs.small_int(3100 + d, -2, 2, d).astype(np.int64)).astype(np.float32)
+    wide = np.arange(d) % 3 == 1
+    b[wide] = (inputs.uniform(3200 + d, d) + 2.0)[wide].astype(np.float32)
+    want = expected(b)
+    k = np.arange(d)
+    wanted = (k[:, None] <= k[None, :])[:, :, None] & (k[None, :, None] <= k[None, None, :])
+    few = (wide.astype(np.int8)[:, None, None] + wide.astype(np.int8)[None, :, None] + wide.astype(np.int8))[wanted] <= 1
+    for x in (0, N // 2, N - 1):
+        B = np.zeros((N, ld), dtype=np.float32)
+        B[x, :d], B[:, d:] = b, np.nan
+        out = gpu.empty(tet(d))
+        gpu.d.pr_a3_f32(N, d, gpu.up(B), ld, out)
+        got = gpu.down(out).astype(np.float64)
+        assert np.array_equal(got[few], want[few])
+        assert (np.abs(got - want) <= 2.0 ** -22.4 * np.abs(want)).all()
+
+
+@pytest.mark.parametrize("N,d,ld", WIDE)
+def test_staged_sums(gpu, N, d, ld):
+    """Slices against products of matrices in double precision.  A term is off by at most 2^-23 (pair) and 2^-22.4 (split), the 16 terms of an instruction are
+    added to a sum of n terms with an error of 2^-23 of it: for terms of either sign, sums of n have size sqrt(n) and 2048 at most run together."""
+    import torch
+    B = gpu.up(inputs.normal(3300 + d, N, ld))
+    out = gpu.empty(tet(d))
+    gpu.d.pr_a3_f32(N, d, B, ld, out)
+    b, run = B[:, :d].double(), min(2048, N)
+    bound = 2.0 ** -23 * (2.6 + 4 / 6 * (run / 16) ** 1.5 * (N / run) ** 0.5 / N ** 0.5 * 4)
+    for i in (0, 1, d // 2, d - 20):
+        want = torch.mm((b * b[:, i:i + 1]).T.contiguous(), b)[i:, i:]
+        want = want[torch.triu(torch.ones_like(want, dtype=torch.bool))]
+        at = tet(d) - tet(d - i)
+        got = out[at:at + len(want)].double()
+        assert float((got - want).norm() / want.norm()) < bound
+
+
+@pytest.mark.parametrize("N,d", [(40, 449), (200, 450), (1030, 460), (2500, 449)])
+def test_one_writer_an_element(gpu, N, d):
+    """From d = 449 on equal calls give equal bits, also where a workgroup adds up its unit in pieces; a value that is not finite in a later piece."""
+    B = inputs.normal(3400 + N, N, d)
+    got = []
+    for _ in range(3):
+        out = gpu.empty(tet(d))
+        gpu.d.pr_a3_f32(N, d, gpu.up(B), d, out)
+        got.append(gpu.down(out))
+    assert got[0].tobytes() == got[1].tobytes() == got[2].tobytes()
+    B[N - 3, d - 2] = np.nan
+    out = gpu.empty(tet(d))
+    gpu.d.pr_a3_f32(N, d, gpu.up(B), d, out)
+    k = np.arange(d)
+    wanted = (k[:, None] <= k[None, :])[:, :, None] & (k[None, :, None] <= k[None, None, :])
+    hit = k == d - 2
+    meets = (hit[:, None, None] | hit[None, :, None] | hit)[wanted]
+    bad = gpu.down(out)
+    assert np.isnan(bad[meets]).all() and np.isfinite(bad[~meets]).all()
+
+
+@pytest.mark.parametrize("N,d", [(15, 20), (60, 40), (1000, 70)])
+@pytest.mark.parametrize("value", [np.nan, np.inf, 1e308])
+def test_one_sample_that_is_not_finite_f64(gpu, oracle, N, d, value):
+    B = inputs.small_int(3500 + N, 1, 2, N, d).astype(np.float64)
+    B[N - 1, d // 2] = value
+    with np.errstate(all="ignore"):
+        want, _ = oracle.pr_a3_f64(B)
+    out = gpu.up(np.full(tet(d), np.nan))
+    gpu.d.pr_a3_f64(N, d, gpu.up(B), d, out)
+    got, want = gpu.down(out).ravel(), want.ravel()
+    assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(np.isposinf(got), np.isposinf(want))
+    ok = np.isfinite(want)
+    assert np.allclose(got[ok], want[ok], rtol=2.0 ** -50, atol=0)
