@@ -109,13 +109,15 @@ int launch(int64_t n, int64_t m, const T *U, const T *B, int64_t ldb, T *C, int6
   return launch_status();
 }
 
-// Sixteen wavefronts shorten a workgroup's chain of windows while few workgroups share a compute unit, as always up to 32 columns in single precision; eight
-// waste less of it otherwise (us, eight and sixteen: fp32 m=8, n=1000 6.4, 6.5; n=2500 13.3, 10.9; n=3000, m=100, 376 workgroups 21.8, 17.5; m=200, 658 25.5, 27.7; n=1000, m=200, 224 8.1, 7.5; m=400, 416 9.8, 10.9; fp64 n=1500, m=64, 188
-// 11.9, 12.3; m=100, 376 15.4, 12.7; m=200, 658 18.5, 21.3).
+// Sixteen wavefronts shorten a workgroup's chain of windows while few workgroups share a compute unit; eight waste less of it otherwise.  Up to 32 columns in
+// single precision the length of the chain decides (us, four, eight and sixteen: n=64, m=8 2.8, 2.9, 3.5; n=200 3.6, 3.9, 4.3; n=400 4.5, 4.5, 4.9;
+// n=1000 7.4, 6.8, 7.0; n=1400 9.2, 8.3, 8.2; n=2500 13.3 with eight, 10.9); else it is (us, eight and sixteen) fp32 n=3000, m=100, 376 workgroups 21.8, 17.5;
+// m=200, 658 25.5, 27.7; n=1000, m=200, 224 8.1, 7.5; m=400, 416 9.8, 10.9; fp64 n=1500, m=64, 188 11.9, 12.3; m=100, 376 15.4, 12.7; m=200, 658 18.5, 21.3.
 template <typename S, typename T = typename S::Type>
 int run(int64_t n, int64_t m, const T *U, const T *B, int64_t ldb, T *C, int64_t ldc, void *stream) {
   const int64_t groups = ceil_div(n, S::kRows) * ceil_div(m, 32);
-  const bool wide = S::kSets > 1 || (S::kSplit ? n >= 500 && groups <= 512 && groups <= n / 4 + 100 : n >= 1000 && groups > 256 && groups <= 512);
+  if (S::kSets > 1 && n <= 200) return launch<S, 4>(n, m, U, B, ldb, C, ldc, (hipStream_t)stream);
+  const bool wide = S::kSets > 1 ? n > 1200 : (S::kSplit ? n >= 500 && groups <= 512 && groups <= n / 4 + 100 : n >= 1000 && groups > 256 && groups <= 512);
   return wide ? launch<S, 16>(n, m, U, B, ldb, C, ldc, (hipStream_t)stream) : launch<S, 8>(n, m, U, B, ldb, C, ldc, (hipStream_t)stream);
 }
 
