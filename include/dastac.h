@@ -165,11 +165,11 @@ int dastac_trmv_f32(int64_t n, const float *Up, const float *x, float *y, void *
 /* y(i) := S(i,j) * x(j), S symmetric with its unique elements S(i,j), i<=j, packed as an upper triangle
  * (Section 3, "Redundancy map": the other half is reached by swapping the two indices).  Every packed
  * element is read once and used twice.  Up[tri_count(n)], x[n], y[n]; n <= 524288 (beyond: DASTAC_EOVERFLOW).
- * Up to n = 4096 (fp64: 2048) every output has one writer and equal calls give equal bits; above, the output is accumulated with
+ * From n = 8 to 4096 (fp64: 2048) every output has one writer and equal calls give equal bits; else the output is accumulated with
  * floating-point atomics, so its last bits may differ between calls. */
 int dastac_symv_f32(int64_t n, const float *Up, const float *x, float *y, void *stream);
 
-/* The other products one packed triangle admits, same limits and same accumulation as symv (fp64: one writer up to n = 3072):
+/* The other products one packed triangle admits, same limits and same accumulation as symv:
  *   trmv_t        y(j) := U(i,j) * x(i), i<=j     the transposed product of the packed upper triangle
  *   trmv_lower    y(i) := L(i,j) * x(j), j<=i     L packed as a LOWER triangle: row i holds columns 0..i, at
  *                                                 tril(n,i,j) = i(i+1)/2 + j (Section 4, worked example, Eq. 2)

@@ -402,9 +402,9 @@ int run(int64_t n, const E *Tp, const E *x, E *y, void *stream) {
   };
   // Eight outputs a workgroup fill one layer of workgroups up to n=2048, sixteen up to 4096 (us, eight and sixteen: n=2300 10.8, 8.4; n=3000
   // 13.7, 10.2).  The panels take over where a second read of the triangle costs more than the launch that clears (us, panels and one launch: fp32
-  // n=2048 9.0, 6.9; n=4000 15.7, 12.8; fp64 symv n=2048 10.4, 8.1; n=2300 11.0, 11.7; trmv_t n=3000 12.4, 11.5; n=3500 14.3, 14.5; trmv_lower
-  // n=3000 10.4, 9.9; n=3500 12.7, 13.1).
-  constexpr int64_t kMostSmall = sizeof(E) == 4 ? 4096 : MODE == MODE_SYM ? 2048 : 3072;
+  // n=2048 9.0, 6.9; n=4000 15.7, 12.8; fp64 symv n=2048 9.2, 7.5; n=2300 11.0, 11.7; trmv_t n=2048 8.0, 6.4; n=2600 9.2, 10.6; trmv_lower n=2048
+  // 6.5, 3.9; n=2600 7.0, 8.5; n=3000 9.3, 9.5).
+  constexpr int64_t kMostSmall = sizeof(E) == 4 ? 4096 : 2048;
   if (n >= 8 && n <= 2048) return small(trimv_small_kernel<E, 8, LOWER, MODE>, 8);
   if (kMostSmall > 2048 && n > 2048 && n <= kMostSmall) return small(trimv_small_kernel<E, 16, LOWER, MODE>, 16);
   return launch<E, 4, LOWER, MODE>(n, Tp, x, y, (hipStream_t)stream);
