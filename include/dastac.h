@@ -228,11 +228,11 @@ int dastac_tet_ttv_f32(int64_t n, const float *Ap, const float *v, float *Mp, vo
 
 /* M(i,r) := A(i,j,k) * B(j,r) * C(k,r), i<=j<=k, 0<=r<R  (Table 1 MTTKRP rule on the upper tetrahedron).
  * B, C are n x R row-major with row strides ldb, ldc >= R; M is n x R with row stride ldm >= R.
- * 1 <= R <= 2^20.  Up to n = 88 (110 with R > 32; fp64 80) every output has one writer.  Above, tiles of 32 columns of the factor
+ * 1 <= R <= 2^20.  Up to n = 88 (100 with 32 < R <= 512, 110 with 32 < R <= 192; fp64 64, 80 with R <= 512) every output has one writer.  Above, tiles of 32 columns of the factor
  * matrices share a launch, in groups where their work-items pass 2^32; each tile reads the packed tetrahedron once.  M is
  * cleared first and the blocks of a slice add their parts with floating-point atomics, so the last bits
  * may differ between calls (integer-valued inputs whose partial sums are exact give identical results).
- * The sum is evaluated factored (A with one factor first, then with the other), above these sizes on blocks padded with zeros, so a non-finite
+ * The sum is evaluated factored (A with B first, then with C), above these sizes on blocks padded with zeros, so a non-finite
  * element of B(j,:) or C(k,:), j,k >= i, makes M(i,r) non-finite as the plain rule does, but possibly NaN
  * where the plain rule gives an infinity. */
 int dastac_tet_mttkrp_f32(int64_t n, int64_t R, const float *Ap, const float *B, int64_t ldb, const float *C,

@@ -500,8 +500,11 @@ int run(int64_t n, int64_t R, const T *Ap, const T *B, int64_t ldb, const T *C, 
     return DASTAC_EALIAS;
   hipStream_t st = (hipStream_t)stream;
   // (us, two launches and one: fp32 R=8, n=48 10.1, 6.4; n=64 10.2, 8.2; n=90 11.5, 10.5; n=110 12.4, 12.6; R=50, n=90 13.0, 10.8; n=110 14.2, 12.8; n=128
-  // 14.8, 15.4; fp64 R=8, n=64 10.2, 8.7; n=90 10.8, 11.4; R=50, n=90 11.3, 11.5)
-  if (n <= (sizeof(T) == 8 ? 80 : R > 32 ? kMostSmall : 88)) {
+  // 14.8, 15.4; fp64 R=8, n=64 10.2, 8.7; n=90 10.8, 11.4; R=50, n=90 11.3, 11.5.  Many columns fill the chip, and from some n on the matrix instructions then do more for
+  // the time: fp32 n=88, R=4096 84, 82; n=110, R=128 16.4, 13.2; R=512 30, 28; R=1024 39, 49; R=16384 563, 688; fp64 n=64, R=16384 191, 181; n=80, R=512 19.8, 13.2;
+  // R=1024 21.8, 24.1; R=4096 67, 79)
+  const bool one_launch = sizeof(T) == 8 ? n <= (R <= 512 ? 80 : 64) : n <= 88 || (n <= kMostSmall && R > 32 && R <= (n <= 100 ? 512 : 192));
+  if (one_launch) {
     mttkrp_small_kernel<T><<<dim3((unsigned)n, (unsigned)ceil_div(R, 64)), 64 * (unsigned)ceil_div(n, 8), 0, st>>>((int)n, (int)R, Ap, B, ldb, C, ldc, M, ldm);
     return launch_status();
   }

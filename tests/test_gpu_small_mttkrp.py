@@ -31,6 +31,13 @@ def test_exact_on_integers(gpu, oracle, n, R, ld, f64):
     assert np.isnan(got[:, R:]).all()
 
 
+@pytest.mark.parametrize("f64", [False, True])
+@pytest.mark.parametrize("n,R", [(64, 513), (65, 512), (65, 513), (80, 512), (80, 513), (88, 600), (100, 512), (100, 513), (101, 192), (101, 193)])
+def test_many_columns(gpu, oracle, n, R, f64):
+    """Both sides of the lines that columns draw between the kernels."""
+    test_exact_on_integers(gpu, oracle, n, R, R, f64)
+
+
 @pytest.mark.parametrize("n,R", [(50, 20), (100, 64)])
 def test_equal_calls_give_equal_bits(gpu, n, R):
     A, B, C = inputs.normal(7200, tet(n)), inputs.normal(7201, n, R), inputs.normal(7202, n, R)
