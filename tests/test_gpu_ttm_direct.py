@@ -30,6 +30,14 @@ def test_exact_on_integers(gpu, oracle, n, Q, K, ldc, f64):
     assert ttm(gpu, n, Q, K, ldc, B, C).tobytes() == want.astype(B.dtype).tobytes()
 
 
+@pytest.mark.parametrize("f64,n,Q,K", [(True, 142, 32, 33), (True, 143, 32, 33), (True, 201, 128, 64), (True, 202, 128, 64), (True, 160, 144, 100), (True, 161, 144, 100),
+                                       (True, 308, 65, 48), (True, 308, 63, 48), (True, 312, 256, 34), (True, 312, 257, 34), (True, 220, 48, 32), (False, 187, 200, 64),
+                                       (False, 188, 200, 64)])
+def test_both_sides_of_the_choice(gpu, oracle, f64, n, Q, K):
+    """By remainder of Q, number of tiles and columns."""
+    test_exact_on_integers(gpu, oracle, n, Q, K, Q, f64)
+
+
 @pytest.mark.parametrize("f64", [False, True])
 @pytest.mark.parametrize("Q", [16, 37, 260])
 @pytest.mark.parametrize("value", [np.nan, np.inf, 3e38])
