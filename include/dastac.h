@@ -142,10 +142,11 @@ int dastac_pack_leslie_f32(int64_t n, const float *dense, int64_t ld, float *R, 
 int dastac_unpack_leslie_f32(int64_t n, const float *R, const float *S, float *dense, int64_t ld, void *stream);
 
 /* ---- contractions: DEVICE, fp32 storage and precision ----------------------------
- * TRMM (with at most 32 columns up to n = 1536, 2048), TTM_UT and A3 split their operands exactly into bf16 parts, at all but
- * the smallest sizes, and accumulate in fp32.  Sums of more than a few terms are then closer to the exact result than
+ * TRMM with more than 32 columns, TTM_UT and A3 split their operands exactly into bf16 parts, at all but
+ * small sizes, and accumulate in fp32.  Sums of more than a few terms are then closer to the exact result than
  * with fp32 products; a single product is within 2^-22.4 of its value (2^-23 outside the largest TRMM calls)
- * against 2^-24.  Operands that the split cannot hold -- Inf, NaN, sums beyond 2^80 -- are evaluated again with
+ * against 2^-24.  (Not split: A3 of fewer than 16 samples, TTM_UT with Q <= 32 and few rows; A3 of up to 64 samples, 128 from d = 256 on,
+ * adds all parts' products, so that a product is within 2^-24.)  Operands that the split cannot hold -- Inf, NaN, sums beyond 2^80 -- are evaluated again with
  * fp32 products; such a call takes up to three times as long as with these alone.
  * Summation order is unspecified (the paper compiles with fast-math, Section 6.1);
  * each output element is within 1e-4 * sum|products| of the exactly rounded result.
@@ -183,8 +184,8 @@ int dastac_symv_lower_f32(int64_t n, const float *Lp, const float *x, float *y, 
 
 /* C(i,c) := U(i,k) * B(k,c), i<=k, 0<=c<m  (the SpMV_UT rule with a matrix right-hand side).
  * B is n x m row-major with row stride ldb >= m, C is n x m with row stride ldc >= m; m >= 1.
- * Only columns 0..m-1 of every row of C are written.  Small products (about n*n*m <= 2e9, fp64 8.5e8) give every element of C one writer.
- * Beyond, where the tiles of C do not fill the
+ * Only columns 0..m-1 of every row of C are written.  Every element of C has one writer where m <= 2048, n*n*m <= 2e9 (fp64 8.5e8) and
+ * n is 64 to 3500 (fp64 with m <= 32: to 2000, with m <= 16: to 1100).  Else, where the tiles of C do not fill the
  * device the reduction range is shared out over several workgroups, which add into a cleared C with
  * floating-point atomics.  From three shares on the last bits may differ between calls (fp32 n=16384, m=256 has
  * four); with two the order of the two addends does not matter, with one (enough columns: n=16384, m=1024) every
@@ -250,8 +251,9 @@ int dastac_ttm_ut_f32(int64_t n, int64_t Q, int64_t K, const float *Bp, const fl
  *   pr_a2   A2(i,j)   := B(x,i) * B(x,j),          i<=j      A2p[tri_count(d)] at tri(d,i,j)
  *   pr_a3   A3(i,j,k) := B(x,i) * B(x,j) * B(x,k), i<=j<=k   A3p[tet_count(d)] at tet(d,i,j,k)
  * B is N x d row-major with row stride ldb >= d.  d == 0 is a no-op; N == 0 writes zeros.  d <= 65536 (a2),
- * d <= 8192 (a3), N <= 2^31.  When the output has few tiles, and in large fp32 a3 calls, the sample range is split over workgroups
- * that add into the zeroed output with floating-point atomics (last bits may then differ between calls). */
+ * d <= 8192 (a3), N <= 2^31.  When the output has few tiles, and in fp32 a3 calls of more than 100 or so
+ * columns, the sample range is split over workgroups that add into the zeroed output with floating-point atomics (last bits may then differ
+ * between calls); a3 with d >= 449 or N < 16 gives every element one writer. */
 int dastac_pr_a2_f32(int64_t N, int64_t d, const float *B, int64_t ldb, float *A2p, void *stream);
 int dastac_pr_a3_f32(int64_t N, int64_t d, const float *B, int64_t ldb, float *A3p, void *stream);
 

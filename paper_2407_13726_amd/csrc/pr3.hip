@@ -425,10 +425,11 @@ void pr3_direct_kernel(int64_t N, int d, const T *__restrict__ B, int64_t ldb, T
 // a tile's rows in one run with the matrix cores idle.
 //
 // The work of all units (row block, columns, slices, samples) is one line in units of cube_weight(WN) per step, cut into equal parts, one
-// workgroup per compute unit; a part may begin and end inside a unit, all parts add into a cleared output.  The weights are fitted: a step
-// of one column block costs more than half of one of four (N=10000, d=256 with weights 16:19:24:29 411-415 us, 13:14:23:33 475, 20:22:25:28 441; WN at most
-// 3, 2: 462, 491).  Bound by the matrix cores at the clock that their power leaves (half of the 1.86 GHz cycles, 0.98 PFLOP/s of bf16; a library product
-// 1.35) -- neither bank conflicts, nor reads from another XCD's L2, nor the split's instruction count show in the time any more.
+// workgroup per compute unit; a part may begin and end inside a unit, all parts add into a cleared output.  (From d = 449 on a workgroup takes
+// a unit, see kOwnedFrom.)  The weights are fitted, at one size: a step of one column block costs more than half of one of four (N=10000, d=256 with
+// weights 16:19:24:29 411-415 us, 13:14:23:33 475, 20:22:25:28 441; WN at most 3, 2: 462, 491).  Bound by the matrix cores at the clock that their power leaves (half of the 1.86 GHz cycles, 0.98 PFLOP/s of bf16; a library product
+// 1.35): a third fewer vector instructions and one range of samples per XCD change nothing (below).  What the bank conflicts (a quarter of the LDS cycles) and the
+// samples' forty passes from the memory-side cache cost has not been taken apart.
 // us here and in the tiles of 64 x 64: N=10000, d=256 411, 687; N=2000, d=256 105, 170; N=20000, d=160 266, 611.
 // Measured and not kept: v_dot2_f32_bf16 for the remainders of the split (a third fewer instructions, the same time; in the other kernels it
 // takes the matrix cores' time); two and four row tiles a wavefront where there are few columns (414 against 411, and 138 against 105 at N=2000); one

@@ -42,6 +42,7 @@ namespace {
 constexpr int kBlock = 256;
 constexpr int kWavesPerBlock = kBlock / 64;
 constexpr int kMaxPanels = 512;
+constexpr int NQ = 4;  // pieces of a row that a lane has in a panel
 constexpr int kMaxN = 524288;  // 512 panels of 1024 columns; such a triangle is far larger than device memory
 
 enum { MODE_ROWS = 0, MODE_COLS = 1, MODE_SYM = 2 };
@@ -104,7 +105,7 @@ DASTAC_HD void panel_rows(int64_t n, int64_t c0, int64_t kW, int64_t &lo, int64_
   }
 }
 
-template <typename E, int NQ, bool LOWER, int MODE>
+template <typename E, bool LOWER, int MODE>
 __global__ __launch_bounds__(kBlock) void trimv_kernel(int n, const E *__restrict__ T,
                                                        const E *__restrict__ x, E *__restrict__ y,
                                                        int R, int npanels, Panels pn) {
@@ -351,7 +352,7 @@ __global__ void zero_kernel(E *__restrict__ y, int64_t n) {
   if (t < n) y[t] = E(0);
 }
 
-template <typename E, int NQ, bool LOWER, int MODE>
+template <typename E, bool LOWER, int MODE>
 int launch(int64_t n, const E *Tp, const E *x, E *y, hipStream_t st) {
   constexpr int kW = 64 * Piece<E>::kPer * NQ;
   const int npanels = (int)ceil_div(n, kW);
@@ -366,7 +367,7 @@ int launch(int64_t n, const E *Tp, const E *x, E *y, hipStream_t st) {
   // the chip idle while the stragglers of a second round run (measured for the symmetric product at
   // n=8192, where three workgroups fit a compute unit: 768 workgroups 34 us, 1024 38 us, 2048 46 us).
   // At least 4 rows per wavefront.  Workgroups of 256 threads: 512 measured 42 us, 1024 67 us.
-  const int64_t slots = resident_blocks(trimv_kernel<E, NQ, LOWER, MODE>, kBlock);
+  const int64_t slots = resident_blocks(trimv_kernel<E, LOWER, MODE>, kBlock);
   if (slots <= 0) return DASTAC_EHIP;
   int64_t R = ceil_div(steps, slots * kWavesPerBlock);
   if (R < 4) R = 4;
@@ -383,7 +384,7 @@ int launch(int64_t n, const E *Tp, const E *x, E *y, hipStream_t st) {
   }
   pn.first[npanels] = blocks;
   zero_kernel<E><<<(unsigned)ceil_div(n, 256), 256, 0, st>>>(y, n);
-  trimv_kernel<E, NQ, LOWER, MODE><<<(unsigned)blocks, kBlock, 0, st>>>((int)n, Tp, x, y, (int)R, npanels, pn);
+  trimv_kernel<E, LOWER, MODE><<<(unsigned)blocks, kBlock, 0, st>>>((int)n, Tp, x, y, (int)R, npanels, pn);
   return launch_status();
 }
 
@@ -407,7 +408,7 @@ int run(int64_t n, const E *Tp, const E *x, E *y, void *stream) {
   constexpr int64_t kMostSmall = sizeof(E) == 4 ? 4096 : 2048;
   if (n >= 8 && n <= 2048) return small(trimv_small_kernel<E, 8, LOWER, MODE>, 8);
   if (kMostSmall > 2048 && n > 2048 && n <= kMostSmall) return small(trimv_small_kernel<E, 16, LOWER, MODE>, 16);
-  return launch<E, 4, LOWER, MODE>(n, Tp, x, y, (hipStream_t)stream);
+  return launch<E, LOWER, MODE>(n, Tp, x, y, (hipStream_t)stream);
 }
 
 }  // namespace
