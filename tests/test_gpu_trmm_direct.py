@@ -1,4 +1,4 @@
-"""Triangular products in one launch: edges of its row blocks (32, 16), windows (16), column blocks (32) and of the choice between 8 and 16
+"""Triangular products in one launch: edges of its row blocks (32, 16), windows (16), column blocks (32) and of the choice between 4, 8 and 16
 wavefronts and the tiles of the large products; small integers bit for bit, row strides, equal bits on equal calls, values that are not finite."""
 import numpy as np
 import pytest
@@ -87,3 +87,19 @@ def test_few_columns_have_the_products_of_the_type(gpu, n, m):
         rows = i[i <= k[c]]
         assert np.array_equal(got[rows, c], U[rows * n - rows * (rows - 1) // 2 + k[c] - rows] * B[k[c], c])
         assert not got[k[c] + 1:, c].any()
+
+
+@pytest.mark.parametrize("f64,n,m", [(False, 64, 2048), (False, 976, 2048), (False, 3500, 163), (False, 3500, 8), (True, 64, 2048), (True, 644, 2048), (True, 3500, 69), (True, 2000, 32),
+                                     (True, 1100, 16)])
+def test_one_writer_up_to_the_edges_of_the_choice(gpu, f64, n, m):
+    uniform = inputs.uniform64 if f64 else inputs.uniform
+    U, B = uniform(6500 + n, n * (n + 1) // 2), uniform(6600 + n, n * m).reshape(n, m)
+    got = [product(gpu, n, m, m, U, B).tobytes() for _ in range(3)]
+    assert got[0] == got[1] == got[2]
+
+
+@pytest.mark.parametrize("n", [199, 200, 201, 1200, 1201])
+@pytest.mark.parametrize("m", [1, 31, 32])
+def test_wavefronts_by_rows(gpu, oracle, n, m):
+    """Up to 32 columns in single precision: four, eight or sixteen wavefronts."""
+    test_exact_on_integers(gpu, oracle, n, m, m, False)
