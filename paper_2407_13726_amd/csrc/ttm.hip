@@ -476,7 +476,7 @@ int uhc_copy(int64_t n, int64_t Q, const T *src, T *dst, void *stream) {
 // In double precision the tiles here are 128 columns wide, so 32 columns or fewer go there with any number of rows (n=500, Q=434, K=16 310, 149; n=700, Q=32,
 // K=32 50, 47).  With two column blocks the line depends on the remainder of Q by 16, for which these kernels take a whole step and the direct one
 // moves a window back (us: n=150, 1416 tiles, K=33, Q=32 5.9, 6.7; Q=40 7.5, 6.0; n=200, 2514 tiles, K=64, Q=64 14.3, 15.2; Q=128 24.4, 22.9; Q=100 21.7, 13.9; n=240, 3616 tiles, K=33,
-// Q=128 24.1, 30.0; Q=100 21.4, 18.1; n=300, K=48, 5644 tiles, Q=48 17.6, 23.6; Q=100 34, 25; Q=1000 0.77 of the time; n=700, Q=32 51, 86; Q=100 152, 120; Q=434, K=33 589, 694).
+// Q=128 24.1, 30.0; Q=100 21.4, 18.1; n=300, K=48, 5644 tiles, Q=48 17.6, 23.6; Q=24 12.7, 13.0; Q=100 34, 25; Q=1000 0.77 of the time; n=257, 4146 tiles, K=46, Q=24 12.4, 10.8; n=700, Q=32 51, 86; Q=100 152, 120; Q=434, K=33 589, 694).
 template <typename T>
 bool direct_serves(int64_t rows, int64_t Q, int64_t K) {
   const int64_t tiles = ceil_div(rows, sizeof(T) == 4 ? 32 : 16) * ceil_div(K, 32);
@@ -485,7 +485,7 @@ bool direct_serves(int64_t rows, int64_t Q, int64_t K) {
   if (K <= 32) return true;
   if (Q % 16 == 0) return tiles <= (Q < 128 ? 1280 : K <= 64 ? 2560 : 2048);
   if (K <= 48 && Q >= 64 && Q <= (tiles <= 6000 ? 1024 : 256)) return true;
-  return tiles <= (K <= 64 ? 4096 : 2048);
+  return tiles <= (K <= 48 ? 4700 : K <= 64 ? 4096 : 2048);
 }
 
 // The split's offsets within a row block are 32 bits and a piece needs four l; beyond that the fp32 matrix cores take over, and
