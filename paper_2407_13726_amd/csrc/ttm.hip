@@ -470,7 +470,7 @@ int uhc_copy(int64_t n, int64_t Q, const T *src, T *dst, void *stream) {
 
 // Few rows run straight from memory with l cut among wavefronts (ttm_direct.hip).  A workgroup of the kernels here takes a time that grows with Q, the
 // direct tiles together one that grows with their number times Q, so the line is a number of direct tiles (us, here and there, fp32: 1068 tiles
-// n=130, Q=250, K=100 14.4, 12.5; 1280 n=90, Q=400, K=300 20.4, 17.0; 1258 n=200, K=33, Q=100 8.8, 6.8; Q=256 12.9, 13.7; 2122 n=260, Q=K=60 9.5, 9.0; 2550 n=180,
+// n=130, Q=250, K=100 14.4, 12.5; 1280 n=90, Q=400, K=300 20.4, 17.0; 1144 n=270, K=18, Q=228 13.9, 10.4; 1146 n=191, K=34, Q=410 19.0, 17.2; 1258 n=200, K=33, Q=100 8.8, 6.8; Q=256 12.9, 13.7; 2122 n=260, Q=K=60 9.5, 9.0; 2550 n=180,
 // Q=200, K=150 15.8, 20.6).  Q and K above 2^20 stay here.
 //
 // In double precision the tiles here are 128 columns wide, so 32 columns or fewer go there with any number of rows (n=500, Q=434, K=16 310, 149; n=700, Q=32,
@@ -481,7 +481,7 @@ template <typename T>
 bool direct_serves(int64_t rows, int64_t Q, int64_t K) {
   const int64_t tiles = ceil_div(rows, sizeof(T) == 4 ? 32 : 16) * ceil_div(K, 32);
   if (Q < 16 || Q > (1 << 20) || K > (1 << 20) || rows > (1 << 24)) return false;
-  if (sizeof(T) == 4) return tiles <= (Q < 200 ? 1280 : 1100);
+  if (sizeof(T) == 4) return tiles <= 1280;
   if (K <= 32) return true;
   if (Q % 16 == 0) return tiles <= (Q < 128 ? 1280 : K <= 64 ? 2560 : 2048);
   if (K <= 48 && Q >= 64 && Q <= (tiles <= 6000 ? 1024 : 256)) return true;

@@ -31,8 +31,8 @@ def test_exact_on_integers(gpu, oracle, n, Q, K, ldc, f64):
 
 
 @pytest.mark.parametrize("f64,n,Q,K", [(True, 142, 32, 33), (True, 143, 32, 33), (True, 201, 128, 64), (True, 202, 128, 64), (True, 160, 144, 100), (True, 161, 144, 100),
-                                       (True, 308, 65, 48), (True, 308, 63, 48), (True, 312, 256, 34), (True, 312, 257, 34), (True, 220, 48, 32), (False, 187, 200, 64),
-                                       (False, 188, 200, 64)])
+                                       (True, 308, 65, 48), (True, 308, 63, 48), (True, 312, 256, 34), (True, 312, 257, 34), (True, 220, 48, 32), (False, 201, 200, 64),
+                                       (False, 202, 200, 64)])
 def test_both_sides_of_the_choice(gpu, oracle, f64, n, Q, K):
     """By remainder of Q, number of tiles and columns."""
     test_exact_on_integers(gpu, oracle, n, Q, K, Q, f64)
