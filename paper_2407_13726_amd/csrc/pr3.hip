@@ -54,8 +54,9 @@ __device__ inline unsigned near_slice(int d, int i0, int t, int j, int k) {
 }
 
 // ---- rows --------------------------------------------------------------------------------------------------------
-// A wavefront owns two slices i, sixteen rows j and 64 columns k, a workgroup those rows: two contiguous runs of the output.  Rows of the matrix instruction are
-// columns k, its columns the rows j with their products B(x,i) B(x,j), so that a lane ends up with four consecutive elements and writes them at once.
+// A wavefront owns two slices i (one in double precision), sixteen rows j and 64 columns k, a workgroup those rows: one contiguous run of the output a slice.  Rows of
+// the matrix instruction are columns k, its columns the rows j with their products B(x,i) B(x,j), so that a lane ends up with four consecutive elements (two
+// and two) and writes them at once.
 // Four samples an instruction, all requested at once; nothing is staged, split or shared.  Bound by the writes (N=1, d=1024 fp32 186-220 us for 718 MB, fp64 368 for
 // 1436) and, below d=300, by the latency of one load and a launch.  us, columns a lane on vector instructions and here: fp32 N=8, d=64 5.2, 3.5; d=256 18,
 // 7.8; N=15, d=512 104, 24; fp64 N=8, d=64 5.8, 2.9; N=15, d=256 33, 10; d=512 168, 43; d=1024 757, 371.  In double precision two slices of 32 columns, with runs
@@ -444,7 +445,8 @@ void pr3_direct_kernel(int64_t N, int d, const T *__restrict__ B, int64_t ldb, T
 // The work of all units (row block, columns, slices, samples) is one line in units of cube_weight(WN) per step, cut into equal parts, one
 // workgroup per compute unit; a part may begin and end inside a unit, all parts add into a cleared output.  (From d = 449 on a workgroup takes
 // a unit, see kOwnedFrom.)  The weights are fitted, at one size: a step of one column block costs more than half of one of four (N=10000, d=256 with
-// weights 16:19:24:29 411-415 us, 13:14:23:33 475, 20:22:25:28 441; WN at most 3, 2: 462, 491).  Bound by the matrix cores at the clock that their power leaves (half of the 1.86 GHz cycles, 0.98 PFLOP/s of bf16; a library product
+// weights 16:19:24:29 411-415 us, 13:14:23:33 475, 20:22:25:28 441; WN at most 3, 2: 462, 491).  Bound by the matrix cores at the clock that their power leaves
+// (half of the 1.86 GHz cycles, 0.98 PFLOP/s of bf16; a library product
 // 1.35): a third fewer vector instructions and one range of samples per XCD change nothing (below).  What the bank conflicts (a quarter of the LDS cycles) and the
 // samples' forty passes from the memory-side cache cost has not been taken apart.
 // us here and in the tiles of 64 x 64: N=10000, d=256 411, 687; N=2000, d=256 105, 170; N=20000, d=160 266, 611.

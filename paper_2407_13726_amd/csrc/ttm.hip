@@ -470,13 +470,15 @@ int uhc_copy(int64_t n, int64_t Q, const T *src, T *dst, void *stream) {
 
 // Few rows run straight from memory with l cut among wavefronts (ttm_direct.hip).  A workgroup of the kernels here takes a time that grows with Q, the
 // direct tiles together one that grows with their number times Q, so the line is a number of direct tiles (us, here and there, fp32: 1068 tiles
-// n=130, Q=250, K=100 14.4, 12.5; 1280 n=90, Q=400, K=300 20.4, 17.0; 1144 n=270, K=18, Q=228 13.9, 10.4; 1146 n=191, K=34, Q=410 19.0, 17.2; 1258 n=200, K=33, Q=100 8.8, 6.8; Q=256 12.9, 13.7; 2122 n=260, Q=K=60 9.5, 9.0; 2550 n=180,
+// n=130, Q=250, K=100 14.4, 12.5; 1280 n=90, Q=400, K=300 20.4, 17.0; 1144 n=270, K=18, Q=228 13.9, 10.4; 1146 n=191, K=34, Q=410 19.0, 17.2; 1258 n=200, K=33,
+// Q=100 8.8, 6.8; Q=256 12.9, 13.7; 2122 n=260, Q=K=60 9.5, 9.0; 2550 n=180,
 // Q=200, K=150 15.8, 20.6).  Q and K above 2^20 stay here.
 //
 // In double precision the tiles here are 128 columns wide, so 32 columns or fewer go there with any number of rows (n=500, Q=434, K=16 310, 149; n=700, Q=32,
 // K=32 50, 47).  With two column blocks the line depends on the remainder of Q by 16, for which these kernels take a whole step and the direct one
 // moves a window back (us: n=150, 1416 tiles, K=33, Q=32 5.9, 6.7; Q=40 7.5, 6.0; n=200, 2514 tiles, K=64, Q=64 14.3, 15.2; Q=128 24.4, 22.9; Q=100 21.7, 13.9; n=240, 3616 tiles, K=33,
-// Q=128 24.1, 30.0; Q=100 21.4, 18.1; n=300, K=48, 5644 tiles, Q=48 17.6, 23.6; Q=24 12.7, 13.0; Q=100 34, 25; Q=1000 0.77 of the time; n=257, 4146 tiles, K=46, Q=24 12.4, 10.8; n=700, Q=32 51, 86; Q=100 152, 120; Q=434, K=33 589, 694).
+// Q=128 24.1, 30.0; Q=100 21.4, 18.1; n=300, K=48, 5644 tiles, Q=48 17.6, 23.6; Q=24 12.7, 13.0; Q=100 34, 25; Q=1000 0.77 of the time; n=257, 4146 tiles, K=46,
+// Q=24 12.4, 10.8; n=700, Q=32 51, 86; Q=100 152, 120; Q=434, K=33 589, 694).
 template <typename T>
 bool direct_serves(int64_t rows, int64_t Q, int64_t K) {
   const int64_t tiles = ceil_div(rows, sizeof(T) == 4 ? 32 : 16) * ceil_div(K, 32);
