@@ -63,6 +63,36 @@ def test_elements_that_are_not_finite_reach_their_slice_only(gpu, n, R):
             assert np.array_equal(got[keep], whole[keep]) and not np.isfinite(got[i]).any()
 
 
+def element(n, i, j, k):
+    """Place of A(i,j,k)."""
+    m, a = n - i, j - i
+    return tet(n) - tet(m) + a * m - a * (a - 1) // 2 + k - j
+
+
+# n: one block wider than the rows, two and three blocks, the last of them 1 to 74 wide (fp32 of 128, fp64 of 64), and whole ones
+@pytest.mark.parametrize("dtype,n,R", [("f32", 111, 20), ("f32", 129, 8), ("f32", 200, 33), ("f32", 256, 20), ("f32", 330, 64), ("f32", 460, 20),
+                                       ("f64", 100, 20), ("f64", 128, 20), ("f64", 129, 8), ("f64", 200, 33), ("f64", 330, 64)])
+@pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan, "largest"])
+def test_elements_that_are_not_finite_arrive_as_they_are(gpu, dtype, n, R, bad):
+    """One infinite element in a slice and positive factors: the slice's sums are that infinity, wherever the element stands in its block; two infinities of one sign
+    likewise.  The largest number, doubled by B, is an infinity from there on."""
+    t, block = (np.float32, 128) if dtype == "f32" else (np.float64, 64)
+    A, B, C = (inputs.small_int(7500 + s, 2, 3, *shape).astype(t) for s, shape in enumerate(((tet(n),), (n, R), (n, R))))
+    whole = call(gpu, A, B, C, n, R, R)
+    value = np.finfo(t).max if bad == "largest" else bad
+    want = np.inf if bad == "largest" else bad
+    w = n % block if n % block else block  # columns of the block in the top left corner
+    spoilt, slices = A.copy(), set()
+    for i, j, k in ((0, 0, min(w, n - 1)), (1, 1, min(w + 2, n - 1)), (2, w - 1 if w > 2 else 2, min(w + 20, n - 1)), (w - 1 if w > 3 else 3, w - 1 if w > 3 else 3, min(w + 5, n - 1)),
+                    (n // 2, n // 2, n // 2), (n // 2 + 1, n // 2 + 3, n - 2), (n - 4, n - 3, n - 1), (n - 2, n - 2, n - 1), (n - 1, n - 1, n - 1)):
+        spoilt[element(n, i, j, k)] = value
+        slices.add(i)
+    spoilt[element(n, 0, 0, n - 1)] = value
+    got = call(gpu, spoilt, B, C, n, R, R)
+    for i in range(n):
+        assert np.array_equal(got[i], np.full(R, want, t) if i in slices else whole[i], equal_nan=True), i
+
+
 @pytest.mark.parametrize("n,R", [(111, 20), (200, 33), (330, 64)])
 @pytest.mark.parametrize("a,b,c", [(1e35, 1e-30, 1e3), (1e-30, 1e35, 1e3), (1e3, 1e3, 1e25), (3e-38, 1e20, 1e15), (1e20, 3e-38, 1e17), (1e15, 1e15, 1e-36)])
 def test_magnitudes(gpu, n, R, a, b, c):
