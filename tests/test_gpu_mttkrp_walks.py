@@ -107,3 +107,41 @@ def test_magnitudes(gpu, n, R, a, b, c):
         U[np.triu_indices(m)] = A[at:at + m * (m + 1) // 2]
         want = np.einsum("jr,jr->r", U @ C[i:].astype(np.float64), B[i:].astype(np.float64))
         assert np.allclose(got[i], want, rtol=3.1e-5, atol=0)
+
+
+def significands(seed, *shape):
+    """24-bit significands in [1, 2), every seventh the one whose second and third part are the largest."""
+    x = (1 + inputs.small_int(seed, 0, 2 ** 23 - 1, *shape).astype(np.float64) / 2.0 ** 23).astype(np.float32)
+    x.ravel()[::7] = np.float32(1 + 2.0 ** -8 - 2.0 ** -17)
+    return x
+
+
+@pytest.mark.parametrize("n,R", [(89, 30), (111, 40), (200, 33), (330, 64), (460, 32)])
+def test_single_products(gpu, n, R):
+    """One element a slice and C of ones, so every output is one product of A and B.  The partial products that are left out reach 2^-24 of it and the cuts of the
+    accumulator 2^-23 and a little: 1.5 2^-23 in all (a third part left out would be 2^-17).  Three in the slice of order 2, one in the last: each product rounded once,
+    and two additions."""
+    A, B, C = np.zeros(tet(n), np.float32), significands(7601, n, R), np.ones((n, R), np.float32)
+    values, at = significands(7602, n), np.random.RandomState(n)
+    want = np.zeros((n, R))
+    for i in range(n - 2):
+        j = at.randint(i, n)
+        A[element(n, i, j, at.randint(j, n))] = values[i]
+        want[i] = values[i].astype(np.float64) * B[j]
+    A[-4:] = values[:4]
+    want[n - 2] = values[:2].astype(np.float64).sum() * B[n - 2] + values[2].astype(np.float64) * B[n - 1]
+    want[n - 1] = values[3].astype(np.float64) * B[n - 1]
+    off = np.abs(call(gpu, A, B, C, n, R, R).astype(np.float64) - want) / want
+    assert off[:n - 2].max() <= 1.5 * 2.0 ** -23 * (1 + 2.0 ** -6)
+    assert off[n - 2].max() <= 3 * 2.0 ** -24 * (1 + 2.0 ** -6) and off[n - 1].max() <= 2.0 ** -24
+
+
+@pytest.mark.parametrize("n,R", [(130, 20), (333, 50), (640, 32)])
+def test_sums_of_one_sign(gpu, oracle, n, R):
+    """Positive numbers of 24 bits, where the accumulator's cuts have one sign.  A block's sum takes eight steps; each cuts off between nothing and one unit of a sum that
+    grows to its last value: a quarter of eight units on average, of 0.72 2^-23 of the value on average (measured 0.4 to 0.6 2^-23 in all)."""
+    A, B, C = significands(7611, tet(n)), significands(7612, n, R), significands(7613, n, R)
+    got = call(gpu, A, B, C, n, R, R)
+    for lo, hi in ((0, 3), (n // 2, n // 2 + 3), (n - 40, n)):
+        want = oracle.tet_mttkrp_f64(n, R, A, B, C, rows=(lo, hi))[0][lo:hi]
+        assert np.linalg.norm(got[lo:hi] - want) <= 8 / 4 * 0.72 * 2.0 ** -23 * np.linalg.norm(want), lo
