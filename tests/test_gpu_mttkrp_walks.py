@@ -109,6 +109,29 @@ def test_magnitudes(gpu, n, R, a, b, c):
         assert np.allclose(got[i], want, rtol=3.1e-5, atol=0)
 
 
+@pytest.mark.parametrize("n,R", [(130, 33), (460, 20), (640, 40)])
+@pytest.mark.parametrize("pattern", ["all", "third", "pairs", "half", "last"])
+def test_slices_that_are_evaluated_again(gpu, n, R, pattern):
+    """Slices that the split cannot hold, alone, in pairs and one after the other, among others, with several to a wavefront's walk.  An infinity, and numbers of 2^104
+    whose sums are exact: in A, and in all of B, which then has no parts either."""
+    of = {"all": lambda i: True, "third": lambda i: i % 3 == 1, "pairs": lambda i: i % 5 < 2, "half": lambda i: i > n // 2, "last": lambda i: i == n - 4}[pattern]
+    A, B, C = (inputs.small_int(7700 + s, 1, 2, *shape).astype(np.float32) for s, shape in enumerate(((tet(n),), (n, R), (n, R))))
+    whole = call(gpu, A, B, C, n, R, R)
+    again = np.array([of(i) for i in range(n)])
+    at = np.random.RandomState(n)
+    infinite, large, up = A.copy(), A.copy(), np.float32(2.0 ** 104)
+    for i in np.flatnonzero(again):
+        j = at.randint(i, n)
+        infinite[element(n, i, j, at.randint(j, n))] = np.inf
+        large[element(n, i, i, i):element(n, i, n - 1, n - 1) + 1] *= up
+    got = call(gpu, infinite, B, C, n, R, R)
+    assert np.array_equal(got[~again], whole[~again]) and (got[again] == np.inf).all()
+    got = call(gpu, large, B, C, n, R, R)
+    assert np.array_equal(got[~again], whole[~again]) and np.array_equal(got[again], whole[again] * up)
+    if pattern == "all":
+        assert np.array_equal(call(gpu, A, B * up, C, n, R, R), whole * up)
+
+
 def significands(seed, *shape):
     """24-bit significands in [1, 2), every seventh the one whose second and third part are the largest."""
     x = (1 + inputs.small_int(seed, 0, 2 ** 23 - 1, *shape).astype(np.float64) / 2.0 ** 23).astype(np.float32)
