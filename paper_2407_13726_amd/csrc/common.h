@@ -96,9 +96,15 @@ int trmm_direct(int64_t n, int64_t m, const double *Up, const double *B, int64_t
 // defined in ttm_direct.hip: Ap[p, k] = sum over l of Bp[p, l] C[k, l], 16 <= Q, rows, Q and K < 2^24 (arguments already validated)
 int ttm_direct(int64_t rows, int64_t Q, int64_t K, const float *Bp, const float *C, int64_t ldc, float *Ap, void *stream);
 int ttm_direct(int64_t rows, int64_t Q, int64_t K, const double *Bp, const double *C, int64_t ldc, double *Ap, void *stream);
-// defined in mttkrp_walk.hip: 128 (fp64 64) <= n (arguments already validated)
+// defined in mttkrp_walk.hip: 3 <= n (arguments already validated)
 int mttkrp_by_walks(int64_t n, int64_t R, const float *Ap, const float *B, int64_t ldb, const float *C, int64_t ldc, float *M, int64_t ldm, void *stream);
 int mttkrp_by_walks(int64_t n, int64_t R, const double *Ap, const double *B, int64_t ldb, const double *C, int64_t ldc, double *M, int64_t ldm, void *stream);
+// (and how its work is cut in double precision: tiles of 16 columns a workgroup, and steps a wavefront)
+struct WalkCut {
+  int tiles;
+  double steps;
+};
+WalkCut mttkrp_walk_cut_f64(int64_t n, int64_t R, int64_t cus);
 // defined in trmm_columns.hip: C := U B with m a multiple of 128 (arguments already validated)
 // (and the part of its last layer of workgroups that has work)
 double trmm_columns_fill(int64_t n, int64_t m, int64_t cus);

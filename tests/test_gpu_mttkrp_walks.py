@@ -18,9 +18,11 @@ def call(gpu, A, B, C, n, R, ld):
 
 
 @pytest.mark.parametrize("dtype,n,R,pad", [
-    ("f32", 73, 513, 0), ("f32", 81, 193, 0), ("f32", 88, 193, 0), ("f32", 89, 600, 0), ("f32", 104, 33, 0), ("f32", 105, 3, 0), ("f32", 111, 40, 1), ("f32", 126, 32, 0), ("f32", 127, 65, 0), ("f32", 128, 32, 0), ("f32", 129, 64, 3),
+    ("f32", 88, 32, 0), ("f32", 88, 600, 0), ("f32", 89, 32, 0), ("f32", 89, 512, 0), ("f32", 89, 600, 0), ("f32", 100, 512, 0), ("f32", 100, 513, 0), ("f32", 101, 192, 0), ("f32", 101, 193, 0), ("f32", 104, 33, 0), ("f32", 110, 192, 0), ("f32", 110, 193, 0), ("f32", 110, 32, 0), ("f32", 105, 3, 0), ("f32", 111, 40, 1), ("f32", 126, 32, 0), ("f32", 127, 65, 0), ("f32", 128, 32, 0), ("f32", 129, 64, 3),
     ("f32", 255, 20, 0), ("f32", 257, 97, 0), ("f32", 300, 64, 0), ("f32", 301, 64, 1), ("f32", 301, 65, 0), ("f32", 385, 33, 0), ("f32", 400, 130, 2), ("f32", 641, 7, 0),
     ("f64", 65, 600, 0), ("f64", 76, 513, 0), ("f64", 77, 5, 0), ("f64", 81, 16, 0), ("f64", 90, 311, 0), ("f64", 90, 312, 0), ("f64", 127, 17, 3), ("f64", 179, 50, 0), ("f64", 180, 32, 0), ("f64", 180, 33, 0),
+    ("f64", 66, 1100, 0), ("f64", 81, 500, 0), ("f64", 81, 700, 0), ("f64", 175, 129, 0), ("f64", 179, 128, 0), ("f64", 224, 160, 0), ("f64", 236, 160, 0), ("f64", 236, 96, 0), ("f64", 320, 24, 1),
+    ("f64", 333, 17, 0), ("f64", 333, 16, 0), ("f64", 360, 32, 0), ("f64", 364, 32, 0), ("f64", 780, 1, 0), ("f64", 781, 1, 0),
     ("f64", 193, 48, 1), ("f64", 224, 65, 0), ("f64", 225, 65, 0), ("f64", 230, 96, 0), ("f64", 230, 97, 0), ("f64", 269, 65, 0), ("f64", 270, 64, 0), ("f64", 270, 65, 0), ("f64", 300, 40, 0), ("f64", 310, 32, 0), ("f64", 311, 32, 0), ("f64", 420, 20, 0)])
 def test_exact_on_integers(gpu, oracle, dtype, n, R, pad):
     t, ref = (np.float32, oracle.tet_mttkrp) if dtype == "f32" else (np.float64, oracle.tet_mttkrp_f64)
