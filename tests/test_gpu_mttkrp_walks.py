@@ -37,6 +37,19 @@ def test_exact_on_integers(gpu, oracle, dtype, n, R, pad):
         assert np.array_equal(got[lo:hi, :R], want[lo:hi]), (lo, hi)
 
 
+@pytest.mark.parametrize("n,R", [(1149, 9), (1150, 9), (1290, 33), (1290, 4)])
+def test_two_and_four_blocks_at_a_time(gpu, n, R):
+    """Large tensors of small integers, single precision against double precision's other kernels: the sums are exact in both."""
+    torch = gpu.torch
+    gen = torch.Generator(device=gpu.dev)
+    gen.manual_seed(n + R)
+    A, B, C = (torch.randint(-2, 3, shape, generator=gen, device=gpu.dev, dtype=torch.float32) for shape in ((tet(n),), (n, R), (n, R)))
+    got, want = gpu.empty(n, R), torch.full((n, R), float("nan"), dtype=torch.float64, device=gpu.dev)
+    gpu.d.tet_mttkrp_f32(n, R, A, B, R, C, R, got, R)
+    gpu.d.tet_mttkrp_f64(n, R, A.double(), B.double(), R, C.double(), R, want, R)
+    assert torch.equal(got.double(), want) and float(want.abs().max()) > 0
+
+
 @pytest.mark.parametrize("dtype,n", [("f32", 111), ("f32", 128), ("f32", 200), ("f32", 330), ("f64", 100), ("f64", 200), ("f64", 330)])
 def test_factor_rows_of_smaller_index_do_not_reach_a_slice(gpu, dtype, n):
     t = np.float32 if dtype == "f32" else np.float64

@@ -78,7 +78,10 @@ def check(tmp_path_factory):
 @pytest.mark.parametrize("kB,n,run,groups,wgs", [
     (128, 3, 4, 1, 8), (128, 89, 4, 2, 16), (128, 127, 4, 1, 80), (128, 128, 4, 1, 80), (128, 129, 4, 3, 256), (128, 256, 4, 1, 256), (128, 257, 2, 2, 256),
     (128, 300, 4, 1, 40), (128, 400, 2, 2, 256), (128, 513, 4, 1, 256), (128, 700, 2, 1, 304), (64, 65, 4, 5, 40), (64, 127, 4, 1, 104), (64, 128, 4, 2, 256),
-    (64, 180, 2, 3, 256), (64, 193, 4, 1, 8), (64, 333, 2, 1, 256), (64, 450, 4, 1, 256)])
+    (64, 180, 2, 3, 256), (64, 193, 4, 1, 8), (64, 333, 2, 1, 256), (64, 450, 4, 1, 256),
+    # what the kernels launch: one block at a time but for one tile of single precision, two from n=450 on, four from n=1150 on
+    (128, 111, 1, 1, 72), (128, 129, 1, 3, 112), (128, 333, 1, 1, 256), (128, 449, 1, 2, 256), (128, 450, 2, 1, 256), (128, 640, 1, 2, 256), (128, 1149, 2, 1, 256), (128, 1150, 4, 1, 256),
+    (64, 65, 1, 33, 256), (64, 81, 1, 6, 80), (64, 128, 1, 3, 256), (64, 179, 1, 4, 256), (64, 229, 1, 3, 256), (64, 333, 1, 1, 256), (64, 450, 1, 1, 240), (64, 700, 1, 2, 256)])
 def test_every_step_has_one_wavefront(check, kB, n, run, groups, wgs):
     longest, steps = check(kB, n, run, groups, wgs)
     if steps > 8 * wgs * 4:  # no wavefront has much more than its share
