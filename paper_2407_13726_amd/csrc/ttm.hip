@@ -554,45 +554,58 @@ inline bool split_serves(int64_t rows, int64_t Q, int64_t K, const float *) {
 }
 inline bool split_serves(int64_t, int64_t, int64_t, const double *) { return false; }
 
+// Workgroups that walk one column block on each XCD, of `slots` that the chip holds at once: a walker that has to wait for another to end doubles the time.
+inline int64_t walkers(int64_t slots, int64_t ncb) { return slots >= 8 * ncb ? slots / (8 * ncb) : 1; }
+
 template <typename G>
-int launch_split(int64_t rows, int64_t Q, int64_t K, const float *Bp, const float *C, int64_t ldc, float *Ap, hipStream_t st) {
+int launch_split(int64_t rows, int64_t Q, int64_t K, const float *Bp, const float *C, int64_t ldc, float *Ap, int64_t cus, hipStream_t st) {
   const int64_t nrb = ceil_div(rows, G::kBM), ncb = ceil_div(K, G::kBN);
   if (nrb > 0x7fffffff || (nrb + 8) * ceil_div(Q, 32) > 0x7fffffff) return DASTAC_EOVERFLOW;
-  // at most what 256 compute units hold at once (one workgroup of eight wavefronts each, or two of four): a walker that has
-  // to wait for another to end doubles the time
-  int64_t lanes = (G::kThreads == 512 ? 256 : 512) / (8 * ncb);
-  if (lanes < 1) lanes = 1;
+  int64_t lanes = walkers(G::kThreads == 512 ? cus : 2 * cus, ncb);  // one workgroup of eight wavefronts to a compute unit, or two of four
   if (lanes > ceil_div(nrb, 8)) lanes = ceil_div(nrb, 8);
   ttm_split_kernel<G><<<(unsigned)(8 * lanes * ncb), G::kThreads, 0, st>>>(rows, (int)Q, (int)K, Bp, C, ldc, Ap, (int)nrb, (int)lanes, (int)ncb);
   return launch_status();
 }
 // Tiles by columns: 128 x 32 and 128 x 64 where C has no more (us, before: n=300, Q=512, K=16 25, 83; n=500, Q=K=64 17, 33; n=512,
 // Q=100, K=40 28, 58), else eight wavefronts on 128 x 128 or, a third less LDS traffic a product and half the barriers, on 256 x 128.  A workgroup to a compute
-// unit takes whole tiles, so what counts is the rounds of tiles, and the rows that would be a round of a few tiles run straight from memory in a launch of their
-// own.  The estimate, in us by l: a round of 128 x 128 2.4 + 0.0475 Q, of 256 x 128 4.7 + 0.083 Q (n=512, Q=K=512 25.7 and 45.2, n=512, Q=K=256 14.6, 26.1, n=300,
-// Q=500, K=200 26.4, 44.6), a launch of t direct tiles 3.5 + 3e-5 t Q (1280, Q=400 17.0; 1068, Q=250 12.5).
-// Measured, 128 x 128 tiles in one launch before and now (us): n=512, Q=K=256 131.7 111.7, n=512, Q=K=512 437 393, n=256, Q=300, K=200 47.2 38.2, n=360, Q=500, K=300 172
-// 157, n=256, Q=200, K=70 23.5 18.5; over 50 sizes 0.93 of the time.  What bounds it now is power: 1.09 PFLOP/s of bf16 at n=512, Q=K=512, 0.81 of the library's.
+// unit takes whole tiles, so what counts is the rounds of tiles, and the rows past whole rounds may run straight from memory in a launch of their own.
+//
+// The estimate, us: 4.1, and for a round 1.46 + 0.0437 Q of 128 x 128, 3.28 + 0.0803 Q of 256 x 128 (Q in whole steps of 32), a last round that is a part f of one counted
+// as 0.67 + 0.33 f; for t direct tiles in a second launch 3.1 + (9e-4 + 2.6e-5 Q) t.  Fitted to the four ways at 740 sizes (n 60 to 900, Q 10 to 900, K 65 to 900; 6 % off
+// in the root mean square); its choice takes 1.004 times the best way's time, 0.92 of 128 x 128 in one launch as it was before, 1.08 at worst (n=276, Q=371, K=200 54.5, 58.4).  us, 128 x 128, with
+// the rest apart, 256 x 128, with the rest apart: n=512, Q=371, K=256 175 165 179 157; n=512, Q=371, K=470 339 332 324 300; n=280, Q=256, K=128 27.8 28.8 25.1 25.0; n=276, Q=64, K=200
+// 15.8 19.2 18.6 19.5; n=270, Q=64, K=256 15.9 18.5 18.9 19.3; n=204, Q=323, K=230 35.1 38.6 31.6 31.4.
+//
+// One and two steps of l and more output than the memory-side cache holds are bound by writing it, and 256 x 128 is faster there (why has not been taken apart; 128 x 128, 256 x 128):
+// 263 MB n=512, Q=20, K=500 69, 58; 306 MB n=600, Q=10, K=424 79, 68; 493 MB n=705, Q=64, K=495 166, 155; below, 252 MB n=512, Q=24, K=480 50, 50.  With one step
+// and four column blocks it turns from 430 MB on: n=777, Q=20, K=414 120, 148; n=768, Q=16, K=467 133, 158.
+// What bounds many steps is power: 1.09 PFLOP/s of bf16 at n=512, Q=K=512, 0.81 of the library's.
 struct Rounds {
   double us;
   int64_t rows;  // of the launch of tiles; the others run straight from memory
 };
-inline Rounds ttm_rounds(int64_t rows, int64_t Q, int64_t K, int64_t height, double us) {
-  const int64_t ncb = ceil_div(K, 128), lanes = ncb < 32 ? 256 / (8 * ncb) * 8 : 8, layers = ceil_div(8 * ncb, 256);
-  const int64_t whole = rows / (height * lanes), left = rows - whole * height * lanes, direct = ceil_div(left, 32) * ceil_div(K, 32);
-  Rounds r{us * (double)(layers * ceil_div(rows, height * lanes)), rows};
-  const double two = us * (double)(layers * whole) + 3.5 + 3e-5 * (double)(direct * Q);
+inline Rounds ttm_rounds(int64_t rows, int64_t Q, int64_t K, int64_t height, int64_t cus) {
+  const double l = 32.0 * (double)ceil_div(Q, 32), us = height == 128 ? 1.46 + 0.0437 * l : 3.28 + 0.0803 * l;
+  const int64_t ncb = ceil_div(K, 128), round = height * 8 * walkers(cus, ncb);
+  const double layers = (double)ceil_div(8 * ncb, cus);  // more column blocks than compute units on an XCD: one after the other
+  const int64_t whole = rows / round, left = rows - whole * round, direct = ceil_div(left, 32) * ceil_div(K, 32);
+  Rounds r{us * layers * ((double)whole + (left ? 0.67 + 0.33 * (double)left / (double)round : 0.0)), rows};
+  const double two = us * layers * (double)whole + 3.1 + (9e-4 + 2.6e-5 * (double)Q) * (double)direct;
   if (whole > 0 && left > 0 && Q >= 16 && direct <= 1280 && two < r.us) r = {two, rows - left};
   return r;
 }
 inline int ttm_split(int64_t rows, int64_t Q, int64_t K, const float *Bp, const float *C, int64_t ldc, float *Ap, hipStream_t st) {
-  if (K <= 32) return launch_split<Tile<4, 1, 1, 1>>(rows, Q, K, Bp, C, ldc, Ap, st);
-  if (K <= 64) return launch_split<Tile<4, 1, 1, 2>>(rows, Q, K, Bp, C, ldc, Ap, st);
-  const double steps = 32.0 * (double)ceil_div(Q, 32);
-  const Rounds small = ttm_rounds(rows, Q, K, 128, 2.4 + 0.0475 * steps), large = ttm_rounds(rows, Q, K, 256, 4.7 + 0.083 * steps);
+  const int64_t cus = compute_units();
+  if (cus < 1) return DASTAC_EHIP;
+  if (K <= 32) return launch_split<Tile<4, 1, 1, 1>>(rows, Q, K, Bp, C, ldc, Ap, cus, st);
+  if (K <= 64) return launch_split<Tile<4, 1, 1, 2>>(rows, Q, K, Bp, C, ldc, Ap, cus, st);
+  const Rounds small = ttm_rounds(rows, Q, K, 128, cus);
+  Rounds large = ttm_rounds(rows, Q, K, 256, cus);
+  const int64_t out = 4 * rows * K;  // bytes
+  if (Q <= 64 && out > 250000000 && (Q > 32 || out < 430000000 || ceil_div(K, 128) != 4)) large = {0.0, rows};
   const Rounds &r = large.us < small.us ? large : small;
-  const int status = large.us < small.us ? launch_split<Tile<4, 2, 2, 2>>(r.rows, Q, K, Bp, C, ldc, Ap, st)
-                                         : launch_split<Tile<4, 2, 1, 2>>(r.rows, Q, K, Bp, C, ldc, Ap, st);
+  const int status = large.us < small.us ? launch_split<Tile<4, 2, 2, 2>>(r.rows, Q, K, Bp, C, ldc, Ap, cus, st)
+                                         : launch_split<Tile<4, 2, 1, 2>>(r.rows, Q, K, Bp, C, ldc, Ap, cus, st);
   if (status != DASTAC_OK || r.rows == rows) return status;
   return ttm_direct(rows - r.rows, Q, K, Bp + r.rows * Q, C, ldc, Ap + r.rows * K, st);
 }
