@@ -26,12 +26,13 @@ __global__ __launch_bounds__(256) void mttkrp_clear_kernel(Index n, Index R, con
   }
 }
 template <typename T>
-inline void mttkrp_clear(int64_t n, int64_t R, const T *A, const T *B, int64_t ldb, const T *C, int64_t ldc, T *M, int64_t ldm, hipStream_t st) {
+inline int mttkrp_clear(int64_t n, int64_t R, const T *A, const T *B, int64_t ldb, const T *C, int64_t ldc, T *M, int64_t ldm, hipStream_t st) {
   const int64_t cb = ceil_div(n * R, 256);
   if (n * R < ((int64_t)1 << 24))  // (a division of 64 bits is 0.3 us of a launch)
     mttkrp_clear_kernel<T, unsigned><<<(unsigned)cb, 256, 0, st>>>((unsigned)n, (unsigned)R, A + tet(n), B, ldb, C, ldc, M, ldm);
   else
     mttkrp_clear_kernel<T, int64_t><<<(unsigned)(cb < (1 << 23) ? cb : 1 << 23), 256, 0, st>>>(n, R, A + tet(n), B, ldb, C, ldc, M, ldm);
+  return launch_status();
 }
 
 }  // namespace dastac
