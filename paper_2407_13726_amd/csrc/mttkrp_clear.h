@@ -17,10 +17,14 @@ __global__ __launch_bounds__(256) void mttkrp_clear_kernel(Index n, Index R, con
     T s = T(0);
     if (n - i < kMinOrder) {  // (all reads at once)
       const T *b = Bm + ((int64_t)i * ldb + r), *c = Cm + ((int64_t)i * ldc + r);
-      if (n - i == 1)
-        s = end_of_A[-1] * b[0] * c[0];
-      else
-        s = end_of_A[-4] * b[0] * c[0] + end_of_A[-3] * b[0] * c[ldc] + end_of_A[-2] * b[ldb] * c[ldc];
+      // (added to zero: a product that is -0 leaves +0, as in every other sum)
+      if (n - i == 1) {
+        s += end_of_A[-1] * b[0] * c[0];
+      } else {
+        s += end_of_A[-4] * b[0] * c[0];
+        s += end_of_A[-3] * b[0] * c[ldc];
+        s += end_of_A[-2] * b[ldb] * c[ldc];
+      }
     }
     M[(int64_t)i * ldm + r] = s;
   }
