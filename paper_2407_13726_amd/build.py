@@ -11,7 +11,9 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libdastac_hip.so")
-CALLS = os.path.join(HERE, "_calls.so")  # the binding's native calls, host code
+# The binding's native calls: host code for this interpreter and no other, hence its tag in the name.  Without the interpreter's headers
+# the binding goes through ctypes.
+CALLS = os.path.join(HERE, "_calls" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 # Packed-fp32 VALU forms are switched off for the device pass (the host pass warns that it does
 # not know the feature; harmless).
@@ -36,8 +38,14 @@ def build(jobs: int = 8) -> str:
     with ThreadPoolExecutor(max_workers=jobs) as ex:
         objs = list(ex.map(_compile, sources()))
     subprocess.check_call(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs])
-    subprocess.check_call(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", "-Wno-missing-field-initializers",
-                           "-I", sysconfig.get_paths()["include"], os.path.join(CSRC, "calls.cpp"), "-o", CALLS])
+    for old in glob.glob(os.path.join(HERE, "_calls*.so")):
+        os.remove(old)
+    include = sysconfig.get_paths()["include"]
+    if os.path.exists(os.path.join(include, "Python.h")):
+        subprocess.check_call(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", "-Wno-missing-field-initializers",
+                               "-I", include, os.path.join(CSRC, "calls.cpp"), "-o", CALLS])
+    else:
+        print("no Python.h in %s: calls go through ctypes" % include)
     return LIB
 
 

@@ -1,6 +1,6 @@
 // The binding's calls without ctypes: one object per entry point of the C library that checks a call's arguments, asks torch for the addresses and
-// the current stream, and calls.  It serves the ordinary call -- exact Python integers, torch tensors of the entry's type on a HIP device or None, no stream given -- and
-// leaves every other one, and every complaint, to the Python code in dastac.py.
+// the current stream, or takes the given one's handle, and calls.  It serves the ordinary call -- Python's or numpy's integers, torch tensors of the entry's type on a HIP device or
+// None -- and leaves every other one, and every complaint, to the Python code in dastac.py.
 //
 // Why: a small product takes the GPU 3 to 4 us; the host took 4.1 to 4.5 through ctypes and takes 3.3 to 3.6 here, of which the launch itself is two (band_spmv n=8192
 // 4.3 -> 3.6 us a call, ttm_ut n=30 4.5 -> 3.7, pack and unpack of n=512 9.1 -> 7.7).
@@ -23,7 +23,7 @@ struct Entry {
 };
 
 PyObject *tensor_type, *dtypes[2], *raw_stream, *get_device, *declined;
-PyObject *name_is_cuda, *name_dtype, *name_data_ptr;
+PyObject *name_is_cuda, *name_dtype, *name_data_ptr, *name_cuda_stream;
 
 // The answer for a call that the Python code has to make: -1.
 PyObject *decline() {
@@ -51,6 +51,21 @@ bool address_of(PyObject *t, PyObject *dtype, int64_t &out) {
   return !PyErr_Occurred();
 }
 
+// A Python integer or what numpy has for one.
+bool integer_of(PyObject *v, int64_t &out) {
+  int over = 0;
+  if (PyLong_CheckExact(v)) {
+    out = PyLong_AsLongLongAndOverflow(v, &over);
+    return !over;
+  }
+  if (PyLong_Check(v) || !PyIndex_Check(v)) return false;
+  PyObject *whole = PyNumber_Index(v);
+  if (!whole) return false;
+  out = PyLong_AsLongLongAndOverflow(whole, &over);
+  Py_DECREF(whole);
+  return !over && !PyErr_Occurred();
+}
+
 // arguments 0.. of the C function, whose parameters are all 64-bit integers or pointers
 int invoke(void *f, int n, const int64_t *a) {
   typedef int64_t I;
@@ -69,25 +84,31 @@ int invoke(void *f, int n, const int64_t *a) {
 
 PyObject *entry_call(PyObject *self, PyObject *const *args, size_t nargsf, PyObject *kwnames) {
   const Entry *e = (const Entry *)self;
-  if (!e->address || kwnames || PyVectorcall_NARGS(nargsf) != e->count + 1 || args[e->count] != Py_None) return decline();
+  if (!e->address || kwnames || PyVectorcall_NARGS(nargsf) != e->count + 1) return decline();
   int64_t a[kMostArgs + 1];
   bool tensors = false;  // (with one, torch has a device)
   for (int k = 0; k < e->count; ++k) {
     if (e->kind[k] == 'i') {
-      if (!PyLong_CheckExact(args[k])) return decline();
-      int over = 0;
-      a[k] = PyLong_AsLongLongAndOverflow(args[k], &over);
-      if (over) return decline();
+      if (!integer_of(args[k], a[k])) return decline();
     } else {
       if (!address_of(args[k], dtypes[e->kind[k] == 'd'], a[k])) return decline();
       tensors |= args[k] != Py_None;
     }
   }
   if (!tensors) return decline();
-  PyObject *device = PyObject_CallNoArgs(get_device);
-  PyObject *stream = device ? PyObject_CallOneArg(raw_stream, device) : NULL;
-  Py_XDECREF(device);
+  PyObject *stream;
+  if (args[e->count] == Py_None) {
+    PyObject *device = PyObject_CallNoArgs(get_device);
+    stream = device ? PyObject_CallOneArg(raw_stream, device) : NULL;
+    Py_XDECREF(device);
+  } else {
+    stream = PyObject_GetAttr(args[e->count], name_cuda_stream);
+  }
   if (!stream) return decline();
+  if (!PyLong_CheckExact(stream)) {
+    Py_DECREF(stream);
+    return decline();
+  }
   a[e->count] = (int64_t)PyLong_AsUnsignedLongLong(stream);
   Py_DECREF(stream);
   if (PyErr_Occurred()) return decline();
@@ -150,6 +171,7 @@ PyMODINIT_FUNC PyInit__calls(void) {
   name_is_cuda = PyUnicode_InternFromString("is_cuda");
   name_dtype = PyUnicode_InternFromString("dtype");
   name_data_ptr = PyUnicode_InternFromString("data_ptr");
-  if (!declined || !name_is_cuda || !name_dtype || !name_data_ptr) return NULL;
+  name_cuda_stream = PyUnicode_InternFromString("cuda_stream");
+  if (!declined || !name_is_cuda || !name_dtype || !name_data_ptr || !name_cuda_stream) return NULL;
   return PyModule_Create(&module);
 }

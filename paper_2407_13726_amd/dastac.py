@@ -133,7 +133,7 @@ def lib() -> ctypes.CDLL:
 
 # ---- calls without ctypes ----------------------------------------------------
 # The functions below try an entry of the native module first.  It makes the ordinary call itself (csrc/calls.cpp says
-# which) and returns its status; for any other call, and for the first, it returns -1, and the call goes through ctypes.
+# which) and returns its status; for any other call, and for the first, it returns -1, and _settle makes it through ctypes.
 try:
     from . import _calls
 except ImportError:  # not built: everything goes through ctypes
@@ -141,10 +141,16 @@ except ImportError:  # not built: everything goes through ctypes
 _entries = {}
 
 
-def _entry(name, kinds):
+def _kinds(name):
+    """One letter for each argument before the stream: i, an integer; f or d, a float32 or float64 tensor."""
+    real = "d" if name.endswith("f64") else "f"
+    return "".join("i" if kind is _i64 else real for kind in SIGNATURES["dastac_" + name][1][:-1])
+
+
+def _entry(name):
     if _calls is None:
         return lambda *args: -1
-    _entries[name] = _calls.entry(kinds)
+    _entries[name] = _calls.entry(_kinds(name))
     return _entries[name]
 
 
@@ -173,6 +179,19 @@ def strerror(status: int) -> str:
 def _check(status: int, where: str) -> None:
     if status != OK:
         raise DastacError(status, where)
+
+
+_ctypes_calls = {}  # name -> the C function, and how each argument before the stream is handed to it (None: as it is)
+
+
+def _settle(status, name, *args):
+    """The outcome of a call whose entry did not return OK: an error, or a call that the entry left, made through ctypes."""
+    if status < 0:
+        if name not in _ctypes_calls:
+            _ctypes_calls[name] = getattr(lib(), "dastac_" + name), [{"i": None, "f": _ptr, "d": _ptr64}[k] for k in _kinds(name)]
+        call, hand = _ctypes_calls[name]
+        status = call(*[a if h is None else h(a) for h, a in zip(hand, args)], _stream(args[-1]))
+    _check(status, name)
 
 
 def _ptr(t):
@@ -249,684 +268,617 @@ def tet_inverse(n, p):
 
 # ---- device operations -----------------------------------------------------------
 
-_call_pack_triu_f32 = _entry("pack_triu_f32", "ifif")
+_pack_triu_f32 = _entry("pack_triu_f32")
 
 
 def pack_triu_f32(n, dense, ld, packed, stream=None):
-    status = _call_pack_triu_f32(n, dense, ld, packed, stream)
+    status = _pack_triu_f32(n, dense, ld, packed, stream)
     if status:
-        _check(lib().dastac_pack_triu_f32(n, _ptr(dense), ld, _ptr(packed), _stream(stream))
-               if status < 0 else status, "pack_triu_f32")
+        _settle(status, "pack_triu_f32", n, dense, ld, packed, stream)
 
 
-_call_unpack_triu_f32 = _entry("unpack_triu_f32", "iffi")
+_unpack_triu_f32 = _entry("unpack_triu_f32")
 
 
 def unpack_triu_f32(n, packed, dense, ld, stream=None):
-    status = _call_unpack_triu_f32(n, packed, dense, ld, stream)
+    status = _unpack_triu_f32(n, packed, dense, ld, stream)
     if status:
-        _check(lib().dastac_unpack_triu_f32(n, _ptr(packed), _ptr(dense), ld, _stream(stream))
-               if status < 0 else status, "unpack_triu_f32")
+        _settle(status, "unpack_triu_f32", n, packed, dense, ld, stream)
 
 
-_call_pack_tet_f32 = _entry("pack_tet_f32", "iff")
+_pack_tet_f32 = _entry("pack_tet_f32")
 
 
 def pack_tet_f32(n, dense, packed, stream=None):
-    status = _call_pack_tet_f32(n, dense, packed, stream)
+    status = _pack_tet_f32(n, dense, packed, stream)
     if status:
-        _check(lib().dastac_pack_tet_f32(n, _ptr(dense), _ptr(packed), _stream(stream))
-               if status < 0 else status, "pack_tet_f32")
+        _settle(status, "pack_tet_f32", n, dense, packed, stream)
 
 
-_call_unpack_tet_f32 = _entry("unpack_tet_f32", "iff")
+_unpack_tet_f32 = _entry("unpack_tet_f32")
 
 
 def unpack_tet_f32(n, packed, dense, stream=None):
-    status = _call_unpack_tet_f32(n, packed, dense, stream)
+    status = _unpack_tet_f32(n, packed, dense, stream)
     if status:
-        _check(lib().dastac_unpack_tet_f32(n, _ptr(packed), _ptr(dense), _stream(stream))
-               if status < 0 else status, "unpack_tet_f32")
+        _settle(status, "unpack_tet_f32", n, packed, dense, stream)
 
 
-_call_pack_band_f32 = _entry("pack_band_f32", "iifif")
+_pack_band_f32 = _entry("pack_band_f32")
 
 
 def pack_band_f32(n, w, dense, ld, diag_major, stream=None):
-    status = _call_pack_band_f32(n, w, dense, ld, diag_major, stream)
+    status = _pack_band_f32(n, w, dense, ld, diag_major, stream)
     if status:
-        _check(lib().dastac_pack_band_f32(n, w, _ptr(dense), ld, _ptr(diag_major), _stream(stream))
-               if status < 0 else status, "pack_band_f32")
+        _settle(status, "pack_band_f32", n, w, dense, ld, diag_major, stream)
 
 
-_call_unpack_band_f32 = _entry("unpack_band_f32", "iiffi")
+_unpack_band_f32 = _entry("unpack_band_f32")
 
 
 def unpack_band_f32(n, w, diag_major, dense, ld, stream=None):
-    status = _call_unpack_band_f32(n, w, diag_major, dense, ld, stream)
+    status = _unpack_band_f32(n, w, diag_major, dense, ld, stream)
     if status:
-        _check(lib().dastac_unpack_band_f32(n, w, _ptr(diag_major), _ptr(dense), ld, _stream(stream))
-               if status < 0 else status, "unpack_band_f32")
+        _settle(status, "unpack_band_f32", n, w, diag_major, dense, ld, stream)
 
 
-_call_trmv_f32 = _entry("trmv_f32", "ifff")
+_trmv_f32 = _entry("trmv_f32")
 
 
 def trmv_f32(n, Up, x, y, stream=None):
-    status = _call_trmv_f32(n, Up, x, y, stream)
+    status = _trmv_f32(n, Up, x, y, stream)
     if status:
-        _check(lib().dastac_trmv_f32(n, _ptr(Up), _ptr(x), _ptr(y), _stream(stream))
-               if status < 0 else status, "trmv_f32")
+        _settle(status, "trmv_f32", n, Up, x, y, stream)
 
 
-_call_trmm_f32 = _entry("trmm_f32", "iiffifi")
+_trmm_f32 = _entry("trmm_f32")
 
 
 def trmm_f32(n, m, Up, B, ldb, C, ldc, stream=None):
-    status = _call_trmm_f32(n, m, Up, B, ldb, C, ldc, stream)
+    status = _trmm_f32(n, m, Up, B, ldb, C, ldc, stream)
     if status:
-        _check(lib().dastac_trmm_f32(n, m, _ptr(Up), _ptr(B), ldb, _ptr(C), ldc, _stream(stream))
-               if status < 0 else status, "trmm_f32")
+        _settle(status, "trmm_f32", n, m, Up, B, ldb, C, ldc, stream)
 
 
-_call_band_spmv_f32 = _entry("band_spmv_f32", "iifff")
+_band_spmv_f32 = _entry("band_spmv_f32")
 
 
 def band_spmv_f32(n, w, D, x, y, stream=None):
-    status = _call_band_spmv_f32(n, w, D, x, y, stream)
+    status = _band_spmv_f32(n, w, D, x, y, stream)
     if status:
-        _check(lib().dastac_band_spmv_f32(n, w, _ptr(D), _ptr(x), _ptr(y), _stream(stream))
-               if status < 0 else status, "band_spmv_f32")
+        _settle(status, "band_spmv_f32", n, w, D, x, y, stream)
 
 
-_call_tet_ttv_f32 = _entry("tet_ttv_f32", "ifff")
+_tet_ttv_f32 = _entry("tet_ttv_f32")
 
 
 def tet_ttv_f32(n, Ap, v, Mp, stream=None):
-    status = _call_tet_ttv_f32(n, Ap, v, Mp, stream)
+    status = _tet_ttv_f32(n, Ap, v, Mp, stream)
     if status:
-        _check(lib().dastac_tet_ttv_f32(n, _ptr(Ap), _ptr(v), _ptr(Mp), _stream(stream))
-               if status < 0 else status, "tet_ttv_f32")
+        _settle(status, "tet_ttv_f32", n, Ap, v, Mp, stream)
 
 
-_call_tet_mttkrp_f32 = _entry("tet_mttkrp_f32", "iiffififi")
+_tet_mttkrp_f32 = _entry("tet_mttkrp_f32")
 
 
 def tet_mttkrp_f32(n, R, Ap, B, ldb, C, ldc, M, ldm, stream=None):
-    status = _call_tet_mttkrp_f32(n, R, Ap, B, ldb, C, ldc, M, ldm, stream)
+    status = _tet_mttkrp_f32(n, R, Ap, B, ldb, C, ldc, M, ldm, stream)
     if status:
-        _check(lib().dastac_tet_mttkrp_f32(n, R, _ptr(Ap), _ptr(B), ldb, _ptr(C), ldc, _ptr(M), ldm, _stream(stream))
-               if status < 0 else status, "tet_mttkrp_f32")
+        _settle(status, "tet_mttkrp_f32", n, R, Ap, B, ldb, C, ldc, M, ldm, stream)
 
 
 def uhc_count(n, Q): return int(lib().dastac_uhc_count(n, Q))
 def uhc_offset(n, Q, i, j, l): return int(lib().dastac_uhc_offset(n, Q, i, j, l))
 
 
-_call_pack_uhc_f32 = _entry("pack_uhc_f32", "iiff")
+_pack_uhc_f32 = _entry("pack_uhc_f32")
 
 
 def pack_uhc_f32(n, Q, dense, packed, stream=None):
-    status = _call_pack_uhc_f32(n, Q, dense, packed, stream)
+    status = _pack_uhc_f32(n, Q, dense, packed, stream)
     if status:
-        _check(lib().dastac_pack_uhc_f32(n, Q, _ptr(dense), _ptr(packed), _stream(stream))
-               if status < 0 else status, "pack_uhc_f32")
+        _settle(status, "pack_uhc_f32", n, Q, dense, packed, stream)
 
 
-_call_unpack_uhc_f32 = _entry("unpack_uhc_f32", "iiff")
+_unpack_uhc_f32 = _entry("unpack_uhc_f32")
 
 
 def unpack_uhc_f32(n, Q, packed, dense, stream=None):
-    status = _call_unpack_uhc_f32(n, Q, packed, dense, stream)
+    status = _unpack_uhc_f32(n, Q, packed, dense, stream)
     if status:
-        _check(lib().dastac_unpack_uhc_f32(n, Q, _ptr(packed), _ptr(dense), _stream(stream))
-               if status < 0 else status, "unpack_uhc_f32")
+        _settle(status, "unpack_uhc_f32", n, Q, packed, dense, stream)
 
 
-_call_ttm_ut_f32 = _entry("ttm_ut_f32", "iiiffif")
+_ttm_ut_f32 = _entry("ttm_ut_f32")
 
 
 def ttm_ut_f32(n, Q, K, Bp, C, ldc, Ap, stream=None):
-    status = _call_ttm_ut_f32(n, Q, K, Bp, C, ldc, Ap, stream)
+    status = _ttm_ut_f32(n, Q, K, Bp, C, ldc, Ap, stream)
     if status:
-        _check(lib().dastac_ttm_ut_f32(n, Q, K, _ptr(Bp), _ptr(C), ldc, _ptr(Ap), _stream(stream))
-               if status < 0 else status, "ttm_ut_f32")
+        _settle(status, "ttm_ut_f32", n, Q, K, Bp, C, ldc, Ap, stream)
 
 
-_call_symv_f32 = _entry("symv_f32", "ifff")
+_symv_f32 = _entry("symv_f32")
 
 
 def symv_f32(n, Up, x, y, stream=None):
-    status = _call_symv_f32(n, Up, x, y, stream)
+    status = _symv_f32(n, Up, x, y, stream)
     if status:
-        _check(lib().dastac_symv_f32(n, _ptr(Up), _ptr(x), _ptr(y), _stream(stream))
-               if status < 0 else status, "symv_f32")
+        _settle(status, "symv_f32", n, Up, x, y, stream)
 
 
-_call_trmv_t_f32 = _entry("trmv_t_f32", "ifff")
+_trmv_t_f32 = _entry("trmv_t_f32")
 
 
 def trmv_t_f32(n, Up, x, y, stream=None):
-    status = _call_trmv_t_f32(n, Up, x, y, stream)
+    status = _trmv_t_f32(n, Up, x, y, stream)
     if status:
-        _check(lib().dastac_trmv_t_f32(n, _ptr(Up), _ptr(x), _ptr(y), _stream(stream))
-               if status < 0 else status, "trmv_t_f32")
+        _settle(status, "trmv_t_f32", n, Up, x, y, stream)
 
 
-_call_trmv_lower_f32 = _entry("trmv_lower_f32", "ifff")
+_trmv_lower_f32 = _entry("trmv_lower_f32")
 
 
 def trmv_lower_f32(n, Lp, x, y, stream=None):
-    status = _call_trmv_lower_f32(n, Lp, x, y, stream)
+    status = _trmv_lower_f32(n, Lp, x, y, stream)
     if status:
-        _check(lib().dastac_trmv_lower_f32(n, _ptr(Lp), _ptr(x), _ptr(y), _stream(stream))
-               if status < 0 else status, "trmv_lower_f32")
+        _settle(status, "trmv_lower_f32", n, Lp, x, y, stream)
 
 
-_call_trmv_lower_t_f32 = _entry("trmv_lower_t_f32", "ifff")
+_trmv_lower_t_f32 = _entry("trmv_lower_t_f32")
 
 
 def trmv_lower_t_f32(n, Lp, x, y, stream=None):
-    status = _call_trmv_lower_t_f32(n, Lp, x, y, stream)
+    status = _trmv_lower_t_f32(n, Lp, x, y, stream)
     if status:
-        _check(lib().dastac_trmv_lower_t_f32(n, _ptr(Lp), _ptr(x), _ptr(y), _stream(stream))
-               if status < 0 else status, "trmv_lower_t_f32")
+        _settle(status, "trmv_lower_t_f32", n, Lp, x, y, stream)
 
 
-_call_symv_lower_f32 = _entry("symv_lower_f32", "ifff")
+_symv_lower_f32 = _entry("symv_lower_f32")
 
 
 def symv_lower_f32(n, Lp, x, y, stream=None):
-    status = _call_symv_lower_f32(n, Lp, x, y, stream)
+    status = _symv_lower_f32(n, Lp, x, y, stream)
     if status:
-        _check(lib().dastac_symv_lower_f32(n, _ptr(Lp), _ptr(x), _ptr(y), _stream(stream))
-               if status < 0 else status, "symv_lower_f32")
+        _settle(status, "symv_lower_f32", n, Lp, x, y, stream)
 
 
 def tril_offset(n, i, j): return int(lib().dastac_tril_offset(n, i, j))
 
 
-_call_pack_tril_f32 = _entry("pack_tril_f32", "ifif")
+_pack_tril_f32 = _entry("pack_tril_f32")
 
 
 def pack_tril_f32(n, dense, ld, packed, stream=None):
-    status = _call_pack_tril_f32(n, dense, ld, packed, stream)
+    status = _pack_tril_f32(n, dense, ld, packed, stream)
     if status:
-        _check(lib().dastac_pack_tril_f32(n, _ptr(dense), ld, _ptr(packed), _stream(stream))
-               if status < 0 else status, "pack_tril_f32")
+        _settle(status, "pack_tril_f32", n, dense, ld, packed, stream)
 
 
-_call_unpack_tril_f32 = _entry("unpack_tril_f32", "iffi")
+_unpack_tril_f32 = _entry("unpack_tril_f32")
 
 
 def unpack_tril_f32(n, packed, dense, ld, stream=None):
-    status = _call_unpack_tril_f32(n, packed, dense, ld, stream)
+    status = _unpack_tril_f32(n, packed, dense, ld, stream)
     if status:
-        _check(lib().dastac_unpack_tril_f32(n, _ptr(packed), _ptr(dense), ld, _stream(stream))
-               if status < 0 else status, "unpack_tril_f32")
+        _settle(status, "unpack_tril_f32", n, packed, dense, ld, stream)
 
 
 
 def subtri_offset(N, k, i, j): return int(lib().dastac_subtri_offset(N, k, i, j))
 
 
-_call_pack_sband_f32 = _entry("pack_sband_f32", "iiifif")
+_pack_sband_f32 = _entry("pack_sband_f32")
 
 
 def pack_sband_f32(n, w, s, dense, ld, diag_major, stream=None):
-    status = _call_pack_sband_f32(n, w, s, dense, ld, diag_major, stream)
+    status = _pack_sband_f32(n, w, s, dense, ld, diag_major, stream)
     if status:
-        _check(lib().dastac_pack_sband_f32(n, w, s, _ptr(dense), ld, _ptr(diag_major), _stream(stream))
-               if status < 0 else status, "pack_sband_f32")
+        _settle(status, "pack_sband_f32", n, w, s, dense, ld, diag_major, stream)
 
 
-_call_unpack_sband_f32 = _entry("unpack_sband_f32", "iiiffi")
+_unpack_sband_f32 = _entry("unpack_sband_f32")
 
 
 def unpack_sband_f32(n, w, s, diag_major, dense, ld, stream=None):
-    status = _call_unpack_sband_f32(n, w, s, diag_major, dense, ld, stream)
+    status = _unpack_sband_f32(n, w, s, diag_major, dense, ld, stream)
     if status:
-        _check(lib().dastac_unpack_sband_f32(n, w, s, _ptr(diag_major), _ptr(dense), ld, _stream(stream))
-               if status < 0 else status, "unpack_sband_f32")
+        _settle(status, "unpack_sband_f32", n, w, s, diag_major, dense, ld, stream)
 
 
-_call_pack_subtri_f32 = _entry("pack_subtri_f32", "iifif")
+_pack_subtri_f32 = _entry("pack_subtri_f32")
 
 
 def pack_subtri_f32(N, k, dense, ld, packed, stream=None):
-    status = _call_pack_subtri_f32(N, k, dense, ld, packed, stream)
+    status = _pack_subtri_f32(N, k, dense, ld, packed, stream)
     if status:
-        _check(lib().dastac_pack_subtri_f32(N, k, _ptr(dense), ld, _ptr(packed), _stream(stream))
-               if status < 0 else status, "pack_subtri_f32")
+        _settle(status, "pack_subtri_f32", N, k, dense, ld, packed, stream)
 
 
-_call_unpack_subtri_f32 = _entry("unpack_subtri_f32", "iiffi")
+_unpack_subtri_f32 = _entry("unpack_subtri_f32")
 
 
 def unpack_subtri_f32(N, k, packed, dense, ld, stream=None):
-    status = _call_unpack_subtri_f32(N, k, packed, dense, ld, stream)
+    status = _unpack_subtri_f32(N, k, packed, dense, ld, stream)
     if status:
-        _check(lib().dastac_unpack_subtri_f32(N, k, _ptr(packed), _ptr(dense), ld, _stream(stream))
-               if status < 0 else status, "unpack_subtri_f32")
+        _settle(status, "unpack_subtri_f32", N, k, packed, dense, ld, stream)
 
 
-_call_pack_leslie_f32 = _entry("pack_leslie_f32", "ififf")
+_pack_leslie_f32 = _entry("pack_leslie_f32")
 
 
 def pack_leslie_f32(n, dense, ld, R, S, stream=None):
-    status = _call_pack_leslie_f32(n, dense, ld, R, S, stream)
+    status = _pack_leslie_f32(n, dense, ld, R, S, stream)
     if status:
-        _check(lib().dastac_pack_leslie_f32(n, _ptr(dense), ld, _ptr(R), _ptr(S), _stream(stream))
-               if status < 0 else status, "pack_leslie_f32")
+        _settle(status, "pack_leslie_f32", n, dense, ld, R, S, stream)
 
 
-_call_unpack_leslie_f32 = _entry("unpack_leslie_f32", "ifffi")
+_unpack_leslie_f32 = _entry("unpack_leslie_f32")
 
 
 def unpack_leslie_f32(n, R, S, dense, ld, stream=None):
-    status = _call_unpack_leslie_f32(n, R, S, dense, ld, stream)
+    status = _unpack_leslie_f32(n, R, S, dense, ld, stream)
     if status:
-        _check(lib().dastac_unpack_leslie_f32(n, _ptr(R), _ptr(S), _ptr(dense), ld, _stream(stream))
-               if status < 0 else status, "unpack_leslie_f32")
+        _settle(status, "unpack_leslie_f32", n, R, S, dense, ld, stream)
 
 
-_call_sband_spmv_f32 = _entry("sband_spmv_f32", "iiifff")
+_sband_spmv_f32 = _entry("sband_spmv_f32")
 
 
 def sband_spmv_f32(n, w, s, D, x, y, stream=None):
-    status = _call_sband_spmv_f32(n, w, s, D, x, y, stream)
+    status = _sband_spmv_f32(n, w, s, D, x, y, stream)
     if status:
-        _check(lib().dastac_sband_spmv_f32(n, w, s, _ptr(D), _ptr(x), _ptr(y), _stream(stream))
-               if status < 0 else status, "sband_spmv_f32")
+        _settle(status, "sband_spmv_f32", n, w, s, D, x, y, stream)
 
 
-_call_subtri_spmv_f32 = _entry("subtri_spmv_f32", "iifff")
+_subtri_spmv_f32 = _entry("subtri_spmv_f32")
 
 
 def subtri_spmv_f32(N, k, Ap, x, y, stream=None):
-    status = _call_subtri_spmv_f32(N, k, Ap, x, y, stream)
+    status = _subtri_spmv_f32(N, k, Ap, x, y, stream)
     if status:
-        _check(lib().dastac_subtri_spmv_f32(N, k, _ptr(Ap), _ptr(x), _ptr(y), _stream(stream))
-               if status < 0 else status, "subtri_spmv_f32")
+        _settle(status, "subtri_spmv_f32", N, k, Ap, x, y, stream)
 
 
-_call_leslie_spmv_f32 = _entry("leslie_spmv_f32", "iffff")
+_leslie_spmv_f32 = _entry("leslie_spmv_f32")
 
 
 def leslie_spmv_f32(n, R, S, x, y, stream=None):
-    status = _call_leslie_spmv_f32(n, R, S, x, y, stream)
+    status = _leslie_spmv_f32(n, R, S, x, y, stream)
     if status:
-        _check(lib().dastac_leslie_spmv_f32(n, _ptr(R), _ptr(S), _ptr(x), _ptr(y), _stream(stream))
-               if status < 0 else status, "leslie_spmv_f32")
+        _settle(status, "leslie_spmv_f32", n, R, S, x, y, stream)
 
 
-_call_stream_sum_f32 = _entry("stream_sum_f32", "iffi")
+_stream_sum_f32 = _entry("stream_sum_f32")
 
 
 def stream_sum_f32(count, src, partial, npartial, stream=None):
-    status = _call_stream_sum_f32(count, src, partial, npartial, stream)
+    status = _stream_sum_f32(count, src, partial, npartial, stream)
     if status:
-        _check(lib().dastac_stream_sum_f32(count, _ptr(src), _ptr(partial), npartial, _stream(stream))
-               if status < 0 else status, "stream_sum_f32")
+        _settle(status, "stream_sum_f32", count, src, partial, npartial, stream)
 
 
-_call_symm_f32 = _entry("symm_f32", "iiffifi")
+_symm_f32 = _entry("symm_f32")
 
 
 def symm_f32(n, m, Up, B, ldb, C, ldc, stream=None):
-    status = _call_symm_f32(n, m, Up, B, ldb, C, ldc, stream)
+    status = _symm_f32(n, m, Up, B, ldb, C, ldc, stream)
     if status:
-        _check(lib().dastac_symm_f32(n, m, _ptr(Up), _ptr(B), ldb, _ptr(C), ldc, _stream(stream))
-               if status < 0 else status, "symm_f32")
+        _settle(status, "symm_f32", n, m, Up, B, ldb, C, ldc, stream)
 
 
-_call_pr_a2_f32 = _entry("pr_a2_f32", "iifif")
+_pr_a2_f32 = _entry("pr_a2_f32")
 
 
 def pr_a2_f32(N, d, B, ldb, A2p, stream=None):
-    status = _call_pr_a2_f32(N, d, B, ldb, A2p, stream)
+    status = _pr_a2_f32(N, d, B, ldb, A2p, stream)
     if status:
-        _check(lib().dastac_pr_a2_f32(N, d, _ptr(B), ldb, _ptr(A2p), _stream(stream))
-               if status < 0 else status, "pr_a2_f32")
+        _settle(status, "pr_a2_f32", N, d, B, ldb, A2p, stream)
 
 
-_call_pr_a3_f32 = _entry("pr_a3_f32", "iifif")
+_pr_a3_f32 = _entry("pr_a3_f32")
 
 
 def pr_a3_f32(N, d, B, ldb, A3p, stream=None):
-    status = _call_pr_a3_f32(N, d, B, ldb, A3p, stream)
+    status = _pr_a3_f32(N, d, B, ldb, A3p, stream)
     if status:
-        _check(lib().dastac_pr_a3_f32(N, d, _ptr(B), ldb, _ptr(A3p), _stream(stream))
-               if status < 0 else status, "pr_a3_f32")
+        _settle(status, "pr_a3_f32", N, d, B, ldb, A3p, stream)
 
 
 # ---- double precision ---------------------------------------------------------
 
-_call_pack_triu_f64 = _entry("pack_triu_f64", "idid")
+_pack_triu_f64 = _entry("pack_triu_f64")
 
 
 def pack_triu_f64(n, dense, ld, packed, stream=None):
-    status = _call_pack_triu_f64(n, dense, ld, packed, stream)
+    status = _pack_triu_f64(n, dense, ld, packed, stream)
     if status:
-        _check(lib().dastac_pack_triu_f64(n, _ptr64(dense), ld, _ptr64(packed), _stream(stream))
-               if status < 0 else status, "pack_triu_f64")
+        _settle(status, "pack_triu_f64", n, dense, ld, packed, stream)
 
 
-_call_unpack_triu_f64 = _entry("unpack_triu_f64", "iddi")
+_unpack_triu_f64 = _entry("unpack_triu_f64")
 
 
 def unpack_triu_f64(n, packed, dense, ld, stream=None):
-    status = _call_unpack_triu_f64(n, packed, dense, ld, stream)
+    status = _unpack_triu_f64(n, packed, dense, ld, stream)
     if status:
-        _check(lib().dastac_unpack_triu_f64(n, _ptr64(packed), _ptr64(dense), ld, _stream(stream))
-               if status < 0 else status, "unpack_triu_f64")
+        _settle(status, "unpack_triu_f64", n, packed, dense, ld, stream)
 
 
-_call_pack_tet_f64 = _entry("pack_tet_f64", "idd")
+_pack_tet_f64 = _entry("pack_tet_f64")
 
 
 def pack_tet_f64(n, dense, packed, stream=None):
-    status = _call_pack_tet_f64(n, dense, packed, stream)
+    status = _pack_tet_f64(n, dense, packed, stream)
     if status:
-        _check(lib().dastac_pack_tet_f64(n, _ptr64(dense), _ptr64(packed), _stream(stream))
-               if status < 0 else status, "pack_tet_f64")
+        _settle(status, "pack_tet_f64", n, dense, packed, stream)
 
 
-_call_unpack_tet_f64 = _entry("unpack_tet_f64", "idd")
+_unpack_tet_f64 = _entry("unpack_tet_f64")
 
 
 def unpack_tet_f64(n, packed, dense, stream=None):
-    status = _call_unpack_tet_f64(n, packed, dense, stream)
+    status = _unpack_tet_f64(n, packed, dense, stream)
     if status:
-        _check(lib().dastac_unpack_tet_f64(n, _ptr64(packed), _ptr64(dense), _stream(stream))
-               if status < 0 else status, "unpack_tet_f64")
+        _settle(status, "unpack_tet_f64", n, packed, dense, stream)
 
 
-_call_pack_band_f64 = _entry("pack_band_f64", "iidid")
+_pack_band_f64 = _entry("pack_band_f64")
 
 
 def pack_band_f64(n, w, dense, ld, diag_major, stream=None):
-    status = _call_pack_band_f64(n, w, dense, ld, diag_major, stream)
+    status = _pack_band_f64(n, w, dense, ld, diag_major, stream)
     if status:
-        _check(lib().dastac_pack_band_f64(n, w, _ptr64(dense), ld, _ptr64(diag_major), _stream(stream))
-               if status < 0 else status, "pack_band_f64")
+        _settle(status, "pack_band_f64", n, w, dense, ld, diag_major, stream)
 
 
-_call_unpack_band_f64 = _entry("unpack_band_f64", "iiddi")
+_unpack_band_f64 = _entry("unpack_band_f64")
 
 
 def unpack_band_f64(n, w, diag_major, dense, ld, stream=None):
-    status = _call_unpack_band_f64(n, w, diag_major, dense, ld, stream)
+    status = _unpack_band_f64(n, w, diag_major, dense, ld, stream)
     if status:
-        _check(lib().dastac_unpack_band_f64(n, w, _ptr64(diag_major), _ptr64(dense), ld, _stream(stream))
-               if status < 0 else status, "unpack_band_f64")
+        _settle(status, "unpack_band_f64", n, w, diag_major, dense, ld, stream)
 
 
-_call_trmv_f64 = _entry("trmv_f64", "iddd")
+_trmv_f64 = _entry("trmv_f64")
 
 
 def trmv_f64(n, Up, x, y, stream=None):
-    status = _call_trmv_f64(n, Up, x, y, stream)
+    status = _trmv_f64(n, Up, x, y, stream)
     if status:
-        _check(lib().dastac_trmv_f64(n, _ptr64(Up), _ptr64(x), _ptr64(y), _stream(stream))
-               if status < 0 else status, "trmv_f64")
+        _settle(status, "trmv_f64", n, Up, x, y, stream)
 
 
-_call_band_spmv_f64 = _entry("band_spmv_f64", "iiddd")
+_band_spmv_f64 = _entry("band_spmv_f64")
 
 
 def band_spmv_f64(n, w, D, x, y, stream=None):
-    status = _call_band_spmv_f64(n, w, D, x, y, stream)
+    status = _band_spmv_f64(n, w, D, x, y, stream)
     if status:
-        _check(lib().dastac_band_spmv_f64(n, w, _ptr64(D), _ptr64(x), _ptr64(y), _stream(stream))
-               if status < 0 else status, "band_spmv_f64")
+        _settle(status, "band_spmv_f64", n, w, D, x, y, stream)
 
 
-_call_tet_ttv_f64 = _entry("tet_ttv_f64", "iddd")
+_tet_ttv_f64 = _entry("tet_ttv_f64")
 
 
 def tet_ttv_f64(n, Ap, v, Mp, stream=None):
-    status = _call_tet_ttv_f64(n, Ap, v, Mp, stream)
+    status = _tet_ttv_f64(n, Ap, v, Mp, stream)
     if status:
-        _check(lib().dastac_tet_ttv_f64(n, _ptr64(Ap), _ptr64(v), _ptr64(Mp), _stream(stream))
-               if status < 0 else status, "tet_ttv_f64")
+        _settle(status, "tet_ttv_f64", n, Ap, v, Mp, stream)
 
 
-_call_trmm_f64 = _entry("trmm_f64", "iiddidi")
+_trmm_f64 = _entry("trmm_f64")
 
 
 def trmm_f64(n, m, Up, B, ldb, C, ldc, stream=None):
-    status = _call_trmm_f64(n, m, Up, B, ldb, C, ldc, stream)
+    status = _trmm_f64(n, m, Up, B, ldb, C, ldc, stream)
     if status:
-        _check(lib().dastac_trmm_f64(n, m, _ptr64(Up), _ptr64(B), ldb, _ptr64(C), ldc, _stream(stream))
-               if status < 0 else status, "trmm_f64")
+        _settle(status, "trmm_f64", n, m, Up, B, ldb, C, ldc, stream)
 
 
-_call_symm_f64 = _entry("symm_f64", "iiddidi")
+_symm_f64 = _entry("symm_f64")
 
 
 def symm_f64(n, m, Up, B, ldb, C, ldc, stream=None):
-    status = _call_symm_f64(n, m, Up, B, ldb, C, ldc, stream)
+    status = _symm_f64(n, m, Up, B, ldb, C, ldc, stream)
     if status:
-        _check(lib().dastac_symm_f64(n, m, _ptr64(Up), _ptr64(B), ldb, _ptr64(C), ldc, _stream(stream))
-               if status < 0 else status, "symm_f64")
+        _settle(status, "symm_f64", n, m, Up, B, ldb, C, ldc, stream)
 
 
-_call_pack_uhc_f64 = _entry("pack_uhc_f64", "iidd")
+_pack_uhc_f64 = _entry("pack_uhc_f64")
 
 
 def pack_uhc_f64(n, Q, dense, packed, stream=None):
-    status = _call_pack_uhc_f64(n, Q, dense, packed, stream)
+    status = _pack_uhc_f64(n, Q, dense, packed, stream)
     if status:
-        _check(lib().dastac_pack_uhc_f64(n, Q, _ptr64(dense), _ptr64(packed), _stream(stream))
-               if status < 0 else status, "pack_uhc_f64")
+        _settle(status, "pack_uhc_f64", n, Q, dense, packed, stream)
 
 
-_call_unpack_uhc_f64 = _entry("unpack_uhc_f64", "iidd")
+_unpack_uhc_f64 = _entry("unpack_uhc_f64")
 
 
 def unpack_uhc_f64(n, Q, packed, dense, stream=None):
-    status = _call_unpack_uhc_f64(n, Q, packed, dense, stream)
+    status = _unpack_uhc_f64(n, Q, packed, dense, stream)
     if status:
-        _check(lib().dastac_unpack_uhc_f64(n, Q, _ptr64(packed), _ptr64(dense), _stream(stream))
-               if status < 0 else status, "unpack_uhc_f64")
+        _settle(status, "unpack_uhc_f64", n, Q, packed, dense, stream)
 
 
-_call_ttm_ut_f64 = _entry("ttm_ut_f64", "iiiddid")
+_ttm_ut_f64 = _entry("ttm_ut_f64")
 
 
 def ttm_ut_f64(n, Q, K, Bp, C, ldc, Ap, stream=None):
-    status = _call_ttm_ut_f64(n, Q, K, Bp, C, ldc, Ap, stream)
+    status = _ttm_ut_f64(n, Q, K, Bp, C, ldc, Ap, stream)
     if status:
-        _check(lib().dastac_ttm_ut_f64(n, Q, K, _ptr64(Bp), _ptr64(C), ldc, _ptr64(Ap), _stream(stream))
-               if status < 0 else status, "ttm_ut_f64")
+        _settle(status, "ttm_ut_f64", n, Q, K, Bp, C, ldc, Ap, stream)
 
 
-_call_pr_a2_f64 = _entry("pr_a2_f64", "iidid")
+_pr_a2_f64 = _entry("pr_a2_f64")
 
 
 def pr_a2_f64(N, d, B, ldb, A2p, stream=None):
-    status = _call_pr_a2_f64(N, d, B, ldb, A2p, stream)
+    status = _pr_a2_f64(N, d, B, ldb, A2p, stream)
     if status:
-        _check(lib().dastac_pr_a2_f64(N, d, _ptr64(B), ldb, _ptr64(A2p), _stream(stream))
-               if status < 0 else status, "pr_a2_f64")
+        _settle(status, "pr_a2_f64", N, d, B, ldb, A2p, stream)
 
 
-_call_pr_a3_f64 = _entry("pr_a3_f64", "iidid")
+_pr_a3_f64 = _entry("pr_a3_f64")
 
 
 def pr_a3_f64(N, d, B, ldb, A3p, stream=None):
-    status = _call_pr_a3_f64(N, d, B, ldb, A3p, stream)
+    status = _pr_a3_f64(N, d, B, ldb, A3p, stream)
     if status:
-        _check(lib().dastac_pr_a3_f64(N, d, _ptr64(B), ldb, _ptr64(A3p), _stream(stream))
-               if status < 0 else status, "pr_a3_f64")
+        _settle(status, "pr_a3_f64", N, d, B, ldb, A3p, stream)
 
 
-_call_tet_mttkrp_f64 = _entry("tet_mttkrp_f64", "iiddididi")
+_tet_mttkrp_f64 = _entry("tet_mttkrp_f64")
 
 
 def tet_mttkrp_f64(n, R, Ap, B, ldb, C, ldc, M, ldm, stream=None):
-    status = _call_tet_mttkrp_f64(n, R, Ap, B, ldb, C, ldc, M, ldm, stream)
+    status = _tet_mttkrp_f64(n, R, Ap, B, ldb, C, ldc, M, ldm, stream)
     if status:
-        _check(lib().dastac_tet_mttkrp_f64(n, R, _ptr64(Ap), _ptr64(B), ldb, _ptr64(C), ldc, _ptr64(M), ldm, _stream(stream))
-               if status < 0 else status, "tet_mttkrp_f64")
+        _settle(status, "tet_mttkrp_f64", n, R, Ap, B, ldb, C, ldc, M, ldm, stream)
 
 
-_call_pack_tril_f64 = _entry("pack_tril_f64", "idid")
+_pack_tril_f64 = _entry("pack_tril_f64")
 
 
 def pack_tril_f64(n, dense, ld, packed, stream=None):
-    status = _call_pack_tril_f64(n, dense, ld, packed, stream)
+    status = _pack_tril_f64(n, dense, ld, packed, stream)
     if status:
-        _check(lib().dastac_pack_tril_f64(n, _ptr64(dense), ld, _ptr64(packed), _stream(stream))
-               if status < 0 else status, "pack_tril_f64")
+        _settle(status, "pack_tril_f64", n, dense, ld, packed, stream)
 
 
-_call_unpack_tril_f64 = _entry("unpack_tril_f64", "iddi")
+_unpack_tril_f64 = _entry("unpack_tril_f64")
 
 
 def unpack_tril_f64(n, packed, dense, ld, stream=None):
-    status = _call_unpack_tril_f64(n, packed, dense, ld, stream)
+    status = _unpack_tril_f64(n, packed, dense, ld, stream)
     if status:
-        _check(lib().dastac_unpack_tril_f64(n, _ptr64(packed), _ptr64(dense), ld, _stream(stream))
-               if status < 0 else status, "unpack_tril_f64")
+        _settle(status, "unpack_tril_f64", n, packed, dense, ld, stream)
 
 
-_call_symv_f64 = _entry("symv_f64", "iddd")
+_symv_f64 = _entry("symv_f64")
 
 
 def symv_f64(n, Up, x, y, stream=None):
-    status = _call_symv_f64(n, Up, x, y, stream)
+    status = _symv_f64(n, Up, x, y, stream)
     if status:
-        _check(lib().dastac_symv_f64(n, _ptr64(Up), _ptr64(x), _ptr64(y), _stream(stream))
-               if status < 0 else status, "symv_f64")
+        _settle(status, "symv_f64", n, Up, x, y, stream)
 
 
-_call_trmv_t_f64 = _entry("trmv_t_f64", "iddd")
+_trmv_t_f64 = _entry("trmv_t_f64")
 
 
 def trmv_t_f64(n, Up, x, y, stream=None):
-    status = _call_trmv_t_f64(n, Up, x, y, stream)
+    status = _trmv_t_f64(n, Up, x, y, stream)
     if status:
-        _check(lib().dastac_trmv_t_f64(n, _ptr64(Up), _ptr64(x), _ptr64(y), _stream(stream))
-               if status < 0 else status, "trmv_t_f64")
+        _settle(status, "trmv_t_f64", n, Up, x, y, stream)
 
 
-_call_symv_lower_f64 = _entry("symv_lower_f64", "iddd")
+_symv_lower_f64 = _entry("symv_lower_f64")
 
 
 def symv_lower_f64(n, Lp, x, y, stream=None):
-    status = _call_symv_lower_f64(n, Lp, x, y, stream)
+    status = _symv_lower_f64(n, Lp, x, y, stream)
     if status:
-        _check(lib().dastac_symv_lower_f64(n, _ptr64(Lp), _ptr64(x), _ptr64(y), _stream(stream))
-               if status < 0 else status, "symv_lower_f64")
+        _settle(status, "symv_lower_f64", n, Lp, x, y, stream)
 
 
-_call_trmv_lower_f64 = _entry("trmv_lower_f64", "iddd")
+_trmv_lower_f64 = _entry("trmv_lower_f64")
 
 
 def trmv_lower_f64(n, Lp, x, y, stream=None):
-    status = _call_trmv_lower_f64(n, Lp, x, y, stream)
+    status = _trmv_lower_f64(n, Lp, x, y, stream)
     if status:
-        _check(lib().dastac_trmv_lower_f64(n, _ptr64(Lp), _ptr64(x), _ptr64(y), _stream(stream))
-               if status < 0 else status, "trmv_lower_f64")
+        _settle(status, "trmv_lower_f64", n, Lp, x, y, stream)
 
 
-_call_trmv_lower_t_f64 = _entry("trmv_lower_t_f64", "iddd")
+_trmv_lower_t_f64 = _entry("trmv_lower_t_f64")
 
 
 def trmv_lower_t_f64(n, Lp, x, y, stream=None):
-    status = _call_trmv_lower_t_f64(n, Lp, x, y, stream)
+    status = _trmv_lower_t_f64(n, Lp, x, y, stream)
     if status:
-        _check(lib().dastac_trmv_lower_t_f64(n, _ptr64(Lp), _ptr64(x), _ptr64(y), _stream(stream))
-               if status < 0 else status, "trmv_lower_t_f64")
+        _settle(status, "trmv_lower_t_f64", n, Lp, x, y, stream)
 
 
-_call_pack_sband_f64 = _entry("pack_sband_f64", "iiidid")
+_pack_sband_f64 = _entry("pack_sband_f64")
 
 
 def pack_sband_f64(n, w, s, dense, ld, diag_major, stream=None):
-    status = _call_pack_sband_f64(n, w, s, dense, ld, diag_major, stream)
+    status = _pack_sband_f64(n, w, s, dense, ld, diag_major, stream)
     if status:
-        _check(lib().dastac_pack_sband_f64(n, w, s, _ptr64(dense), ld, _ptr64(diag_major), _stream(stream))
-               if status < 0 else status, "pack_sband_f64")
+        _settle(status, "pack_sband_f64", n, w, s, dense, ld, diag_major, stream)
 
 
-_call_unpack_sband_f64 = _entry("unpack_sband_f64", "iiiddi")
+_unpack_sband_f64 = _entry("unpack_sband_f64")
 
 
 def unpack_sband_f64(n, w, s, diag_major, dense, ld, stream=None):
-    status = _call_unpack_sband_f64(n, w, s, diag_major, dense, ld, stream)
+    status = _unpack_sband_f64(n, w, s, diag_major, dense, ld, stream)
     if status:
-        _check(lib().dastac_unpack_sband_f64(n, w, s, _ptr64(diag_major), _ptr64(dense), ld, _stream(stream))
-               if status < 0 else status, "unpack_sband_f64")
+        _settle(status, "unpack_sband_f64", n, w, s, diag_major, dense, ld, stream)
 
 
-_call_sband_spmv_f64 = _entry("sband_spmv_f64", "iiiddd")
+_sband_spmv_f64 = _entry("sband_spmv_f64")
 
 
 def sband_spmv_f64(n, w, s, D, x, y, stream=None):
-    status = _call_sband_spmv_f64(n, w, s, D, x, y, stream)
+    status = _sband_spmv_f64(n, w, s, D, x, y, stream)
     if status:
-        _check(lib().dastac_sband_spmv_f64(n, w, s, _ptr64(D), _ptr64(x), _ptr64(y), _stream(stream))
-               if status < 0 else status, "sband_spmv_f64")
+        _settle(status, "sband_spmv_f64", n, w, s, D, x, y, stream)
 
 
-_call_pack_subtri_f64 = _entry("pack_subtri_f64", "iidid")
+_pack_subtri_f64 = _entry("pack_subtri_f64")
 
 
 def pack_subtri_f64(N, k, dense, ld, packed, stream=None):
-    status = _call_pack_subtri_f64(N, k, dense, ld, packed, stream)
+    status = _pack_subtri_f64(N, k, dense, ld, packed, stream)
     if status:
-        _check(lib().dastac_pack_subtri_f64(N, k, _ptr64(dense), ld, _ptr64(packed), _stream(stream))
-               if status < 0 else status, "pack_subtri_f64")
+        _settle(status, "pack_subtri_f64", N, k, dense, ld, packed, stream)
 
 
-_call_unpack_subtri_f64 = _entry("unpack_subtri_f64", "iiddi")
+_unpack_subtri_f64 = _entry("unpack_subtri_f64")
 
 
 def unpack_subtri_f64(N, k, packed, dense, ld, stream=None):
-    status = _call_unpack_subtri_f64(N, k, packed, dense, ld, stream)
+    status = _unpack_subtri_f64(N, k, packed, dense, ld, stream)
     if status:
-        _check(lib().dastac_unpack_subtri_f64(N, k, _ptr64(packed), _ptr64(dense), ld, _stream(stream))
-               if status < 0 else status, "unpack_subtri_f64")
+        _settle(status, "unpack_subtri_f64", N, k, packed, dense, ld, stream)
 
 
-_call_subtri_spmv_f64 = _entry("subtri_spmv_f64", "iiddd")
+_subtri_spmv_f64 = _entry("subtri_spmv_f64")
 
 
 def subtri_spmv_f64(N, k, Ap, x, y, stream=None):
-    status = _call_subtri_spmv_f64(N, k, Ap, x, y, stream)
+    status = _subtri_spmv_f64(N, k, Ap, x, y, stream)
     if status:
-        _check(lib().dastac_subtri_spmv_f64(N, k, _ptr64(Ap), _ptr64(x), _ptr64(y), _stream(stream))
-               if status < 0 else status, "subtri_spmv_f64")
+        _settle(status, "subtri_spmv_f64", N, k, Ap, x, y, stream)
 
 
-_call_pack_leslie_f64 = _entry("pack_leslie_f64", "ididd")
+_pack_leslie_f64 = _entry("pack_leslie_f64")
 
 
 def pack_leslie_f64(n, dense, ld, R, S, stream=None):
-    status = _call_pack_leslie_f64(n, dense, ld, R, S, stream)
+    status = _pack_leslie_f64(n, dense, ld, R, S, stream)
     if status:
-        _check(lib().dastac_pack_leslie_f64(n, _ptr64(dense), ld, _ptr64(R), _ptr64(S), _stream(stream))
-               if status < 0 else status, "pack_leslie_f64")
+        _settle(status, "pack_leslie_f64", n, dense, ld, R, S, stream)
 
 
-_call_unpack_leslie_f64 = _entry("unpack_leslie_f64", "idddi")
+_unpack_leslie_f64 = _entry("unpack_leslie_f64")
 
 
 def unpack_leslie_f64(n, R, S, dense, ld, stream=None):
-    status = _call_unpack_leslie_f64(n, R, S, dense, ld, stream)
+    status = _unpack_leslie_f64(n, R, S, dense, ld, stream)
     if status:
-        _check(lib().dastac_unpack_leslie_f64(n, _ptr64(R), _ptr64(S), _ptr64(dense), ld, _stream(stream))
-               if status < 0 else status, "unpack_leslie_f64")
+        _settle(status, "unpack_leslie_f64", n, R, S, dense, ld, stream)
 
 
-_call_leslie_spmv_f64 = _entry("leslie_spmv_f64", "idddd")
+_leslie_spmv_f64 = _entry("leslie_spmv_f64")
 
 
 def leslie_spmv_f64(n, R, S, x, y, stream=None):
-    status = _call_leslie_spmv_f64(n, R, S, x, y, stream)
+    status = _leslie_spmv_f64(n, R, S, x, y, stream)
     if status:
-        _check(lib().dastac_leslie_spmv_f64(n, _ptr64(R), _ptr64(S), _ptr64(x), _ptr64(y), _stream(stream))
-               if status < 0 else status, "leslie_spmv_f64")
+        _settle(status, "leslie_spmv_f64", n, R, S, x, y, stream)

@@ -2,6 +2,7 @@
 import ctypes
 import inspect
 
+import numpy as np
 import pytest
 
 from paper_2407_13726_amd import dastac
@@ -70,11 +71,39 @@ def test_every_entry_has_its_functions_arguments():
         assert [p.name for p in params][-1] == "stream" and params[-1].default is None and len(params) == len(args)
         kinds = "".join("i" if a is ints else "d" if name.endswith("f64") else "f" for a in args[:-1])
         assert set(args) <= {ints, ptrs}
-        assert dastac_kinds(name) == kinds
+        assert dastac._kinds(name) == kinds
 
 
-def dastac_kinds(name):
-    """As written in the source, next to the function."""
-    src = inspect.getsource(dastac)
-    at = src.index('_entry("%s", "' % name)
-    return src[at:].split('"')[3]
+def test_numpy_integers_are_integers(seen):
+    e, got = seen
+    assert e(np.int64(2), None, Tensor(16, "d"), np.uint8(5), None) == 14 and got == [(2, 0, 16, 5, 1003)]
+    assert e(1, None, Tensor(16, "d"), np.uint64(2 ** 63), None) == -1 and e(1, None, Tensor(16, "d"), np.float64(2), None) == -1 and len(got) == 1
+
+
+class Stream:
+    def __init__(self, handle):
+        self.cuda_stream = handle
+
+
+def test_a_given_stream_is_handed_on(seen):
+    e, got = seen
+    assert e(1, Tensor(8), Tensor(16, "d"), 2, Stream(77)) == 7 and got == [(1, 8, 16, 2, 77)]
+
+
+@pytest.mark.parametrize("handle", [None, "text", 1.0, -1, 2 ** 64])
+def test_handles_that_are_no_addresses_are_left_to_python(seen, handle):
+    e, got = seen
+    assert e(1, Tensor(8), Tensor(16, "d"), 2, Stream(handle)) == -1 and not got
+
+
+@pytest.mark.parametrize("name,args", [("trmv_f32", (3, Tensor(8, "f"), None, Tensor(24, "f"))), ("tet_mttkrp_f64", (3, 2, Tensor(8, "d"), Tensor(16, "d"), 5, None, 6, Tensor(24, "d"), 7))])
+def test_every_call_can_go_through_ctypes(monkeypatch, name, args):
+    """What an entry leaves gets the same arguments, in the order of the C function, and its complaints the function's name."""
+    got = []
+    fn = lambda *a: got.append(a) or 4
+    monkeypatch.setitem(dastac._ctypes_calls, name, (fn, [None if k == "i" else (lambda t: None if t is None else t.data_ptr()) for k in dastac._kinds(name)]))
+    monkeypatch.setattr(dastac, "_" + name, lambda *a: -1)
+    with pytest.raises(dastac.DastacError, match=name) as error:
+        getattr(dastac, name)(*args, stream=Stream(99))
+    assert error.value.status == 4
+    assert got == [(*[a.at if isinstance(a, Tensor) else a for a in args], 99)]
