@@ -14,7 +14,7 @@ namespace dastac {
 
 constexpr int kWalkers = 8;             // wavefronts of a workgroup
 constexpr int kSwitch = 3 * kWalkers;   // (without it n=256, R=32 fp32 19.1 us, with it 13.1; six steps a wavefront instead of three 13.5)
-constexpr int kWalkMost = 2048;         // steps of one walk of a wavefront
+constexpr int kWalkMost = 2048;         // steps of one walk of a wavefront, and so slices that it can note (a bit each)
 
 template <int kB>
 DASTAC_HD int ragged_before(int v) {  // steps of the slices that begin at rows 0..v-1 of a block row

@@ -112,7 +112,8 @@ def test_elements_that_are_not_finite_arrive_as_they_are(gpu, dtype, n, R, bad):
 @pytest.mark.parametrize("a,b,c", [(1e35, 1e-30, 1e3), (1e-30, 1e35, 1e3), (1e3, 1e3, 1e25), (3e-38, 1e20, 1e15), (1e20, 3e-38, 1e17), (1e15, 1e15, 1e-36)])
 def test_magnitudes(gpu, n, R, a, b, c):
     """Operands beyond what the split holds, sums beyond it, and the smallest normal numbers: every term is a b c times (1 + k/8), so all sums are positive and
-    each rounding is at most 2^-23 of them; (n^2/2) terms in blocks of 128, products and adds: 256 roundings bound the relative error by 3.1e-5."""
+    each rounding is at most 2^-23 of them, a split product within 1.5 2^-23; (n^2/2) terms in blocks of 128, products and adds: 256 of these bound the relative error by 3.1e-5.  (How
+    close products and sums are is test_single_products and test_sums_of_one_sign.)"""
     rng = np.random.RandomState(n)
     A, B, C = (np.float32(s) * (1 + rng.randint(0, 8, shape).astype(np.float32) / 8) for s, shape in ((a, tet(n)), (b, (n, R)), (c, (n, R))))
     got = call(gpu, A, B, C, n, R, R).astype(np.float64)
